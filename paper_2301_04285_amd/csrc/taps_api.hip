@@ -553,16 +553,51 @@ uint32_t max_edge_rank(const taps_graph *graph) {
     return r;
 }
 
-// Row segments of every computed table (rep[e] == e; rows are the source
-// side's strategies, columns the target side's): each row cut into segments
-// of `cols` columns and its remainder.  Ordered, the launch takes every
-// full-length segment first (edges in order, a row's segments together) and
-// the remainders last, longest first, so that it ends on its shortest
+// What the two-class edge kernels compute: every edge (edges and starts empty:
+// the tables are the output's, end to end), or with shared tables the first of
+// each group (rep[e] == e), laid end to end in starts.
+struct window_plan {
+    std::vector<uint32_t> edges;
+    std::vector<uint64_t> starts;
+    uint32_t n_edges = 0, tiles = 1;
+    uint64_t total = 0, n_windows = 0;
+};
+
+std::atomic<uint64_t> g_long_segs_min{TAPS_LONG_SEGS_MIN};
+
+window_plan plan_windows(const std::vector<uint64_t> &eoff, const std::vector<uint32_t> &rep) {
+    window_plan p;
+    const uint32_t n_edges = (uint32_t)rep.size();
+    p.n_edges = n_edges;
+    p.total = eoff[n_edges];
+    bool shared = false;
+    for (uint32_t e = 0; e < n_edges; ++e) shared = shared || rep[e] != e;
+    if (shared) {
+        p.total = 0;
+        for (uint32_t e = 0; e < n_edges; ++e) {
+            if (rep[e] != e) continue;
+            p.edges.push_back(e);
+            p.starts.push_back(p.total);
+            p.total += eoff[e + 1] - eoff[e];
+        }
+        p.starts.push_back(p.total);
+        p.n_edges = (uint32_t)p.edges.size();
+    }
+    const uint64_t tiles = (p.total + TAPS_TILE_COLS - 1) / TAPS_TILE_COLS;
+    const uint64_t longs = (tiles + TAPS_WINDOW_LONG - 1) / TAPS_WINDOW_LONG;
+    p.tiles = longs >= g_long_segs_min.load(std::memory_order_relaxed) ? TAPS_WINDOW_LONG : 1;
+    p.n_windows = (tiles + p.tiles - 1) / p.tiles;
+    return p;
+}
+
+// Row segments of the link-class kernel: each row of every edge cut into
+// segments of `cols` columns and its remainder.  Ordered, the launch takes
+// every full-length segment first (edges in order, a row's segments together)
+// and the remainders last, longest first, so that it ends on its shortest
 // segments; otherwise each row's segments, remainder included, run together.
 // Returns the number of segments.
-uint64_t plan_segments(const taps_graph *graph, const uint64_t *op_offsets, bool reverse,
-                       const std::vector<uint32_t> &rep, uint32_t cols, bool ordered,
-                       std::vector<taps_seg_group> &groups) {
+uint64_t plan_segments(const taps_graph *graph, const uint64_t *op_offsets, uint32_t cols,
+                       bool ordered, std::vector<taps_seg_group> &groups) {
     struct remainder {
         uint32_t edge, rows, first_col, cols;
     };
@@ -570,11 +605,9 @@ uint64_t plan_segments(const taps_graph *graph, const uint64_t *op_offsets, bool
     groups.clear();
     uint64_t start = 0;
     for (uint32_t e = 0; e < graph->n_edges; ++e) {
-        if (rep[e] != e) continue;
         const taps_edge &E = graph->edges[e];
-        const uint64_t np = op_offsets[E.src_op + 1] - op_offsets[E.src_op];
-        const uint64_t nc = op_offsets[E.dst_op + 1] - op_offsets[E.dst_op];
-        const uint64_t ns = reverse ? nc : np, nd = reverse ? np : nc;
+        const uint64_t ns = op_offsets[E.src_op + 1] - op_offsets[E.src_op];
+        const uint64_t nd = op_offsets[E.dst_op + 1] - op_offsets[E.dst_op];
         if (ns == 0 || nd == 0) continue;
         if (!ordered) {
             const uint64_t per_row = (nd + cols - 1) / cols;
@@ -598,21 +631,34 @@ uint64_t plan_segments(const taps_graph *graph, const uint64_t *op_offsets, bool
     return start;
 }
 
-// The segments of a one-table launch: long segments (remainders last) when
-// there are enough of them to fill the GPU many times over, else short ones in
-// row order.
-std::atomic<uint64_t> g_long_segs_min{TAPS_LONG_SEGS_MIN};
+// The link-class kernel's segments: long ones (remainders last) when there are
+// enough of them to fill the GPU many times over, else short ones in row order.
+uint64_t plan_rows(const taps_graph *graph, const uint64_t *op_offsets,
+                   std::vector<taps_seg_group> &groups) {
+    const uint64_t n = plan_segments(graph, op_offsets, TAPS_TILE_COLS * TAPS_SEG_TILES_LONG, true,
+                                     groups);
+    if (n >= g_long_segs_min.load(std::memory_order_relaxed)) return n;
+    return plan_segments(graph, op_offsets, TAPS_TILE_COLS * TAPS_SEG_TILES_SHORT, true, groups);
+}
 
-uint64_t plan_launch(const taps_graph *graph, const uint64_t *op_offsets, bool reverse,
-                     const std::vector<uint32_t> &rep, bool one_table,
-                     std::vector<taps_seg_group> &groups) {
-    if (one_table) {
-        const uint64_t n = plan_segments(graph, op_offsets, reverse, rep,
-                                         TAPS_TILE_COLS * TAPS_SEG_TILES_LONG, true, groups);
-        if (n >= g_long_segs_min.load(std::memory_order_relaxed)) return n;
-    }
-    return plan_segments(graph, op_offsets, reverse, rep, TAPS_TILE_COLS * TAPS_SEG_TILES_SHORT,
-                         one_table, groups);
+// The window plan in device memory: the uploaded chunks (the tables' offsets,
+// and with shared tables the computed edges and their starts) and the arrays
+// the plan kernel fills.
+taps_windows device_windows(const window_plan &p, uint64_t n_windows, const taps_edge_params *params,
+                            const uint32_t *window_edge, void *dev, const chunk &offsets,
+                            const chunk &starts) {
+    return {params, at<uint64_t>(dev, p.edges.empty() ? offsets : starts), window_edge, n_windows,
+            p.total, p.tiles, 0u};
+}
+
+taps_plan_args device_plan(const window_plan &p, const taps_windows &w, void *dev, const chunk &ops,
+                           const chunk &edges, const chunk &op_offsets, const chunk &edge_offsets,
+                           const chunk &computed, taps_edge_params *params, uint32_t *window_edge,
+                           bool reverse) {
+    return {at<taps_op>(dev, ops), at<taps_edge>(dev, edges), at<uint64_t>(dev, op_offsets),
+            at<uint64_t>(dev, edge_offsets),
+            p.edges.empty() ? nullptr : at<uint32_t>(dev, computed), w.starts, params, window_edge,
+            w.n_windows, p.n_edges, p.tiles * TAPS_TILE_COLS, reverse ? 1u : 0u, 0u};
 }
 
 // Edge tables of one graph at n_points bandwidth points (clusters that differ
@@ -674,11 +720,12 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
     std::iota(rep.begin(), rep.end(), 0u);
     if (share && (st = share_edges(graph, op_offsets, strategies, stream, rep)) != TAPS_OK)
         return st;
-    // row segments of every computed table (shared tables: the first of each group)
-    // (the bandwidth sweep runs over aligned windows of the tables instead)
+    // windows over the computed tables (shared tables: the first of each group), or
+    // the link classes' row segments
     std::vector<taps_seg_group> groups;
-    const uint64_t n_segs =
-        n_points == 1 ? plan_launch(graph, op_offsets, reverse, rep, true, groups) : 0;
+    const uint64_t n_segs = hier ? plan_rows(graph, op_offsets, groups) : 0;
+    const window_plan win = plan_windows(eoff, rep);
+    const uint64_t n_windows = hier ? 0 : win.n_windows;
     // shared tables: every chunk of a computed table is stored into each table sharing it
     std::vector<uint64_t> dst_list;
     std::vector<taps_copy_task> copies;
@@ -692,40 +739,42 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
                           {eoff.data(), sizeof(uint64_t) * (n_edges + 1), 0},
                           {groups.data(), sizeof(taps_seg_group) * groups.size(), 0},
                           {copies.data(), sizeof(taps_copy_task) * copies.size(), 0},
-                          {dst_list.data(), sizeof(uint64_t) * dst_list.size(), 0}};
+                          {dst_list.data(), sizeof(uint64_t) * dst_list.size(), 0},
+                          {win.edges.data(), sizeof(uint32_t) * win.edges.size(), 0},
+                          {win.starts.data(), sizeof(uint64_t) * win.starts.size(), 0}};
     void *dev = nullptr;
     if ((st = upload(sc, ch, &dev)) != TAPS_OK) return st;
-    taps_desc *d_desc = nullptr;
+    void *d_desc = nullptr;   // taps_packed, or taps_desc for the link classes
     taps_edge_params *d_params = nullptr;
     taps_row_ref *d_segs = nullptr;
-    if ((st = sc.alloc((void **)&d_desc, sizeof(taps_desc) * total)) != TAPS_OK) return st;
-    if ((st = sc.alloc((void **)&d_params, sizeof(taps_edge_params) * n_edges)) != TAPS_OK) return st;
-    if ((st = sc.alloc((void **)&d_segs, sizeof(taps_row_ref) * n_segs)) != TAPS_OK) return st;
-    // the bandwidth sweep runs over aligned 64-entry windows: each window's edge
     uint32_t *d_win = nullptr;
-    const uint64_t n_windows = (eoff[n_edges] + TAPS_TILE_COLS * TAPS_WIN_TILES - 1) /
-                               (TAPS_TILE_COLS * TAPS_WIN_TILES);
-    if (n_points > 1 && !hier &&
-        (st = sc.alloc((void **)&d_win, sizeof(uint32_t) * n_windows)) != TAPS_OK)
+    static_assert(sizeof(taps_desc) == sizeof(taps_packed), "one scratch array for either");
+    if ((st = sc.alloc(&d_desc, sizeof(taps_packed) * total)) != TAPS_OK) return st;
+    if ((st = sc.alloc((void **)&d_params, sizeof(taps_edge_params) * win.n_edges)) != TAPS_OK)
         return st;
-    hipError_t err = taps_launch_describe(strategies, total, d_desc, stream);
+    if ((st = sc.alloc((void **)&d_segs, sizeof(taps_row_ref) * n_segs)) != TAPS_OK) return st;
+    if ((st = sc.alloc((void **)&d_win, sizeof(uint32_t) * n_windows)) != TAPS_OK) return st;
+    hipError_t err = hier ? taps_launch_describe_h(strategies, total, lp.n, (taps_desc *)d_desc, stream)
+                          : taps_launch_describe(strategies, total, lp.n, (taps_packed *)d_desc, stream);
+    const taps_windows tw = device_windows(win, n_windows, d_params, d_win, dev, ch[3], ch[8]);
     if (err == hipSuccess) {
-        const taps_plan_args pa{at<taps_op>(dev, ch[0]), at<taps_edge>(dev, ch[1]),
-                                at<uint64_t>(dev, ch[2]), at<uint64_t>(dev, ch[3]),
-                                at<taps_seg_group>(dev, ch[4]), d_params, d_segs, n_segs,
-                                n_edges, (uint32_t)groups.size(), reverse ? 1u : 0u, 0u};
+        const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[7],
+                                              d_params, d_win, reverse);
         err = taps_launch_edge_setup(pa, lp, stream);
     }
+    if (err == hipSuccess && hier)
+        err = taps_launch_row_plan({at<taps_edge>(dev, ch[1]), at<uint64_t>(dev, ch[2]),
+                                    at<taps_seg_group>(dev, ch[4]), d_segs, n_segs,
+                                    (uint32_t)groups.size(), 0u}, stream);
     // the edge-table kernel launches (entries > 0): use the events, if any, once
     const hipEvent_t before = g_kernel_before, after = g_kernel_after;
     g_kernel_before = g_kernel_after = nullptr;
     if (err == hipSuccess && before) err = hipEventRecord(before, stream);
     if (err == hipSuccess && hier) {
-        err = taps_launch_edge_costs_h(d_params, d_segs, n_segs, d_desc, lp, max_edge_rank(graph),
-                                       *hier, outs[0], stream);
+        err = taps_launch_edge_costs_h(d_params, d_segs, n_segs, (taps_desc *)d_desc, lp,
+                                       max_edge_rank(graph), *hier, outs[0], stream);
     } else if (err == hipSuccess && n_points == 1) {
-        err = taps_launch_edge_costs(d_params, d_segs, n_segs, d_desc, lp, max_edge_rank(graph),
-                                     outs[0], stream);
+        err = taps_launch_edge_costs(tw, (taps_packed *)d_desc, lp, outs[0], stream);
     } else if (err == hipSuccess) {
         taps_sweep sw;
         std::memset(&sw, 0, sizeof(sw));
@@ -738,9 +787,7 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
             sw.inv_n_binter[k] = lps[k].inv_n_binter;
             sw.out[k] = outs[k];
         }
-        err = taps_launch_edge_costs_sweep_win(d_params, n_edges, at<uint64_t>(dev, ch[3]),
-                                               eoff[n_edges], d_win, d_desc, lp,
-                                               max_edge_rank(graph), sw, stream);
+        err = taps_launch_edge_costs_sweep(tw, (taps_packed *)d_desc, lp, sw, stream);
     }
     for (uint32_t k = 0; k < n_points && err == hipSuccess; ++k)
         err = taps_launch_copy_tables(at<taps_copy_task>(dev, ch[5]), (uint32_t)copies.size(),
@@ -1134,23 +1181,23 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
     hipStream_t stream = (hipStream_t)stream_;
     std::vector<taps_build_chunk> bchunks;
     if ((st = plan_build(graph, lp.n, allowed, offs, bchunks)) != TAPS_OK) return st;
-    std::vector<taps_seg_group> groups;
     const uint64_t total = offs[n_ops];
-    const uint64_t n_segs = plan_launch(graph, offs.data(), false, rep, true, groups);
+    const window_plan win = plan_windows(eoff, rep);
     std::vector<chunk> ch{{graph->ops, sizeof(taps_op) * n_ops, 0},
                           {graph->edges, sizeof(taps_edge) * n_edges, 0},
                           {offs.data(), sizeof(uint64_t) * (n_ops + 1), 0},
                           {eoff.data(), sizeof(uint64_t) * (n_edges + 1), 0},
-                          {groups.data(), sizeof(taps_seg_group) * groups.size(), 0},
+                          {win.edges.data(), sizeof(uint32_t) * win.edges.size(), 0},
                           {copies.data(), sizeof(taps_copy_task) * copies.size(), 0},
                           {dst_list.data(), sizeof(uint64_t) * dst_list.size(), 0},
-                          {bchunks.data(), sizeof(taps_build_chunk) * bchunks.size(), 0}};
+                          {bchunks.data(), sizeof(taps_build_chunk) * bchunks.size(), 0},
+                          {win.starts.data(), sizeof(uint64_t) * win.starts.size(), 0}};
     if (fixed) {   // the whole need, checked on the host before any HIP call
         size_t up = 0;
         for (const chunk &c : ch) up += align256(c.bytes);
-        const size_t need = carve_size(up) + carve_size(sizeof(taps_desc) * total) +
-                            carve_size(sizeof(taps_edge_params) * (n_edges ? n_edges : 1)) +
-                            carve_size(sizeof(taps_row_ref) * (n_segs ? n_segs : 1));
+        const size_t need = carve_size(up) + carve_size(sizeof(taps_packed) * total) +
+                            carve_size(sizeof(taps_edge_params) * win.n_edges) +
+                            carve_size(sizeof(uint32_t) * win.n_windows);
         if (need > TAPS_NOALLOC_SCRATCH_BYTES)
             return fail(TAPS_ERR_CAPACITY,
                         "this build needs %llu bytes of device workspace; the fixed workspace of "
@@ -1170,23 +1217,18 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
     }
     void *dev = nullptr;
     if ((st = ws->put(ch, &dev)) != TAPS_OK) return st;
-    taps_desc *d_desc = nullptr;
+    taps_packed *d_desc = nullptr;
     taps_edge_params *d_params = nullptr;
-    taps_row_ref *d_segs = nullptr;
-    if ((st = ws->carve((void **)&d_desc, sizeof(taps_desc) * total)) != TAPS_OK) return st;
-    if ((st = ws->carve((void **)&d_params, sizeof(taps_edge_params) * (n_edges ? n_edges : 1))) !=
-        TAPS_OK)
+    uint32_t *d_win = nullptr;
+    if ((st = ws->carve((void **)&d_desc, sizeof(taps_packed) * total)) != TAPS_OK) return st;
+    if ((st = ws->carve((void **)&d_params, sizeof(taps_edge_params) * win.n_edges)) != TAPS_OK)
         return st;
-    if ((st = ws->carve((void **)&d_segs, sizeof(taps_row_ref) * (n_segs ? n_segs : 1))) !=
-        TAPS_OK)
-        return st;
+    if ((st = ws->carve((void **)&d_win, sizeof(uint32_t) * win.n_windows)) != TAPS_OK) return st;
     // the strategies, and the edge plan when there are edge entries, in one launch
     const bool edges_on = eoff[n_edges] > 0;
-    const taps_plan_args pa{at<taps_op>(dev, ch[0]), at<taps_edge>(dev, ch[1]),
-                            at<uint64_t>(dev, ch[2]), at<uint64_t>(dev, ch[3]),
-                            at<taps_seg_group>(dev, ch[4]), d_params, d_segs,
-                            edges_on ? n_segs : 0u, edges_on ? n_edges : 0u,
-                            edges_on ? (uint32_t)groups.size() : 0u, 0u, 0u};
+    const taps_windows tw = device_windows(win, win.n_windows, d_params, d_win, dev, ch[3], ch[8]);
+    const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[4], d_params,
+                                          d_win, false);
     hipError_t err = taps_launch_build_front(at<taps_build_chunk>(dev, ch[7]),
                                              (uint32_t)bchunks.size(), allowed, lp, strategies,
                                              d_desc, node, pa, stream);
@@ -1195,8 +1237,7 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
         g_kernel_before = g_kernel_after = nullptr;
         if (err == hipSuccess && before) err = hipEventRecord(before, stream);
         if (err == hipSuccess)
-            err = taps_launch_edge_costs(d_params, d_segs, n_segs, d_desc, lp,
-                                         max_edge_rank(graph), edge, stream);
+            err = taps_launch_edge_costs(tw, d_desc, lp, edge, stream);
         if (err == hipSuccess)
             err = taps_launch_copy_tables(at<taps_copy_task>(dev, ch[5]), (uint32_t)copies.size(),
                                           at<uint64_t>(dev, ch[6]), edge, stream);
@@ -1286,9 +1327,9 @@ taps_status taps_node_costs(const taps_graph *graph, const taps_cluster *cluster
                           {op_offsets, sizeof(uint64_t) * (n_ops + 1), 0}};
     void *dev = nullptr;
     if ((st = upload(sc, ch, &dev)) != TAPS_OK) return st;
-    taps_desc *d_desc = nullptr;
-    if ((st = sc.alloc((void **)&d_desc, sizeof(taps_desc) * total)) != TAPS_OK) return st;
-    hipError_t err = taps_launch_describe(strategies, total, d_desc, stream);
+    taps_packed *d_desc = nullptr;
+    if ((st = sc.alloc((void **)&d_desc, sizeof(taps_packed) * total)) != TAPS_OK) return st;
+    hipError_t err = taps_launch_describe(strategies, total, lp.n, d_desc, stream);
     if (err == hipSuccess)
         err = taps_launch_node_costs(at<taps_op>(dev, ch[0]), n_ops, at<uint64_t>(dev, ch[1]),
                                      d_desc, total, lp, out, stream);
@@ -1336,13 +1377,13 @@ taps_status taps_node_costs_topology(const taps_graph *graph, const taps_topolog
                           {op_offsets, sizeof(uint64_t) * (n_ops + 1), 0}};
     void *dev = nullptr;
     if ((st = upload(sc, ch, &dev)) != TAPS_OK) return st;
-    taps_desc *d_desc = nullptr;
-    if ((st = sc.alloc((void **)&d_desc, sizeof(taps_desc) * total)) != TAPS_OK) return st;
-    hipError_t err = taps_launch_describe(strategies, total, d_desc, stream);
+    const uint32_t n = log2u(topology->domain[H.n_classes - 1]);
+    taps_packed *d_desc = nullptr;
+    if ((st = sc.alloc((void **)&d_desc, sizeof(taps_packed) * total)) != TAPS_OK) return st;
+    hipError_t err = taps_launch_describe(strategies, total, n, d_desc, stream);
     if (err == hipSuccess)
         err = taps_launch_node_costs_h(at<taps_op>(dev, ch[0]), n_ops, at<uint64_t>(dev, ch[1]),
-                                       d_desc, total, log2u(topology->domain[H.n_classes - 1]), H,
-                                       out, stream);
+                                       d_desc, total, n, H, out, stream);
     if (err != hipSuccess) return hip_fail(err, "node costs");
     return TAPS_OK;
 }

@@ -1,0 +1,562 @@
+// taps_entry.h -- the candidates of one edge entry on byte vectors.
+//
+// The same method as taps_device.h (binary levels; a unified axis is named by
+// its top level; positions, closures and costs as described there), laid out
+// for one entry per lane with no loop over dimensions and no table per row, so
+// that the lanes of a wavefront may hold different rows.
+//
+//   * A set of levels is a vector of 8 bytes (two registers), byte l = FF when
+//     level l is in it.  A map between levels is a vector of 8 indices, and
+//     v_perm_b32 applies it: two instructions carry a whole set or a whole
+//     vector of widths through a map, whatever the tensor's rank.  An index of
+//     0x0D or more gives FF ("no level"), and so maps compose.
+//   * Everything that propagates along chains of positions -- the cuts of the
+//     unification, the AllToAll closures -- is found by pointer doubling: three
+//     steps cover the at most seven hops, with no loop that would run until the
+//     wavefront's slowest lane is done.
+//   * The state of a sequence is one number G: the shard's exponent in the low
+//     5 bits and the number of free levels inside a node in the upper 3.  A
+//     gather of an axis adds the axis's byte of `D` (its width, and its levels
+//     inside a node << 5), a slice subtracts it.  Where the order of the gathers
+//     is known beforehand ("remove", "rearrange", the untargeted gathers of
+//     Algorithm 1) the states before all of them come from one prefix sum over
+//     bytes in producer order: a multiplication by 0x01010101 per half.
+//   * Each axis held off its target is moved exactly once by every candidate,
+//     so a candidate is described by the state each axis was moved at, and one
+//     pass over the levels costs all three.  Whether a level lies inside a node
+//     is the same for every lane: the pass branches on it uniformly.
+#pragma once
+
+#include "taps_device.h"
+
+// ---------------------------------------------------------------------------
+// Vectors of 8 bytes
+// ---------------------------------------------------------------------------
+struct taps_b8 {
+    uint32_t lo, hi;   // bytes 0-3, 4-7
+};
+
+// v_perm_b32: byte k of the result is byte sel_k of (hi, lo) for sel_k < 8,
+// 0 for 0x0C, FF for 0x0D and above (8-11, the signs of odd bytes, are used
+// by taps_not_lowest alone).
+__host__ __device__ inline uint32_t taps_perm(uint32_t hi, uint32_t lo, uint32_t sel) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_perm(hi, lo, sel);
+#else
+    const uint64_t d = ((uint64_t)hi << 32) | lo;
+    uint32_t r = 0;
+    for (uint32_t k = 0; k < 4u; ++k) {
+        const uint32_t s = (sel >> (8u * k)) & 0xFFu;
+        uint32_t b = 0xFFu;
+        if (s < 8u)
+            b = (uint32_t)(d >> (8u * s)) & 0xFFu;
+        else if (s < 12u)
+            b = ((d >> (16u * (s - 8u) + 15u)) & 1u) ? 0xFFu : 0u;
+        else if (s == 12u)
+            b = 0u;
+        r |= b << (8u * k);
+    }
+    return r;
+#endif
+}
+
+__host__ __device__ inline taps_b8 taps_map(const taps_b8 &x, const taps_b8 &index) {
+    return {taps_perm(x.hi, x.lo, index.lo), taps_perm(x.hi, x.lo, index.hi)};
+}
+
+// v_bitop3_b32 (the issue rate of a 32-bit add); truth table T, bit 4a + 2b + c.
+template <uint32_t T>
+__host__ __device__ inline uint32_t taps_bitop3(uint32_t a, uint32_t b, uint32_t c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_bitop3_b32(a, b, c, T);
+#else
+    uint32_t r = 0;
+    for (uint32_t k = 0; k < 8u; ++k)
+        if ((T >> k) & 1u) r |= ((k & 4u) ? a : ~a) & ((k & 2u) ? b : ~b) & ((k & 1u) ? c : ~c);
+    return r;
+#endif
+}
+template <uint32_t T>
+__host__ __device__ inline taps_b8 taps_bitop3(const taps_b8 &a, const taps_b8 &b, const taps_b8 &c) {
+    return {taps_bitop3<T>(a.lo, b.lo, c.lo), taps_bitop3<T>(a.hi, b.hi, c.hi)};
+}
+constexpr uint32_t TAPS_A = 0xF0, TAPS_B = 0xCC, TAPS_C = 0xAA;   // the operands' truth tables
+constexpr uint32_t TAPS_AND3 = TAPS_A & TAPS_B & TAPS_C;
+constexpr uint32_t TAPS_A_NOTB_C = TAPS_A & (0xFFu ^ TAPS_B) & TAPS_C;
+
+__host__ __device__ inline taps_b8 operator&(const taps_b8 &a, const taps_b8 &b) {
+    return {a.lo & b.lo, a.hi & b.hi};
+}
+__host__ __device__ inline taps_b8 operator|(const taps_b8 &a, const taps_b8 &b) {
+    return {a.lo | b.lo, a.hi | b.hi};
+}
+__host__ __device__ inline taps_b8 operator~(const taps_b8 &a) { return {~a.lo, ~a.hi}; }
+// Byte sums and differences; no byte may carry or borrow.
+__host__ __device__ inline taps_b8 operator+(const taps_b8 &a, const taps_b8 &b) {
+    return {a.lo + b.lo, a.hi + b.hi};
+}
+__host__ __device__ inline taps_b8 operator-(const taps_b8 &a, const taps_b8 &b) {
+    return {a.lo - b.lo, a.hi - b.hi};
+}
+__host__ __device__ inline taps_b8 taps_all(uint32_t word) { return {word, word}; }
+__host__ __device__ inline bool taps_any(const taps_b8 &a) { return (a.lo | a.hi) != 0u; }
+__host__ __device__ inline uint64_t taps_u64(const taps_b8 &a) { return ((uint64_t)a.hi << 32) | a.lo; }
+__host__ __device__ inline taps_b8 taps_from(uint64_t x) { return {(uint32_t)x, (uint32_t)(x >> 32)}; }
+
+// a in the bits of m, b in the others.
+__host__ __device__ inline taps_b8 taps_blend(const taps_b8 &m, const taps_b8 &a, const taps_b8 &b) {
+    return taps_bitop3<(TAPS_A & TAPS_B) | ((0xFFu ^ TAPS_A) & TAPS_C)>(m, a, b);
+}
+
+// FF where bit 7 of the byte is set (an index that names no level), else 0.
+__host__ __device__ inline taps_b8 taps_none(const taps_b8 &x) {
+    return {taps_perm(0u, 0u, x.lo & 0x80808080u), taps_perm(0u, 0u, x.hi & 0x80808080u)};
+}
+
+// FF where bit 3 is clear, 0 where it is set (selector 8 reads a sign that is 0).
+__host__ __device__ inline taps_b8 taps_not_lowest(const taps_b8 &x) {
+    return {taps_perm(0u, 0xFFu, x.lo & 0x08080808u), taps_perm(0u, 0xFFu, x.hi & 0x08080808u)};
+}
+
+// c plus the sum of the bytes.
+__host__ __device__ inline uint32_t taps_sum(const taps_b8 &x, uint32_t c) {
+    return taps_dot4(x.hi, 0x01010101u, taps_dot4(x.lo, 0x01010101u, c));
+}
+
+// The set as a bit mask.
+__host__ __device__ inline uint32_t taps_bits(const taps_b8 &x) {
+    return taps_dot4(x.hi & 0x01010101u, 0x80402010u, taps_dot4(x.lo & 0x01010101u, 0x08040201u, 0u));
+}
+
+// States before each of the steps whose changes are the bytes of e, from state
+// g, in ascending bytes; `end` receives the state after the last.  The changes may be negative
+// (e is then the plain 32-bit sum of its bytes' values): every state is a byte,
+// so the sums below come out digit by digit.
+__host__ __device__ inline taps_b8 taps_states(const taps_b8 &e, uint32_t g, uint32_t &end) {
+    taps_b8 x;
+    x.lo = ((e.lo << 8) + g) * 0x01010101u;
+    const uint32_t mid = (x.lo + e.lo) >> 24;
+    x.hi = ((e.hi << 8) + mid) * 0x01010101u;
+    end = (x.hi + e.hi) >> 24;
+    return x;
+}
+
+// ---------------------------------------------------------------------------
+// Strategy descriptors
+// ---------------------------------------------------------------------------
+
+// A strategy on binary levels, every field 8 indexed nibbles in the order that
+// two masks turn into a byte vector: index k < 4 in the low nibble of byte k,
+// k >= 4 in the high nibble of byte k - 4.
+struct taps_packed {
+    uint32_t owner;   // per level: the op axis that owns it (0 above the last level)
+    uint32_t place;   // per level: its distance from the top of its axis's run, + 8 when it is the
+                      // run's lowest level (15 above the last level)
+    uint32_t end;     // per op axis: top level + 1 of its run (0 = not split)
+    uint32_t width;   // per op axis: the run's width
+};
+
+__host__ __device__ inline taps_b8 taps_unnibble(uint32_t x) {
+    return {x & 0x0F0F0F0Fu, (x >> 4) & 0x0F0F0F0Fu};
+}
+__host__ __device__ inline uint32_t taps_nibble_shift(uint32_t k) {
+    return k < 4u ? 8u * k : 8u * k - 28u;
+}
+// nibbles 0-7 in ascending order (taps_nib) to the order above
+__host__ __device__ inline uint32_t taps_deal(uint32_t x) {
+    uint32_t r = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 8u; ++k) r |= taps_nib(x, k) << taps_nibble_shift(k);
+    return r;
+}
+
+__host__ __device__ inline taps_packed taps_pack(const taps_desc &D, uint32_t n) {
+    taps_packed p = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (uint32_t a = 0; a < TAPS_D_MAX_AXES; ++a) {
+        const uint32_t w = taps_nib(D.width, a), lo = taps_nib(D.lo, a);
+        p.width |= w << taps_nibble_shift(a);
+        p.end |= (w ? (lo + w) & 15u : 0u) << taps_nibble_shift(a);
+    }
+#pragma unroll
+    for (uint32_t l = 0; l < TAPS_D_MAX_LEVELS; ++l) {
+        const uint32_t a = taps_nib(D.owner, l) & 7u;
+        const uint32_t lo = taps_nib(D.lo, a), end = lo + taps_nib(D.width, a);
+        p.owner |= (l < n ? a : 0u) << taps_nibble_shift(l);
+        p.place |= (l < n ? ((end - 1u - l) & 7u) | (l == lo ? 8u : 0u) : 15u) << taps_nibble_shift(l);
+    }
+    return p;
+}
+
+// Levels of op axis a.
+__host__ __device__ inline uint32_t taps_axis_levels(const taps_packed &p, uint32_t a) {
+    const uint32_t s = taps_nibble_shift(a);
+    const uint32_t w = (p.width >> s) & 15u, end = (p.end >> s) & 15u;
+    return taps_levels(end < w ? 0u : end - w, w);
+}
+
+// One side of an edge: which tensor dimension an op axis carries (7: none; a
+// tensor of rank 8 uses every axis) and which axis a dimension lies on (0x0C:
+// none), as nibbles in the order of taps_packed.
+struct taps_side {
+    uint32_t dim_of, axis_of;
+};
+
+__host__ __device__ inline taps_side taps_make_side(uint32_t axes, uint32_t rank) {
+    taps_side s = {0x77777777u, 0xCCCCCCCCu};
+    for (uint32_t d = 0; d < rank && d < TAPS_D_MAX_RANK; ++d) {
+        const uint32_t a = taps_nib(axes, d) & 7u;
+        const uint32_t sa = taps_nibble_shift(a), sd = taps_nibble_shift(d);
+        s.dim_of = (s.dim_of & ~(15u << sa)) | (d << sa);
+        s.axis_of = (s.axis_of & ~(15u << sd)) | (a << sd);
+    }
+    return s;
+}
+
+// ---------------------------------------------------------------------------
+// What a launch, an edge and a row fix
+// ---------------------------------------------------------------------------
+
+// Levels and the node boundary (uniform over a launch).
+struct taps_levels_model {
+    uint32_t n;       // levels
+    uint32_t full;    // taps_low_mask(n)
+    uint32_t n_in;    // levels inside a node
+    uint32_t shift;   // n_in when some level lies outside, else 0: sums are kept << shift, so that
+                      // a link's share is a right shift by the free in-node levels
+    taps_b8 in01;     // 01 at the levels inside a node
+};
+
+__host__ __device__ inline taps_levels_model taps_make_levels(uint32_t n, uint32_t lam) {
+    taps_levels_model m;
+    m.n = n;
+    m.full = taps_low_mask(n);
+    m.n_in = lam < n ? lam : n;
+    m.shift = lam < n ? lam : 0u;
+    m.in01 = taps_from(m.n_in >= 8u ? 0x0101010101010101ull
+                                    : 0x0101010101010101ull & ((1ull << (8u * m.n_in)) - 1ull));
+    return m;
+}
+
+// By tops mask, in LDS: byte t of d is, for every top t, the width of its axis
+// and (<< 5, when the model has levels outside a node) its levels inside a
+// node; byte t of tops is FF for every top.
+struct taps_top_row {
+    taps_b8 d, tops;
+};
+
+// From the axes' widths w (bytes at the tops): an axis inside the node has
+// all its levels there, of those above only the lowest can reach below the
+// boundary.
+__host__ __device__ inline taps_b8 taps_top_bytes(const taps_b8 &w, uint32_t tp,
+                                                  const taps_levels_model &m) {
+    if (m.shift == 0u) return w;
+    const taps_b8 in = {m.in01.lo * 0xFFu, m.in01.hi * 0xFFu};
+    uint64_t d = taps_u64(w) | (taps_u64(w & in) << 5);
+    const uint32_t out = (tp & m.full) >> m.shift;
+    if (out) {
+        const uint32_t s = m.shift + taps_ctz(out);
+        const uint32_t ws = (uint32_t)(taps_u64(w) >> (8u * s)) & 15u;
+        const uint32_t above = s + 1u - m.shift;
+        if (ws > above) d |= (uint64_t)(ws - above) << (8u * s + 5u);
+    }
+    return taps_from(d);
+}
+
+// The widths above by tops mask, independent of the node boundary.
+struct taps_top_table {
+    uint32_t w_lo[256], w_hi[256];
+};
+
+__host__ __device__ constexpr taps_top_table taps_make_tops() {
+    taps_top_table t{};
+    for (uint32_t m = 0; m < 256u; ++m) {
+        uint64_t w = 0;
+        uint32_t lo = 0;
+        for (uint32_t l = 0; l < 8u; ++l)
+            if ((m >> l) & 1u) {
+                w |= (uint64_t)(l + 1u - lo) << (8u * l);
+                lo = l + 1u;
+            }
+        t.w_lo[m] = (uint32_t)w;
+        t.w_hi[m] = (uint32_t)(w >> 32);
+    }
+    return t;
+}
+
+__host__ __device__ inline taps_top_row taps_make_top_row(const taps_top_table &T, uint32_t tp,
+                                                          const taps_levels_model &m) {
+    const taps_b8 w = {T.w_lo[tp], T.w_hi[tp]};
+    // FF where a width (at most 8) is not 0
+    const taps_b8 tops = taps_none(w + taps_all(0x7F7F7F7Fu));
+    return {taps_top_bytes(w, tp, m), tops};
+}
+
+// The source side of a row: its levels' dimensions and places, the ends and
+// widths of its dimensions, its positions in order.
+struct taps_source {
+    taps_b8 dim;      // per level: tensor dimension (7: none)
+    taps_b8 place;    // per level: position bit in the dimension (taps_packed::place without the flag)
+    taps_b8 next;     // per level: place + 1, at least 9 for a run's lowest level
+    taps_b8 top;      // per dimension: 7F + end of its run
+    taps_b8 room;     // per dimension: 80 - width
+    taps_b8 held;     // FF at the levels the tensor's map uses
+    taps_b8 uncut;    // FF where no cut lies below the level
+    taps_b8 rank;     // per level: its place among the positions in order (dimension, then bit)
+    taps_b8 order;    // per place in that order: the level (0x0C: none)
+    uint32_t g;       // the state G before the first step
+};
+
+// FF at the dimensions that an edge's tensor has (dimension 7 stands for
+// "none" below rank 8).
+__host__ __device__ inline taps_b8 taps_in_tensor(uint32_t rank, const taps_b8 &dim) {
+    const uint32_t hi = rank < TAPS_D_MAX_RANK ? 0x00FFFFFFu : 0xFFFFFFFFu;
+    return {taps_perm(hi, 0xFFFFFFFFu, dim.lo), taps_perm(hi, 0xFFFFFFFFu, dim.hi)};
+}
+
+__host__ __device__ inline taps_source taps_make_source(const taps_packed &p, const taps_side &side,
+                                                        uint32_t rank, const taps_levels_model &m) {
+    taps_source P;
+    const taps_b8 axis_of = taps_unnibble(side.axis_of);
+    P.dim = taps_map(taps_unnibble(side.dim_of), taps_unnibble(p.owner));
+    const taps_b8 place = taps_unnibble(p.place);
+    P.place = place & taps_all(0x07070707u);
+    P.next = place + taps_all(0x01010101u);
+    const taps_b8 width = taps_map(taps_unnibble(p.width), axis_of);
+    P.top = taps_map(taps_unnibble(p.end), axis_of) + taps_all(0x7F7F7F7Fu);
+    P.room = taps_all(0x80808080u) - width;
+    P.held = taps_in_tensor(rank, P.dim);
+    P.uncut = taps_not_lowest(place);
+    uint32_t used;
+    const taps_b8 first = taps_states(width, 0u, used);   // positions before each dimension
+    P.rank = (taps_map(first, P.dim) + P.place) & taps_all(0x07070707u);
+    uint64_t order = 0x0C0C0C0C0C0C0C0Cull;
+#pragma unroll
+    for (uint32_t l = 0; l < TAPS_D_MAX_LEVELS; ++l) {
+        const uint32_t rank_l = ((l < 4u ? P.rank.lo : P.rank.hi) >> (8u * (l & 3u))) & 7u;
+        const uint32_t held_l = ((l < 4u ? P.held.lo : P.held.hi) >> (8u * (l & 3u))) & 0xFFu;
+        if (l < m.n) order ^= (uint64_t)((l ^ 0x0Cu) & held_l) << (8u * rank_l);
+    }
+    P.order = taps_from(order);
+    const uint32_t free_in = m.shift ? m.shift - taps_sum(P.held & m.in01, 0u) : 0u;
+    P.g = ((m.n - used + 8u + m.shift) & 31u) | (free_in << 5);
+    return P;
+}
+
+// ---------------------------------------------------------------------------
+// One entry
+// ---------------------------------------------------------------------------
+
+// Replace (Algorithm 1), rearrange (the same without AllToAll) and remove.
+struct taps_three {
+    taps_fac c[3];
+    uint32_t coll;   // collectives of every candidate (bits 0-7), inter-node ones (8-15)
+};
+
+// One pointer-doubling step of "not reached": x stays FF only where the level
+// it points to is FF too.
+__host__ __device__ inline taps_b8 taps_hop(const taps_b8 &x, const taps_b8 &to) {
+    return x & taps_map(x, to);
+}
+
+__host__ __device__ inline void taps_three_candidates(const taps_source &P, const taps_packed &q,
+                                                      const taps_side &side, uint32_t rank,
+                                                      const taps_levels_model &m,
+                                                      const taps_top_row *tab, taps_three &out) {
+    // the target side's levels and dimensions, as in taps_source
+    const taps_b8 axis_of = taps_unnibble(side.axis_of);
+    const taps_b8 dim = taps_map(taps_unnibble(side.dim_of), taps_unnibble(q.owner));
+    const taps_b8 flagged = taps_unnibble(q.place);
+    const taps_b8 place = flagged & taps_all(0x07070707u);
+    const taps_b8 top = taps_map(taps_unnibble(q.end), axis_of) + taps_all(0x7F7F7F7Fu);
+    const taps_b8 room = taps_all(0x80808080u) - taps_map(taps_unnibble(q.width), axis_of);
+
+    // prev[c]: the source level at the position that target level c goes to;
+    // next[p]: the target level that goes to source level p's position.  The
+    // byte differences keep bit 7 set; place + 80 - width has it set when the
+    // position lies past the other side's run.  below_*: the same for the cuts
+    // inside what both sides split (all levels there but the lowest).
+    const taps_b8 high = taps_all(0x80808080u);
+    const taps_b8 past = taps_map(P.room, dim), from = taps_map(P.top, dim) - place;
+    const taps_b8 prev = taps_blend(high, place + past, from);
+    taps_b8 below_c = taps_blend(high, flagged + taps_all(0x01010101u) + past, from);
+    const taps_b8 past_p = taps_map(room, P.dim), from_p = taps_map(top, P.dim) - P.place;
+    const taps_b8 next = taps_blend(high, P.place + past_p, from_p);
+    taps_b8 below_p = taps_blend(high, P.next + past_p, from_p);
+
+    // unification (Table 1): the cuts of both sides, closed under both maps
+    taps_b8 uncut = taps_not_lowest(flagged) & P.uncut;
+    uncut = taps_bitop3<TAPS_AND3>(uncut, taps_map(uncut, below_c), taps_map(uncut, below_p));
+    below_c = taps_map(below_c, below_c);
+    below_p = taps_map(below_p, below_p);
+    uncut = taps_bitop3<TAPS_AND3>(uncut, taps_map(uncut, below_c), taps_map(uncut, below_p));
+    below_c = taps_map(below_c, below_c);
+    below_p = taps_map(below_p, below_p);
+    uncut = taps_bitop3<TAPS_AND3>(uncut, taps_map(uncut, below_c), taps_map(uncut, below_p));
+    const uint32_t tp = m.full & ~(taps_bits(uncut) >> 1);
+    const taps_top_row row = taps_entry<4>(tab, tp);
+    const taps_b8 D = row.d;
+
+    // away: not at the same position on both sides
+    const taps_b8 away = {taps_perm(0xFFFFFFFFu, 0xFFFFFF00u, prev.lo ^ 0x03020100u),
+                          taps_perm(0xFFFFFFFFu, 0xFFFFFF00u, prev.hi ^ 0x07060504u)};
+    const taps_b8 dst = row.tops & taps_in_tensor(rank, dim);
+    const taps_b8 held = taps_bitop3<TAPS_AND3>(row.tops, P.held, away);
+    const taps_b8 unwanted = taps_none(next);   // source positions no target axis goes to
+    // the common start of Algorithm 1 and "rearrange": the first InferSlice
+    const taps_b8 open = taps_map(~held, prev);   // targets no held axis blocks
+    const taps_b8 todo0 = dst & away;
+    const taps_b8 sliced = taps_bitop3<TAPS_A_NOTB_C>(todo0, held, open);
+    const taps_b8 todo = todo0 & ~sliced;
+    const uint32_t G = P.g - taps_sum(D & sliced, 0u);
+
+    // ---- Algorithm 1: the state every axis is moved at, and the axes that
+    // AllToAlls move (taps_alg1_t has the schedule)
+    taps_b8 at, a2a;
+    {
+        // the first closure: movable axes, then those whose targets they free
+        const taps_b8 movers = todo & held;
+        taps_b8 stay = ~(movers & open);
+        const taps_b8 hop1 = taps_bitop3<(TAPS_A | (0xFFu ^ TAPS_B) | TAPS_C)>(prev, movers, open);
+        stay = taps_hop(stay, hop1);
+        const taps_b8 hop2 = taps_map(hop1, hop1);
+        stay = taps_hop(stay, hop2);
+        const taps_b8 hop4 = taps_map(hop2, hop2);
+        stay = taps_hop(stay, hop4);
+        a2a = ~stay;
+        at = taps_all(G * 0x01010101u);
+        taps_b8 left = held & stay, wait = todo & stay;
+        // the slices those moves make possible: at once if the first InferSlice
+        // found something, else with the next pass
+        const taps_b8 freed = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
+        const uint32_t f = taps_sum(D & freed, 0u);
+        const bool now = taps_any(sliced);
+        uint32_t g = now ? G - f : G;
+        // untargeted gathers in producer order; a pending slice follows the first
+        const taps_b8 ug = left & unwanted;
+        const taps_b8 us = taps_map(ug, P.order);
+        taps_b8 e = taps_map(D & ug, P.order);
+        const uint32_t pending = now ? 0u : f;
+        e.lo -= (us.lo & (0u - us.lo)) * pending;
+        e.hi -= (us.lo ? 0u : us.hi & (0u - us.hi)) * pending;
+        const taps_b8 ug_at = taps_map(taps_states(e, g, g), P.rank);
+        at = taps_blend(ug, ug_at, at);
+        wait = wait & ~(freed & taps_all(now || taps_any(ug) ? ~0u : 0u));
+        left = left & ~ug;
+        // AllGatherFirstUndoneDim and a pass, until nothing is held; each round
+        // takes at least one held axis
+        uint32_t hb = taps_bits(taps_map(left, P.order));
+        for (uint32_t it = 0; it < TAPS_D_MAX_LEVELS && hb; ++it) {
+            const uint32_t level = taps_perm(P.order.hi, P.order.lo, taps_ctz(hb) | 0x0C0C0C00u) & 7u;
+            const taps_b8 x = taps_from(0xFFull << (8u * level));
+            at = taps_blend(x, taps_all(g * 0x01010101u), at);
+            g = taps_sum(D & x, g);
+            left = left & ~x;
+            const taps_b8 s1 = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
+            wait = wait & ~s1;
+            g -= taps_sum(D & s1, 0u);
+            // the axes the gathered one's position holds up, directly or not
+            taps_b8 keep = ~x;
+            keep = taps_hop(keep, hop1);
+            keep = taps_hop(keep, hop2);
+            keep = taps_hop(keep, hop4);
+            const taps_b8 moved = left & ~keep;
+            at = taps_blend(moved, taps_all(g * 0x01010101u), at);
+            a2a = a2a | moved;
+            left = left & ~moved;
+            wait = wait & ~moved;
+            if (taps_any(s1)) {
+                const taps_b8 s2 = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
+                wait = wait & ~s2;
+                g -= taps_sum(D & s2, 0u);
+            }
+            hb = taps_bits(taps_map(left, P.order));
+        }
+    }
+
+    // ---- "rearrange": untargeted axes in producer order, then targeted ones
+    taps_b8 at_r;
+    {
+        // a targeted axis whose blocker comes before it
+        const taps_b8 before = taps_none((P.rank + taps_all(0x7F7F7F7Fu)) -
+                                         (taps_map(P.rank, prev) & taps_all(0x0F0F0F0Fu)));
+        const taps_b8 ready = open | taps_bitop3<TAPS_A_NOTB_C>(held, unwanted, before);
+        // sliced straight back when its target is open by then; the others stay
+        // gathered and are sliced, like the axes not held at all, when their
+        // blocker is gathered
+        const taps_b8 kept = taps_bitop3<TAPS_A & (0xFFu ^ (TAPS_B & TAPS_C))>(held, dst, ready);
+        const taps_b8 later = todo & ~ready;
+        const taps_b8 ns = taps_map(next, P.order);
+        const taps_b8 us = taps_none(ns);
+        const taps_b8 plus = taps_map(D & kept, P.order);
+        const taps_b8 minus = taps_map(D & later, ns) & ~us;
+        uint32_t g;
+        const taps_b8 first = taps_states(plus & us, G, g);
+        const taps_b8 then = taps_states((plus & ~us) - minus, g, g);
+        at_r = taps_map(taps_blend(us, first, then), P.rank);
+    }
+
+    // ---- "remove": every axis gathered in producer order
+    const taps_b8 Dh = D & held;
+    uint32_t g_end;
+    const taps_b8 at_m = taps_map(taps_states(taps_map(Dh, P.order), P.g, g_end), P.rank);
+
+    // ---- costs.  An AllToAll of an axis of width w at shard 2^s costs what a
+    // gather at 2^(s - w) does (Eq. 9, Eq. 10), so its state counts w less; the
+    // free levels inside a node, the axis's own among them, divide the link's
+    // share (Algorithm 3).
+    const taps_b8 in_node = Dh & taps_all(0xE0E0E0E0u);
+    const taps_b8 x1 = (at & held) + in_node -
+                       taps_bitop3<TAPS_AND3>(Dh, a2a, taps_all(0x0F0F0F0Fu));
+    const taps_b8 x2 = at_r + in_node, x3 = at_m + in_node;
+    const taps_b8 one = held & taps_all(0x01010101u << m.shift);
+    uint32_t in1 = 0, in2 = 0, out1 = 0, out2 = 0, out3 = 0;
+    uint32_t link1 = 0, link2 = 0, link3 = 0, ct1 = 0, ct2 = 0, ct3 = 0;
+#pragma unroll
+    for (uint32_t l = 0; l < TAPS_D_MAX_LEVELS; ++l) {
+        if (l >= m.n) break;   // uniform
+        const uint32_t b = 8u * (l & 3u);
+        const uint32_t d = l < 4u ? Dh.lo : Dh.hi;
+        const uint32_t y1 = l < 4u ? x1.lo : x1.hi, y2 = l < 4u ? x2.lo : x2.hi;
+        const uint32_t w = (d >> b) & 15u;
+        const uint32_t v1 = taps_bfm(w, (y1 >> b) & 31u), v2 = taps_bfm(w, (y2 >> b) & 31u);
+        if (l < m.n_in) {   // uniform
+            in1 += v1;
+            in2 += v2;
+        } else {
+            const uint32_t y3 = l < 4u ? x3.lo : x3.hi;
+            const uint32_t c = ((l < 4u ? one.lo : one.hi) >> b) & 0xFFu;
+            const uint32_t v3 = taps_bfm(w, (y3 >> b) & 31u);
+            const uint32_t u1 = (y1 >> (b + 5u)) & 7u, u2 = (y2 >> (b + 5u)) & 7u;
+            const uint32_t u3 = (y3 >> (b + 5u)) & 7u;
+            out1 += v1;
+            out2 += v2;
+            out3 += v3;
+            link1 += v1 >> u1;
+            link2 += v2 >> u2;
+            link3 += v3 >> u3;
+            ct1 += c >> u1;
+            ct2 += c >> u2;
+            ct3 += c >> u3;
+        }
+    }
+    // Eq. 14: an AllToAll of the axis across the node boundary keeps its
+    // 2^kap members inside a node off the link
+    if (m.shift && !((tp >> (m.shift - 1u)) & 1u)) {
+        const uint32_t above = tp >> m.shift;
+        const uint32_t s8 = 8u * (m.shift + taps_ctz(above | 0x100u));
+        if (above && ((taps_u64(a2a & held) >> (s8 & 63u)) & 1u)) {
+            const uint32_t d = (uint32_t)(taps_u64(Dh) >> s8) & 0xFFu;
+            const uint32_t x = (uint32_t)(taps_u64(x1) >> s8) & 0xFFu;
+            const uint32_t w = d & 15u, kap = d >> 5, s = x & 31u, u = x >> 5;
+            link1 += (taps_bfm(w - kap, s + kap) >> ((u - kap) & 7u)) - (taps_bfm(w, s) >> u);
+        }
+    }
+    const uint32_t vol_m = (1u << (g_end & 31u)) - (1u << (P.g & 31u));   // telescopes
+    out.c[0] = {(in1 + out1) >> m.shift, in1 >> m.shift, link1, ct1};
+    out.c[1] = {(in2 + out2) >> m.shift, in2 >> m.shift, link2, ct2};
+    out.c[2] = {vol_m >> m.shift, (vol_m - out3) >> m.shift, link3, ct3};
+    const taps_b8 h01 = held & taps_all(0x01010101u);
+    const uint32_t all = taps_sum(h01, 0u), inside = taps_sum(h01 & m.in01, 0u);
+    out.coll = all | ((all - inside) << 8);
+}

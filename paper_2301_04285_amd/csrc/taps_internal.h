@@ -6,6 +6,7 @@
 
 #include "taps.h"
 #include "taps_device.h"
+#include "taps_entry.h"
 
 // Uniform parameters of a table launch.
 struct taps_launch {
@@ -29,6 +30,7 @@ struct taps_edge_params {
     uint32_t paxes;        // nibble d: source op axis of tensor dimension d
     uint32_t caxes;        // nibble d: target op axis of tensor dimension d
     uint32_t pad;
+    taps_side from, to;    // the same two maps for taps_entry.h
 };
 
 // Shared tables: entries [src, src + count) of every array are copied to
@@ -41,24 +43,23 @@ struct taps_copy_task {
 #define TAPS_COPY_CHUNK 2048    // entries per copy task (8 per thread of 256)
 #define TAPS_COPY_DSTS 6        // tables one copy task writes (4-6 measured best, 16 is 20 % slower)
 
-// One wavefront per row segment: producer strategy i of one edge and the
-// consumer strategies [first_col, last_col) of its row, walked 64 at a time.
-// A workgroup holds TAPS_ROWS_PER_BLOCK segments.  A segment builds its
-// producer side once (about 0.15 ms of the 96-layer GPT's launch at two
-// tiles per segment); TAPS_SEG_TILES_LONG tiles amortise that in launches of
-// many segments, and launching the full-length segments before the shorter
-// remainders keeps the longer segments from stretching the end of the launch
-// (1, 2, 4, 8, 16 and 32 tiles measured).  Launches with few segments use
-// TAPS_SEG_TILES_SHORT.  The bandwidth sweep, bound by its four sets of
-// stores per entry, does not use segments: it runs one wavefront per window of
-// TAPS_WIN_TILES aligned 64-entry tiles of the tables (k_edge_costs_sweep_win).
+// The two-class edge kernels run over windows: window w is the 64 T entries
+// [64 T w, 64 T (w + 1)) of the computed tables laid end to end (aligned, so
+// that every store covers whole lines), taken by one wavefront 64 at a time.
 #define TAPS_TILE_COLS 64
+// T: launches with at least taps_set_long_segments_min() windows of
+// TAPS_WINDOW_LONG tiles take those, smaller ones single tiles.
+#define TAPS_WINDOW_LONG 8
+#define TAPS_LONG_SEGS_MIN 32768
+
+// The link-class kernel runs over row segments: one wavefront per producer
+// strategy i of one edge and the consumer strategies [first_col, last_col) of
+// its row, walked 64 at a time, TAPS_ROWS_PER_BLOCK segments per workgroup.
+// Segments of TAPS_SEG_TILES_LONG tiles amortise the producer side in launches
+// of many of them (full-length segments first, the shorter remainders last);
+// launches with few segments use TAPS_SEG_TILES_SHORT.
 #define TAPS_SEG_TILES_LONG 8
 #define TAPS_SEG_TILES_SHORT 2
-#ifndef TAPS_WIN_TILES
-#define TAPS_WIN_TILES 2
-#endif
-#define TAPS_LONG_SEGS_MIN 32768   // long segments only when there are at least this many
 #define TAPS_ROWS_PER_BLOCK 2
 
 // A run of row segments of one edge: every row of the edge's table cut into
@@ -80,34 +81,55 @@ struct taps_row_ref {
     uint32_t last_col;
 };
 
-hipError_t taps_launch_describe(const taps_strategy *s, uint64_t total, taps_desc *desc,
-                                hipStream_t stream);
+hipError_t taps_launch_describe(const taps_strategy *s, uint64_t total, uint32_t n,
+                                taps_packed *desc, hipStream_t stream);
+hipError_t taps_launch_describe_h(const taps_strategy *s, uint64_t total, uint32_t n,
+                                  taps_desc *desc, hipStream_t stream);
 hipError_t taps_launch_node_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
-                                  const taps_desc *desc, uint64_t total, const taps_launch &lp,
+                                  const taps_packed *desc, uint64_t total, const taps_launch &lp,
                                   taps_table out, hipStream_t stream);
-// The edge plan of a launch (device arrays): per-edge constants into params
-// and the row segments of the groups into segs; reverse: the backward tables
-// (source side = the consumer's input map).
+// The edge plan of a launch (device arrays): the constants of the n_edges
+// computed edges (edge computed[k], or k without that list) into params, and
+// the edge that each window starts in.  starts: n_edges + 1 first entries of
+// the computed tables laid end to end; window: entries per window; reverse:
+// the backward tables (source side = the consumer's input map).
 struct taps_plan_args {
     const taps_op *ops;
     const taps_edge *edges;
     const uint64_t *op_offsets;
     const uint64_t *edge_offsets;
-    const taps_seg_group *groups;
+    const uint32_t *computed;
+    const uint64_t *starts;
     taps_edge_params *params;
-    taps_row_ref *segs;
-    uint64_t n_segs;
-    uint32_t n_edges, n_groups, reverse, pad;
+    uint32_t *window_edge;
+    uint64_t n_windows;
+    uint32_t n_edges, window, reverse, pad;
 };
 hipError_t taps_launch_edge_setup(const taps_plan_args &pa, const taps_launch &lp,
                                   hipStream_t stream);
-// max_rank: the largest tensor rank of the launch's edges; up to
-// TAPS_LOW_RANK the kernels are compiled for that many dimensions (fewer
-// registers for the producer side, shorter per-dimension loops).
+// What the two-class edge kernels run over (the plan's results).
+struct taps_windows {
+    const taps_edge_params *params;
+    const uint64_t *starts;
+    const uint32_t *window_edge;
+    uint64_t n_windows, total;   // total: computed entries
+    uint32_t tiles, pad;         // tiles per window
+};
+hipError_t taps_launch_edge_costs(const taps_windows &win, const taps_packed *desc,
+                                  const taps_launch &lp, taps_table out, hipStream_t stream);
+// The row segments of the link-class kernel's groups into segs.
+struct taps_row_plan {
+    const taps_edge *edges;
+    const uint64_t *op_offsets;
+    const taps_seg_group *groups;
+    taps_row_ref *segs;
+    uint64_t n_segs;
+    uint32_t n_groups, pad;
+};
+hipError_t taps_launch_row_plan(const taps_row_plan &pa, hipStream_t stream);
+// max_rank: the largest tensor rank of the launch's edges; up to TAPS_LOW_RANK
+// the link-class kernel is compiled for that many dimensions.
 #define TAPS_LOW_RANK 4
-hipError_t taps_launch_edge_costs(const taps_edge_params *params, const taps_row_ref *rows,
-                                  uint64_t n_rows, const taps_desc *desc, const taps_launch &lp,
-                                  uint32_t max_rank, taps_table out, hipStream_t stream);
 hipError_t taps_launch_memory_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
                                    const taps_strategy *s, uint64_t total, uint64_t *memory,
                                    hipStream_t stream);
@@ -122,14 +144,9 @@ struct taps_sweep {
     double inv_n_binter[TAPS_MAX_SWEEP];
     taps_table out[TAPS_MAX_SWEEP];
 };
-// The sweep over aligned windows of TAPS_WIN_TILES 64-entry tiles of the
-// concatenated tables (eoff: device, n_edges + 1 entry offsets; win_edge:
-// device scratch of one uint32 per window, ceil(total / (64 TAPS_WIN_TILES))).
-hipError_t taps_launch_edge_costs_sweep_win(const taps_edge_params *params, uint32_t n_edges,
-                                            const uint64_t *eoff, uint64_t total,
-                                            uint32_t *win_edge, const taps_desc *desc,
-                                            const taps_launch &lp, uint32_t max_rank,
-                                            const taps_sweep &sw, hipStream_t stream);
+hipError_t taps_launch_edge_costs_sweep(const taps_windows &win, const taps_packed *desc,
+                                        const taps_launch &lp, const taps_sweep &sw,
+                                        hipStream_t stream);
 // One workgroup of k_build_strategies: candidate ranks [first, first +
 // TAPS_BUILD_CHUNK) of operator `op`, of which `count` pass the filter; they
 // are strategies base, base + 1, ... in rank order.
@@ -143,13 +160,13 @@ struct taps_build_chunk {
 // records unless desc / node.t are NULL.
 hipError_t taps_launch_build_strategies(const taps_op *ops, const taps_build_chunk *chunks,
                                         uint32_t n_chunks, uint32_t allowed_cuts,
-                                        const taps_launch &lp, taps_strategy *out, taps_desc *desc,
-                                        taps_table node, hipStream_t stream);
+                                        const taps_launch &lp, taps_strategy *out,
+                                        taps_packed *desc, taps_table node, hipStream_t stream);
 // taps_launch_build_strategies and taps_launch_edge_setup as one launch (the
 // plan needs only the host-counted strategy offsets).
 hipError_t taps_launch_build_front(const taps_build_chunk *chunks, uint32_t n_chunks,
                                    uint32_t allowed_cuts, const taps_launch &lp, taps_strategy *out,
-                                   taps_desc *desc, taps_table node, const taps_plan_args &pa,
+                                   taps_packed *desc, taps_table node, const taps_plan_args &pa,
                                    hipStream_t stream);
 // Link-class hierarchies: the edge and node tables under the classes of H.
 hipError_t taps_launch_edge_costs_h(const taps_edge_params *params, const taps_row_ref *rows,
@@ -157,7 +174,7 @@ hipError_t taps_launch_edge_costs_h(const taps_edge_params *params, const taps_r
                                     uint32_t max_rank, const taps_hier &H, taps_table out,
                                     hipStream_t stream);
 hipError_t taps_launch_node_costs_h(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
-                                    const taps_desc *desc, uint64_t total, uint32_t n,
+                                    const taps_packed *desc, uint64_t total, uint32_t n,
                                     const taps_hier &H, taps_table out, hipStream_t stream);
 // Copies `bytes` (a multiple of 16, below 2^36) from src, fine-grained pinned
 // host memory mapped for the device, to device memory at dst.

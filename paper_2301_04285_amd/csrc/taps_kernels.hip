@@ -7,21 +7,15 @@
 //   k_describe    one thread per strategy: level runs, owners and cuts
 //   k_node_costs  one thread per strategy: the intra-op AllReduces
 //   k_memory_costs one thread per strategy: weight and output shard bytes
-//   k_edge_plan   one thread per edge (its constants), then one thread per
-//                 row segment (its edge, producer strategy and consumer
-//                 range: every edge's full-length segments first, the rows'
-//                 remainders last, longest first)
+//   k_edge_plan   one thread per computed edge (its constants), then one
+//                 thread per window (the edge it starts in)
 //   k_build_front k_build_strategies and k_edge_plan in one launch
-//   k_edge_costs  one wavefront per row segment (one producer strategy,
-//                 uniform: its descriptor sits in scalar registers; 2 or 8
-//                 tiles of 64 consumer strategies, one per lane, the
-//                 next 64 prefetched), TAPS_ROWS_PER_BLOCK segments per workgroup; five
-//                 coalesced SoA stores per entry
-//   k_edge_costs_sweep_win  several bandwidth points: one wavefront per
-//                 aligned 64-entry window of the tables (row by row where a
-//                 window crosses rows), the candidates once per entry, one
-//                 selection and store per point; k_window_edges maps windows
-//                 to edges
+//   k_edge_costs  one wavefront per window of aligned 64-entry tiles of the
+//                 concatenated tables, one entry per lane whatever its row
+//                 (taps_entry.h); whole-line stores
+//   k_edge_costs_sweep  the same at several bandwidth points: the candidates
+//                 once per entry, one selection and store per point
+//   k_edge_costs_h  link classes: one wavefront per row segment (k_row_plan)
 //   k_copy_tables shared tables: one workgroup per chunk of a computed
 //                 table, written to every table that shares it
 //   k_pull        a call's upload, read from pinned host memory
@@ -31,6 +25,8 @@ namespace {
 
 constexpr uint32_t kWave = 64;
 
+// Widths of the unified axes by their tops, copied to LDS by the edge kernels.
+__constant__ taps_top_table kTops = taps_make_tops();
 // Completion counts w(k, s, z) for k, s, z in 0..8 (see taps_completions),
 // evaluated by the compiler.
 __constant__ taps_completion_table kCompletions = taps_make_completions();
@@ -41,18 +37,6 @@ __constant__ taps_width_table kWidths = taps_make_widths();
 // taps_make_expand), copied to LDS by the two-class edge kernels.
 __constant__ taps_a2a_table kA2a = taps_make_a2a();
 __constant__ taps_expand_table kExpand = taps_make_expand();
-
-// The per-workgroup LDS tables of the two-class AllToAll costing: the shard
-// fractions split at the node boundary lam (bytes below lam: in-node tops).
-__device__ inline void fill_a2a_tables(taps_a2a_row *a2a, taps_pair *expand, uint32_t lam) {
-    const uint32_t in_lo = lam >= 4u ? ~0u : (1u << (8u * lam)) - 1u;
-    const uint32_t in_hi = lam <= 4u ? 0u : lam >= 8u ? ~0u : (1u << (8u * (lam - 4u))) - 1u;
-    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) {
-        const uint32_t lo = kA2a.lo[x], hi = kA2a.hi[x];
-        a2a[x] = taps_a2a_row{lo, hi, lo & in_lo, hi & in_hi};
-        expand[x] = taps_pair{kExpand.lo[x], kExpand.hi[x]};
-    }
-}
 
 // The per-workgroup LDS tables of the link-class AllToAll costing: per tops
 // mask, the shard-fraction bytes of the tops in each class (a level's byte
@@ -100,8 +84,14 @@ __device__ inline uint32_t lanes_below(uint64_t mask) {
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// The packed descriptor of the two-class kernels or the link classes' form.
+__device__ inline void put_desc(taps_packed *p, const taps_desc &D, uint32_t n) { *p = taps_pack(D, n); }
+__device__ inline void put_desc(taps_desc *p, const taps_desc &D, uint32_t) { *p = D; }
+
+template <typename Desc>
 __global__ __launch_bounds__(256) void k_describe(const taps_strategy *__restrict__ s,
-                                                  uint64_t total, taps_desc *__restrict__ desc) {
+                                                  uint64_t total, uint32_t n,
+                                                  Desc *__restrict__ desc) {
     const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= total) return;
     const taps_strategy st = s[idx];
@@ -112,7 +102,7 @@ __global__ __launch_bounds__(256) void k_describe(const taps_strategy *__restric
         expo[a] = st.log2_deg[a];
         pos[a] = st.pos[a];
     }
-    desc[idx] = taps_describe(TAPS_D_MAX_AXES, expo, pos);
+    put_desc(desc + idx, taps_describe(TAPS_D_MAX_AXES, expo, pos), n);
 }
 
 // largest k in [0, n) with offsets[k] <= x
@@ -128,13 +118,19 @@ __device__ inline uint32_t find_owner(const uint64_t *offsets, uint32_t n, uint6
     return lo;
 }
 
+__device__ inline uint32_t axis_levels(const taps_packed &D, uint32_t a) { return taps_axis_levels(D, a); }
+__device__ inline uint32_t axis_levels(const taps_desc &D, uint32_t a) {
+    return taps_levels(taps_nib(D.lo, a), taps_nib(D.width, a));
+}
+
+template <typename Desc>
 __device__ inline void node_tensor(taps_acc &c, const taps_op &op, const taps_tensor &t,
-                                   const taps_desc &D, uint32_t full, uint32_t lam) {
+                                   const Desc &D, uint32_t full, uint32_t lam) {
     uint32_t used = 0;
     uint64_t bytes = op.dtype_bytes;
     for (uint32_t d = 0; d < t.rank && d < TAPS_MAX_RANK; ++d) {
         const uint32_t a = t.axis[d] & 7u;
-        used |= taps_levels(taps_nib(D.lo, a), taps_nib(D.width, a));
+        used |= axis_levels(D, a);
         bytes *= (uint64_t)op.axis_len[a];
     }
     taps_allreduce(c, full & ~used, bytes, lam);
@@ -142,12 +138,12 @@ __device__ inline void node_tensor(taps_acc &c, const taps_op &op, const taps_te
 
 __global__ __launch_bounds__(256) void k_node_costs(const taps_op *__restrict__ ops, uint32_t n_ops,
                                                     const uint64_t *__restrict__ offsets,
-                                                    const taps_desc *__restrict__ desc,
+                                                    const taps_packed *__restrict__ desc,
                                                     uint64_t total, taps_launch lp, taps_table out) {
     const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= total) return;
     const taps_op &op = ops[find_owner(offsets, n_ops, idx)];
-    const taps_desc D = desc[idx];
+    const taps_packed D = desc[idx];
     const uint32_t full = taps_low_mask(lp.n);
     taps_acc c;
     taps_acc_zero(c);
@@ -178,8 +174,8 @@ constexpr uint32_t kBuildThreads = TAPS_BUILD_CHUNK;
 // The strategies of one chunk of candidate ranks (a whole workgroup).
 __device__ inline void build_chunk(const taps_build_chunk &ck, const taps_op *__restrict__ ops,
                                    uint32_t allowed_cuts, const taps_launch &lp,
-                                   taps_strategy *__restrict__ out, taps_desc *__restrict__ desc,
-                                   const taps_table &node) {
+                                   taps_strategy *__restrict__ out,
+                                   taps_packed *__restrict__ desc, const taps_table &node) {
     __shared__ uint32_t W[9 * 9 * 9];
     __shared__ uint32_t wave_count[kBuildThreads / kWave];
     const uint32_t tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
@@ -215,7 +211,7 @@ __device__ inline void build_chunk(const taps_build_chunk &ck, const taps_op *__
             st.pos[a] = a < n_axes ? (int8_t)pos[a] : (int8_t)-1;
         }
         out[idx] = st;
-        if (desc) desc[idx] = D;   // uniform: descriptors and node records are optional
+        if (desc) desc[idx] = taps_pack(D, lp.n);   // uniform: descriptors and node records are optional
         if (node.t) {
             taps_acc c;
             taps_acc_zero(c);
@@ -236,7 +232,7 @@ __device__ inline void build_chunk(const taps_build_chunk &ck, const taps_op *__
 __global__ __launch_bounds__(kBuildThreads) void k_build_strategies(
     const taps_op *__restrict__ ops, const taps_build_chunk *__restrict__ chunks,
     uint32_t allowed_cuts, taps_launch lp, taps_strategy *__restrict__ out,
-    taps_desc *__restrict__ desc, taps_table node) {
+    taps_packed *__restrict__ desc, taps_table node) {
     build_chunk(chunks[blockIdx.x], ops, allowed_cuts, lp, out, desc, node);
 }
 
@@ -267,8 +263,9 @@ __global__ __launch_bounds__(256) void k_memory_costs(const taps_op *__restrict_
     memory[idx] = m;
 }
 
-// Per-edge constants of edge e.
-__device__ inline void edge_setup_one(uint32_t e, const taps_plan_args &pa, const taps_launch &lp) {
+// Constants of computed edge k.
+__device__ inline void edge_setup_one(uint32_t k, const taps_plan_args &pa, const taps_launch &lp) {
+    const uint32_t e = pa.computed ? pa.computed[k] : k;
     const taps_edge E = pa.edges[e];
     const taps_op &src = pa.ops[E.src_op];
     const taps_op &dst = pa.ops[E.dst_op];
@@ -295,12 +292,51 @@ __device__ inline void edge_setup_one(uint32_t e, const taps_plan_args &pa, cons
     p.paxes = pa.reverse ? cax : pax;
     p.caxes = pa.reverse ? pax : cax;
     p.pad = 0;
-    pa.params[e] = p;
+    p.from = taps_make_side(p.paxes, T.rank);
+    p.to = taps_make_side(p.caxes, T.rank);
+    pa.params[k] = p;
 }
 
-// Row segment r: its edge, producer strategy and consumer range (from the
-// strategy offsets, so it does not wait for the edge constants).
-__device__ inline void row_map_one(uint64_t r, const taps_plan_args &pa) {
+// The computed edge that holds the first entry of window w.
+__device__ inline void window_one(uint64_t w, const taps_plan_args &pa) {
+    pa.window_edge[w] = find_owner(pa.starts, pa.n_edges, w * pa.window);
+}
+
+// The edge plan in one launch: blocks [0, setup_blocks) set up the edges, the
+// rest map the windows.
+__device__ inline void edge_plan_block(uint32_t b, uint32_t setup_blocks, const taps_plan_args &pa,
+                                       const taps_launch &lp) {
+    if (b < setup_blocks) {
+        const uint32_t e = b * blockDim.x + threadIdx.x;
+        if (e < pa.n_edges) edge_setup_one(e, pa, lp);
+    } else {
+        const uint64_t w = (uint64_t)(b - setup_blocks) * blockDim.x + threadIdx.x;
+        if (w < pa.n_windows) window_one(w, pa);
+    }
+}
+
+__global__ __launch_bounds__(256) void k_edge_plan(taps_plan_args pa, taps_launch lp,
+                                                   uint32_t setup_blocks) {
+    edge_plan_block(blockIdx.x, setup_blocks, pa, lp);
+}
+
+// The front of a single-call build: the strategy chunks, then the edge plan
+// (which needs only the strategy offsets, which the host counted), in one
+// launch.
+__global__ __launch_bounds__(kBuildThreads) void k_build_front(
+    const taps_build_chunk *__restrict__ chunks, uint32_t n_chunks, uint32_t allowed_cuts,
+    taps_launch lp, taps_strategy *__restrict__ out, taps_packed *__restrict__ desc,
+    taps_table node, taps_plan_args pa, uint32_t setup_blocks) {
+    if (blockIdx.x < n_chunks)
+        build_chunk(chunks[blockIdx.x], pa.ops, allowed_cuts, lp, out, desc, node);
+    else
+        edge_plan_block(blockIdx.x - n_chunks, setup_blocks, pa, lp);
+}
+
+// Row segment r of the link classes' launch: its edge, producer strategy and
+// consumer range (from the strategy offsets, so it does not wait for the edge
+// constants).
+__device__ inline void row_map_one(uint64_t r, const taps_row_plan &pa) {
     // the last group starting at or before r (groups[0].start == 0)
     uint32_t lo = 0, hi = pa.n_groups - 1;
     while (lo < hi) {
@@ -312,221 +348,173 @@ __device__ inline void row_map_one(uint64_t r, const taps_plan_args &pa) {
     }
     const taps_seg_group G = pa.groups[lo];
     const taps_edge E = pa.edges[G.edge];
-    const uint32_t from = pa.reverse ? E.dst_op : E.src_op, to = pa.reverse ? E.src_op : E.dst_op;
-    const uint32_t nd = (uint32_t)(pa.op_offsets[to + 1] - pa.op_offsets[to]);
+    const uint32_t nd = (uint32_t)(pa.op_offsets[E.dst_op + 1] - pa.op_offsets[E.dst_op]);
     const uint64_t k = r - G.start;
     taps_row_ref ref;
     ref.edge = G.edge;
-    ref.strategy = (uint32_t)(pa.op_offsets[from] + k / G.per_row);
+    ref.strategy = (uint32_t)(pa.op_offsets[E.src_op] + k / G.per_row);
     ref.first_col = G.first_col + (uint32_t)(k % G.per_row) * G.cols;
     ref.last_col = nd - ref.first_col < G.cols ? nd : ref.first_col + G.cols;
     pa.segs[r] = ref;
 }
 
-// The edge plan in one launch: blocks [0, setup_blocks) set up the edges, the
-// rest map the row segments.
-__global__ __launch_bounds__(256) void k_edge_plan(taps_plan_args pa, taps_launch lp,
-                                                   uint32_t setup_blocks) {
-    if (blockIdx.x < setup_blocks) {
-        const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-        if (e < pa.n_edges) edge_setup_one(e, pa, lp);
+__global__ __launch_bounds__(256) void k_row_plan(taps_row_plan pa) {
+    const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < pa.n_segs) row_map_one(r, pa);
+}
+
+// ---------------------------------------------------------------------------
+// The two-class edge kernels.
+//
+// Wavefront w takes window w, one 64-entry tile at a time, lane l entry l of
+// the tile: its edge is uniform (a tile that runs into the next edge is taken
+// in two passes), its row and column are its own.  Every store covers whole
+// 128-byte lines, and rows shorter than a wavefront leave no lane idle.  The
+// source side of a lane's row is made again only in tiles where a lane's row
+// changes.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kWindowsPerBlock = 4;
+
+// A lane's row and column; `mul`: how often nd < 64 goes into up to 127.
+struct cell {
+    uint32_t i, j;
+};
+__device__ inline uint32_t row_multiplier(uint32_t nd) { return 65535u / nd + 1u; }
+__device__ inline void wrap(cell &c, uint32_t nd, uint32_t mul) {
+    if (nd >= kWave) {   // uniform; j < nd + 64
+        const uint32_t over = c.j >= nd ? 1u : 0u;
+        c.i += over;
+        c.j -= over ? nd : 0u;
     } else {
-        const uint64_t r = (uint64_t)(blockIdx.x - setup_blocks) * blockDim.x + threadIdx.x;
-        if (r < pa.n_segs) row_map_one(r, pa);
+        const uint32_t q = (c.j * mul) >> 16;
+        c.i += q;
+        c.j -= q * nd;
     }
 }
 
-// The front of a single-call build: the strategy chunks, then the edge plan
-// (the edge setup and the row map need only the strategy offsets, which the
-// host counted), in one launch.
-__global__ __launch_bounds__(kBuildThreads) void k_build_front(
-    const taps_build_chunk *__restrict__ chunks, uint32_t n_chunks, uint32_t allowed_cuts,
-    taps_launch lp, taps_strategy *__restrict__ out, taps_desc *__restrict__ desc,
-    taps_table node, taps_plan_args pa, uint32_t setup_blocks) {
-    if (blockIdx.x < n_chunks) {
-        build_chunk(chunks[blockIdx.x], pa.ops, allowed_cuts, lp, out, desc, node);
-        return;
-    }
-    const uint32_t b = blockIdx.x - n_chunks;
-    if (b < setup_blocks) {
-        const uint32_t e = b * blockDim.x + threadIdx.x;
-        if (e < pa.n_edges) edge_setup_one(e, pa, lp);
-    } else {
-        const uint64_t r = (uint64_t)(b - setup_blocks) * blockDim.x + threadIdx.x;
-        if (r < pa.n_segs) row_map_one(r, pa);
-    }
-}
-
-// R: the launch's tensors have rank R at most; Narrow: both reduced
-// bandwidths are below 2^32 (64-bit keys), so the other order is not compiled.
-template <uint32_t R, bool Narrow>
-__global__ __launch_bounds__(TAPS_TILE_COLS *TAPS_ROWS_PER_BLOCK) void k_edge_costs(
-    const taps_edge_params *__restrict__ params, const taps_row_ref *__restrict__ rows,
-    uint32_t n_segs, const taps_desc *__restrict__ desc, taps_launch lp, taps_table out) {
-    __shared__ uint8_t rank_tab[TAPS_ROWS_PER_BLOCK][256];
-    __shared__ uint32_t width_tab[256];
-    __shared__ taps_a2a_row a2a_tab[256];
-    __shared__ taps_pair expand_tab[256];
-    const uint32_t lane = threadIdx.x % TAPS_TILE_COLS;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / TAPS_TILE_COLS);
-    const uint32_t r = blockIdx.x * TAPS_ROWS_PER_BLOCK + wave;
-    const bool live = r < n_segs;
-    const taps_row_ref ref = rows[live ? r : 0u];
-    const taps_edge_params E = params[ref.edge];
-    __builtin_assume(E.rank <= R);   // the launch's tensors have rank R at most
-    const taps_desc Dp = desc[ref.strategy];
-    const uint32_t i = ref.strategy - E.src_base;
-    taps_row P;
-    taps_make_row(P, Dp, E.paxes, E.rank, lp.n, lp.lam);
-    taps_fill_rank_table(P, rank_tab[wave], lane, TAPS_TILE_COLS);
-    fill_a2a_tables(a2a_tab, expand_tab, lp.lam);
-    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) width_tab[x] = kWidths.v[x];
+// Emit(E, v, r): stores the entry of an edge with constants E at entry v of
+// the computed tables, from its candidates r.
+template <typename Emit>
+__device__ inline void run_window(const taps_windows &win, const taps_packed *__restrict__ desc,
+                                  const taps_launch &lp, const Emit &emit) {
+    __shared__ taps_top_row tops[256];
+    const taps_levels_model m = taps_make_levels(lp.n, lp.lam);
+    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) tops[x] = taps_make_top_row(kTops, x, m);
     __syncthreads();
-    if (!live) return;
-    P.to_rank = rank_tab[wave];
-    P.widths = width_tab;
-    P.a2a = a2a_tab;
-    P.expand = expand_tab;
-    taps_keys K;
-    K.b_inter_red = lp.b_inter_red;
-    K.b_intra_red = lp.b_intra_red;
-    K.narrow = Narrow;
-    // the row's records start here; lane j writes entry j
-    const uint64_t row_out = E.out_offset + (uint64_t)i * E.nd;
-    const taps_desc *col = desc + E.dst_base;
-    const uint32_t c0 = ref.first_col;
-    const uint32_t c1 = ref.last_col;
-    // consumer descriptors one tile ahead
-    taps_desc next = col[c0 + lane < c1 ? c0 + lane : c0];
-    for (uint32_t j0 = c0; j0 < c1; j0 += TAPS_TILE_COLS) {
-        const taps_desc cur = next;
-        const uint32_t j = j0 + lane;
-        const uint32_t jn = j + TAPS_TILE_COLS;
-        if (jn < c1) next = col[jn];
-        if (j < c1) {
-            taps_col Q;
-            taps_make_col(Q, cur, E.caxes, E.rank);
-            const taps_entry_out o = taps_entry_finish(taps_edge_select(P, Q, K), E.scale);
-            store_entry(out, row_out, j, o, o.ok ? o.meta : 0xFFFFFFFFu);
+    const uint32_t lane = threadIdx.x % kWave;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint64_t w = (uint64_t)blockIdx.x * kWindowsPerBlock + wave;
+    if (w >= win.n_windows) return;
+    const uint64_t span = (uint64_t)win.tiles * kWave;
+    const uint64_t begin = w * span;
+    const uint64_t end = win.total - begin < span ? win.total : begin + span;
+    uint32_t e = win.window_edge[w];
+    taps_edge_params E = win.params[e];
+    uint64_t e_end = win.starts[e + 1u];
+    uint32_t mul = row_multiplier(E.nd);
+    const uint64_t local = begin - win.starts[e];   // below ns * nd
+    cell c;
+    c.i = (uint32_t)(local / E.nd);
+    c.j = (uint32_t)(local % E.nd) + lane;
+    wrap(c, E.nd, mul);
+    taps_source P = {};
+    uint32_t row = ~0u;   // the row P holds
+    for (uint64_t v0 = begin; v0 < end; v0 += kWave) {
+        const uint64_t tile_end = end - v0 < kWave ? end : v0 + kWave;
+        uint32_t first = 0;   // lanes below this are done
+        for (;;) {            // uniform: one edge per pass
+            const uint32_t last = (uint32_t)((e_end < tile_end ? e_end : tile_end) - v0);
+            const bool mine = lane >= first && lane < last;
+            const taps_packed q = desc[E.dst_base + (mine ? c.j : 0u)];
+            if (__any(mine && c.i != row)) {
+                P = taps_make_source(desc[E.src_base + (mine ? c.i : 0u)], E.from, E.rank, m);
+                row = mine ? c.i : ~0u;
+            }
+            if (mine) {
+                taps_three r;
+                taps_three_candidates(P, q, E.to, E.rank, m, tops, r);
+                emit(E, v0 - win.starts[e] + E.out_offset, lane, r);
+            }
+            if (e_end >= tile_end) break;
+            first = last;
+            ++e;
+            E = win.params[e];
+            e_end = win.starts[e + 1u];
+            mul = row_multiplier(E.nd);
+            c.i = 0u;
+            c.j = lane - first;   // lanes below `first` stay out of this edge's passes
+            if (lane >= first) wrap(c, E.nd, mul);
+            row = ~0u;
         }
+        if (e_end == tile_end && tile_end < end) {   // the next tile starts an edge
+            ++e;
+            E = win.params[e];
+            e_end = win.starts[e + 1u];
+            mul = row_multiplier(E.nd);
+            c.i = 0u;
+            c.j = lane;
+            row = ~0u;
+        } else {
+            if (lane < first) {   // entered the edge in this tile: continue as its lanes do
+                c.i = 0u;
+                c.j = lane - first;
+            }
+            c.j += kWave;
+        }
+        wrap(c, E.nd, mul);
     }
+}
+
+// Selection among the candidates under one bandwidth point's keys (ties go to
+// the earlier candidate), scaled.
+__device__ inline taps_entry_out select_entry(const taps_three &r, const taps_keys &K,
+                                              const taps_scaler &S) {
+    taps_cands k;
+    k.c[0] = r.c[0];
+    k.c[1] = r.c[1];
+    k.c[2] = r.c[2];
+    k.vmin = r.c[1].vol < r.c[0].vol ? r.c[1].vol : r.c[0].vol;
+    k.vmin = r.c[2].vol < k.vmin ? r.c[2].vol : k.vmin;
+    k.coll = r.coll;
+    k.has_rearrange = true;
+    k.ok = true;
+    return taps_entry_finish(taps_pick_for(k, K), S);
+}
+
+// Narrow: both reduced bandwidths are below 2^32 (64-bit keys).
+template <bool Narrow>
+__global__ __launch_bounds__(256) void k_edge_costs(taps_windows win,
+                                                    const taps_packed *__restrict__ desc,
+                                                    taps_launch lp, taps_table out) {
+    const taps_keys K = {lp.b_inter_red, lp.b_intra_red, Narrow};
+    run_window(win, desc, lp, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
+                                  const taps_three &r) {
+        const taps_entry_out o = select_entry(r, K, E.scale);
+        store_entry(out, at, lane, o, o.meta);
+    });
 }
 
 // Several bandwidth points: the candidates of each entry are costed once and
 // selected, scaled and stored once per point.
-//
-// The sweep runs over aligned windows: wavefront w handles the entries
-// [64 T w, 64 T (w + 1)) of the concatenated tables (T = TAPS_WIN_TILES), one
-// 64-entry tile at a time (lane l entry 64 t + l of the tile), so every store
-// covers whole 128-byte lines (store-only kernels of the sweep's four tables:
-// 5.75 TB/s this way against 2.7-3.4 TB/s for row segments that start inside a
-// line).  A tile that crosses rows (or edges) is taken row by row; the
-// wavefront builds a row's producer side once and keeps it while the row
-// continues into the next tile.  win_edge[w] is the edge holding entry 64 T w.
-__global__ void k_window_edges(const uint64_t *__restrict__ eoff, uint32_t n_edges,
-                               uint64_t n_windows, uint32_t *__restrict__ win_edge) {
-    const uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= n_windows) return;
-    const uint64_t g = w * (TAPS_TILE_COLS * TAPS_WIN_TILES);
-    // the last edge e with eoff[e] <= g (edges without entries share an offset
-    // with the next one, so this is the edge that holds g)
-    uint32_t lo = 0, hi = n_edges;   // eoff[lo] <= g < eoff[hi]
-    while (hi - lo > 1u) {
-        const uint32_t mid = (lo + hi) / 2u;
-        if (eoff[mid] <= g) lo = mid; else hi = mid;
-    }
-    win_edge[w] = lo;
-}
-
-template <uint32_t R, bool Narrow>
-__global__ __launch_bounds__(TAPS_TILE_COLS *TAPS_ROWS_PER_BLOCK) void k_edge_costs_sweep_win(
-    const taps_edge_params *__restrict__ params, uint32_t n_edges,
-    const uint32_t *__restrict__ win_edge, uint64_t n_windows, uint64_t total,
-    const taps_desc *__restrict__ desc, taps_launch lp, taps_sweep sw) {
-    __shared__ uint8_t rank_tab[TAPS_ROWS_PER_BLOCK][256];
-    __shared__ uint32_t width_tab[256];
-    __shared__ taps_a2a_row a2a_tab[256];
-    __shared__ taps_pair expand_tab[256];
-    const uint32_t lane = threadIdx.x % TAPS_TILE_COLS;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / TAPS_TILE_COLS);
-    const uint64_t w = (uint64_t)blockIdx.x * TAPS_ROWS_PER_BLOCK + wave;
-    fill_a2a_tables(a2a_tab, expand_tab, lp.lam);
-    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) width_tab[x] = kWidths.v[x];
-    __syncthreads();
-    if (w >= n_windows) return;
-    taps_keys any;
-    any.b_inter_red = sw.b_inter_red[0];
-    any.b_intra_red = sw.b_intra_red[0];
-    any.narrow = sw.narrow[0] != 0;
-    // the window: TAPS_WIN_TILES aligned tiles of 64 entries, [g_begin, g_end)
-    const uint64_t g_begin = w * (TAPS_TILE_COLS * TAPS_WIN_TILES);
-    const uint64_t g_end = total - g_begin < TAPS_TILE_COLS * TAPS_WIN_TILES
-                               ? total : g_begin + TAPS_TILE_COLS * TAPS_WIN_TILES;
-    uint32_t e = win_edge[w];
-    taps_edge_params E = params[e];
-    const uint64_t local = g_begin - E.out_offset;   // below ns * nd
-    uint32_t i = (uint32_t)(local / E.nd), j0 = (uint32_t)(local % E.nd);
-    taps_row P;
-    bool built = false;   // P (and this wavefront's rank table) hold row i of edge e
-    for (uint64_t g0 = g_begin; g0 < g_end; g0 += TAPS_TILE_COLS) {
-        const uint32_t n_here = (uint32_t)(g_end - g0 < TAPS_TILE_COLS ? g_end - g0 : TAPS_TILE_COLS);
-        uint32_t done = 0;   // lanes below this are handled
-        while (done < n_here) {   // uniform: one row of one edge per pass
-            __builtin_assume(E.rank <= R);
-            const uint32_t len = n_here - done < E.nd - j0 ? n_here - done : E.nd - j0;
-            if (len == 0) break;   // (cannot happen: entries remain only in edges that hold them)
-            if (!built) {
-                taps_make_row(P, desc[E.src_base + i], E.paxes, E.rank, lp.n, lp.lam);
-                // the row's producer-order table, written and read by this wavefront only
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                taps_fill_rank_table(P, rank_tab[wave], lane, TAPS_TILE_COLS);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                P.to_rank = rank_tab[wave];
-                P.widths = width_tab;
-                P.a2a = a2a_tab;
-                P.expand = expand_tab;
-                built = true;
-            }
-            if (lane >= done && lane < done + len) {
-                const uint32_t j = j0 + (lane - done);
-                taps_col Q;
-                taps_make_col(Q, desc[E.dst_base + j], E.caxes, E.rank);
-                const taps_cands cands = taps_edge_candidates(P, Q, any);
-                for (uint32_t k = 0; k < sw.count; ++k) {
-                    taps_keys K;
-                    K.b_inter_red = sw.b_inter_red[k];
-                    K.b_intra_red = sw.b_intra_red[k];
-                    K.narrow = Narrow || sw.narrow[k] != 0;   // Narrow: 64-bit keys at every point
-                    const taps_scaler S = taps_make_scaler(E.scale.tbytes, sw.inv_n_bintra[k],
-                                                           sw.inv_n_binter[k]);
-                    const taps_entry_out o = taps_entry_finish(taps_pick_for(cands, K), S);
-                    store_entry(sw.out[k], g0, lane, o, o.ok ? o.meta : 0xFFFFFFFFu);
-                }
-            }
-            done += len;
-            j0 += len;
-            // the row is done and entries remain in the window: the next row, or
-            // the first row of the next edge with entries
-            if (j0 == E.nd && g0 + done < g_end) {
-                j0 = 0;
-                built = false;
-                if (++i == E.ns) {
-                    i = 0;
-                    do {
-                        ++e;
-                        E = params[e];
-                    } while (e + 1u < n_edges && (uint64_t)E.ns * E.nd == 0u);
-                }
-            }
+template <bool Narrow>
+__global__ __launch_bounds__(256) void k_edge_costs_sweep(taps_windows win,
+                                                          const taps_packed *__restrict__ desc,
+                                                          taps_launch lp, taps_sweep sw) {
+    run_window(win, desc, lp, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
+                                  const taps_three &r) {
+        for (uint32_t k = 0; k < sw.count; ++k) {
+            // Narrow: 64-bit keys at every point
+            const taps_keys K = {sw.b_inter_red[k], sw.b_intra_red[k], Narrow || sw.narrow[k] != 0};
+            const taps_scaler S =
+                taps_make_scaler(E.scale.tbytes, sw.inv_n_bintra[k], sw.inv_n_binter[k]);
+            const taps_entry_out o = select_entry(r, K, S);
+            store_entry(sw.out[k], at, lane, o, o.meta);
         }
-    }
+    });
 }
 
-// Link-class hierarchies: as k_edge_costs, each entry selected and scaled
-// under the classes of H.
+// Link-class hierarchies: one wavefront per row segment, each entry selected and
+// scaled under the classes of H.
 // C: the hierarchy's number of classes.
 template <uint32_t R, uint32_t C>
 __global__ __launch_bounds__(TAPS_TILE_COLS *TAPS_ROWS_PER_BLOCK) void k_edge_costs_h(
@@ -572,13 +560,13 @@ __global__ __launch_bounds__(TAPS_TILE_COLS *TAPS_ROWS_PER_BLOCK) void k_edge_co
 __global__ __launch_bounds__(256) void k_node_costs_h(const taps_op *__restrict__ ops,
                                                       uint32_t n_ops,
                                                       const uint64_t *__restrict__ offsets,
-                                                      const taps_desc *__restrict__ desc,
+                                                      const taps_packed *__restrict__ desc,
                                                       uint64_t total, uint32_t n, taps_hier H,
                                                       taps_table out) {
     const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= total) return;
     const taps_op &op = ops[find_owner(offsets, n_ops, idx)];
-    const taps_desc D = desc[idx];
+    const taps_packed D = desc[idx];
     const uint32_t full = taps_low_mask(n);
     taps_acch c = {0, 0, 0, 0, 0, 0, 0, 0};
     auto tensor = [&](const taps_tensor &t) {
@@ -586,7 +574,7 @@ __global__ __launch_bounds__(256) void k_node_costs_h(const taps_op *__restrict_
         uint64_t bytes = op.dtype_bytes;
         for (uint32_t d = 0; d < t.rank && d < TAPS_MAX_RANK; ++d) {
             const uint32_t a = t.axis[d] & 7u;
-            used |= taps_levels(taps_nib(D.lo, a), taps_nib(D.width, a));
+            used |= axis_levels(D, a);
             bytes *= (uint64_t)op.axis_len[a];
         }
         taps_allreduce_h(c, full & ~used, bytes, H);
@@ -680,16 +668,24 @@ inline uint32_t blocks_for(uint64_t n, uint32_t per) { return (uint32_t)((n + pe
 
 }  // namespace
 
-hipError_t taps_launch_describe(const taps_strategy *s, uint64_t total, taps_desc *desc,
-                                hipStream_t stream) {
+hipError_t taps_launch_describe(const taps_strategy *s, uint64_t total, uint32_t n,
+                                taps_packed *desc, hipStream_t stream) {
     if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_describe, dim3(blocks_for(total, 256)), dim3(256), 0, stream, s, total,
-                       desc);
+    hipLaunchKernelGGL(k_describe<taps_packed>, dim3(blocks_for(total, 256)), dim3(256), 0, stream,
+                       s, total, n, desc);
+    return hipGetLastError();
+}
+
+hipError_t taps_launch_describe_h(const taps_strategy *s, uint64_t total, uint32_t n,
+                                  taps_desc *desc, hipStream_t stream) {
+    if (total == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_describe<taps_desc>, dim3(blocks_for(total, 256)), dim3(256), 0, stream,
+                       s, total, n, desc);
     return hipGetLastError();
 }
 
 hipError_t taps_launch_node_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
-                                  const taps_desc *desc, uint64_t total, const taps_launch &lp,
+                                  const taps_packed *desc, uint64_t total, const taps_launch &lp,
                                   taps_table out, hipStream_t stream) {
     if (total == 0) return hipSuccess;
     hipLaunchKernelGGL(k_node_costs, dim3(blocks_for(total, 256)), dim3(256), 0, stream, ops,
@@ -710,64 +706,47 @@ hipError_t taps_launch_edge_setup(const taps_plan_args &pa, const taps_launch &l
                                   hipStream_t stream) {
     if (pa.n_edges == 0) return hipSuccess;
     const uint32_t setup_blocks = blocks_for(pa.n_edges, 256);
-    const uint64_t map_blocks = pa.n_groups ? blocks_for(pa.n_segs, 256) : 0;
-    hipLaunchKernelGGL(k_edge_plan, dim3((uint32_t)(setup_blocks + map_blocks)), dim3(256), 0,
-                       stream, pa, lp, setup_blocks);
+    const uint32_t map_blocks = blocks_for(pa.n_windows, 256);
+    hipLaunchKernelGGL(k_edge_plan, dim3(setup_blocks + map_blocks), dim3(256), 0, stream, pa, lp,
+                       setup_blocks);
     return hipGetLastError();
 }
 
-hipError_t taps_launch_edge_costs(const taps_edge_params *params, const taps_row_ref *segs,
-                                  uint64_t n_segs, const taps_desc *desc, const taps_launch &lp,
-                                  uint32_t max_rank, taps_table out, hipStream_t stream) {
-    if (n_segs == 0) return hipSuccess;
-    const dim3 grid(blocks_for(n_segs, TAPS_ROWS_PER_BLOCK)), block(TAPS_TILE_COLS * TAPS_ROWS_PER_BLOCK);
-    const bool low = max_rank <= TAPS_LOW_RANK, narrow = lp.narrow != 0;
-    if (low && narrow)
-        hipLaunchKernelGGL((k_edge_costs<TAPS_LOW_RANK, true>), grid, block, 0, stream, params,
-                           segs, (uint32_t)n_segs, desc, lp, out);
-    else if (low)
-        hipLaunchKernelGGL((k_edge_costs<TAPS_LOW_RANK, false>), grid, block, 0, stream, params,
-                           segs, (uint32_t)n_segs, desc, lp, out);
-    else if (narrow)
-        hipLaunchKernelGGL((k_edge_costs<TAPS_D_MAX_RANK, true>), grid, block, 0, stream, params,
-                           segs, (uint32_t)n_segs, desc, lp, out);
+hipError_t taps_launch_row_plan(const taps_row_plan &pa, hipStream_t stream) {
+    if (pa.n_segs == 0 || pa.n_groups == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_row_plan, dim3(blocks_for(pa.n_segs, 256)), dim3(256), 0, stream, pa);
+    return hipGetLastError();
+}
+
+hipError_t taps_launch_edge_costs(const taps_windows &win, const taps_packed *desc,
+                                  const taps_launch &lp, taps_table out, hipStream_t stream) {
+    if (win.n_windows == 0) return hipSuccess;
+    const dim3 grid(blocks_for(win.n_windows, kWindowsPerBlock)), block(kWave * kWindowsPerBlock);
+    if (lp.narrow)
+        hipLaunchKernelGGL(k_edge_costs<true>, grid, block, 0, stream, win, desc, lp, out);
     else
-        hipLaunchKernelGGL((k_edge_costs<TAPS_D_MAX_RANK, false>), grid, block, 0, stream, params,
-                           segs, (uint32_t)n_segs, desc, lp, out);
+        hipLaunchKernelGGL(k_edge_costs<false>, grid, block, 0, stream, win, desc, lp, out);
     return hipGetLastError();
 }
 
-hipError_t taps_launch_edge_costs_sweep_win(const taps_edge_params *params, uint32_t n_edges,
-                                            const uint64_t *eoff, uint64_t total,
-                                            uint32_t *win_edge, const taps_desc *desc,
-                                            const taps_launch &lp, uint32_t max_rank,
-                                            const taps_sweep &sw, hipStream_t stream) {
-    if (total == 0) return hipSuccess;
-    const uint64_t span = TAPS_TILE_COLS * TAPS_WIN_TILES;
-    const uint64_t n_windows = (total + span - 1) / span;
-    hipLaunchKernelGGL(k_window_edges, dim3(blocks_for(n_windows, 256)), dim3(256), 0, stream, eoff,
-                       n_edges, n_windows, win_edge);
-    const hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    const dim3 grid(blocks_for(n_windows, TAPS_ROWS_PER_BLOCK)), block(TAPS_TILE_COLS * TAPS_ROWS_PER_BLOCK);
+hipError_t taps_launch_edge_costs_sweep(const taps_windows &win, const taps_packed *desc,
+                                        const taps_launch &lp, const taps_sweep &sw,
+                                        hipStream_t stream) {
+    if (win.n_windows == 0) return hipSuccess;
+    const dim3 grid(blocks_for(win.n_windows, kWindowsPerBlock)), block(kWave * kWindowsPerBlock);
     bool narrow = true;
     for (uint32_t k = 0; k < sw.count; ++k) narrow = narrow && sw.narrow[k] != 0;
-    const bool low = max_rank <= TAPS_LOW_RANK;
-#define TAPS_WIN_LAUNCH(RR, NN)                                                                  \
-    hipLaunchKernelGGL((k_edge_costs_sweep_win<RR, NN>), grid, block, 0, stream, params, n_edges, \
-                       win_edge, n_windows, total, desc, lp, sw)
-    if (low && narrow) TAPS_WIN_LAUNCH(TAPS_LOW_RANK, true);
-    else if (low) TAPS_WIN_LAUNCH(TAPS_LOW_RANK, false);
-    else if (narrow) TAPS_WIN_LAUNCH(TAPS_D_MAX_RANK, true);
-    else TAPS_WIN_LAUNCH(TAPS_D_MAX_RANK, false);
-#undef TAPS_WIN_LAUNCH
+    if (narrow)
+        hipLaunchKernelGGL(k_edge_costs_sweep<true>, grid, block, 0, stream, win, desc, lp, sw);
+    else
+        hipLaunchKernelGGL(k_edge_costs_sweep<false>, grid, block, 0, stream, win, desc, lp, sw);
     return hipGetLastError();
 }
 
 hipError_t taps_launch_build_strategies(const taps_op *ops, const taps_build_chunk *chunks,
                                         uint32_t n_chunks, uint32_t allowed_cuts,
-                                        const taps_launch &lp, taps_strategy *out, taps_desc *desc,
-                                        taps_table node, hipStream_t stream) {
+                                        const taps_launch &lp, taps_strategy *out,
+                                        taps_packed *desc, taps_table node, hipStream_t stream) {
     if (n_chunks == 0) return hipSuccess;
     hipLaunchKernelGGL(k_build_strategies, dim3(n_chunks), dim3(kBuildThreads), 0, stream, ops,
                        chunks, allowed_cuts, lp, out, desc, node);
@@ -776,14 +755,13 @@ hipError_t taps_launch_build_strategies(const taps_op *ops, const taps_build_chu
 
 hipError_t taps_launch_build_front(const taps_build_chunk *chunks, uint32_t n_chunks,
                                    uint32_t allowed_cuts, const taps_launch &lp, taps_strategy *out,
-                                   taps_desc *desc, taps_table node, const taps_plan_args &pa,
+                                   taps_packed *desc, taps_table node, const taps_plan_args &pa,
                                    hipStream_t stream) {
-    const uint32_t setup_blocks = pa.n_edges ? blocks_for(pa.n_edges, 256) : 0;
-    const uint64_t map_blocks = pa.n_groups ? blocks_for(pa.n_segs, 256) : 0;
-    const uint64_t blocks = n_chunks + setup_blocks + map_blocks;
+    const uint32_t setup_blocks = blocks_for(pa.n_edges, 256);
+    const uint32_t blocks = n_chunks + setup_blocks + blocks_for(pa.n_windows, 256);
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_build_front, dim3((uint32_t)blocks), dim3(kBuildThreads), 0, stream,
-                       chunks, n_chunks, allowed_cuts, lp, out, desc, node, pa, setup_blocks);
+    hipLaunchKernelGGL(k_build_front, dim3(blocks), dim3(kBuildThreads), 0, stream, chunks,
+                       n_chunks, allowed_cuts, lp, out, desc, node, pa, setup_blocks);
     return hipGetLastError();
 }
 
@@ -812,7 +790,7 @@ hipError_t taps_launch_edge_costs_h(const taps_edge_params *params, const taps_r
 }
 
 hipError_t taps_launch_node_costs_h(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
-                                    const taps_desc *desc, uint64_t total, uint32_t n,
+                                    const taps_packed *desc, uint64_t total, uint32_t n,
                                     const taps_hier &H, taps_table out, hipStream_t stream) {
     if (total == 0) return hipSuccess;
     hipLaunchKernelGGL(k_node_costs_h, dim3(blocks_for(total, 256)), dim3(256), 0, stream, ops,
