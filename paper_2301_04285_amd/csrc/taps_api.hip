@@ -565,7 +565,8 @@ struct window_plan {
 
 std::atomic<uint64_t> g_long_segs_min{TAPS_LONG_SEGS_MIN};
 
-window_plan plan_windows(const std::vector<uint64_t> &eoff, const std::vector<uint32_t> &rep) {
+window_plan plan_windows(const std::vector<uint64_t> &eoff, const std::vector<uint32_t> &rep,
+                         uint32_t n_points) {
     window_plan p;
     const uint32_t n_edges = (uint32_t)rep.size();
     p.n_edges = n_edges;
@@ -584,8 +585,14 @@ window_plan plan_windows(const std::vector<uint64_t> &eoff, const std::vector<ui
         p.n_edges = (uint32_t)p.edges.size();
     }
     const uint64_t tiles = (p.total + TAPS_TILE_COLS - 1) / TAPS_TILE_COLS;
-    const uint64_t longs = (tiles + TAPS_WINDOW_LONG - 1) / TAPS_WINDOW_LONG;
-    p.tiles = longs >= g_long_segs_min.load(std::memory_order_relaxed) ? TAPS_WINDOW_LONG : 1;
+    const uint64_t most = n_points == 1 ? TAPS_WINDOW_LONG : TAPS_WINDOW_SWEEP;
+    if (tiles / most >= g_long_segs_min.load(std::memory_order_relaxed)) {
+        p.tiles = (uint32_t)most;
+    } else {
+        uint64_t t = 1;   // sqrt(tiles / 2048)
+        while (t < most && (t + 1) * (t + 1) * 2048 <= tiles) ++t;
+        p.tiles = (uint32_t)t;
+    }
     p.n_windows = (tiles + p.tiles - 1) / p.tiles;
     return p;
 }
@@ -645,20 +652,20 @@ uint64_t plan_rows(const taps_graph *graph, const uint64_t *op_offsets,
 // and with shared tables the computed edges and their starts) and the arrays
 // the plan kernel fills.
 taps_windows device_windows(const window_plan &p, uint64_t n_windows, const taps_edge_params *params,
-                            const uint32_t *window_edge, void *dev, const chunk &offsets,
-                            const chunk &starts) {
-    return {params, at<uint64_t>(dev, p.edges.empty() ? offsets : starts), window_edge, n_windows,
-            p.total, p.tiles, 0u};
+                            const uint32_t *window_edge, const taps_top_row *tops, void *dev,
+                            const chunk &offsets, const chunk &starts) {
+    return {params, at<uint64_t>(dev, p.edges.empty() ? offsets : starts), window_edge, tops,
+            n_windows, p.total, p.tiles, 0u};
 }
 
 taps_plan_args device_plan(const window_plan &p, const taps_windows &w, void *dev, const chunk &ops,
                            const chunk &edges, const chunk &op_offsets, const chunk &edge_offsets,
                            const chunk &computed, taps_edge_params *params, uint32_t *window_edge,
-                           bool reverse) {
+                           taps_top_row *tops, bool reverse) {
     return {at<taps_op>(dev, ops), at<taps_edge>(dev, edges), at<uint64_t>(dev, op_offsets),
             at<uint64_t>(dev, edge_offsets),
             p.edges.empty() ? nullptr : at<uint32_t>(dev, computed), w.starts, params, window_edge,
-            w.n_windows, p.n_edges, p.tiles * TAPS_TILE_COLS, reverse ? 1u : 0u, 0u};
+            tops, w.n_windows, p.n_edges, p.tiles * TAPS_TILE_COLS, reverse ? 1u : 0u, 0u};
 }
 
 // Edge tables of one graph at n_points bandwidth points (clusters that differ
@@ -724,7 +731,7 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
     // the link classes' row segments
     std::vector<taps_seg_group> groups;
     const uint64_t n_segs = hier ? plan_rows(graph, op_offsets, groups) : 0;
-    const window_plan win = plan_windows(eoff, rep);
+    const window_plan win = plan_windows(eoff, rep, n_points);
     const uint64_t n_windows = hier ? 0 : win.n_windows;
     // shared tables: every chunk of a computed table is stored into each table sharing it
     std::vector<uint64_t> dst_list;
@@ -753,13 +760,15 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
     if ((st = sc.alloc((void **)&d_params, sizeof(taps_edge_params) * win.n_edges)) != TAPS_OK)
         return st;
     if ((st = sc.alloc((void **)&d_segs, sizeof(taps_row_ref) * n_segs)) != TAPS_OK) return st;
+    taps_top_row *d_tops = nullptr;
     if ((st = sc.alloc((void **)&d_win, sizeof(uint32_t) * n_windows)) != TAPS_OK) return st;
+    if (!hier && (st = sc.alloc((void **)&d_tops, sizeof(taps_top_row) * 256)) != TAPS_OK) return st;
     hipError_t err = hier ? taps_launch_describe_h(strategies, total, lp.n, (taps_desc *)d_desc, stream)
                           : taps_launch_describe(strategies, total, lp.n, (taps_packed *)d_desc, stream);
-    const taps_windows tw = device_windows(win, n_windows, d_params, d_win, dev, ch[3], ch[8]);
+    const taps_windows tw = device_windows(win, n_windows, d_params, d_win, d_tops, dev, ch[3], ch[8]);
     if (err == hipSuccess) {
         const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[7],
-                                              d_params, d_win, reverse);
+                                              d_params, d_win, d_tops, reverse);
         err = taps_launch_edge_setup(pa, lp, stream);
     }
     if (err == hipSuccess && hier)
@@ -1182,7 +1191,7 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
     std::vector<taps_build_chunk> bchunks;
     if ((st = plan_build(graph, lp.n, allowed, offs, bchunks)) != TAPS_OK) return st;
     const uint64_t total = offs[n_ops];
-    const window_plan win = plan_windows(eoff, rep);
+    const window_plan win = plan_windows(eoff, rep, 1);
     std::vector<chunk> ch{{graph->ops, sizeof(taps_op) * n_ops, 0},
                           {graph->edges, sizeof(taps_edge) * n_edges, 0},
                           {offs.data(), sizeof(uint64_t) * (n_ops + 1), 0},
@@ -1197,7 +1206,8 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
         for (const chunk &c : ch) up += align256(c.bytes);
         const size_t need = carve_size(up) + carve_size(sizeof(taps_packed) * total) +
                             carve_size(sizeof(taps_edge_params) * win.n_edges) +
-                            carve_size(sizeof(uint32_t) * win.n_windows);
+                            carve_size(sizeof(uint32_t) * win.n_windows) +
+                            carve_size(sizeof(taps_top_row) * 256);
         if (need > TAPS_NOALLOC_SCRATCH_BYTES)
             return fail(TAPS_ERR_CAPACITY,
                         "this build needs %llu bytes of device workspace; the fixed workspace of "
@@ -1220,15 +1230,18 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
     taps_packed *d_desc = nullptr;
     taps_edge_params *d_params = nullptr;
     uint32_t *d_win = nullptr;
+    taps_top_row *d_tops = nullptr;
     if ((st = ws->carve((void **)&d_desc, sizeof(taps_packed) * total)) != TAPS_OK) return st;
     if ((st = ws->carve((void **)&d_params, sizeof(taps_edge_params) * win.n_edges)) != TAPS_OK)
         return st;
     if ((st = ws->carve((void **)&d_win, sizeof(uint32_t) * win.n_windows)) != TAPS_OK) return st;
+    if ((st = ws->carve((void **)&d_tops, sizeof(taps_top_row) * 256)) != TAPS_OK) return st;
     // the strategies, and the edge plan when there are edge entries, in one launch
     const bool edges_on = eoff[n_edges] > 0;
-    const taps_windows tw = device_windows(win, win.n_windows, d_params, d_win, dev, ch[3], ch[8]);
+    const taps_windows tw = device_windows(win, win.n_windows, d_params, d_win, d_tops, dev, ch[3],
+                                           ch[8]);
     const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[4], d_params,
-                                          d_win, false);
+                                          d_win, d_tops, false);
     hipError_t err = taps_launch_build_front(at<taps_build_chunk>(dev, ch[7]),
                                              (uint32_t)bchunks.size(), allowed, lp, strategies,
                                              d_desc, node, pa, stream);

@@ -14,17 +14,20 @@
 //     unification, the AllToAll closures -- is found by pointer doubling: three
 //     steps cover the at most seven hops, with no loop that would run until the
 //     wavefront's slowest lane is done.
-//   * The state of a sequence is one number G: the shard's exponent in the low
-//     5 bits and the number of free levels inside a node in the upper 3.  A
+//   * The state of a sequence is one byte G: the shard's exponent in the low
+//     bits and the number of free levels inside a node in the upper 3.  A
 //     gather of an axis adds the axis's byte of `D` (its width, and its levels
 //     inside a node << 5), a slice subtracts it.  Where the order of the gathers
 //     is known beforehand ("remove", "rearrange", the untargeted gathers of
 //     Algorithm 1) the states before all of them come from one prefix sum over
 //     bytes in producer order: a multiplication by 0x01010101 per half.
 //   * Each axis held off its target is moved exactly once by every candidate,
-//     so a candidate is described by the state each axis was moved at, and one
-//     pass over the levels costs all three.  Whether a level lies inside a node
-//     is the same for every lane: the pass branches on it uniformly.
+//     so a candidate is described by the state each axis was moved at.  Powers
+//     of two of a byte are a table lookup by v_perm_b32, a gather's volume fits
+//     a byte (its exponent and width add up to at most 8), and the sums over the
+//     axes are byte dot products.  Whether a level lies inside a node is the
+//     same for every lane, so either kind's levels are brought to the low bytes
+//     of one register by a uniform selection.
 #pragma once
 
 #include "taps_device.h"
@@ -121,6 +124,28 @@ __host__ __device__ inline taps_b8 taps_not_lowest(const taps_b8 &x) {
 // c plus the sum of the bytes.
 __host__ __device__ inline uint32_t taps_sum(const taps_b8 &x, uint32_t c) {
     return taps_dot4(x.hi, 0x01010101u, taps_dot4(x.lo, 0x01010101u, c));
+}
+
+// 2^x for bytes x < 8.
+__host__ __device__ inline uint32_t taps_pow2(uint32_t x) {
+    return taps_perm(0x80402010u, 0x08040201u, x);
+}
+
+// Selector of levels l .. l + 3, 0 from `end` on.
+__host__ __device__ inline uint32_t taps_four(uint32_t l, uint32_t end) {
+    const uint32_t idx = 0x03020100u + l * 0x01010101u;
+    const uint32_t k = end - l;   // at least 1
+    const uint32_t keep = k >= 4u ? ~0u : (1u << (8u * k)) - 1u;
+    return (idx & keep) | (0x0C0C0C0Cu & ~keep);
+}
+
+// Whether any lane of the wavefront (on the host: this one) has c.
+__host__ __device__ inline bool taps_wave_any(bool c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __any(c);
+#else
+    return c;
+#endif
 }
 
 // The set as a bit mask.
@@ -222,9 +247,11 @@ struct taps_levels_model {
     uint32_t n;       // levels
     uint32_t full;    // taps_low_mask(n)
     uint32_t n_in;    // levels inside a node
-    uint32_t shift;   // n_in when some level lies outside, else 0: sums are kept << shift, so that
-                      // a link's share is a right shift by the free in-node levels
+    uint32_t shift;   // n_in when some level lies outside, else 0
     taps_b8 in01;     // 01 at the levels inside a node
+    taps_b8 coll;     // an axis's collective at its places in meta: 4, and 128 more outside a node
+    taps_b8 share;    // byte u: 2^(shift - u), the groups that share a node's link when u of its
+                      // levels are free
 };
 
 __host__ __device__ inline taps_levels_model taps_make_levels(uint32_t n, uint32_t lam) {
@@ -235,14 +262,22 @@ __host__ __device__ inline taps_levels_model taps_make_levels(uint32_t n, uint32
     m.shift = lam < n ? lam : 0u;
     m.in01 = taps_from(m.n_in >= 8u ? 0x0101010101010101ull
                                     : 0x0101010101010101ull & ((1ull << (8u * m.n_in)) - 1ull));
+    m.coll = {0x84848484u - m.in01.lo * 0x80u, 0x84848484u - m.in01.hi * 0x80u};
+    uint64_t share = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < 8u; ++u)
+        if (u <= m.shift) share |= (uint64_t)(1u << (m.shift - u)) << (8u * u);
+    m.share = taps_from(share);
     return m;
 }
 
-// By tops mask, in LDS: byte t of d is, for every top t, the width of its axis
-// and (<< 5, when the model has levels outside a node) its levels inside a
-// node; byte t of tops is FF for every top.
+// By tops mask, in LDS.  For every top t, with w the width of its axis and k
+// the axis's levels inside a node (0 when no level lies outside): byte t of d
+// is w + (k << 5), of tops FF, of a2a 256 - 2^(8 - w) (an AllToAll moves all
+// but 2^-w of the shard, Eq. 10), of link 256 - 2^(8 - w + k) (of that, all but
+// what stays inside the nodes, Eq. 14).  0 at the other levels.
 struct taps_top_row {
-    taps_b8 d, tops;
+    taps_b8 d, tops, a2a, link;
 };
 
 // From the axes' widths w (bytes at the tops): an axis inside the node has
@@ -289,7 +324,14 @@ __host__ __device__ inline taps_top_row taps_make_top_row(const taps_top_table &
     const taps_b8 w = {T.w_lo[tp], T.w_hi[tp]};
     // FF where a width (at most 8) is not 0
     const taps_b8 tops = taps_none(w + taps_all(0x7F7F7F7Fu));
-    return {taps_top_bytes(w, tp, m), tops};
+    const taps_b8 d = taps_top_bytes(w, tp, m);
+    // 256 - 2^(8 - x) for x = 1 .. 8 by x - 1
+    const taps_b8 parts = {0xF0E0C080u, 0xFFFEFCF8u};
+    const taps_b8 one = tops & taps_all(0x01010101u);
+    // an axis inside a node sends nothing over the link
+    const taps_b8 out = {tops.lo & ~(m.in01.lo * 0xFFu), tops.hi & ~(m.in01.hi * 0xFFu)};
+    const taps_b8 kap = taps_from((taps_u64(d) >> 5) & 0x0707070707070707ull) & out;
+    return {d, tops, taps_map(parts, w - one) & tops, taps_map(parts, w - one - kap) & out};
 }
 
 // The source side of a row: its levels' dimensions and places, the ends and
@@ -339,7 +381,7 @@ __host__ __device__ inline taps_source taps_make_source(const taps_packed &p, co
     }
     P.order = taps_from(order);
     const uint32_t free_in = m.shift ? m.shift - taps_sum(P.held & m.in01, 0u) : 0u;
-    P.g = ((m.n - used + 8u + m.shift) & 31u) | (free_in << 5);
+    P.g = ((m.n - used) & 15u) | (free_in << 5);
     return P;
 }
 
@@ -350,7 +392,8 @@ __host__ __device__ inline taps_source taps_make_source(const taps_packed &p, co
 // Replace (Algorithm 1), rearrange (the same without AllToAll) and remove.
 struct taps_three {
     taps_fac c[3];
-    uint32_t coll;   // collectives of every candidate (bits 0-7), inter-node ones (8-15)
+    uint32_t coll;   // collectives of every candidate and inter-node ones among them, at their
+                     // places in the record's meta (bits 2 and 7 up)
 };
 
 // One pointer-doubling step of "not reached": x stays FF only where the level
@@ -394,7 +437,7 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     below_p = taps_map(below_p, below_p);
     uncut = taps_bitop3<TAPS_AND3>(uncut, taps_map(uncut, below_c), taps_map(uncut, below_p));
     const uint32_t tp = m.full & ~(taps_bits(uncut) >> 1);
-    const taps_top_row row = taps_entry<4>(tab, tp);
+    const taps_top_row row = taps_entry<5>(tab, tp);
     const taps_b8 D = row.d;
 
     // away: not at the same position on both sides
@@ -424,31 +467,38 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
         const taps_b8 hop4 = taps_map(hop2, hop2);
         stay = taps_hop(stay, hop4);
         a2a = ~stay;
-        at = taps_all(G * 0x01010101u);
+        at = taps_all(G * 0x01010101u) & a2a;
         taps_b8 left = held & stay, wait = todo & stay;
         // the slices those moves make possible: at once if the first InferSlice
         // found something, else with the next pass
-        const taps_b8 freed = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
-        const uint32_t f = taps_sum(D & freed, 0u);
-        const bool now = taps_any(sliced);
-        uint32_t g = now ? G - f : G;
-        // untargeted gathers in producer order; a pending slice follows the first
         const taps_b8 ug = left & unwanted;
-        const taps_b8 us = taps_map(ug, P.order);
-        taps_b8 e = taps_map(D & ug, P.order);
-        const uint32_t pending = now ? 0u : f;
-        e.lo -= (us.lo & (0u - us.lo)) * pending;
-        e.hi -= (us.lo ? 0u : us.hi & (0u - us.hi)) * pending;
-        const taps_b8 ug_at = taps_map(taps_states(e, g, g), P.rank);
-        at = taps_blend(ug, ug_at, at);
-        wait = wait & ~(freed & taps_all(now || taps_any(ug) ? ~0u : 0u));
-        left = left & ~ug;
+        const bool now = taps_any(sliced), gathers = taps_any(ug);
+        uint32_t g = G, pending = 0u;
+        if (taps_wave_any(now | gathers)) {
+            taps_b8 freed = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
+            freed = freed & taps_all(now | gathers ? ~0u : 0u);
+            wait = wait & ~freed;
+            const uint32_t f = taps_sum(D & freed, 0u);
+            g -= now ? f : 0u;
+            pending = now ? 0u : f;
+        }
+        // untargeted gathers in producer order; a pending slice follows the first
+        if (taps_wave_any(gathers)) {
+            const taps_b8 us = taps_map(ug, P.order);
+            taps_b8 e = taps_map(D & ug, P.order);
+            e.lo -= (us.lo & (0u - us.lo)) * pending;
+            e.hi -= (us.lo ? 0u : us.hi & (0u - us.hi)) * pending;
+            const taps_b8 ug_at = taps_map(taps_states(e, g, g), P.rank);
+            at = taps_blend(ug, ug_at, at);
+            left = left & ~ug;
+        }
         // AllGatherFirstUndoneDim and a pass, until nothing is held; each round
         // takes at least one held axis
         uint32_t hb = taps_bits(taps_map(left, P.order));
         for (uint32_t it = 0; it < TAPS_D_MAX_LEVELS && hb; ++it) {
-            const uint32_t level = taps_perm(P.order.hi, P.order.lo, taps_ctz(hb) | 0x0C0C0C00u) & 7u;
-            const taps_b8 x = taps_from(0xFFull << (8u * level));
+            const uint32_t level = taps_perm(P.order.hi, P.order.lo, taps_ctz(hb) * 0x01010101u);
+            const taps_b8 x = {taps_perm(0u, 0xFFu, level ^ 0x03020100u),
+                               taps_perm(0u, 0xFFu, level ^ 0x07060504u)};
             at = taps_blend(x, taps_all(g * 0x01010101u), at);
             g = taps_sum(D & x, g);
             left = left & ~x;
@@ -501,62 +551,75 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     uint32_t g_end;
     const taps_b8 at_m = taps_map(taps_states(taps_map(Dh, P.order), P.g, g_end), P.rank);
 
-    // ---- costs.  An AllToAll of an axis of width w at shard 2^s costs what a
-    // gather at 2^(s - w) does (Eq. 9, Eq. 10), so its state counts w less; the
-    // free levels inside a node, the axis's own among them, divide the link's
-    // share (Algorithm 3).
-    const taps_b8 in_node = Dh & taps_all(0xE0E0E0E0u);
-    const taps_b8 x1 = (at & held) + in_node -
-                       taps_bitop3<TAPS_AND3>(Dh, a2a, taps_all(0x0F0F0F0Fu));
-    const taps_b8 x2 = at_r + in_node, x3 = at_m + in_node;
-    const taps_b8 one = held & taps_all(0x01010101u << m.shift);
-    uint32_t in1 = 0, in2 = 0, out1 = 0, out2 = 0, out3 = 0;
-    uint32_t link1 = 0, link2 = 0, link3 = 0, ct1 = 0, ct2 = 0, ct3 = 0;
-#pragma unroll
-    for (uint32_t l = 0; l < TAPS_D_MAX_LEVELS; ++l) {
-        if (l >= m.n) break;   // uniform
-        const uint32_t b = 8u * (l & 3u);
-        const uint32_t d = l < 4u ? Dh.lo : Dh.hi;
-        const uint32_t y1 = l < 4u ? x1.lo : x1.hi, y2 = l < 4u ? x2.lo : x2.hi;
-        const uint32_t w = (d >> b) & 15u;
-        const uint32_t v1 = taps_bfm(w, (y1 >> b) & 31u), v2 = taps_bfm(w, (y2 >> b) & 31u);
-        if (l < m.n_in) {   // uniform
-            in1 += v1;
-            in2 += v2;
-        } else {
-            const uint32_t y3 = l < 4u ? x3.lo : x3.hi;
-            const uint32_t c = ((l < 4u ? one.lo : one.hi) >> b) & 0xFFu;
-            const uint32_t v3 = taps_bfm(w, (y3 >> b) & 31u);
-            const uint32_t u1 = (y1 >> (b + 5u)) & 7u, u2 = (y2 >> (b + 5u)) & 7u;
-            const uint32_t u3 = (y3 >> (b + 5u)) & 7u;
-            out1 += v1;
-            out2 += v2;
-            out3 += v3;
-            link1 += v1 >> u1;
-            link2 += v2 >> u2;
-            link3 += v3 >> u3;
-            ct1 += c >> u1;
-            ct2 += c >> u2;
-            ct3 += c >> u3;
-        }
-    }
-    // Eq. 14: an AllToAll of the axis across the node boundary keeps its
-    // 2^kap members inside a node off the link
-    if (m.shift && !((tp >> (m.shift - 1u)) & 1u)) {
-        const uint32_t above = tp >> m.shift;
-        const uint32_t s8 = 8u * (m.shift + taps_ctz(above | 0x100u));
-        if (above && ((taps_u64(a2a & held) >> (s8 & 63u)) & 1u)) {
-            const uint32_t d = (uint32_t)(taps_u64(Dh) >> s8) & 0xFFu;
-            const uint32_t x = (uint32_t)(taps_u64(x1) >> s8) & 0xFFu;
-            const uint32_t w = d & 15u, kap = d >> 5, s = x & 31u, u = x >> 5;
-            link1 += (taps_bfm(w - kap, s + kap) >> ((u - kap) & 7u)) - (taps_bfm(w, s) >> u);
-        }
-    }
-    const uint32_t vol_m = (1u << (g_end & 31u)) - (1u << (P.g & 31u));   // telescopes
-    out.c[0] = {(in1 + out1) >> m.shift, in1 >> m.shift, link1, ct1};
-    out.c[1] = {(in2 + out2) >> m.shift, in2 >> m.shift, link2, ct2};
-    out.c[2] = {vol_m >> m.shift, (vol_m - out3) >> m.shift, link3, ct3};
+    // ---- costs.  A gather of an axis of width w at shard 2^e (e + w <= 8) moves
+    // 2^(e + w) - 2^e (Eq. 9), an AllToAll 2^e - 2^(e - w) (Eq. 10); out of a node,
+    // 2^(shift - u) groups share the link, u the free levels inside a node, the
+    // axis's own among them (Algorithm 3).
+    const taps_b8 width = Dh & taps_all(0x0F0F0F0Fu), in_node = Dh & taps_all(0xE0E0E0E0u);
+    const taps_b8 x1 = at + in_node, x2 = at_r + in_node, x3 = at_m + in_node;
+    uint32_t in1 = 0, in2 = 0, a2a_in = 0;
+    uint32_t out1 = 0, out2 = 0, out3 = 0, link1 = 0, link2 = 0, link3 = 0;
+    uint32_t ct1 = 0, ct2 = 0, ct3 = 0, a2a_out = 0, a2a_link = 0;
+    // the gathers' volumes, a byte each, of the axes in mask
+    auto volumes = [](uint32_t x, uint32_t more, uint32_t mask) {
+        const uint32_t e = x & 0x07070707u;
+        const uint32_t hi = taps_perm(0xFF7F3F1Fu, 0x0F070301u, e + more);   // 2^(k + 1) - 1
+        const uint32_t lo = taps_perm(0x7F3F1F0Fu, 0x07030100u, e);          // 2^k - 1
+        return taps_bitop3<TAPS_A & (0xFFu ^ TAPS_B) & TAPS_C>(hi, lo, mask);
+    };
+    const taps_b8 more = width - (held & taps_all(0x01010101u));   // w - 1
+    auto inside = [&](uint32_t l) {   // levels l .. l + 3 inside a node
+        const uint32_t sel = taps_four(l, m.n_in);
+        const uint32_t h = taps_perm(held.hi, held.lo, sel), mo = taps_perm(more.hi, more.lo, sel);
+        const uint32_t am = taps_perm(a2a.hi, a2a.lo, sel);
+        const uint32_t y1 = taps_perm(x1.hi, x1.lo, sel), y2 = taps_perm(x2.hi, x2.lo, sel);
+        in1 = taps_dot4(volumes(y1, mo, h & ~am), 0x01010101u, in1);
+        in2 = taps_dot4(volumes(y2, mo, h), 0x01010101u, in2);
+        const uint32_t part = taps_perm(row.a2a.hi, row.a2a.lo, sel) & am;
+        a2a_in = taps_dot4(part, taps_pow2(y1 & 0x07070707u), a2a_in);
+    };
+    auto outside = [&](uint32_t l) {   // levels l .. l + 3 outside
+        const uint32_t sel = taps_four(l, m.n);
+        const uint32_t h = taps_perm(held.hi, held.lo, sel), mo = taps_perm(more.hi, more.lo, sel);
+        const uint32_t am = taps_perm(a2a.hi, a2a.lo, sel);
+        const uint32_t y1 = taps_perm(x1.hi, x1.lo, sel), y2 = taps_perm(x2.hi, x2.lo, sel);
+        const uint32_t y3 = taps_perm(x3.hi, x3.lo, sel), one = h & 0x01010101u;
+        const uint32_t u1 = (y1 >> 5) & 0x07070707u, u2 = (y2 >> 5) & 0x07070707u;
+        const uint32_t u3 = (y3 >> 5) & 0x07070707u;
+        const uint32_t s1 = taps_perm(m.share.hi, m.share.lo, u1);
+        const uint32_t s2 = taps_perm(m.share.hi, m.share.lo, u2);
+        const uint32_t s3 = taps_perm(m.share.hi, m.share.lo, u3);
+        const uint32_t v1 = volumes(y1, mo, h & ~am), v2 = volumes(y2, mo, h), v3 = volumes(y3, mo, h);
+        out1 = taps_dot4(v1, 0x01010101u, out1);
+        out2 = taps_dot4(v2, 0x01010101u, out2);
+        out3 = taps_dot4(v3, 0x01010101u, out3);
+        link1 = taps_dot4(v1, s1, link1);
+        link2 = taps_dot4(v2, s2, link2);
+        link3 = taps_dot4(v3, s3, link3);
+        ct1 = taps_dot4(one, s1, ct1);
+        ct2 = taps_dot4(one, s2, ct2);
+        ct3 = taps_dot4(one, s3, ct3);
+        // AllToAlls: the link carries 2^e times the share without the axis's own
+        // levels, 2^x with x up to 14: the bytes of x < 8 and of x >= 8 apart
+        const uint32_t e = y1 & 0x07070707u;
+        a2a_out = taps_dot4(taps_perm(row.a2a.hi, row.a2a.lo, sel) & am, taps_pow2(e), a2a_out);
+        const uint32_t kap = taps_perm(in_node.hi, in_node.lo, sel) >> 5;
+        const uint32_t x = e + m.shift * 0x01010101u - (u1 & h) + kap;
+        const uint32_t part = taps_perm(row.link.hi, row.link.lo, sel) & am;
+        const uint32_t p = taps_pow2(x & 0x07070707u);
+        const uint32_t big = part & taps_perm(0u, 0x00008000u, x & 0x08080808u);
+        const uint32_t hi = taps_dot4(big, p, 0u);
+        a2a_link += taps_dot4(part, p, 0u) + hi * 255u;
+    };
+    inside(0u);
+    if (m.n_in > 4u) inside(4u);   // uniform, as below
+    outside(m.n_in);
+    if (m.n - m.n_in > 4u) outside(m.n_in + 4u);
+    const uint32_t in_1 = (in1 << 8) + a2a_in, out_1 = (out1 << 8) + a2a_out;
+    out.c[0] = {in_1 + out_1, in_1, (link1 << 8) + a2a_link, ct1};
+    out.c[1] = {(in2 + out2) << 8, in2 << 8, link2 << 8, ct2};
+    const uint32_t vol_m = (1u << (g_end & 15u)) - (1u << (P.g & 15u));   // telescopes
+    out.c[2] = {vol_m << 8, (vol_m - out3) << 8, link3 << 8, ct3};
     const taps_b8 h01 = held & taps_all(0x01010101u);
-    const uint32_t all = taps_sum(h01, 0u), inside = taps_sum(h01 & m.in01, 0u);
-    out.coll = all | ((all - inside) << 8);
+    out.coll = taps_dot4(h01.hi, m.coll.hi, taps_dot4(h01.lo, m.coll.lo, 0u));
 }

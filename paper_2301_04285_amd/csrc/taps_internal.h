@@ -47,9 +47,18 @@ struct taps_copy_task {
 // [64 T w, 64 T (w + 1)) of the computed tables laid end to end (aligned, so
 // that every store covers whole lines), taken by one wavefront 64 at a time.
 #define TAPS_TILE_COLS 64
-// T: launches with at least taps_set_long_segments_min() windows of
-// TAPS_WINDOW_LONG tiles take those, smaller ones single tiles.
-#define TAPS_WINDOW_LONG 8
+// T: a window's set-up (its place, the row cache, the LDS table) is paid once
+// per T tiles, and the launch's end leaves wavefronts idle for up to a window,
+// so T grows with the square root of the tiles, up to TAPS_WINDOW_LONG, which
+// launches of at least taps_set_long_segments_min() such windows take.
+// Measured (us, T = 1 / 2 / 4 / 8 / 16 / 32): 1.5 M tiles 2233 / 1858 / 1680 /
+// 1600 / 1561 / 1565, 145 k tiles 215 / 183 / 169 / 165 / 170 / 197, 64 k tiles
+// 120 / 106 / 101 / 102 / 105 / 119, 16 k tiles 99 / 95 / 94 / 96 / 105 / 131
+// (whole builds).  Several bandwidth points are bound by their stores, which
+// longer windows scatter (four points, 1.5 M tiles: 2633 / 2477 / 2641 / 2745 at
+// T = 2 / 3-4 / 8 / 16).
+#define TAPS_WINDOW_LONG 16
+#define TAPS_WINDOW_SWEEP 4
 #define TAPS_LONG_SEGS_MIN 32768
 
 // The link-class kernel runs over row segments: one wavefront per producer
@@ -102,6 +111,7 @@ struct taps_plan_args {
     const uint64_t *starts;
     taps_edge_params *params;
     uint32_t *window_edge;
+    taps_top_row *tops;          // 256 rows (NULL: not wanted)
     uint64_t n_windows;
     uint32_t n_edges, window, reverse, pad;
 };
@@ -112,6 +122,7 @@ struct taps_windows {
     const taps_edge_params *params;
     const uint64_t *starts;
     const uint32_t *window_edge;
+    const taps_top_row *tops;
     uint64_t n_windows, total;   // total: computed entries
     uint32_t tiles, pad;         // tiles per window
 };

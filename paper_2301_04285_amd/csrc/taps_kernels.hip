@@ -25,7 +25,7 @@ namespace {
 
 constexpr uint32_t kWave = 64;
 
-// Widths of the unified axes by their tops, copied to LDS by the edge kernels.
+// Widths of the unified axes by their tops.
 __constant__ taps_top_table kTops = taps_make_tops();
 // Completion counts w(k, s, z) for k, s, z in 0..8 (see taps_completions),
 // evaluated by the compiler.
@@ -302,10 +302,12 @@ __device__ inline void window_one(uint64_t w, const taps_plan_args &pa) {
     pa.window_edge[w] = find_owner(pa.starts, pa.n_edges, w * pa.window);
 }
 
-// The edge plan in one launch: blocks [0, setup_blocks) set up the edges, the
-// rest map the windows.
+// The edge plan in one launch: blocks [0, setup_blocks) set up the edges (the
+// first also the edge kernels' table by tops mask), the rest map the windows.
 __device__ inline void edge_plan_block(uint32_t b, uint32_t setup_blocks, const taps_plan_args &pa,
                                        const taps_launch &lp) {
+    if (b == 0u && pa.tops && threadIdx.x < 256u)
+        pa.tops[threadIdx.x] = taps_make_top_row(kTops, threadIdx.x, taps_make_levels(lp.n, lp.lam));
     if (b < setup_blocks) {
         const uint32_t e = b * blockDim.x + threadIdx.x;
         if (e < pa.n_edges) edge_setup_one(e, pa, lp);
@@ -392,14 +394,57 @@ __device__ inline void wrap(cell &c, uint32_t nd, uint32_t mul) {
     }
 }
 
+// A value that is the same in every lane, in scalar registers.
+__device__ inline uint64_t uniform(uint64_t x) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// The source sides of 64 consecutive rows of an edge, kept in LDS by each
+// wavefront: lane l makes row first + l, once for the 1024 entries of a window
+// as a rule, and a lane reads its own row's when that changes (5 LDS reads
+// against the 125 instructions of taps_make_source).
+struct row_cache {
+    uint4 w[kWave][5];
+};
+static_assert(sizeof(taps_source) <= sizeof(uint4) * 5, "a row's source side");
+
+__device__ inline void fill_rows(row_cache &cache, const taps_source &P, uint32_t lane) {
+    uint32_t w[20] = {};
+    __builtin_memcpy(w, &P, sizeof P);
+    // the wavefront's earlier reads come before these writes, its later ones after
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (uint32_t k = 0; k < 5u; ++k)
+        cache.w[lane][k] = uint4{w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]};
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ inline taps_source read_row(const row_cache &cache, uint32_t r) {
+    uint32_t w[20];
+#pragma unroll
+    for (uint32_t k = 0; k < 5u; ++k) {
+        const uint4 x = cache.w[r][k];
+        w[4 * k] = x.x, w[4 * k + 1] = x.y, w[4 * k + 2] = x.z, w[4 * k + 3] = x.w;
+    }
+    taps_source P;
+    __builtin_memcpy(&P, w, sizeof P);
+    return P;
+}
+
 // Emit(E, v, r): stores the entry of an edge with constants E at entry v of
 // the computed tables, from its candidates r.
 template <typename Emit>
 __device__ inline void run_window(const taps_windows &win, const taps_packed *__restrict__ desc,
                                   const taps_launch &lp, const Emit &emit) {
     __shared__ taps_top_row tops[256];
+    __shared__ row_cache rows[kWindowsPerBlock];
     const taps_levels_model m = taps_make_levels(lp.n, lp.lam);
-    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) tops[x] = taps_make_top_row(kTops, x, m);
+    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) tops[x] = win.tops[x];
     __syncthreads();
     const uint32_t lane = threadIdx.x % kWave;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -410,75 +455,127 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
     const uint64_t end = win.total - begin < span ? win.total : begin + span;
     uint32_t e = win.window_edge[w];
     taps_edge_params E = win.params[e];
-    uint64_t e_end = win.starts[e + 1u];
+    uint64_t e_start = uniform(win.starts[e]), e_end = uniform(win.starts[e + 1u]);
+    uint64_t to_out = uniform(E.out_offset) - e_start;
     uint32_t mul = row_multiplier(E.nd);
-    const uint64_t local = begin - win.starts[e];   // below ns * nd
+    const uint64_t local = begin - e_start;   // below ns * nd
     cell c;
     c.i = (uint32_t)(local / E.nd);
     c.j = (uint32_t)(local % E.nd) + lane;
     wrap(c, E.nd, mul);
     taps_source P = {};
-    uint32_t row = ~0u;   // the row P holds
+    uint32_t row = ~0u;              // the row P holds
+    uint32_t cached = ~0u - kWave;   // the cache holds rows cached .. cached + 63 of edge e
+    taps_packed q = desc[E.dst_base + (c.i < E.ns ? c.j : 0u)];
     for (uint64_t v0 = begin; v0 < end; v0 += kWave) {
         const uint64_t tile_end = end - v0 < kWave ? end : v0 + kWave;
+        // the next tile's target side, asked for a tile ahead (before this tile's
+        // stores, which a later load would wait for)
+        cell next = c;
+        taps_packed next_q = q;
+        if (e_end > tile_end) {   // uniform
+            next.j += kWave;
+            wrap(next, E.nd, mul);
+            next_q = desc[E.dst_base + (next.i < E.ns ? next.j : 0u)];
+        }
         uint32_t first = 0;   // lanes below this are done
         for (;;) {            // uniform: one edge per pass
             const uint32_t last = (uint32_t)((e_end < tile_end ? e_end : tile_end) - v0);
             const bool mine = lane >= first && lane < last;
-            const taps_packed q = desc[E.dst_base + (mine ? c.j : 0u)];
             if (__any(mine && c.i != row)) {
-                P = taps_make_source(desc[E.src_base + (mine ? c.i : 0u)], E.from, E.rank, m);
+                if (__any(mine && c.i - cached >= kWave)) {
+                    cached = __builtin_amdgcn_readlane(c.i, first);
+                    const uint32_t r = cached + lane;
+                    fill_rows(rows[wave], taps_make_source(desc[E.src_base + (r < E.ns ? r : cached)],
+                                                           E.from, E.rank, m), lane);
+                }
+                // (an entry's row is within 63 of the first's, as every row has one at least)
+                P = read_row(rows[wave], mine ? c.i - cached : 0u);
                 row = mine ? c.i : ~0u;
             }
-            if (mine) {
-                taps_three r;
-                taps_three_candidates(P, q, E.to, E.rank, m, tops, r);
-                emit(E, v0 - win.starts[e] + E.out_offset, lane, r);
-            }
-            if (e_end >= tile_end) break;
+            // every lane, so that the branches on the node boundary stay uniform
+            // (a lane without an entry computes one that it does not store)
+            taps_three r;
+            taps_three_candidates(P, q, E.to, E.rank, m, tops, r);
+            if (mine) emit(E, v0 + to_out, lane, r);
+            if (e_end >= tile_end && (e_end > tile_end || tile_end == end)) break;
+            // the next edge starts in this tile, or with the next one
             first = last;
             ++e;
             E = win.params[e];
-            e_end = win.starts[e + 1u];
+            e_start = e_end;
+            e_end = uniform(win.starts[e + 1u]);
+            to_out = uniform(E.out_offset) - e_start;
             mul = row_multiplier(E.nd);
+            row = ~0u;
+            cached = ~0u - kWave;
             c.i = 0u;
-            c.j = lane - first;   // lanes below `first` stay out of this edge's passes
+            c.j = lane - first;   // lanes below `first` come to this edge with the next tile
             if (lane >= first) wrap(c, E.nd, mul);
-            row = ~0u;
-        }
-        if (e_end == tile_end && tile_end < end) {   // the next tile starts an edge
-            ++e;
-            E = win.params[e];
-            e_end = win.starts[e + 1u];
-            mul = row_multiplier(E.nd);
-            c.i = 0u;
-            c.j = lane;
-            row = ~0u;
-        } else {
-            if (lane < first) {   // entered the edge in this tile: continue as its lanes do
-                c.i = 0u;
-                c.j = lane - first;
+            next = c;
+            if (lane < first) next.i = 0u;
+            next.j += kWave;
+            if (first == (uint32_t)(tile_end - v0)) {
+                // it starts with the next tile (first == 64): lane l there is its entry l
+                wrap(next, E.nd, mul);
+                next_q = desc[E.dst_base + (next.i < E.ns ? next.j : 0u)];
+                break;
             }
-            c.j += kWave;
+            wrap(next, E.nd, mul);
+            q = desc[E.dst_base + (lane >= first && c.i < E.ns ? c.j : 0u)];
+            next_q = desc[E.dst_base + (next.i < E.ns ? next.j : 0u)];
         }
-        wrap(c, E.nd, mul);
+        c = next;
+        q = next_q;
     }
 }
 
 // Selection among the candidates under one bandwidth point's keys (ties go to
-// the earlier candidate), scaled.
+// the earlier candidate), scaled.  Narrow: 64-bit keys.
+template <bool Narrow>
 __device__ inline taps_entry_out select_entry(const taps_three &r, const taps_keys &K,
                                               const taps_scaler &S) {
-    taps_cands k;
-    k.c[0] = r.c[0];
-    k.c[1] = r.c[1];
-    k.c[2] = r.c[2];
-    k.vmin = r.c[1].vol < r.c[0].vol ? r.c[1].vol : r.c[0].vol;
-    k.vmin = r.c[2].vol < k.vmin ? r.c[2].vol : k.vmin;
-    k.coll = r.coll;
-    k.has_rearrange = true;
-    k.ok = true;
-    return taps_entry_finish(taps_pick_for(k, K), S);
+    uint32_t intra = r.c[0].intra, inter = r.c[0].inter, ct = r.c[0].ct, cand = 0u;
+    if (Narrow) {
+        uint64_t best = taps_key64(r.c[0], K);
+        const uint64_t k1 = taps_key64(r.c[1], K), k2 = taps_key64(r.c[2], K);
+#pragma unroll
+        for (uint32_t c = 1; c < 3u; ++c) {
+            const uint64_t k = c == 1u ? k1 : k2;
+            const bool less = k < best;
+            best = less ? k : best;
+            intra = less ? r.c[c].intra : intra;
+            inter = less ? r.c[c].inter : inter;
+            ct = less ? r.c[c].ct : ct;
+            cand = less ? c : cand;
+        }
+    } else {
+        taps_fac best = r.c[0];
+        for (uint32_t c = 1; c < 3u; ++c)
+            if (taps_less(r.c[c], best, K)) {
+                best = r.c[c];
+                cand = c;
+            }
+        intra = best.intra;
+        inter = best.inter;
+        ct = best.ct;
+    }
+    uint32_t vol = r.c[1].vol < r.c[0].vol ? r.c[1].vol : r.c[0].vol;
+    vol = r.c[2].vol < vol ? r.c[2].vol : vol;
+    taps_entry_out o;
+    if (S.q) {   // uniform over the edge
+        o.vol = (uint64_t)S.q * vol;
+        o.intra = (uint64_t)S.q * intra;
+        o.inter = (uint64_t)S.q * inter;
+    } else {
+        o.vol = taps_scale(S, vol);
+        o.intra = taps_scale(S, intra);
+        o.inter = taps_scale(S, inter);
+    }
+    o.t = (double)intra * S.a_intra + (double)inter * S.a_inter;
+    o.meta = cand | r.coll | (ct << 12);
+    o.ok = true;
+    return o;
 }
 
 // Narrow: both reduced bandwidths are below 2^32 (64-bit keys).
@@ -489,7 +586,7 @@ __global__ __launch_bounds__(256) void k_edge_costs(taps_windows win,
     const taps_keys K = {lp.b_inter_red, lp.b_intra_red, Narrow};
     run_window(win, desc, lp, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
                                   const taps_three &r) {
-        const taps_entry_out o = select_entry(r, K, E.scale);
+        const taps_entry_out o = select_entry<Narrow>(r, K, E.scale);
         store_entry(out, at, lane, o, o.meta);
     });
 }
@@ -507,7 +604,8 @@ __global__ __launch_bounds__(256) void k_edge_costs_sweep(taps_windows win,
             const taps_keys K = {sw.b_inter_red[k], sw.b_intra_red[k], Narrow || sw.narrow[k] != 0};
             const taps_scaler S =
                 taps_make_scaler(E.scale.tbytes, sw.inv_n_bintra[k], sw.inv_n_binter[k]);
-            const taps_entry_out o = select_entry(r, K, S);
+            const taps_entry_out o = Narrow || K.narrow ? select_entry<true>(r, K, S)
+                                                        : select_entry<false>(r, K, S);
             store_entry(sw.out[k], at, lane, o, o.meta);
         }
     });
