@@ -763,7 +763,7 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
     taps_top_row *d_tops = nullptr;
     if ((st = sc.alloc((void **)&d_win, sizeof(uint32_t) * n_windows)) != TAPS_OK) return st;
     if (!hier && (st = sc.alloc((void **)&d_tops, sizeof(taps_top_row) * 256)) != TAPS_OK) return st;
-    hipError_t err = hier ? taps_launch_describe_h(strategies, total, lp.n, (taps_desc *)d_desc, stream)
+    hipError_t err = hier ? taps_launch_describe_h(strategies, total, (taps_desc *)d_desc, stream)
                           : taps_launch_describe(strategies, total, lp.n, (taps_packed *)d_desc, stream);
     const taps_windows tw = device_windows(win, n_windows, d_params, d_win, d_tops, dev, ch[3], ch[8]);
     if (err == hipSuccess) {
@@ -936,13 +936,11 @@ const std::vector<uint32_t> &chunk_counts(const taps_op &op, uint32_t n, uint32_
     const uint32_t total = W.v[(taps_popc(op.part_mask) * 9u + n) * 9u];
     std::vector<uint32_t> counts((total + TAPS_BUILD_CHUNK - 1) / TAPS_BUILD_CHUNK, 0);
     for (uint32_t r = 0; r < total; ++r) {
-        uint32_t expo[TAPS_D_MAX_AXES];
-        int32_t pos[TAPS_D_MAX_AXES];
-        if (!taps_unrank(op.n_axes, op.part_mask, n, r, W.v, expo, pos)) continue;
+        const taps_nibbles S = taps_unrank(op.part_mask, n, r, W.v);
         bool valid = true;
         for (uint32_t a = 0; a < op.n_axes; ++a)
-            if (op.axis_len[a] & (((int64_t)1 << expo[a]) - 1)) valid = false;
-        if (valid && (taps_describe(op.n_axes, expo, pos).cuts & ~allowed)) valid = false;
+            if (op.axis_len[a] & (((int64_t)1 << taps_nib(S.expo, a)) - 1)) valid = false;
+        if (valid && (taps_lay_out(S, op.part_mask, n).cuts & ~allowed)) valid = false;
         counts[r / TAPS_BUILD_CHUNK] += valid ? 1u : 0u;
     }
     return memo.emplace(key, std::move(counts)).first->second;

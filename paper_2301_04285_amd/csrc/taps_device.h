@@ -221,51 +221,56 @@ __host__ __device__ constexpr taps_completion_table taps_make_completions() {
     return t;
 }
 
-// Decodes candidate r (0 <= r < w(p, n, 0)) into per-axis exponents and
-// device-map positions.  part: partitionable-axis mask; W: the completion
-// table.  Returns false if r is out of range.
-__host__ __device__ inline bool taps_unrank(uint32_t n_axes, uint32_t part, uint32_t n, uint32_t r,
-                                            const uint32_t *W, uint32_t *expo, int32_t *pos) {
+// A strategy as nibbles by op axis: log2 degrees and device-matrix positions
+// (15: not split).
+struct taps_nibbles {
+    uint32_t expo, pos;
+};
+
+// Decodes candidate r (0 <= r < w(p, n, 0)) of the partitionable axes `part`;
+// W: the completion table (in LDS on the device).  No array is indexed by a
+// value that varies over a wavefront, so everything stays in registers.
+__host__ __device__ inline taps_nibbles taps_unrank(uint32_t part, uint32_t n, uint32_t r,
+                                                    const uint32_t *W) {
+    taps_nibbles S = {0u, ~0u};
     uint32_t s = n, z = 0;
-    for (uint32_t a = 0; a < n_axes; ++a) {
-        expo[a] = 0;
-        pos[a] = -1;
-        if (!((part >> a) & 1u)) continue;
-        const uint32_t k = taps_popc(part >> (a + 1));
-        bool placed = false;
-        for (uint32_t e = 0; e <= s; ++e) {
-            const uint32_t z2 = z + (e > 0 ? 1u : 0u);
-            const uint32_t c = W[(k * 9u + (s - e)) * 9u + z2];
-            if (r < c) {
-                expo[a] = e;
-                s -= e;
-                z = z2;
-                placed = true;
-                break;
-            }
+    for (uint32_t m = part; m; m &= m - 1u) {   // uniform
+        const uint32_t k = taps_popc(m) - 1u, a = taps_ctz(m);
+        const uint32_t *row = W + k * 81u + z;
+        const uint32_t none = row[s * 9u];
+        if (r < none) continue;
+        r -= none;
+        uint32_t e = 1;
+        for (; e < s; ++e) {   // the last exponent takes what is left
+            const uint32_t c = row[(s - e) * 9u + 1u];
+            if (r < c) break;
             r -= c;
         }
-        if (!placed) return false;
+        S.expo |= e << (4u * a);
+        s = s > e ? s - e : 0u;
+        ++z;
     }
-    if (s != 0) return false;
     // r is now the rank of the position tuple among the z! orderings, in
-    // descending order; decode the (z! - 1 - r)-th ascending permutation.
-    uint32_t q = taps_fact(z) - 1u - r;
-    uint32_t free_pos = taps_low_mask(z);
-    uint32_t t = 0;
-    for (uint32_t a = 0; a < n_axes; ++a) {
-        if (expo[a] == 0) continue;
-        const uint32_t f = taps_fact(z - 1u - t);
-        const uint32_t idx = q / f;
-        q -= idx * f;
-        uint32_t m = free_pos;
-        for (uint32_t x = 0; x < idx; ++x) m &= m - 1u;   // drop the idx lowest free positions
-        const uint32_t p = taps_ctz(m);
-        free_pos &= ~(1u << p);
-        pos[a] = (int32_t)p;
-        ++t;
+    // descending order: the (z! - 1 - r)-th ascending permutation, its digits
+    // (how many of the j positions left are passed over) from the last
+    uint32_t q = taps_fact(z) - 1u - r, digits = 0;
+#pragma unroll
+    for (uint32_t j = 2; j <= 8u; ++j) {
+        const uint32_t d = q / j;
+        digits |= (q - d * j) << (4u * (j - 1u));
+        q = d;
     }
-    return true;
+    uint32_t left = 0x76543210u;   // the free positions, ascending
+    for (uint32_t m = part; m; m &= m - 1u) {   // uniform
+        const uint32_t a4 = 4u * taps_ctz(m);
+        if (!((S.expo >> a4) & 15u)) continue;
+        --z;
+        const uint32_t d4 = 4u * ((digits >> (4u * z)) & 7u);
+        const uint32_t below = (1u << d4) - 1u, p = (left >> d4) & 15u;
+        left = (left & below) | ((left >> 4) & ~below);
+        S.pos = (S.pos & ~(15u << a4)) | (p << a4);
+    }
+    return S;
 }
 
 // Level runs of a strategy: the axis at position 0 owns the lowest levels.

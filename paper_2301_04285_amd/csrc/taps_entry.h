@@ -187,30 +187,59 @@ __host__ __device__ inline taps_b8 taps_unnibble(uint32_t x) {
 __host__ __device__ inline uint32_t taps_nibble_shift(uint32_t k) {
     return k < 4u ? 8u * k : 8u * k - 28u;
 }
+// nibbles 0-3 of x (< 2^16) to the low nibbles of four bytes
+__host__ __device__ inline uint32_t taps_spread(uint32_t x) {
+    x = (x | (x << 8)) & 0x00FF00FFu;
+    return (x | (x << 4)) & 0x0F0F0F0Fu;
+}
 // nibbles 0-7 in ascending order (taps_nib) to the order above
 __host__ __device__ inline uint32_t taps_deal(uint32_t x) {
-    uint32_t r = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < 8u; ++k) r |= taps_nib(x, k) << taps_nibble_shift(k);
-    return r;
+    return taps_spread(x & 0xFFFFu) | (taps_spread(x >> 16) << 4);
 }
 
-__host__ __device__ inline taps_packed taps_pack(const taps_desc &D, uint32_t n) {
-    taps_packed p = {0u, 0u, 0u, 0u};
+// The level runs of a strategy: the axis at position 0 owns the lowest levels.
+// Positions past 7 leave an axis whole; a malformed strategy gives meaningless
+// numbers but never an out-of-range index.
+struct taps_runs {
+    taps_packed packed;
+    uint32_t lo, width;   // nibble a: lowest level and width of axis a's run (width 0: not split)
+    uint32_t cuts;        // bit c: levels c - 1 and c belong to different axes
+};
+
+// axes: the axes that may be split (others are whole).
+__host__ __device__ inline taps_runs taps_lay_out(const taps_nibbles &S, uint32_t axes, uint32_t n) {
+    taps_runs R = {{0u, 0u, 0u, 0u}, 0u, 0u, 0u};
+    uint32_t by_pos = 0;   // nibble p: width of the axis at position p
 #pragma unroll
     for (uint32_t a = 0; a < TAPS_D_MAX_AXES; ++a) {
-        const uint32_t w = taps_nib(D.width, a), lo = taps_nib(D.lo, a);
-        p.width |= w << taps_nibble_shift(a);
-        p.end |= (w ? (lo + w) & 15u : 0u) << taps_nibble_shift(a);
+        if (!((axes >> a) & 1u)) continue;
+        const uint32_t p = taps_nib(S.pos, a), w = p < 8u ? taps_nib(S.expo, a) : 0u;
+        R.width |= w << (4u * a);
+        by_pos |= w << (4u * (p & 7u));
     }
+    const uint32_t first = (by_pos << 4) * 0x11111111u;   // nibble p: levels below position p
+    uint32_t owner = 0, place = 0, end = 0;
 #pragma unroll
-    for (uint32_t l = 0; l < TAPS_D_MAX_LEVELS; ++l) {
-        const uint32_t a = taps_nib(D.owner, l) & 7u;
-        const uint32_t lo = taps_nib(D.lo, a), end = lo + taps_nib(D.width, a);
-        p.owner |= (l < n ? a : 0u) << taps_nibble_shift(l);
-        p.place |= (l < n ? ((end - 1u - l) & 7u) | (l == lo ? 8u : 0u) : 15u) << taps_nibble_shift(l);
+    for (uint32_t a = 0; a < TAPS_D_MAX_AXES; ++a) {
+        if (!((axes >> a) & 1u)) continue;
+        const uint32_t w = taps_nib(R.width, a);
+        if (w == 0u) continue;
+        const uint32_t lo = taps_nib(first, taps_nib(S.pos, a) & 7u);
+        const uint32_t at = (4u * lo) & 31u, cut = (32u - 4u * w) & 31u;
+        R.lo |= lo << (4u * a);
+        end |= ((lo + w) & 15u) << (4u * a);
+        owner |= ((a * 0x11111111u) >> cut) << at;
+        // w - 1, ..., 1, 0 upwards, the lowest level flagged
+        place |= ((0x01234567u >> cut) | 8u) << at;
+        R.cuts |= 1u << lo;
     }
-    return p;
+    R.cuts &= ~1u;
+    const uint32_t above = n < 8u ? ~0u << (4u * n) : 0u;
+    R.packed.owner = taps_deal(owner & ~above);
+    R.packed.place = taps_deal(place | above);
+    R.packed.end = taps_deal(end);
+    R.packed.width = taps_deal(R.width);
+    return R;
 }
 
 // Levels of op axis a.
@@ -476,7 +505,7 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
         uint32_t g = G, pending = 0u;
         if (taps_wave_any(now | gathers)) {
             taps_b8 freed = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
-            freed = freed & taps_all(now | gathers ? ~0u : 0u);
+            freed = freed & taps_all((now | gathers) ? ~0u : 0u);
             wait = wait & ~freed;
             const uint32_t f = taps_sum(D & freed, 0u);
             g -= now ? f : 0u;

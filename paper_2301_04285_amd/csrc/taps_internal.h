@@ -92,8 +92,8 @@ struct taps_row_ref {
 
 hipError_t taps_launch_describe(const taps_strategy *s, uint64_t total, uint32_t n,
                                 taps_packed *desc, hipStream_t stream);
-hipError_t taps_launch_describe_h(const taps_strategy *s, uint64_t total, uint32_t n,
-                                  taps_desc *desc, hipStream_t stream);
+hipError_t taps_launch_describe_h(const taps_strategy *s, uint64_t total, taps_desc *desc,
+                                  hipStream_t stream);
 hipError_t taps_launch_node_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
                                   const taps_packed *desc, uint64_t total, const taps_launch &lp,
                                   taps_table out, hipStream_t stream);

@@ -19,6 +19,8 @@
 //   k_copy_tables shared tables: one workgroup per chunk of a computed
 //                 table, written to every table that shares it
 //   k_pull        a call's upload, read from pinned host memory
+#include <cstddef>
+
 #include "taps_internal.h"
 
 namespace {
@@ -84,14 +86,29 @@ __device__ inline uint32_t lanes_below(uint64_t mask) {
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// The packed descriptor of the two-class kernels or the link classes' form.
-__device__ inline void put_desc(taps_packed *p, const taps_desc &D, uint32_t n) { *p = taps_pack(D, n); }
-__device__ inline void put_desc(taps_desc *p, const taps_desc &D, uint32_t) { *p = D; }
+// A strategy's bytes as nibbles (positions past 7 or negative: 15).
+__device__ inline taps_nibbles strategy_nibbles(const taps_strategy &st) {
+    taps_nibbles S = {0u, 0u};
+#pragma unroll
+    for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a) {
+        const uint32_t p = (uint8_t)st.pos[a];
+        S.expo |= (uint32_t)(st.log2_deg[a] & 15u) << (4u * a);
+        S.pos |= (p < 8u ? p : 15u) << (4u * a);
+    }
+    return S;
+}
 
-template <typename Desc>
 __global__ __launch_bounds__(256) void k_describe(const taps_strategy *__restrict__ s,
                                                   uint64_t total, uint32_t n,
-                                                  Desc *__restrict__ desc) {
+                                                  taps_packed *__restrict__ desc) {
+    const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= total) return;
+    desc[idx] = taps_lay_out(strategy_nibbles(s[idx]), 0xFFu, n).packed;
+}
+
+// The form of the link-class kernel.
+__global__ __launch_bounds__(256) void k_describe_h(const taps_strategy *__restrict__ s,
+                                                    uint64_t total, taps_desc *__restrict__ desc) {
     const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= total) return;
     const taps_strategy st = s[idx];
@@ -102,7 +119,7 @@ __global__ __launch_bounds__(256) void k_describe(const taps_strategy *__restric
         expo[a] = st.log2_deg[a];
         pos[a] = st.pos[a];
     }
-    put_desc(desc + idx, taps_describe(TAPS_D_MAX_AXES, expo, pos), n);
+    desc[idx] = taps_describe(TAPS_D_MAX_AXES, expo, pos);
 }
 
 // largest k in [0, n) with offsets[k] <= x
@@ -118,19 +135,13 @@ __device__ inline uint32_t find_owner(const uint64_t *offsets, uint32_t n, uint6
     return lo;
 }
 
-__device__ inline uint32_t axis_levels(const taps_packed &D, uint32_t a) { return taps_axis_levels(D, a); }
-__device__ inline uint32_t axis_levels(const taps_desc &D, uint32_t a) {
-    return taps_levels(taps_nib(D.lo, a), taps_nib(D.width, a));
-}
-
-template <typename Desc>
 __device__ inline void node_tensor(taps_acc &c, const taps_op &op, const taps_tensor &t,
-                                   const Desc &D, uint32_t full, uint32_t lam) {
+                                   const taps_packed &D, uint32_t full, uint32_t lam) {
     uint32_t used = 0;
     uint64_t bytes = op.dtype_bytes;
     for (uint32_t d = 0; d < t.rank && d < TAPS_MAX_RANK; ++d) {
         const uint32_t a = t.axis[d] & 7u;
-        used |= axis_levels(D, a);
+        used |= taps_axis_levels(D, a);
         bytes *= (uint64_t)op.axis_len[a];
     }
     taps_allreduce(c, full & ~used, bytes, lam);
@@ -180,53 +191,92 @@ __device__ inline void build_chunk(const taps_build_chunk &ck, const taps_op *__
     __shared__ uint32_t wave_count[kBuildThreads / kWave];
     const uint32_t tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     for (uint32_t x = tid; x < 9u * 9u * 9u; x += blockDim.x) W[x] = kCompletions.v[x];
+    // the operator, the same for the whole workgroup: read as words (scalar loads;
+    // its bytes one by one were a chain of some 30 dependent vector loads, most of
+    // this kernel's time) and taken apart on the scalar unit
+    const uint32_t *words = (const uint32_t *)(ops + ck.op);
+    uint32_t op[sizeof(taps_op) / 4u];
+#pragma unroll
+    for (uint32_t x = 0; x < sizeof(taps_op) / 4u; ++x) op[x] = words[x];
+    auto byte = [&](uint32_t at) { return (op[at / 4u] >> (8u * (at % 4u))) & 0xFFu; };
+    auto length = [&](uint32_t a) {
+        const uint32_t at = offsetof(taps_op, axis_len) / 4u + 2u * a;
+        return ((uint64_t)op[at + 1u] << 32) | op[at];
+    };
+    const uint32_t part = byte(offsetof(taps_op, part_mask));
+    const uint32_t n_in = byte(offsetof(taps_op, n_in)), n_w = byte(offsetof(taps_op, n_w));
+    uint32_t most = 0;   // nibble a: the largest exponent that divides axis a's length
+#pragma unroll
+    for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a) {
+        const uint64_t len = length(a) | 256u;   // exponents end at 8
+        most |= (uint32_t)__builtin_ctzll(len) << (4u * a);
+    }
     __syncthreads();
-    const taps_op &op = ops[ck.op];
-    const uint32_t n_axes = op.n_axes, part = op.part_mask;
     const uint32_t total = W[(taps_popc(part) * 9u + lp.n) * 9u];
     const uint32_t full = taps_low_mask(lp.n);
     const uint32_t r = ck.first + tid;
-    uint32_t expo[TAPS_D_MAX_AXES];
-    int32_t pos[TAPS_D_MAX_AXES];
-    bool valid = r < total && taps_unrank(n_axes, part, lp.n, r, W, expo, pos);
-    if (valid)
-        for (uint32_t a = 0; a < n_axes; ++a)
-            if (op.axis_len[a] & (((int64_t)1 << expo[a]) - 1)) valid = false;
-    taps_desc D = {0u, 0u, 0u, 0u};
-    if (valid) {
-        D = taps_describe(n_axes, expo, pos);
-        if (D.cuts & ~allowed_cuts) valid = false;
-    }
+    bool valid = r < total;
+    const taps_nibbles S = taps_unrank(part, lp.n, valid ? r : 0u, W);
+#pragma unroll
+    for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a)
+        valid = valid && taps_nib(S.expo, a) <= taps_nib(most, a);
+    const taps_runs R = taps_lay_out(S, part, lp.n);
+    valid = valid && (R.cuts & ~allowed_cuts) == 0u;
     const uint64_t m = __ballot(valid);
     if (lane == 0) wave_count[wave] = (uint32_t)__builtin_popcountll(m);
     __syncthreads();
     uint32_t before = 0;
     for (uint32_t w = 0; w < wave; ++w) before += wave_count[w];
     const uint32_t k = before + lanes_below(m);
-    if (valid && k < ck.count) {
-        const uint64_t idx = ck.base + k;
-        taps_strategy st;
-        for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a) {
-            st.log2_deg[a] = a < n_axes ? (uint8_t)expo[a] : 0;
-            st.pos[a] = a < n_axes ? (int8_t)pos[a] : (int8_t)-1;
-        }
-        out[idx] = st;
-        if (desc) desc[idx] = taps_pack(D, lp.n);   // uniform: descriptors and node records are optional
-        if (node.t) {
-            taps_acc c;
-            taps_acc_zero(c);
-            node_tensor(c, op, op.out, D, full, lp.lam);
-            for (uint32_t q = 0; q < op.n_in && q < TAPS_MAX_INPUTS; ++q)
-                node_tensor(c, op, op.in[q], D, full, lp.lam);
-            for (uint32_t q = 0; q < op.n_w && q < TAPS_MAX_WEIGHTS; ++q)
-                node_tensor(c, op, op.w[q], D, full, lp.lam);
-            node.t[idx] = (double)c.intra * lp.inv_n_bintra + (double)c.inter * lp.inv_n_binter;
-            node.vol[idx] = c.vol;
-            node.intra[idx] = c.intra;
-            node.inter[idx] = c.inter;
-            node.meta[idx] = taps_meta(0, c);
-        }
+    if (!valid || k >= ck.count) return;
+    const uint64_t idx = ck.base + k;
+    // bytes: degrees, then positions (-1: not split)
+    const uint32_t whole = ~(S.pos & (S.pos >> 1) & (S.pos >> 2) & (S.pos >> 3)) & 0x11111111u;
+    auto bytes = [](uint32_t nibbles) { return taps_spread(nibbles & 0xFFFFu); };
+    const uint32_t not_lo = bytes(0x11111111u & ~whole) * 0xFFu;
+    const uint32_t not_hi = bytes((0x11111111u & ~whole) >> 16) * 0xFFu;
+    *(uint4 *)(out + idx) = uint4{bytes(S.expo), bytes(S.expo >> 16), bytes(S.pos) | not_lo,
+                                  bytes(S.pos >> 16) | not_hi};
+    if (desc) desc[idx] = R.packed;   // uniform: descriptors and node records are optional
+    if (!node.t) return;
+    // levels of every axis, a byte each
+    uint32_t lv_lo = 0, lv_hi = 0;
+#pragma unroll
+    for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a) {
+        if (!((part >> a) & 1u)) continue;
+        const uint32_t v = taps_bfm(taps_nib(R.width, a), taps_nib(R.lo, a)) & 0xFFu;
+        (a < 4u ? lv_lo : lv_hi) |= v << (8u * (a & 3u));
     }
+    taps_acc c;
+    taps_acc_zero(c);
+    auto tensor = [&](uint32_t at) {   // the tensor at byte `at` of the operator
+        const uint32_t rank = byte(at);
+        uint32_t axes = 0;
+        uint64_t size = byte(offsetof(taps_op, dtype_bytes));
+#pragma unroll
+        for (uint32_t d = 0; d < TAPS_MAX_RANK; ++d)
+            if (d < rank) axes |= 1u << (byte(at + 1u + d) & 7u);
+        uint32_t used = 0;
+#pragma unroll
+        for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a)
+            if ((axes >> a) & 1u) {   // uniform; a tensor names an axis at most once
+                size *= length(a);
+                used |= (a < 4u ? lv_lo : lv_hi) >> (8u * (a & 3u));
+            }
+        taps_allreduce(c, full & ~used, size, lp.lam);
+    };
+    tensor(offsetof(taps_op, out));
+#pragma unroll
+    for (uint32_t q = 0; q < TAPS_MAX_INPUTS; ++q)
+        if (q < n_in) tensor(offsetof(taps_op, in) + q * sizeof(taps_tensor));
+#pragma unroll
+    for (uint32_t q = 0; q < TAPS_MAX_WEIGHTS; ++q)
+        if (q < n_w) tensor(offsetof(taps_op, w) + q * sizeof(taps_tensor));
+    node.t[idx] = (double)c.intra * lp.inv_n_bintra + (double)c.inter * lp.inv_n_binter;
+    node.vol[idx] = c.vol;
+    node.intra[idx] = c.intra;
+    node.inter[idx] = c.inter;
+    node.meta[idx] = taps_meta(0, c);
 }
 
 __global__ __launch_bounds__(kBuildThreads) void k_build_strategies(
@@ -326,11 +376,11 @@ __global__ __launch_bounds__(256) void k_edge_plan(taps_plan_args pa, taps_launc
 // (which needs only the strategy offsets, which the host counted), in one
 // launch.
 __global__ __launch_bounds__(kBuildThreads) void k_build_front(
-    const taps_build_chunk *__restrict__ chunks, uint32_t n_chunks, uint32_t allowed_cuts,
-    taps_launch lp, taps_strategy *__restrict__ out, taps_packed *__restrict__ desc,
-    taps_table node, taps_plan_args pa, uint32_t setup_blocks) {
+    const taps_op *__restrict__ ops, const taps_build_chunk *__restrict__ chunks, uint32_t n_chunks,
+    uint32_t allowed_cuts, taps_launch lp, taps_strategy *__restrict__ out,
+    taps_packed *__restrict__ desc, taps_table node, taps_plan_args pa, uint32_t setup_blocks) {
     if (blockIdx.x < n_chunks)
-        build_chunk(chunks[blockIdx.x], pa.ops, allowed_cuts, lp, out, desc, node);
+        build_chunk(chunks[blockIdx.x], ops, allowed_cuts, lp, out, desc, node);
     else
         edge_plan_block(blockIdx.x - n_chunks, setup_blocks, pa, lp);
 }
@@ -672,7 +722,7 @@ __global__ __launch_bounds__(256) void k_node_costs_h(const taps_op *__restrict_
         uint64_t bytes = op.dtype_bytes;
         for (uint32_t d = 0; d < t.rank && d < TAPS_MAX_RANK; ++d) {
             const uint32_t a = t.axis[d] & 7u;
-            used |= axis_levels(D, a);
+            used |= taps_axis_levels(D, a);
             bytes *= (uint64_t)op.axis_len[a];
         }
         taps_allreduce_h(c, full & ~used, bytes, H);
@@ -769,16 +819,16 @@ inline uint32_t blocks_for(uint64_t n, uint32_t per) { return (uint32_t)((n + pe
 hipError_t taps_launch_describe(const taps_strategy *s, uint64_t total, uint32_t n,
                                 taps_packed *desc, hipStream_t stream) {
     if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_describe<taps_packed>, dim3(blocks_for(total, 256)), dim3(256), 0, stream,
-                       s, total, n, desc);
+    hipLaunchKernelGGL(k_describe, dim3(blocks_for(total, 256)), dim3(256), 0, stream, s, total, n,
+                       desc);
     return hipGetLastError();
 }
 
-hipError_t taps_launch_describe_h(const taps_strategy *s, uint64_t total, uint32_t n,
-                                  taps_desc *desc, hipStream_t stream) {
+hipError_t taps_launch_describe_h(const taps_strategy *s, uint64_t total, taps_desc *desc,
+                                  hipStream_t stream) {
     if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_describe<taps_desc>, dim3(blocks_for(total, 256)), dim3(256), 0, stream,
-                       s, total, n, desc);
+    hipLaunchKernelGGL(k_describe_h, dim3(blocks_for(total, 256)), dim3(256), 0, stream, s, total,
+                       desc);
     return hipGetLastError();
 }
 
@@ -858,7 +908,7 @@ hipError_t taps_launch_build_front(const taps_build_chunk *chunks, uint32_t n_ch
     const uint32_t setup_blocks = blocks_for(pa.n_edges, 256);
     const uint32_t blocks = n_chunks + setup_blocks + blocks_for(pa.n_windows, 256);
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_build_front, dim3(blocks), dim3(kBuildThreads), 0, stream, chunks,
+    hipLaunchKernelGGL(k_build_front, dim3(blocks), dim3(kBuildThreads), 0, stream, pa.ops, chunks,
                        n_chunks, allowed_cuts, lp, out, desc, node, pa, setup_blocks);
     return hipGetLastError();
 }
