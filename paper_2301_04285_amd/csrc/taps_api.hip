@@ -543,17 +543,7 @@ void plan_copies(const std::vector<uint64_t> &eoff, const std::vector<uint32_t> 
     }
 }
 
-// The largest rank of the tensors the edges carry (the producers' outputs).
-uint32_t max_edge_rank(const taps_graph *graph) {
-    uint32_t r = 0;
-    for (uint32_t e = 0; e < graph->n_edges; ++e) {
-        const uint32_t k = graph->ops[graph->edges[e].src_op].out.rank;
-        r = k > r ? k : r;
-    }
-    return r;
-}
-
-// What the two-class edge kernels compute: every edge (edges and starts empty:
+// What the edge kernels compute: every edge (edges and starts empty:
 // the tables are the output's, end to end), or with shared tables the first of
 // each group (rep[e] == e), laid end to end in starts.
 struct window_plan {
@@ -597,65 +587,15 @@ window_plan plan_windows(const std::vector<uint64_t> &eoff, const std::vector<ui
     return p;
 }
 
-// Row segments of the link-class kernel: each row of every edge cut into
-// segments of `cols` columns and its remainder.  Ordered, the launch takes
-// every full-length segment first (edges in order, a row's segments together)
-// and the remainders last, longest first, so that it ends on its shortest
-// segments; otherwise each row's segments, remainder included, run together.
-// Returns the number of segments.
-uint64_t plan_segments(const taps_graph *graph, const uint64_t *op_offsets, uint32_t cols,
-                       bool ordered, std::vector<taps_seg_group> &groups) {
-    struct remainder {
-        uint32_t edge, rows, first_col, cols;
-    };
-    std::vector<remainder> rems;
-    groups.clear();
-    uint64_t start = 0;
-    for (uint32_t e = 0; e < graph->n_edges; ++e) {
-        const taps_edge &E = graph->edges[e];
-        const uint64_t ns = op_offsets[E.src_op + 1] - op_offsets[E.src_op];
-        const uint64_t nd = op_offsets[E.dst_op + 1] - op_offsets[E.dst_op];
-        if (ns == 0 || nd == 0) continue;
-        if (!ordered) {
-            const uint64_t per_row = (nd + cols - 1) / cols;
-            groups.push_back({start, e, (uint32_t)per_row, 0u, cols});
-            start += ns * per_row;
-            continue;
-        }
-        const uint64_t full = nd / cols, left = nd % cols;
-        if (full) {
-            groups.push_back({start, e, (uint32_t)full, 0u, cols});
-            start += ns * full;
-        }
-        if (left) rems.push_back({e, (uint32_t)ns, (uint32_t)(full * cols), (uint32_t)left});
-    }
-    std::stable_sort(rems.begin(), rems.end(),
-                     [](const remainder &a, const remainder &b) { return a.cols > b.cols; });
-    for (const remainder &r : rems) {
-        groups.push_back({start, r.edge, 1u, r.first_col, r.cols});
-        start += r.rows;
-    }
-    return start;
-}
-
-// The link-class kernel's segments: long ones (remainders last) when there are
-// enough of them to fill the GPU many times over, else short ones in row order.
-uint64_t plan_rows(const taps_graph *graph, const uint64_t *op_offsets,
-                   std::vector<taps_seg_group> &groups) {
-    const uint64_t n = plan_segments(graph, op_offsets, TAPS_TILE_COLS * TAPS_SEG_TILES_LONG, true,
-                                     groups);
-    if (n >= g_long_segs_min.load(std::memory_order_relaxed)) return n;
-    return plan_segments(graph, op_offsets, TAPS_TILE_COLS * TAPS_SEG_TILES_SHORT, true, groups);
-}
-
 // The window plan in device memory: the uploaded chunks (the tables' offsets,
 // and with shared tables the computed edges and their starts) and the arrays
 // the plan kernel fills.
-taps_windows device_windows(const window_plan &p, uint64_t n_windows, const taps_edge_params *params,
+taps_windows device_windows(const window_plan &p, const taps_edge_params *params,
                             const uint32_t *window_edge, const taps_top_row *tops, void *dev,
-                            const chunk &offsets, const chunk &starts) {
+                            const chunk &offsets, const chunk &starts,
+                            const taps_levels_model &model) {
     return {params, at<uint64_t>(dev, p.edges.empty() ? offsets : starts), window_edge, tops,
-            n_windows, p.total, p.tiles, 0u};
+            p.n_windows, p.total, p.tiles, 0u, model};
 }
 
 taps_plan_args device_plan(const window_plan &p, const taps_windows &w, void *dev, const chunk &ops,
@@ -665,7 +605,14 @@ taps_plan_args device_plan(const window_plan &p, const taps_windows &w, void *de
     return {at<taps_op>(dev, ops), at<taps_edge>(dev, edges), at<uint64_t>(dev, op_offsets),
             at<uint64_t>(dev, edge_offsets),
             p.edges.empty() ? nullptr : at<uint32_t>(dev, computed), w.starts, params, window_edge,
-            tops, w.n_windows, p.n_edges, p.tiles * TAPS_TILE_COLS, reverse ? 1u : 0u, 0u};
+            tops, w.n_windows, p.n_edges, p.tiles * TAPS_TILE_COLS, reverse ? 1u : 0u, 0u, w.model};
+}
+
+// The levels of a hierarchy's classes.
+taps_levels_model hier_levels(const taps_hier &H, uint32_t n) {
+    uint32_t boundary[TAPS_D_MAX_CLASSES] = {n, n, n, n};
+    for (uint32_t c = 1; c < H.n_classes; ++c) boundary[c - 1] = H.boundary[c];
+    return taps_make_levels(n, H.n_classes, boundary);
 }
 
 // Edge tables of one graph at n_points bandwidth points (clusters that differ
@@ -727,12 +674,8 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
     std::iota(rep.begin(), rep.end(), 0u);
     if (share && (st = share_edges(graph, op_offsets, strategies, stream, rep)) != TAPS_OK)
         return st;
-    // windows over the computed tables (shared tables: the first of each group), or
-    // the link classes' row segments
-    std::vector<taps_seg_group> groups;
-    const uint64_t n_segs = hier ? plan_rows(graph, op_offsets, groups) : 0;
+    // windows over the computed tables (shared tables: the first of each group)
     const window_plan win = plan_windows(eoff, rep, n_points);
-    const uint64_t n_windows = hier ? 0 : win.n_windows;
     // shared tables: every chunk of a computed table is stored into each table sharing it
     std::vector<uint64_t> dst_list;
     std::vector<taps_copy_task> copies;
@@ -744,46 +687,37 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
                           {graph->edges, sizeof(taps_edge) * n_edges, 0},
                           {op_offsets, sizeof(uint64_t) * (n_ops + 1), 0},
                           {eoff.data(), sizeof(uint64_t) * (n_edges + 1), 0},
-                          {groups.data(), sizeof(taps_seg_group) * groups.size(), 0},
+                          {win.edges.data(), sizeof(uint32_t) * win.edges.size(), 0},
                           {copies.data(), sizeof(taps_copy_task) * copies.size(), 0},
                           {dst_list.data(), sizeof(uint64_t) * dst_list.size(), 0},
-                          {win.edges.data(), sizeof(uint32_t) * win.edges.size(), 0},
                           {win.starts.data(), sizeof(uint64_t) * win.starts.size(), 0}};
     void *dev = nullptr;
     if ((st = upload(sc, ch, &dev)) != TAPS_OK) return st;
-    void *d_desc = nullptr;   // taps_packed, or taps_desc for the link classes
+    taps_packed *d_desc = nullptr;
     taps_edge_params *d_params = nullptr;
-    taps_row_ref *d_segs = nullptr;
     uint32_t *d_win = nullptr;
-    static_assert(sizeof(taps_desc) == sizeof(taps_packed), "one scratch array for either");
-    if ((st = sc.alloc(&d_desc, sizeof(taps_packed) * total)) != TAPS_OK) return st;
+    taps_top_row *d_tops = nullptr;
+    if ((st = sc.alloc((void **)&d_desc, sizeof(taps_packed) * total)) != TAPS_OK) return st;
     if ((st = sc.alloc((void **)&d_params, sizeof(taps_edge_params) * win.n_edges)) != TAPS_OK)
         return st;
-    if ((st = sc.alloc((void **)&d_segs, sizeof(taps_row_ref) * n_segs)) != TAPS_OK) return st;
-    taps_top_row *d_tops = nullptr;
-    if ((st = sc.alloc((void **)&d_win, sizeof(uint32_t) * n_windows)) != TAPS_OK) return st;
-    if (!hier && (st = sc.alloc((void **)&d_tops, sizeof(taps_top_row) * 256)) != TAPS_OK) return st;
-    hipError_t err = hier ? taps_launch_describe_h(strategies, total, (taps_desc *)d_desc, stream)
-                          : taps_launch_describe(strategies, total, lp.n, (taps_packed *)d_desc, stream);
-    const taps_windows tw = device_windows(win, n_windows, d_params, d_win, d_tops, dev, ch[3], ch[8]);
+    if ((st = sc.alloc((void **)&d_win, sizeof(uint32_t) * win.n_windows)) != TAPS_OK) return st;
+    if ((st = sc.alloc((void **)&d_tops, TAPS_TOPS_BYTES)) != TAPS_OK) return st;
+    hipError_t err = taps_launch_describe(strategies, total, lp.n, d_desc, stream);
+    const taps_windows tw = device_windows(win, d_params, d_win, d_tops, dev, ch[3], ch[7],
+                                           hier ? hier_levels(*hier, lp.n) : taps_make_levels(lp.n, lp.lam));
     if (err == hipSuccess) {
-        const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[7],
+        const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[4],
                                               d_params, d_win, d_tops, reverse);
         err = taps_launch_edge_setup(pa, lp, stream);
     }
-    if (err == hipSuccess && hier)
-        err = taps_launch_row_plan({at<taps_edge>(dev, ch[1]), at<uint64_t>(dev, ch[2]),
-                                    at<taps_seg_group>(dev, ch[4]), d_segs, n_segs,
-                                    (uint32_t)groups.size(), 0u}, stream);
     // the edge-table kernel launches (entries > 0): use the events, if any, once
     const hipEvent_t before = g_kernel_before, after = g_kernel_after;
     g_kernel_before = g_kernel_after = nullptr;
     if (err == hipSuccess && before) err = hipEventRecord(before, stream);
     if (err == hipSuccess && hier) {
-        err = taps_launch_edge_costs_h(d_params, d_segs, n_segs, (taps_desc *)d_desc, lp,
-                                       max_edge_rank(graph), *hier, outs[0], stream);
+        err = taps_launch_edge_costs_h(tw, d_desc, *hier, outs[0], stream);
     } else if (err == hipSuccess && n_points == 1) {
-        err = taps_launch_edge_costs(tw, (taps_packed *)d_desc, lp, outs[0], stream);
+        err = taps_launch_edge_costs(tw, d_desc, lp, outs[0], stream);
     } else if (err == hipSuccess) {
         taps_sweep sw;
         std::memset(&sw, 0, sizeof(sw));
@@ -796,7 +730,7 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
             sw.inv_n_binter[k] = lps[k].inv_n_binter;
             sw.out[k] = outs[k];
         }
-        err = taps_launch_edge_costs_sweep(tw, (taps_packed *)d_desc, lp, sw, stream);
+        err = taps_launch_edge_costs_sweep(tw, d_desc, sw, stream);
     }
     for (uint32_t k = 0; k < n_points && err == hipSuccess; ++k)
         err = taps_launch_copy_tables(at<taps_copy_task>(dev, ch[5]), (uint32_t)copies.size(),
@@ -852,6 +786,7 @@ taps_status check_topology(const taps_topology *t, taps_hier *H, taps_cluster *c
             H->a2a_own = 1;
         }
     }
+    for (uint32_t c = 1; c < C; ++c) H->boundary[c] = log2u(t->domain[c - 1]);
     // class of a collective with top level l: the boundaries log2(domain[c]) <= l (c < C - 1);
     // its ct counts the uplinks of a block of the largest of them
     for (uint32_t l = 0; l < TAPS_MAX_LEVELS; ++l) {
@@ -1205,7 +1140,7 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
         const size_t need = carve_size(up) + carve_size(sizeof(taps_packed) * total) +
                             carve_size(sizeof(taps_edge_params) * win.n_edges) +
                             carve_size(sizeof(uint32_t) * win.n_windows) +
-                            carve_size(sizeof(taps_top_row) * 256);
+                            carve_size(TAPS_TOPS_BYTES);
         if (need > TAPS_NOALLOC_SCRATCH_BYTES)
             return fail(TAPS_ERR_CAPACITY,
                         "this build needs %llu bytes of device workspace; the fixed workspace of "
@@ -1233,11 +1168,11 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
     if ((st = ws->carve((void **)&d_params, sizeof(taps_edge_params) * win.n_edges)) != TAPS_OK)
         return st;
     if ((st = ws->carve((void **)&d_win, sizeof(uint32_t) * win.n_windows)) != TAPS_OK) return st;
-    if ((st = ws->carve((void **)&d_tops, sizeof(taps_top_row) * 256)) != TAPS_OK) return st;
+    if ((st = ws->carve((void **)&d_tops, TAPS_TOPS_BYTES)) != TAPS_OK) return st;
     // the strategies, and the edge plan when there are edge entries, in one launch
     const bool edges_on = eoff[n_edges] > 0;
-    const taps_windows tw = device_windows(win, win.n_windows, d_params, d_win, d_tops, dev, ch[3],
-                                           ch[8]);
+    const taps_windows tw = device_windows(win, d_params, d_win, d_tops, dev, ch[3], ch[8],
+                                           taps_make_levels(lp.n, lp.lam));
     const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[4], d_params,
                                           d_win, d_tops, false);
     hipError_t err = taps_launch_build_front(at<taps_build_chunk>(dev, ch[7]),

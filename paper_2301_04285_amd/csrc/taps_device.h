@@ -1401,6 +1401,7 @@ struct taps_hier {
     uint32_t pad2;
     uint32_t levels_of_cls[TAPS_D_MAX_CLASSES];   // bit l: cls_of_top's nibble l is c
     uint32_t beta_of_cls[TAPS_D_MAX_CLASSES];     // the boundary of class c (0 for class 0)
+    uint32_t boundary[TAPS_D_MAX_CLASSES];        // log2 of the block below class c >= 1
 };
 
 // One candidate in factor units, per link class (x0: inside the innermost block).

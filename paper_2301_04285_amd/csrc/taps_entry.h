@@ -271,63 +271,79 @@ __host__ __device__ inline taps_side taps_make_side(uint32_t axes, uint32_t rank
 // What a launch, an edge and a row fix
 // ---------------------------------------------------------------------------
 
-// Levels and the node boundary (uniform over a launch).
+// Levels and link classes (uniform over a launch).  Class 0 lies inside a
+// node; class c >= 1 holds the levels first[c] .. first[c + 1] - 1, whose
+// groups share the links of blocks of 2^beta[c] ranks (beta[c] = first[c]; 0
+// for a class without levels).  The paper's two classes are C = 2.
 struct taps_levels_model {
     uint32_t n;       // levels
     uint32_t full;    // taps_low_mask(n)
-    uint32_t n_in;    // levels inside a node
-    uint32_t shift;   // n_in when some level lies outside, else 0
+    uint32_t first[TAPS_D_MAX_CLASSES + 1];
+    uint32_t beta[TAPS_D_MAX_CLASSES];
     taps_b8 in01;     // 01 at the levels inside a node
     taps_b8 coll;     // an axis's collective at its places in meta: 4, and 128 more outside a node
-    taps_b8 share;    // byte u: 2^(shift - u), the groups that share a node's link when u of its
-                      // levels are free
+    taps_b8 share[TAPS_D_MAX_CLASSES];   // byte u: 2^(beta - u), the groups that share a link of the
+                                         // class when u of the levels below beta are free
 };
 
-__host__ __device__ inline taps_levels_model taps_make_levels(uint32_t n, uint32_t lam) {
+// Bytes 01 at the levels lo .. hi - 1.
+__host__ __device__ inline taps_b8 taps_range(uint32_t lo, uint32_t hi) {
+    uint64_t m = 0;
+#pragma unroll
+    for (uint32_t l = 0; l < TAPS_D_MAX_LEVELS; ++l)
+        if (l >= lo && l < hi) m |= 1ull << (8u * l);
+    return taps_from(m);
+}
+
+// n_classes classes, class c >= 1 from level boundary[c - 1] up (non-decreasing).
+__host__ __device__ inline taps_levels_model taps_make_levels(uint32_t n, uint32_t n_classes,
+                                                              const uint32_t *boundary) {
     taps_levels_model m;
     m.n = n;
     m.full = taps_low_mask(n);
-    m.n_in = lam < n ? lam : n;
-    m.shift = lam < n ? lam : 0u;
-    m.in01 = taps_from(m.n_in >= 8u ? 0x0101010101010101ull
-                                    : 0x0101010101010101ull & ((1ull << (8u * m.n_in)) - 1ull));
+    m.first[0] = 0u;
+    for (uint32_t c = 1; c <= TAPS_D_MAX_CLASSES; ++c)
+        m.first[c] = c < n_classes && boundary[c - 1u] < n ? boundary[c - 1u] : n;
+    for (uint32_t c = 0; c < TAPS_D_MAX_CLASSES; ++c) {
+        m.beta[c] = c && m.first[c] < m.first[c + 1u] ? m.first[c] : 0u;
+        uint64_t share = 0;
+        for (uint32_t u = 0; u < 8u && u <= m.beta[c]; ++u)
+            share |= (uint64_t)(1u << (m.beta[c] - u)) << (8u * u);
+        m.share[c] = taps_from(share);
+    }
+    m.in01 = taps_range(0u, m.first[1]);
     m.coll = {0x84848484u - m.in01.lo * 0x80u, 0x84848484u - m.in01.hi * 0x80u};
-    uint64_t share = 0;
-#pragma unroll
-    for (uint32_t u = 0; u < 8u; ++u)
-        if (u <= m.shift) share |= (uint64_t)(1u << (m.shift - u)) << (8u * u);
-    m.share = taps_from(share);
     return m;
 }
+__host__ __device__ inline taps_levels_model taps_make_levels(uint32_t n, uint32_t lam) {
+    return taps_make_levels(n, 2u, &lam);
+}
 
-// By tops mask, in LDS.  For every top t, with w the width of its axis and k
-// the axis's levels inside a node (0 when no level lies outside): byte t of d
-// is w + (k << 5), of tops FF, of a2a 256 - 2^(8 - w) (an AllToAll moves all
-// but 2^-w of the shard, Eq. 10), of link 256 - 2^(8 - w + k) (of that, all but
-// what stays inside the nodes, Eq. 14).  0 at the other levels.
+// By tops mask, in LDS.  For every top t, with w the width of its axis and k_c
+// the axis's levels below beta[c]: byte t of d is w + (k_1 << 5), of low (more
+// than two classes) k_2 + (k_3 << 4), of tops FF, of a2a 256 - 2^(8 - w) (an
+// AllToAll moves all but 2^-w of the shard, Eq. 10), of link 256 - 2^(8 - w + k)
+// with k that of the axis's own class (of that, all but what stays inside the
+// blocks, Eq. 14; 0 inside a node).  0 at the other levels.
 struct taps_top_row {
     taps_b8 d, tops, a2a, link;
 };
 
-// From the axes' widths w (bytes at the tops): an axis inside the node has
-// all its levels there, of those above only the lowest can reach below the
-// boundary.
-__host__ __device__ inline taps_b8 taps_top_bytes(const taps_b8 &w, uint32_t tp,
-                                                  const taps_levels_model &m) {
-    if (m.shift == 0u) return w;
-    const taps_b8 in = {m.in01.lo * 0xFFu, m.in01.hi * 0xFFu};
-    uint64_t d = taps_u64(w) | (taps_u64(w & in) << 5);
-    const uint32_t out = (tp & m.full) >> m.shift;
-    if (out) {
-        const uint32_t s = m.shift + taps_ctz(out);
+// Of the axes with widths w (bytes at the tops), the levels below beta: all of
+// an axis that ends below it, and of those above only the lowest can reach there.
+__host__ __device__ inline taps_b8 taps_levels_below(const taps_b8 &w, uint32_t tp, uint32_t beta) {
+    const taps_b8 r = taps_range(0u, beta);
+    uint64_t k = taps_u64(w & taps_b8{r.lo * 0xFFu, r.hi * 0xFFu});
+    const uint32_t above = tp >> beta;
+    if (above) {
+        const uint32_t s = beta + taps_ctz(above);
         const uint32_t ws = (uint32_t)(taps_u64(w) >> (8u * s)) & 15u;
-        const uint32_t above = s + 1u - m.shift;
-        if (ws > above) d |= (uint64_t)(ws - above) << (8u * s + 5u);
+        if (ws > s + 1u - beta) k |= (uint64_t)(ws - (s + 1u - beta)) << (8u * s);
     }
-    return taps_from(d);
+    return taps_from(k);
 }
 
-// The widths above by tops mask, independent of the node boundary.
+// The axes' widths by tops mask.
 struct taps_top_table {
     uint32_t w_lo[256], w_hi[256];
 };
@@ -349,18 +365,28 @@ __host__ __device__ constexpr taps_top_table taps_make_tops() {
 }
 
 __host__ __device__ inline taps_top_row taps_make_top_row(const taps_top_table &T, uint32_t tp,
-                                                          const taps_levels_model &m) {
+                                                          const taps_levels_model &m, taps_b8 &low) {
     const taps_b8 w = {T.w_lo[tp], T.w_hi[tp]};
     // FF where a width (at most 8) is not 0
     const taps_b8 tops = taps_none(w + taps_all(0x7F7F7F7Fu));
-    const taps_b8 d = taps_top_bytes(w, tp, m);
+    const taps_b8 one = tops & taps_all(0x01010101u);
     // 256 - 2^(8 - x) for x = 1 .. 8 by x - 1
     const taps_b8 parts = {0xF0E0C080u, 0xFFFEFCF8u};
-    const taps_b8 one = tops & taps_all(0x01010101u);
-    // an axis inside a node sends nothing over the link
-    const taps_b8 out = {tops.lo & ~(m.in01.lo * 0xFFu), tops.hi & ~(m.in01.hi * 0xFFu)};
-    const taps_b8 kap = taps_from((taps_u64(d) >> 5) & 0x0707070707070707ull) & out;
-    return {d, tops, taps_map(parts, w - one) & tops, taps_map(parts, w - one - kap) & out};
+    taps_top_row row = {w, tops, taps_map(parts, w - one) & tops, {0u, 0u}};
+    low = {0u, 0u};
+#pragma unroll
+    for (uint32_t c = 1; c < TAPS_D_MAX_CLASSES; ++c) {
+        if (m.first[c] >= m.first[c + 1u]) continue;   // uniform
+        const taps_b8 k = m.beta[c] ? taps_levels_below(w, tp, m.beta[c]) : taps_b8{0u, 0u};
+        const uint64_t k64 = taps_u64(k);
+        if (c == 1u) row.d = row.d | taps_from(k64 << 5);
+        if (c == 2u) low = low | k;
+        if (c == 3u) low = low | taps_from(k64 << 4);
+        const taps_b8 r = taps_range(m.first[c], m.first[c + 1u]);
+        const taps_b8 mine = tops & taps_b8{r.lo * 0xFFu, r.hi * 0xFFu};
+        row.link = row.link | (taps_map(parts, w - one - (k & mine)) & mine);
+    }
+    return row;
 }
 
 // The source side of a row: its levels' dimensions and places, the ends and
@@ -375,7 +401,9 @@ struct taps_source {
     taps_b8 uncut;    // FF where no cut lies below the level
     taps_b8 rank;     // per level: its place among the positions in order (dimension, then bit)
     taps_b8 order;    // per place in that order: the level (0x0C: none)
-    uint32_t g;       // the state G before the first step
+    uint32_t g;       // the state G before the first step: the shard's exponent, and << 5 the
+                      // free levels below beta[1]
+    uint32_t h;       // more than two classes: the free levels below beta[2], and << 4 below beta[3]
 };
 
 // FF at the dimensions that an edge's tensor has (dimension 7 stands for
@@ -385,6 +413,7 @@ __host__ __device__ inline taps_b8 taps_in_tensor(uint32_t rank, const taps_b8 &
     return {taps_perm(hi, 0xFFFFFFFFu, dim.lo), taps_perm(hi, 0xFFFFFFFFu, dim.hi)};
 }
 
+template <uint32_t C>
 __host__ __device__ inline taps_source taps_make_source(const taps_packed &p, const taps_side &side,
                                                         uint32_t rank, const taps_levels_model &m) {
     taps_source P;
@@ -409,8 +438,13 @@ __host__ __device__ inline taps_source taps_make_source(const taps_packed &p, co
         if (l < m.n) order ^= (uint64_t)((l ^ 0x0Cu) & held_l) << (8u * rank_l);
     }
     P.order = taps_from(order);
-    const uint32_t free_in = m.shift ? m.shift - taps_sum(P.held & m.in01, 0u) : 0u;
-    P.g = ((m.n - used) & 15u) | (free_in << 5);
+    uint32_t free_below[TAPS_D_MAX_CLASSES];
+#pragma unroll
+    for (uint32_t c = 1; c < TAPS_D_MAX_CLASSES; ++c)
+        free_below[c] = c < C && m.beta[c]
+                            ? m.beta[c] - taps_sum(P.held & taps_range(0u, m.beta[c]), 0u) : 0u;
+    P.g = ((m.n - used) & 15u) | (free_below[1] << 5);
+    P.h = free_below[2] | (free_below[3] << 4);
     return P;
 }
 
@@ -418,11 +452,21 @@ __host__ __device__ inline taps_source taps_make_source(const taps_packed &p, co
 // One entry
 // ---------------------------------------------------------------------------
 
+// One candidate in factor units (taps_fac), by link class: volume, what class
+// 0 carries, what class c carries over its links times the sharing groups, and
+// the sum of the group counts.
+template <uint32_t C>
+struct taps_cost_c {
+    uint32_t vol, in, link[C > 1 ? C - 1 : 1], ct;
+};
+
 // Replace (Algorithm 1), rearrange (the same without AllToAll) and remove.
+template <uint32_t C>
 struct taps_three {
-    taps_fac c[3];
-    uint32_t coll;   // collectives of every candidate and inter-node ones among them, at their
-                     // places in the record's meta (bits 2 and 7 up)
+    taps_cost_c<C> c[3];
+    uint32_t a2a_in;   // what AllToAlls carry of c[0].in
+    uint32_t coll;     // collectives of every candidate and inter-node ones among them, at their
+                       // places in the record's meta (bits 2 and 7 up)
 };
 
 // One pointer-doubling step of "not reached": x stays FF only where the level
@@ -431,10 +475,15 @@ __host__ __device__ inline taps_b8 taps_hop(const taps_b8 &x, const taps_b8 &to)
     return x & taps_map(x, to);
 }
 
+// tab, low: taps_make_top_row's by tops mask (low is read for more than two
+// classes).
+template <uint32_t C>
 __host__ __device__ inline void taps_three_candidates(const taps_source &P, const taps_packed &q,
                                                       const taps_side &side, uint32_t rank,
                                                       const taps_levels_model &m,
-                                                      const taps_top_row *tab, taps_three &out) {
+                                                      const taps_top_row *tab, const taps_b8 *low,
+                                                      taps_three<C> &out) {
+    constexpr bool kLow = C > 2;   // the free levels below further boundaries are followed too
     // the target side's levels and dimensions, as in taps_source
     const taps_b8 axis_of = taps_unnibble(side.axis_of);
     const taps_b8 dim = taps_map(taps_unnibble(side.dim_of), taps_unnibble(q.owner));
@@ -468,6 +517,8 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     const uint32_t tp = m.full & ~(taps_bits(uncut) >> 1);
     const taps_top_row row = taps_entry<5>(tab, tp);
     const taps_b8 D = row.d;
+    taps_b8 D2 = {0u, 0u};
+    if (kLow) D2 = taps_entry<3>(low, tp);
 
     // away: not at the same position on both sides
     const taps_b8 away = {taps_perm(0xFFFFFFFFu, 0xFFFFFF00u, prev.lo ^ 0x03020100u),
@@ -481,10 +532,11 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     const taps_b8 sliced = taps_bitop3<TAPS_A_NOTB_C>(todo0, held, open);
     const taps_b8 todo = todo0 & ~sliced;
     const uint32_t G = P.g - taps_sum(D & sliced, 0u);
+    const uint32_t H = kLow ? P.h - taps_sum(D2 & sliced, 0u) : 0u;
 
     // ---- Algorithm 1: the state every axis is moved at, and the axes that
     // AllToAlls move (taps_alg1_t has the schedule)
-    taps_b8 at, a2a;
+    taps_b8 at, at2 = {0u, 0u}, a2a;   // at2: the free levels of H
     {
         // the first closure: movable axes, then those whose targets they free
         const taps_b8 movers = todo & held;
@@ -497,12 +549,13 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
         stay = taps_hop(stay, hop4);
         a2a = ~stay;
         at = taps_all(G * 0x01010101u) & a2a;
+        if (kLow) at2 = taps_all(H * 0x01010101u) & a2a;
         taps_b8 left = held & stay, wait = todo & stay;
         // the slices those moves make possible: at once if the first InferSlice
         // found something, else with the next pass
         const taps_b8 ug = left & unwanted;
         const bool now = taps_any(sliced), gathers = taps_any(ug);
-        uint32_t g = G, pending = 0u;
+        uint32_t g = G, pending = 0u, h = H, pending2 = 0u;
         if (taps_wave_any(now | gathers)) {
             taps_b8 freed = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
             freed = freed & taps_all((now | gathers) ? ~0u : 0u);
@@ -510,15 +563,26 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
             const uint32_t f = taps_sum(D & freed, 0u);
             g -= now ? f : 0u;
             pending = now ? 0u : f;
+            if (kLow) {
+                const uint32_t f2 = taps_sum(D2 & freed, 0u);
+                h -= now ? f2 : 0u;
+                pending2 = now ? 0u : f2;
+            }
         }
         // untargeted gathers in producer order; a pending slice follows the first
         if (taps_wave_any(gathers)) {
             const taps_b8 us = taps_map(ug, P.order);
+            const uint32_t f_lo = us.lo & (0u - us.lo), f_hi = us.lo ? 0u : us.hi & (0u - us.hi);
             taps_b8 e = taps_map(D & ug, P.order);
-            e.lo -= (us.lo & (0u - us.lo)) * pending;
-            e.hi -= (us.lo ? 0u : us.hi & (0u - us.hi)) * pending;
-            const taps_b8 ug_at = taps_map(taps_states(e, g, g), P.rank);
-            at = taps_blend(ug, ug_at, at);
+            e.lo -= f_lo * pending;
+            e.hi -= f_hi * pending;
+            at = taps_blend(ug, taps_map(taps_states(e, g, g), P.rank), at);
+            if (kLow) {
+                taps_b8 e2 = taps_map(D2 & ug, P.order);
+                e2.lo -= f_lo * pending2;
+                e2.hi -= f_hi * pending2;
+                at2 = taps_blend(ug, taps_map(taps_states(e2, h, h), P.rank), at2);
+            }
             left = left & ~ug;
         }
         // AllGatherFirstUndoneDim and a pass, until nothing is held; each round
@@ -530,10 +594,15 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
                                taps_perm(0u, 0xFFu, level ^ 0x07060504u)};
             at = taps_blend(x, taps_all(g * 0x01010101u), at);
             g = taps_sum(D & x, g);
+            if (kLow) {
+                at2 = taps_blend(x, taps_all(h * 0x01010101u), at2);
+                h = taps_sum(D2 & x, h);
+            }
             left = left & ~x;
             const taps_b8 s1 = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
             wait = wait & ~s1;
             g -= taps_sum(D & s1, 0u);
+            if (kLow) h -= taps_sum(D2 & s1, 0u);
             // the axes the gathered one's position holds up, directly or not
             taps_b8 keep = ~x;
             keep = taps_hop(keep, hop1);
@@ -541,6 +610,7 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
             keep = taps_hop(keep, hop4);
             const taps_b8 moved = left & ~keep;
             at = taps_blend(moved, taps_all(g * 0x01010101u), at);
+            if (kLow) at2 = taps_blend(moved, taps_all(h * 0x01010101u), at2);
             a2a = a2a | moved;
             left = left & ~moved;
             wait = wait & ~moved;
@@ -548,13 +618,14 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
                 const taps_b8 s2 = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
                 wait = wait & ~s2;
                 g -= taps_sum(D & s2, 0u);
+                if (kLow) h -= taps_sum(D2 & s2, 0u);
             }
             hb = taps_bits(taps_map(left, P.order));
         }
     }
 
     // ---- "rearrange": untargeted axes in producer order, then targeted ones
-    taps_b8 at_r;
+    taps_b8 at_r, at_r2 = {0u, 0u};
     {
         // a targeted axis whose blocker comes before it
         const taps_b8 before = taps_none((P.rank + taps_all(0x7F7F7F7Fu)) -
@@ -573,22 +644,38 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
         const taps_b8 first = taps_states(plus & us, G, g);
         const taps_b8 then = taps_states((plus & ~us) - minus, g, g);
         at_r = taps_map(taps_blend(us, first, then), P.rank);
+        if (kLow) {
+            const taps_b8 plus2 = taps_map(D2 & kept, P.order);
+            const taps_b8 minus2 = taps_map(D2 & later, ns) & ~us;
+            uint32_t h;
+            const taps_b8 first2 = taps_states(plus2 & us, H, h);
+            const taps_b8 then2 = taps_states((plus2 & ~us) - minus2, h, h);
+            at_r2 = taps_map(taps_blend(us, first2, then2), P.rank);
+        }
     }
 
     // ---- "remove": every axis gathered in producer order
     const taps_b8 Dh = D & held;
     uint32_t g_end;
     const taps_b8 at_m = taps_map(taps_states(taps_map(Dh, P.order), P.g, g_end), P.rank);
+    taps_b8 at_m2 = {0u, 0u}, Dh2 = {0u, 0u};
+    if (kLow) {
+        uint32_t h_end;
+        Dh2 = D2 & held;
+        at_m2 = taps_map(taps_states(taps_map(Dh2, P.order), P.h, h_end), P.rank);
+    }
 
     // ---- costs.  A gather of an axis of width w at shard 2^e (e + w <= 8) moves
-    // 2^(e + w) - 2^e (Eq. 9), an AllToAll 2^e - 2^(e - w) (Eq. 10); out of a node,
-    // 2^(shift - u) groups share the link, u the free levels inside a node, the
+    // 2^(e + w) - 2^e (Eq. 9), an AllToAll 2^e - 2^(e - w) (Eq. 10); out of a block,
+    // 2^(beta - u) groups share the link, u the free levels below beta, the
     // axis's own among them (Algorithm 3).
-    const taps_b8 width = Dh & taps_all(0x0F0F0F0Fu), in_node = Dh & taps_all(0xE0E0E0E0u);
-    const taps_b8 x1 = at + in_node, x2 = at_r + in_node, x3 = at_m + in_node;
-    uint32_t in1 = 0, in2 = 0, a2a_in = 0;
-    uint32_t out1 = 0, out2 = 0, out3 = 0, link1 = 0, link2 = 0, link3 = 0;
-    uint32_t ct1 = 0, ct2 = 0, ct3 = 0, a2a_out = 0, a2a_link = 0;
+    const taps_b8 width = Dh & taps_all(0x0F0F0F0Fu), below = Dh & taps_all(0xE0E0E0E0u);
+    const taps_b8 x1 = at + below, x2 = at_r + below, x3 = at_m + below;
+    const taps_b8 z1 = at2 + Dh2, z2 = at_r2 + Dh2, z3 = at_m2 + Dh2;
+    uint32_t in1 = 0, in2 = 0, a2a_in = 0, out1 = 0, out2 = 0, out3 = 0, a2a_out = 0;
+    uint32_t ct1 = 0, ct2 = 0, ct3 = 0;
+    uint32_t link1[TAPS_D_MAX_CLASSES] = {0u}, link2[TAPS_D_MAX_CLASSES] = {0u};
+    uint32_t link3[TAPS_D_MAX_CLASSES] = {0u}, a2a_link[TAPS_D_MAX_CLASSES] = {0u};
     // the gathers' volumes, a byte each, of the axes in mask
     auto volumes = [](uint32_t x, uint32_t more, uint32_t mask) {
         const uint32_t e = x & 0x07070707u;
@@ -598,33 +685,39 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     };
     const taps_b8 more = width - (held & taps_all(0x01010101u));   // w - 1
     auto inside = [&](uint32_t l) {   // levels l .. l + 3 inside a node
-        const uint32_t sel = taps_four(l, m.n_in);
-        const uint32_t h = taps_perm(held.hi, held.lo, sel), mo = taps_perm(more.hi, more.lo, sel);
+        const uint32_t sel = taps_four(l, m.first[1]);
+        const uint32_t hm = taps_perm(held.hi, held.lo, sel), mo = taps_perm(more.hi, more.lo, sel);
         const uint32_t am = taps_perm(a2a.hi, a2a.lo, sel);
         const uint32_t y1 = taps_perm(x1.hi, x1.lo, sel), y2 = taps_perm(x2.hi, x2.lo, sel);
-        in1 = taps_dot4(volumes(y1, mo, h & ~am), 0x01010101u, in1);
-        in2 = taps_dot4(volumes(y2, mo, h), 0x01010101u, in2);
+        in1 = taps_dot4(volumes(y1, mo, hm & ~am), 0x01010101u, in1);
+        in2 = taps_dot4(volumes(y2, mo, hm), 0x01010101u, in2);
         const uint32_t part = taps_perm(row.a2a.hi, row.a2a.lo, sel) & am;
         a2a_in = taps_dot4(part, taps_pow2(y1 & 0x07070707u), a2a_in);
     };
-    auto outside = [&](uint32_t l) {   // levels l .. l + 3 outside
-        const uint32_t sel = taps_four(l, m.n);
-        const uint32_t h = taps_perm(held.hi, held.lo, sel), mo = taps_perm(more.hi, more.lo, sel);
-        const uint32_t am = taps_perm(a2a.hi, a2a.lo, sel);
+    auto outside = [&](uint32_t c, uint32_t l) {   // levels l .. l + 3 of class c
+        const uint32_t sel = taps_four(l, m.first[c + 1u]);
+        const uint32_t hm = taps_perm(held.hi, held.lo, sel), mo = taps_perm(more.hi, more.lo, sel);
+        const uint32_t am = taps_perm(a2a.hi, a2a.lo, sel), one = hm & 0x01010101u;
         const uint32_t y1 = taps_perm(x1.hi, x1.lo, sel), y2 = taps_perm(x2.hi, x2.lo, sel);
-        const uint32_t y3 = taps_perm(x3.hi, x3.lo, sel), one = h & 0x01010101u;
-        const uint32_t u1 = (y1 >> 5) & 0x07070707u, u2 = (y2 >> 5) & 0x07070707u;
-        const uint32_t u3 = (y3 >> 5) & 0x07070707u;
-        const uint32_t s1 = taps_perm(m.share.hi, m.share.lo, u1);
-        const uint32_t s2 = taps_perm(m.share.hi, m.share.lo, u2);
-        const uint32_t s3 = taps_perm(m.share.hi, m.share.lo, u3);
-        const uint32_t v1 = volumes(y1, mo, h & ~am), v2 = volumes(y2, mo, h), v3 = volumes(y3, mo, h);
+        const uint32_t y3 = taps_perm(x3.hi, x3.lo, sel);
+        // the free levels below this class's boundary
+        auto u_of = [&](uint32_t y, const taps_b8 &z) {
+            const uint32_t f = c == 1u ? y : taps_perm(z.hi, z.lo, sel);
+            return (c == 1u ? f >> 5 : c == 2u ? f : f >> 4) & 0x07070707u;
+        };
+        const uint32_t u1 = u_of(y1, z1);
+        const taps_b8 share = m.share[c];
+        const uint32_t s1 = taps_perm(share.hi, share.lo, u1);
+        const uint32_t s2 = taps_perm(share.hi, share.lo, u_of(y2, z2));
+        const uint32_t s3 = taps_perm(share.hi, share.lo, u_of(y3, z3));
+        const uint32_t v1 = volumes(y1, mo, hm & ~am), v2 = volumes(y2, mo, hm);
+        const uint32_t v3 = volumes(y3, mo, hm);
         out1 = taps_dot4(v1, 0x01010101u, out1);
         out2 = taps_dot4(v2, 0x01010101u, out2);
         out3 = taps_dot4(v3, 0x01010101u, out3);
-        link1 = taps_dot4(v1, s1, link1);
-        link2 = taps_dot4(v2, s2, link2);
-        link3 = taps_dot4(v3, s3, link3);
+        link1[c] = taps_dot4(v1, s1, link1[c]);
+        link2[c] = taps_dot4(v2, s2, link2[c]);
+        link3[c] = taps_dot4(v3, s3, link3[c]);
         ct1 = taps_dot4(one, s1, ct1);
         ct2 = taps_dot4(one, s2, ct2);
         ct3 = taps_dot4(one, s3, ct3);
@@ -632,23 +725,40 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
         // levels, 2^x with x up to 14: the bytes of x < 8 and of x >= 8 apart
         const uint32_t e = y1 & 0x07070707u;
         a2a_out = taps_dot4(taps_perm(row.a2a.hi, row.a2a.lo, sel) & am, taps_pow2(e), a2a_out);
-        const uint32_t kap = taps_perm(in_node.hi, in_node.lo, sel) >> 5;
-        const uint32_t x = e + m.shift * 0x01010101u - (u1 & h) + kap;
+        const taps_b8 own = c == 1u ? below : Dh2;
+        const uint32_t o = taps_perm(own.hi, own.lo, sel);
+        const uint32_t kap = (c == 1u ? o >> 5 : c == 2u ? o : o >> 4) & 0x07070707u;
+        const uint32_t x = e + m.beta[c] * 0x01010101u - (u1 & hm) + kap;
         const uint32_t part = taps_perm(row.link.hi, row.link.lo, sel) & am;
         const uint32_t p = taps_pow2(x & 0x07070707u);
         const uint32_t big = part & taps_perm(0u, 0x00008000u, x & 0x08080808u);
-        const uint32_t hi = taps_dot4(big, p, 0u);
-        a2a_link += taps_dot4(part, p, 0u) + hi * 255u;
+        a2a_link[c] += taps_dot4(part, p, 0u) + taps_dot4(big, p, 0u) * 255u;
     };
     inside(0u);
-    if (m.n_in > 4u) inside(4u);   // uniform, as below
-    outside(m.n_in);
-    if (m.n - m.n_in > 4u) outside(m.n_in + 4u);
+    if (m.first[1] > 4u) inside(4u);   // uniform, as below
+#pragma unroll
+    for (uint32_t c = 1; c < C; ++c) {
+        if (C == 2 || m.first[c] < m.first[c + 1u]) outside(c, m.first[c]);
+        if (m.first[c + 1u] - m.first[c] > 4u) outside(c, m.first[c] + 4u);
+    }
     const uint32_t in_1 = (in1 << 8) + a2a_in, out_1 = (out1 << 8) + a2a_out;
-    out.c[0] = {in_1 + out_1, in_1, (link1 << 8) + a2a_link, ct1};
-    out.c[1] = {(in2 + out2) << 8, in2 << 8, link2 << 8, ct2};
     const uint32_t vol_m = (1u << (g_end & 15u)) - (1u << (P.g & 15u));   // telescopes
-    out.c[2] = {vol_m << 8, (vol_m - out3) << 8, link3 << 8, ct3};
+    out.c[0].vol = in_1 + out_1;
+    out.c[0].in = in_1;
+    out.c[0].ct = ct1;
+    out.c[1].vol = (in2 + out2) << 8;
+    out.c[1].in = in2 << 8;
+    out.c[1].ct = ct2;
+    out.c[2].vol = vol_m << 8;
+    out.c[2].in = (vol_m - out3) << 8;
+    out.c[2].ct = ct3;
+#pragma unroll
+    for (uint32_t c = 1; c < C; ++c) {
+        out.c[0].link[c - 1u] = (link1[c] << 8) + a2a_link[c];
+        out.c[1].link[c - 1u] = link2[c] << 8;
+        out.c[2].link[c - 1u] = link3[c] << 8;
+    }
+    out.a2a_in = a2a_in;
     const taps_b8 h01 = held & taps_all(0x01010101u);
     out.coll = taps_dot4(h01.hi, m.coll.hi, taps_dot4(h01.lo, m.coll.lo, 0u));
 }

@@ -26,11 +26,8 @@ struct taps_edge_params {
     uint32_t src_base;     // first strategy of the source side (producer; consumer for
     uint32_t dst_base;     //   the backward tables) and of the target side
     uint32_t ns, nd;       // their strategy counts
-    uint32_t rank;
-    uint32_t paxes;        // nibble d: source op axis of tensor dimension d
-    uint32_t caxes;        // nibble d: target op axis of tensor dimension d
-    uint32_t pad;
-    taps_side from, to;    // the same two maps for taps_entry.h
+    uint32_t rank, pad;
+    taps_side from, to;    // tensor dimensions and op axes of the two sides
 };
 
 // Shared tables: entries [src, src + count) of every array are copied to
@@ -43,7 +40,7 @@ struct taps_copy_task {
 #define TAPS_COPY_CHUNK 2048    // entries per copy task (8 per thread of 256)
 #define TAPS_COPY_DSTS 6        // tables one copy task writes (4-6 measured best, 16 is 20 % slower)
 
-// The two-class edge kernels run over windows: window w is the 64 T entries
+// The edge kernels run over windows: window w is the 64 T entries
 // [64 T w, 64 T (w + 1)) of the computed tables laid end to end (aligned, so
 // that every store covers whole lines), taken by one wavefront 64 at a time.
 #define TAPS_TILE_COLS 64
@@ -61,39 +58,8 @@ struct taps_copy_task {
 #define TAPS_WINDOW_SWEEP 4
 #define TAPS_LONG_SEGS_MIN 32768
 
-// The link-class kernel runs over row segments: one wavefront per producer
-// strategy i of one edge and the consumer strategies [first_col, last_col) of
-// its row, walked 64 at a time, TAPS_ROWS_PER_BLOCK segments per workgroup.
-// Segments of TAPS_SEG_TILES_LONG tiles amortise the producer side in launches
-// of many of them (full-length segments first, the shorter remainders last);
-// launches with few segments use TAPS_SEG_TILES_SHORT.
-#define TAPS_SEG_TILES_LONG 8
-#define TAPS_SEG_TILES_SHORT 2
-#define TAPS_ROWS_PER_BLOCK 2
-
-// A run of row segments of one edge: every row of the edge's table cut into
-// per_row segments of `cols` consumer strategies from first_col, the last
-// one ending at the row's end at the latest.  Segment r of a launch belongs
-// to the last group whose start is at most r: row (r - start) / per_row,
-// first consumer first_col + ((r - start) % per_row) * cols.
-struct taps_seg_group {
-    uint64_t start;
-    uint32_t edge, per_row, first_col, cols;
-};
-
-// Segment r of a launch: its edge, the global index of its producer strategy
-// and its consumer strategies [first_col, last_col).
-struct taps_row_ref {
-    uint32_t edge;
-    uint32_t strategy;
-    uint32_t first_col;
-    uint32_t last_col;
-};
-
 hipError_t taps_launch_describe(const taps_strategy *s, uint64_t total, uint32_t n,
                                 taps_packed *desc, hipStream_t stream);
-hipError_t taps_launch_describe_h(const taps_strategy *s, uint64_t total, taps_desc *desc,
-                                  hipStream_t stream);
 hipError_t taps_launch_node_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
                                   const taps_packed *desc, uint64_t total, const taps_launch &lp,
                                   taps_table out, hipStream_t stream);
@@ -111,13 +77,15 @@ struct taps_plan_args {
     const uint64_t *starts;
     taps_edge_params *params;
     uint32_t *window_edge;
-    taps_top_row *tops;          // 256 rows (NULL: not wanted)
+    taps_top_row *tops;          // TAPS_TOPS_BYTES: 256 rows, then their `low` bytes
     uint64_t n_windows;
     uint32_t n_edges, window, reverse, pad;
+    taps_levels_model model;
 };
+#define TAPS_TOPS_BYTES ((sizeof(taps_top_row) + sizeof(taps_b8)) * 256)
 hipError_t taps_launch_edge_setup(const taps_plan_args &pa, const taps_launch &lp,
                                   hipStream_t stream);
-// What the two-class edge kernels run over (the plan's results).
+// What the edge kernels run over (the plan's results).
 struct taps_windows {
     const taps_edge_params *params;
     const uint64_t *starts;
@@ -125,22 +93,10 @@ struct taps_windows {
     const taps_top_row *tops;
     uint64_t n_windows, total;   // total: computed entries
     uint32_t tiles, pad;         // tiles per window
+    taps_levels_model model;
 };
 hipError_t taps_launch_edge_costs(const taps_windows &win, const taps_packed *desc,
                                   const taps_launch &lp, taps_table out, hipStream_t stream);
-// The row segments of the link-class kernel's groups into segs.
-struct taps_row_plan {
-    const taps_edge *edges;
-    const uint64_t *op_offsets;
-    const taps_seg_group *groups;
-    taps_row_ref *segs;
-    uint64_t n_segs;
-    uint32_t n_groups, pad;
-};
-hipError_t taps_launch_row_plan(const taps_row_plan &pa, hipStream_t stream);
-// max_rank: the largest tensor rank of the launch's edges; up to TAPS_LOW_RANK
-// the link-class kernel is compiled for that many dimensions.
-#define TAPS_LOW_RANK 4
 hipError_t taps_launch_memory_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
                                    const taps_strategy *s, uint64_t total, uint64_t *memory,
                                    hipStream_t stream);
@@ -156,8 +112,7 @@ struct taps_sweep {
     taps_table out[TAPS_MAX_SWEEP];
 };
 hipError_t taps_launch_edge_costs_sweep(const taps_windows &win, const taps_packed *desc,
-                                        const taps_launch &lp, const taps_sweep &sw,
-                                        hipStream_t stream);
+                                        const taps_sweep &sw, hipStream_t stream);
 // One workgroup of k_build_strategies: candidate ranks [first, first +
 // TAPS_BUILD_CHUNK) of operator `op`, of which `count` pass the filter; they
 // are strategies base, base + 1, ... in rank order.
@@ -180,10 +135,8 @@ hipError_t taps_launch_build_front(const taps_build_chunk *chunks, uint32_t n_ch
                                    taps_packed *desc, taps_table node, const taps_plan_args &pa,
                                    hipStream_t stream);
 // Link-class hierarchies: the edge and node tables under the classes of H.
-hipError_t taps_launch_edge_costs_h(const taps_edge_params *params, const taps_row_ref *rows,
-                                    uint64_t n_rows, const taps_desc *desc, const taps_launch &lp,
-                                    uint32_t max_rank, const taps_hier &H, taps_table out,
-                                    hipStream_t stream);
+hipError_t taps_launch_edge_costs_h(const taps_windows &win, const taps_packed *desc,
+                                    const taps_hier &H, taps_table out, hipStream_t stream);
 hipError_t taps_launch_node_costs_h(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
                                     const taps_packed *desc, uint64_t total, uint32_t n,
                                     const taps_hier &H, taps_table out, hipStream_t stream);

@@ -15,7 +15,7 @@
 //                 (taps_entry.h); whole-line stores
 //   k_edge_costs_sweep  the same at several bandwidth points: the candidates
 //                 once per entry, one selection and store per point
-//   k_edge_costs_h  link classes: one wavefront per row segment (k_row_plan)
+//   k_edge_costs_h  the same under a hierarchy of link classes
 //   k_copy_tables shared tables: one workgroup per chunk of a computed
 //                 table, written to every table that shares it
 //   k_pull        a call's upload, read from pinned host memory
@@ -32,34 +32,6 @@ __constant__ taps_top_table kTops = taps_make_tops();
 // Completion counts w(k, s, z) for k, s, z in 0..8 (see taps_completions),
 // evaluated by the compiler.
 __constant__ taps_completion_table kCompletions = taps_make_completions();
-// Widths of unified axes by their tops (taps_make_widths), copied to LDS by the
-// edge kernels.
-__constant__ taps_width_table kWidths = taps_make_widths();
-// AllToAll shard fractions by tops mask and masks as bytes (taps_make_a2a,
-// taps_make_expand), copied to LDS by the two-class edge kernels.
-__constant__ taps_a2a_table kA2a = taps_make_a2a();
-__constant__ taps_expand_table kExpand = taps_make_expand();
-
-// The per-workgroup LDS tables of the link-class AllToAll costing: per tops
-// mask, the shard-fraction bytes of the tops in each class (a level's byte
-// kept where the level's class is c).
-__device__ inline void fill_a2a_class_tables(taps_pair *a2a_cls, taps_pair *expand,
-                                             const taps_hier &H) {
-    uint32_t lo_mask[TAPS_D_MAX_CLASSES], hi_mask[TAPS_D_MAX_CLASSES];
-#pragma unroll
-    for (uint32_t c = 0; c < TAPS_D_MAX_CLASSES; ++c) {
-        const uint32_t m = c < H.n_classes ? H.levels_of_cls[c] & 0xFFu : 0u;
-        lo_mask[c] = kExpand.lo[m] * 0xFFu;
-        hi_mask[c] = kExpand.hi[m] * 0xFFu;
-    }
-    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) {
-        const uint32_t lo = kA2a.lo[x], hi = kA2a.hi[x];
-#pragma unroll
-        for (uint32_t c = 0; c < TAPS_D_MAX_CLASSES; ++c)
-            a2a_cls[x * TAPS_D_MAX_CLASSES + c] = taps_pair{lo & lo_mask[c], hi & hi_mask[c]};
-        expand[x] = taps_pair{kExpand.lo[x], kExpand.hi[x]};
-    }
-}
 
 template <typename T>
 __device__ inline T *at_byte(T *base, uint32_t offset) {
@@ -104,22 +76,6 @@ __global__ __launch_bounds__(256) void k_describe(const taps_strategy *__restric
     const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= total) return;
     desc[idx] = taps_lay_out(strategy_nibbles(s[idx]), 0xFFu, n).packed;
-}
-
-// The form of the link-class kernel.
-__global__ __launch_bounds__(256) void k_describe_h(const taps_strategy *__restrict__ s,
-                                                    uint64_t total, taps_desc *__restrict__ desc) {
-    const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const taps_strategy st = s[idx];
-    uint32_t expo[TAPS_D_MAX_AXES];
-    int32_t pos[TAPS_D_MAX_AXES];
-#pragma unroll
-    for (uint32_t a = 0; a < TAPS_D_MAX_AXES; ++a) {
-        expo[a] = st.log2_deg[a];
-        pos[a] = st.pos[a];
-    }
-    desc[idx] = taps_describe(TAPS_D_MAX_AXES, expo, pos);
 }
 
 // largest k in [0, n) with offsets[k] <= x
@@ -339,11 +295,9 @@ __device__ inline void edge_setup_one(uint32_t k, const taps_plan_args &pa, cons
     p.ns = (uint32_t)(pa.op_offsets[from + 1] - pa.op_offsets[from]);
     p.nd = (uint32_t)(pa.op_offsets[to + 1] - pa.op_offsets[to]);
     p.rank = T.rank;
-    p.paxes = pa.reverse ? cax : pax;
-    p.caxes = pa.reverse ? pax : cax;
+    p.from = taps_make_side(pa.reverse ? cax : pax, T.rank);
+    p.to = taps_make_side(pa.reverse ? pax : cax, T.rank);
     p.pad = 0;
-    p.from = taps_make_side(p.paxes, T.rank);
-    p.to = taps_make_side(p.caxes, T.rank);
     pa.params[k] = p;
 }
 
@@ -356,8 +310,11 @@ __device__ inline void window_one(uint64_t w, const taps_plan_args &pa) {
 // first also the edge kernels' table by tops mask), the rest map the windows.
 __device__ inline void edge_plan_block(uint32_t b, uint32_t setup_blocks, const taps_plan_args &pa,
                                        const taps_launch &lp) {
-    if (b == 0u && pa.tops && threadIdx.x < 256u)
-        pa.tops[threadIdx.x] = taps_make_top_row(kTops, threadIdx.x, taps_make_levels(lp.n, lp.lam));
+    if (b == 0u && threadIdx.x < 256u) {
+        taps_b8 low;
+        pa.tops[threadIdx.x] = taps_make_top_row(kTops, threadIdx.x, pa.model, low);
+        ((taps_b8 *)(pa.tops + 256))[threadIdx.x] = low;
+    }
     if (b < setup_blocks) {
         const uint32_t e = b * blockDim.x + threadIdx.x;
         if (e < pa.n_edges) edge_setup_one(e, pa, lp);
@@ -385,38 +342,8 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_front(
         edge_plan_block(blockIdx.x - n_chunks, setup_blocks, pa, lp);
 }
 
-// Row segment r of the link classes' launch: its edge, producer strategy and
-// consumer range (from the strategy offsets, so it does not wait for the edge
-// constants).
-__device__ inline void row_map_one(uint64_t r, const taps_row_plan &pa) {
-    // the last group starting at or before r (groups[0].start == 0)
-    uint32_t lo = 0, hi = pa.n_groups - 1;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1) / 2;
-        if (pa.groups[mid].start <= r)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    const taps_seg_group G = pa.groups[lo];
-    const taps_edge E = pa.edges[G.edge];
-    const uint32_t nd = (uint32_t)(pa.op_offsets[E.dst_op + 1] - pa.op_offsets[E.dst_op]);
-    const uint64_t k = r - G.start;
-    taps_row_ref ref;
-    ref.edge = G.edge;
-    ref.strategy = (uint32_t)(pa.op_offsets[E.src_op] + k / G.per_row);
-    ref.first_col = G.first_col + (uint32_t)(k % G.per_row) * G.cols;
-    ref.last_col = nd - ref.first_col < G.cols ? nd : ref.first_col + G.cols;
-    pa.segs[r] = ref;
-}
-
-__global__ __launch_bounds__(256) void k_row_plan(taps_row_plan pa) {
-    const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < pa.n_segs) row_map_one(r, pa);
-}
-
 // ---------------------------------------------------------------------------
-// The two-class edge kernels.
+// The edge kernels.
 //
 // Wavefront w takes window w, one 64-entry tile at a time, lane l entry l of
 // the tile: its edge is uniform (a tile that runs into the next edge is taken
@@ -488,13 +415,17 @@ __device__ inline taps_source read_row(const row_cache &cache, uint32_t r) {
 
 // Emit(E, v, r): stores the entry of an edge with constants E at entry v of
 // the computed tables, from its candidates r.
-template <typename Emit>
+template <uint32_t C, typename Emit>
 __device__ inline void run_window(const taps_windows &win, const taps_packed *__restrict__ desc,
-                                  const taps_launch &lp, const Emit &emit) {
+                                  const Emit &emit) {
     __shared__ taps_top_row tops[256];
+    __shared__ taps_b8 low[C > 2 ? 256 : 1];
     __shared__ row_cache rows[kWindowsPerBlock];
-    const taps_levels_model m = taps_make_levels(lp.n, lp.lam);
-    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) tops[x] = win.tops[x];
+    const taps_levels_model &m = win.model;
+    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) {
+        tops[x] = win.tops[x];
+        if (C > 2) low[x] = ((const taps_b8 *)(win.tops + 256))[x];
+    }
     __syncthreads();
     const uint32_t lane = threadIdx.x % kWave;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -536,8 +467,9 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
                 if (__any(mine && c.i - cached >= kWave)) {
                     cached = __builtin_amdgcn_readlane(c.i, first);
                     const uint32_t r = cached + lane;
-                    fill_rows(rows[wave], taps_make_source(desc[E.src_base + (r < E.ns ? r : cached)],
-                                                           E.from, E.rank, m), lane);
+                    fill_rows(rows[wave],
+                              taps_make_source<C>(desc[E.src_base + (r < E.ns ? r : cached)],
+                                                  E.from, E.rank, m), lane);
                 }
                 // (an entry's row is within 63 of the first's, as every row has one at least)
                 P = read_row(rows[wave], mine ? c.i - cached : 0u);
@@ -545,8 +477,8 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
             }
             // every lane, so that the branches on the node boundary stay uniform
             // (a lane without an entry computes one that it does not store)
-            taps_three r;
-            taps_three_candidates(P, q, E.to, E.rank, m, tops, r);
+            taps_three<C> r;
+            taps_three_candidates<C>(P, q, E.to, E.rank, m, tops, low, r);
             if (mine) emit(E, v0 + to_out, lane, r);
             if (e_end >= tile_end && (e_end > tile_end || tile_end == end)) break;
             // the next edge starts in this tile, or with the next one
@@ -583,27 +515,31 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
 // Selection among the candidates under one bandwidth point's keys (ties go to
 // the earlier candidate), scaled.  Narrow: 64-bit keys.
 template <bool Narrow>
-__device__ inline taps_entry_out select_entry(const taps_three &r, const taps_keys &K,
+__device__ inline taps_entry_out select_entry(const taps_three<2> &r, const taps_keys &K,
                                               const taps_scaler &S) {
-    uint32_t intra = r.c[0].intra, inter = r.c[0].inter, ct = r.c[0].ct, cand = 0u;
+    auto fac = [&](uint32_t c) {
+        return taps_fac{r.c[c].vol, r.c[c].in, r.c[c].link[0], r.c[c].ct};
+    };
+    uint32_t intra = r.c[0].in, inter = r.c[0].link[0], ct = r.c[0].ct, cand = 0u;
     if (Narrow) {
-        uint64_t best = taps_key64(r.c[0], K);
-        const uint64_t k1 = taps_key64(r.c[1], K), k2 = taps_key64(r.c[2], K);
+        uint64_t best = taps_key64(fac(0), K);
+        const uint64_t k1 = taps_key64(fac(1), K), k2 = taps_key64(fac(2), K);
 #pragma unroll
         for (uint32_t c = 1; c < 3u; ++c) {
             const uint64_t k = c == 1u ? k1 : k2;
             const bool less = k < best;
             best = less ? k : best;
-            intra = less ? r.c[c].intra : intra;
-            inter = less ? r.c[c].inter : inter;
+            intra = less ? r.c[c].in : intra;
+            inter = less ? r.c[c].link[0] : inter;
             ct = less ? r.c[c].ct : ct;
             cand = less ? c : cand;
         }
     } else {
-        taps_fac best = r.c[0];
+        taps_fac best = fac(0);
+#pragma unroll
         for (uint32_t c = 1; c < 3u; ++c)
-            if (taps_less(r.c[c], best, K)) {
-                best = r.c[c];
+            if (taps_less(fac(c), best, K)) {
+                best = fac(c);
                 cand = c;
             }
         intra = best.intra;
@@ -634,8 +570,8 @@ __global__ __launch_bounds__(256) void k_edge_costs(taps_windows win,
                                                     const taps_packed *__restrict__ desc,
                                                     taps_launch lp, taps_table out) {
     const taps_keys K = {lp.b_inter_red, lp.b_intra_red, Narrow};
-    run_window(win, desc, lp, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
-                                  const taps_three &r) {
+    run_window<2>(win, desc, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
+                                 const taps_three<2> &r) {
         const taps_entry_out o = select_entry<Narrow>(r, K, E.scale);
         store_entry(out, at, lane, o, o.meta);
     });
@@ -646,9 +582,9 @@ __global__ __launch_bounds__(256) void k_edge_costs(taps_windows win,
 template <bool Narrow>
 __global__ __launch_bounds__(256) void k_edge_costs_sweep(taps_windows win,
                                                           const taps_packed *__restrict__ desc,
-                                                          taps_launch lp, taps_sweep sw) {
-    run_window(win, desc, lp, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
-                                  const taps_three &r) {
+                                                          taps_sweep sw) {
+    run_window<2>(win, desc, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
+                                 const taps_three<2> &r) {
         for (uint32_t k = 0; k < sw.count; ++k) {
             // Narrow: 64-bit keys at every point
             const taps_keys K = {sw.b_inter_red[k], sw.b_intra_red[k], Narrow || sw.narrow[k] != 0};
@@ -661,48 +597,66 @@ __global__ __launch_bounds__(256) void k_edge_costs_sweep(taps_windows win,
     });
 }
 
-// Link-class hierarchies: one wavefront per row segment, each entry selected and
-// scaled under the classes of H.
-// C: the hierarchy's number of classes.
-template <uint32_t R, uint32_t C>
-__global__ __launch_bounds__(TAPS_TILE_COLS *TAPS_ROWS_PER_BLOCK) void k_edge_costs_h(
-    const taps_edge_params *__restrict__ params, const taps_row_ref *__restrict__ rows,
-    uint32_t n_segs, const taps_desc *__restrict__ desc, taps_launch lp, taps_hier H,
-    taps_table out) {
-    __shared__ uint8_t rank_tab[TAPS_ROWS_PER_BLOCK][256];
-    __shared__ uint32_t width_tab[256];
-    __shared__ taps_pair a2a_cls_tab[256 * TAPS_D_MAX_CLASSES];
-    __shared__ taps_pair expand_tab[256];
-    const uint32_t lane = threadIdx.x % TAPS_TILE_COLS;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / TAPS_TILE_COLS);
-    const uint32_t r = blockIdx.x * TAPS_ROWS_PER_BLOCK + wave;
-    const bool live = r < n_segs;
-    const taps_row_ref ref = rows[live ? r : 0u];
-    const taps_edge_params E = params[ref.edge];
-    __builtin_assume(E.rank <= R);   // the launch's tensors have rank R at most
-    const taps_desc Dp = desc[ref.strategy];
-    const uint32_t i = ref.strategy - E.src_base;
-    taps_row P;
-    taps_make_row(P, Dp, E.paxes, E.rank, lp.n, lp.lam);
-    taps_fill_rank_table(P, rank_tab[wave], lane, TAPS_TILE_COLS);
-    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) width_tab[x] = kWidths.v[x];
-    fill_a2a_class_tables(a2a_cls_tab, expand_tab, H);
-    __syncthreads();
-    if (!live) return;
-    P.to_rank = rank_tab[wave];
-    P.widths = width_tab;
-    P.a2a_cls = a2a_cls_tab;
-    P.expand = expand_tab;
-    const uint64_t row_out = E.out_offset + (uint64_t)i * E.nd;
-    const taps_desc *col = desc + E.dst_base;
-    const uint32_t c0 = ref.first_col;
-    const uint32_t c1 = ref.last_col;
-    for (uint32_t j = c0 + lane; j < c1; j += TAPS_TILE_COLS) {
-        taps_col Q;
-        taps_make_col(Q, col[j], E.caxes, E.rank);
-        const taps_entry_out o = taps_entry_finish_h(taps_edge_select_h<C>(P, Q, H), E.scale, H);
-        store_entry(out, row_out, j, o, o.ok ? o.meta : 0xFFFFFFFFu);
+// Link-class hierarchies: each entry selected by the exact key over the classes
+// of H and scaled.  C: the hierarchy's number of classes.
+template <uint32_t C>
+__device__ inline taps_entry_out select_entry_h(const taps_three<C> &r, const taps_hier &H,
+                                                const taps_scaler &S) {
+    // AllToAlls inside a node at their own bandwidth, if it is set
+    const uint32_t own = H.a2a_own ? r.a2a_in : 0u;
+    auto key = [&](uint32_t c) {
+        uint64_t k = (uint64_t)(r.c[c].in - (c ? 0u : own)) * H.w[0];
+#pragma unroll
+        for (uint32_t x = 1; x < C; ++x) k += (uint64_t)r.c[c].link[x - 1u] * H.w[x];
+        return c ? k : k + (uint64_t)own * H.w_a2a;
+    };
+    const uint64_t k0 = key(0), k1 = key(1), k2 = key(2);
+    const bool one = k1 < k0, two = k2 < (one ? k1 : k0);
+    auto pick = [&](uint32_t a, uint32_t b, uint32_t c) { return two ? c : one ? b : a; };
+    taps_cost_c<C> best;
+    best.in = pick(r.c[0].in, r.c[1].in, r.c[2].in);
+    best.ct = pick(r.c[0].ct, r.c[1].ct, r.c[2].ct);
+#pragma unroll
+    for (uint32_t x = 0; x + 1u < C; ++x)
+        best.link[x] = pick(r.c[0].link[x], r.c[1].link[x], r.c[2].link[x]);
+    best.vol = r.c[1].vol < r.c[0].vol ? r.c[1].vol : r.c[0].vol;   // the smallest of all
+    best.vol = r.c[2].vol < best.vol ? r.c[2].vol : best.vol;
+    const uint32_t cand = pick(0u, 1u, 2u), xa = pick(own, 0u, 0u);
+    uint32_t links = 0;   // below 2^29: 8 axes, 2^16 units, 2^7 groups and 3 classes
+    const double unit = (double)S.tbytes * (1.0 / 256.0);
+    taps_entry_out o;
+    o.t = (double)(best.in - xa) * (unit * H.inv_n_bw[0]);
+#pragma unroll
+    for (uint32_t x = 1; x < C; ++x) {
+        links += best.link[x - 1u];
+        o.t += (double)best.link[x - 1u] * (unit * H.inv_n_bw[x]);
     }
+    o.t += (double)xa * (unit * H.inv_n_bw_a2a);
+    if (S.q) {   // uniform over the edge
+        o.vol = (uint64_t)S.q * best.vol;
+        o.intra = (uint64_t)S.q * best.in;
+        o.inter = (uint64_t)S.q * links;
+    } else {
+        o.vol = taps_scale(S, best.vol);
+        o.intra = taps_scale(S, best.in);
+        o.inter = taps_scale(S, links);
+    }
+    o.meta = cand | r.coll | (best.ct << 12);
+    o.ok = true;
+    return o;
+}
+
+// At least 4 wavefronts per SIMD: three classes take 140 registers without the
+// bound (3 wavefronts: 2220 us on the 96-layer GPT's build against 2180).
+template <uint32_t C>
+__global__ __launch_bounds__(256, 4) void k_edge_costs_h(taps_windows win,
+                                                      const taps_packed *__restrict__ desc,
+                                                      taps_hier H, taps_table out) {
+    run_window<C>(win, desc, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
+                                 const taps_three<C> &r) {
+        const taps_entry_out o = select_entry_h<C>(r, H, E.scale);
+        store_entry(out, at, lane, o, o.meta);
+    });
 }
 
 __global__ __launch_bounds__(256) void k_node_costs_h(const taps_op *__restrict__ ops,
@@ -824,14 +778,6 @@ hipError_t taps_launch_describe(const taps_strategy *s, uint64_t total, uint32_t
     return hipGetLastError();
 }
 
-hipError_t taps_launch_describe_h(const taps_strategy *s, uint64_t total, taps_desc *desc,
-                                  hipStream_t stream) {
-    if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_describe_h, dim3(blocks_for(total, 256)), dim3(256), 0, stream, s, total,
-                       desc);
-    return hipGetLastError();
-}
-
 hipError_t taps_launch_node_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
                                   const taps_packed *desc, uint64_t total, const taps_launch &lp,
                                   taps_table out, hipStream_t stream) {
@@ -860,12 +806,6 @@ hipError_t taps_launch_edge_setup(const taps_plan_args &pa, const taps_launch &l
     return hipGetLastError();
 }
 
-hipError_t taps_launch_row_plan(const taps_row_plan &pa, hipStream_t stream) {
-    if (pa.n_segs == 0 || pa.n_groups == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_row_plan, dim3(blocks_for(pa.n_segs, 256)), dim3(256), 0, stream, pa);
-    return hipGetLastError();
-}
-
 hipError_t taps_launch_edge_costs(const taps_windows &win, const taps_packed *desc,
                                   const taps_launch &lp, taps_table out, hipStream_t stream) {
     if (win.n_windows == 0) return hipSuccess;
@@ -878,16 +818,15 @@ hipError_t taps_launch_edge_costs(const taps_windows &win, const taps_packed *de
 }
 
 hipError_t taps_launch_edge_costs_sweep(const taps_windows &win, const taps_packed *desc,
-                                        const taps_launch &lp, const taps_sweep &sw,
-                                        hipStream_t stream) {
+                                        const taps_sweep &sw, hipStream_t stream) {
     if (win.n_windows == 0) return hipSuccess;
     const dim3 grid(blocks_for(win.n_windows, kWindowsPerBlock)), block(kWave * kWindowsPerBlock);
     bool narrow = true;
     for (uint32_t k = 0; k < sw.count; ++k) narrow = narrow && sw.narrow[k] != 0;
     if (narrow)
-        hipLaunchKernelGGL(k_edge_costs_sweep<true>, grid, block, 0, stream, win, desc, lp, sw);
+        hipLaunchKernelGGL(k_edge_costs_sweep<true>, grid, block, 0, stream, win, desc, sw);
     else
-        hipLaunchKernelGGL(k_edge_costs_sweep<false>, grid, block, 0, stream, win, desc, lp, sw);
+        hipLaunchKernelGGL(k_edge_costs_sweep<false>, grid, block, 0, stream, win, desc, sw);
     return hipGetLastError();
 }
 
@@ -913,27 +852,16 @@ hipError_t taps_launch_build_front(const taps_build_chunk *chunks, uint32_t n_ch
     return hipGetLastError();
 }
 
-hipError_t taps_launch_edge_costs_h(const taps_edge_params *params, const taps_row_ref *rows,
-                                    uint64_t n_rows, const taps_desc *desc, const taps_launch &lp,
-                                    uint32_t max_rank, const taps_hier &H, taps_table out,
-                                    hipStream_t stream) {
-    if (n_rows == 0) return hipSuccess;
-    const dim3 grid(blocks_for(n_rows, TAPS_ROWS_PER_BLOCK)), block(TAPS_TILE_COLS * TAPS_ROWS_PER_BLOCK);
-    const bool low = max_rank <= TAPS_LOW_RANK;
-#define TAPS_H_LAUNCH(RR, CC)                                                                    \
-    hipLaunchKernelGGL((k_edge_costs_h<RR, CC>), grid, block, 0, stream, params, rows,            \
-                       (uint32_t)n_rows, desc, lp, H, out)
-    switch (H.n_classes * 2 + (low ? 0 : 1)) {
-    case 2: TAPS_H_LAUNCH(TAPS_LOW_RANK, 1); break;
-    case 3: TAPS_H_LAUNCH(TAPS_D_MAX_RANK, 1); break;
-    case 4: TAPS_H_LAUNCH(TAPS_LOW_RANK, 2); break;
-    case 5: TAPS_H_LAUNCH(TAPS_D_MAX_RANK, 2); break;
-    case 6: TAPS_H_LAUNCH(TAPS_LOW_RANK, 3); break;
-    case 7: TAPS_H_LAUNCH(TAPS_D_MAX_RANK, 3); break;
-    case 8: TAPS_H_LAUNCH(TAPS_LOW_RANK, 4); break;
-    default: TAPS_H_LAUNCH(TAPS_D_MAX_RANK, 4); break;
+hipError_t taps_launch_edge_costs_h(const taps_windows &win, const taps_packed *desc,
+                                    const taps_hier &H, taps_table out, hipStream_t stream) {
+    if (win.n_windows == 0) return hipSuccess;
+    const dim3 grid(blocks_for(win.n_windows, kWindowsPerBlock)), block(kWave * kWindowsPerBlock);
+    switch (H.n_classes) {
+    case 1: hipLaunchKernelGGL(k_edge_costs_h<1>, grid, block, 0, stream, win, desc, H, out); break;
+    case 2: hipLaunchKernelGGL(k_edge_costs_h<2>, grid, block, 0, stream, win, desc, H, out); break;
+    case 3: hipLaunchKernelGGL(k_edge_costs_h<3>, grid, block, 0, stream, win, desc, H, out); break;
+    default: hipLaunchKernelGGL(k_edge_costs_h<4>, grid, block, 0, stream, win, desc, H, out); break;
     }
-#undef TAPS_H_LAUNCH
     return hipGetLastError();
 }
 

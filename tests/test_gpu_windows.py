@@ -1,0 +1,58 @@
+"""The edge kernels' windows at the sizes where they can go wrong: tables of one
+entry (64 edges in one tile), rows of 2, 52, 63 and 93 entries (rows and edges
+that start inside a tile, more rows than a tile has lanes' worth of), single
+tiles and the longest windows; the single table, the sweep and the link
+classes, entry by entry against the oracle."""
+import random
+
+import pytest
+
+from paper_2301_04285_amd import workloads as W
+from test_gpu_parity import T, _topology_check, full_check, say, sweep_check  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _chain(n_ops, axes, seed):
+    """Element-wise operators over `axes` axes of 256 or more, in a chain with a
+    few second edges; matmuls now and then, so that rows and columns differ."""
+    r = random.Random(seed)
+    g = W.Graph()
+    names, lens = tuple("abcd"[:axes]), (256, 512, 1024, 256)[:axes]
+    prev = None
+    for k in range(n_ops):
+        if axes == 2 and prev is not None and r.random() < 0.3:
+            op = g.add(W.matmul(f"mm{k}", lens[0], lens[1], lens[1], 2))
+        else:
+            op = g.add(W.elementwise(f"e{k}", "e", names, lens, 1, r.choice((1, 2, 3))))
+        if prev is not None:
+            g.connect(prev, op, 0)
+        prev = op
+    return g
+
+
+@pytest.mark.parametrize("devices,axes,ops", [
+    (1, 2, 150),    # one strategy each: tables of one entry
+    (2, 2, 40),     # rows of 2 and 3 entries
+    (8, 4, 6),      # 52
+    (32, 3, 6),     # 63
+    (64, 3, 5),     # 93
+    (256, 3, 4),    # 171
+])
+@pytest.mark.parametrize("long_windows", [False, True])
+def test_windows_at_their_edges(T, devices, axes, ops, long_windows):  # noqa: F811
+    g = _chain(ops, axes, devices + axes)
+    per_node = max(1, devices // 4)
+    cl = W.Cluster(devices // per_node, per_node, 600 * W.GB, 100 * W.GB)
+    name = f"chain of {ops} x {axes} axes on {devices}, long windows {long_windows}"
+    say(f"[gpu] {name}")
+    prev = T.taps_set_long_segments_min(0 if long_windows else 1 << 40)
+    try:
+        full_check(T, g, cl, name)
+        sweep_check(T, g, [cl, W.Cluster(cl.nodes, per_node, 600 * W.GB, 25 * W.GB)], name)
+        domains = sorted({per_node, max(1, devices // 2), devices})
+        _topology_check(T, g, cl, W.Topology(tuple(domains),
+                                             (600 * W.GB, 100 * W.GB, 25 * W.GB)[:len(domains)]),
+                        name)
+    finally:
+        T.taps_set_long_segments_min(prev)
