@@ -214,11 +214,11 @@ def pack_cluster(cluster) -> Cluster:
     return Cluster(cluster.nodes, cluster.devices_per_node, cluster.bw_intra, cluster.bw_inter)
 
 
-def _stream(stream) -> C.c_void_p:
+def _stream(stream) -> int:
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    if stream is None:   # 0.4 us; current_stream() makes a Stream object in 2.8
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _graph(graph) -> PackedGraph:
@@ -227,6 +227,31 @@ def _graph(graph) -> PackedGraph:
 
 def _u64_array(a: np.ndarray):
     return a.ctypes.data_as(C.POINTER(C.c_uint64))
+
+
+# The small calls take less time on the GPU than a few dozen Python calls do,
+# so their arguments are made the short way: 0.4 us per array here against 2.2
+# for _u64_array, 0.8 per table against 1.9, and a result that is the whole of
+# a tensor is that tensor (0.2 us) and not a slice of it (1.5).  A build of two
+# operators into existing tables takes 23 us of host time in all, 44 before.
+
+def _u64(a: np.ndarray):
+    """An argument pointing at a's uint64s."""
+    if a.size and a.flags.writeable:
+        return C.byref(C.c_uint64.from_buffer(a))
+    return _u64_array(a)
+
+
+def _first(v, n: int):
+    return v if v.shape[0] == n else v[:n]
+
+
+def _first_of(tab, n: int):
+    return {k: v if v.shape[0] == n else v[:n] for k, v in tab.items()}
+
+
+def _capacity(tab) -> int:
+    return min([v.numel() for v in tab.values()])
 
 
 # ---------------------------------------------------------------------------
@@ -258,7 +283,7 @@ def taps_enumerate_strategies(graph, cluster, device="cuda", stream=None, size_o
         name = "taps_enumerate_strategies"
 
         def call(ptr, cap):
-            return L.taps_enumerate_strategies(C.byref(g.struct), C.byref(cl), _u64_array(offs),
+            return L.taps_enumerate_strategies(C.byref(g.struct), C.byref(cl), _u64(offs),
                                                ptr, cap, _stream(stream))
     else:
         name = "taps_enumerate_strategies_mesh"
@@ -266,15 +291,15 @@ def taps_enumerate_strategies(graph, cluster, device="cuda", stream=None, size_o
 
         def call(ptr, cap):
             return L.taps_enumerate_strategies_mesh(C.byref(g.struct), C.byref(cl), C.byref(ms),
-                                                    _u64_array(offs), ptr, cap, _stream(stream))
+                                                    _u64(offs), ptr, cap, _stream(stream))
     if out is None:
         _check(call(None, 0), name)
         if size_only:
             return offs, None
         out = torch.empty((max(int(offs[-1]), 1), STRATEGY_BYTES), dtype=torch.uint8,
                           device=device)
-    _check(call(C.c_void_p(out.data_ptr()), int(out.shape[0])), name)
-    return offs, out[:int(offs[-1])]
+    _check(call(out.data_ptr(), int(out.shape[0])), name)
+    return offs, _first(out, int(offs[-1]))
 
 
 def alloc_table(n: int, device="cuda") -> Dict[str, "torch.Tensor"]:
@@ -290,7 +315,8 @@ def alloc_table(n: int, device="cuda") -> Dict[str, "torch.Tensor"]:
 def _table(tab) -> Table:
     if tab is None:
         return Table(None, None, None, None, None)
-    return Table(*(C.c_void_p(tab[k].data_ptr()) for k in ("t", "vol", "intra", "inter", "meta")))
+    return Table(tab["t"].data_ptr(), tab["vol"].data_ptr(), tab["intra"].data_ptr(),
+                 tab["inter"].data_ptr(), tab["meta"].data_ptr())
 
 
 def taps_node_costs(graph, cluster, strategies, op_offsets, out=None, stream=None):
@@ -301,10 +327,10 @@ def taps_node_costs(graph, cluster, strategies, op_offsets, out=None, stream=Non
     total = int(offs[-1])
     if out is None:
         out = alloc_table(total, device=strategies.device)
-    st = load().taps_node_costs(C.byref(g.struct), C.byref(cl), C.c_void_p(strategies.data_ptr()),
-                                _u64_array(offs), _table(out), _stream(stream))
+    st = load().taps_node_costs(C.byref(g.struct), C.byref(cl), strategies.data_ptr(),
+                                _u64(offs), _table(out), _stream(stream))
     _check(st, "taps_node_costs")
-    return {k: v[:total] for k, v in out.items()}
+    return _first_of(out, total)
 
 
 def pack_topology(topo) -> TopologyS:
@@ -324,10 +350,10 @@ def taps_node_costs_topology(graph, topology, strategies, op_offsets, out=None, 
     if out is None:
         out = alloc_table(total, device=strategies.device)
     st = load().taps_node_costs_topology(C.byref(g.struct), C.byref(tp),
-                                         C.c_void_p(strategies.data_ptr()), _u64_array(offs),
+                                         strategies.data_ptr(), _u64(offs),
                                          _table(out), _stream(stream))
     _check(st, "taps_node_costs_topology")
-    return {k: v[:total] for k, v in out.items()}
+    return _first_of(out, total)
 
 
 def taps_edge_costs_topology(graph, topology, strategies, op_offsets, out=None, stream=None,
@@ -339,20 +365,20 @@ def taps_edge_costs_topology(graph, topology, strategies, op_offsets, out=None, 
     offs = np.ascontiguousarray(op_offsets, dtype=np.uint64)
     eoffs = np.zeros(g.n_edges + 1, dtype=np.uint64)
     L = load()
-    sptr = C.c_void_p(strategies.data_ptr()) if strategies is not None else None
+    sptr = strategies.data_ptr() if strategies is not None else None
     if out is None or size_only:
-        st = L.taps_edge_costs_topology(C.byref(g.struct), C.byref(tp), sptr, _u64_array(offs),
-                                        _u64_array(eoffs), _table(None), 0, _stream(stream))
+        st = L.taps_edge_costs_topology(C.byref(g.struct), C.byref(tp), sptr, _u64(offs),
+                                        _u64(eoffs), _table(None), 0, _stream(stream))
         _check(st, "taps_edge_costs_topology")
         if size_only:
             return eoffs, None
         out = alloc_table(int(eoffs[-1]), device=strategies.device)
-    cap = min(int(v.numel()) for v in out.values())
-    st = L.taps_edge_costs_topology(C.byref(g.struct), C.byref(tp), sptr, _u64_array(offs),
-                                    _u64_array(eoffs), _table(out), cap, _stream(stream))
+    cap = _capacity(out)
+    st = L.taps_edge_costs_topology(C.byref(g.struct), C.byref(tp), sptr, _u64(offs),
+                                    _u64(eoffs), _table(out), cap, _stream(stream))
     _check(st, "taps_edge_costs_topology")
     total = int(eoffs[-1])
-    return eoffs, {k: v[:total] for k, v in out.items()}
+    return eoffs, _first_of(out, total)
 
 
 def taps_edge_costs(graph, cluster, strategies, op_offsets, out=None, stream=None,
@@ -368,22 +394,22 @@ def taps_edge_costs(graph, cluster, strategies, op_offsets, out=None, stream=Non
     offs = np.ascontiguousarray(op_offsets, dtype=np.uint64)
     eoffs = np.zeros(g.n_edges + 1, dtype=np.uint64)
     L = load()
-    sptr = C.c_void_p(strategies.data_ptr()) if strategies is not None else None
+    sptr = strategies.data_ptr() if strategies is not None else None
     if out is None or size_only:   # size query first
-        st = L.taps_edge_costs(C.byref(g.struct), C.byref(cl), sptr, _u64_array(offs),
-                               _u64_array(eoffs), _table(None), 0, _stream(stream))
+        st = L.taps_edge_costs(C.byref(g.struct), C.byref(cl), sptr, _u64(offs),
+                               _u64(eoffs), _table(None), 0, _stream(stream))
         _check(st, "taps_edge_costs")
         if size_only:
             return eoffs, None
         out = alloc_table(int(eoffs[-1]), device=strategies.device)
-    cap = min(int(v.numel()) for v in out.values())
+    cap = _capacity(out)
     name = ("taps_edge_costs_shared" if shared else
             "taps_edge_costs_backward" if backward else "taps_edge_costs")
-    st = getattr(L, name)(C.byref(g.struct), C.byref(cl), sptr, _u64_array(offs),
-                          _u64_array(eoffs), _table(out), cap, _stream(stream))
+    st = getattr(L, name)(C.byref(g.struct), C.byref(cl), sptr, _u64(offs),
+                          _u64(eoffs), _table(out), cap, _stream(stream))
     _check(st, name)
     total = int(eoffs[-1])
-    return eoffs, {k: v[:total] for k, v in out.items()}
+    return eoffs, _first_of(out, total)
 
 
 def taps_memory_costs(graph, strategies, op_offsets, out=None, stream=None):
@@ -397,10 +423,10 @@ def taps_memory_costs(graph, strategies, op_offsets, out=None, stream=None):
     if int(out.numel()) < total:
         raise ValueError(f"memory output holds {out.numel()} entries, {total} needed")
     st = load().taps_memory_costs(C.byref(g.struct),
-                                  C.c_void_p(strategies.data_ptr()) if strategies is not None else None,
-                                  _u64_array(offs), C.c_void_p(out.data_ptr()), _stream(stream))
+                                  strategies.data_ptr() if strategies is not None else None,
+                                  _u64(offs), out.data_ptr(), _stream(stream))
     _check(st, "taps_memory_costs")
-    return out[:total]
+    return _first(out, total)
 
 
 def taps_edge_costs_sweep(graph, clusters, strategies, op_offsets, out=None, stream=None,
@@ -414,23 +440,23 @@ def taps_edge_costs_sweep(graph, clusters, strategies, op_offsets, out=None, str
     offs = np.ascontiguousarray(op_offsets, dtype=np.uint64)
     eoffs = np.zeros(g.n_edges + 1, dtype=np.uint64)
     L = load()
-    sptr = C.c_void_p(strategies.data_ptr()) if strategies is not None else None
+    sptr = strategies.data_ptr() if strategies is not None else None
     if out is None or size_only:   # size query first
-        st = L.taps_edge_costs_sweep(C.byref(g.struct), arr, len(cls), sptr, _u64_array(offs),
-                                     _u64_array(eoffs), None, 0, _stream(stream))
+        st = L.taps_edge_costs_sweep(C.byref(g.struct), arr, len(cls), sptr, _u64(offs),
+                                     _u64(eoffs), None, 0, _stream(stream))
         _check(st, "taps_edge_costs_sweep")
         if size_only:
             return eoffs, None
         out = [alloc_table(int(eoffs[-1]), device=strategies.device) for _ in cls]
     if len(out) != len(cls):
         raise ValueError(f"{len(out)} tables for {len(cls)} bandwidth points")
-    cap = min(int(v.numel()) for o in out for v in o.values())
+    cap = min([_capacity(o) for o in out])
     tabs = (Table * len(out))(*[_table(o) for o in out])
-    st = L.taps_edge_costs_sweep(C.byref(g.struct), arr, len(cls), sptr, _u64_array(offs),
-                                 _u64_array(eoffs), tabs, cap, _stream(stream))
+    st = L.taps_edge_costs_sweep(C.byref(g.struct), arr, len(cls), sptr, _u64(offs),
+                                 _u64(eoffs), tabs, cap, _stream(stream))
     _check(st, "taps_edge_costs_sweep")
     total = int(eoffs[-1])
-    return eoffs, [{k: v[:total] for k, v in o.items()} for o in out]
+    return eoffs, [_first_of(o, total) for o in out]
 
 
 def taps_set_long_segments_min(min_segments: int) -> int:
@@ -519,7 +545,7 @@ def taps_build_tables(graph, cluster, mesh=None, out: Optional["Tables"] = None,
 
     def call(strat, s_cap, node, edge, e_cap):
         return L.taps_build_tables(C.byref(g.struct), C.byref(cl), C.byref(ms) if ms else None,
-                                   _u64_array(offs), strat, s_cap, _table(node), _u64_array(eoffs),
+                                   _u64(offs), strat, s_cap, _table(node), _u64(eoffs),
                                    _table(edge), e_cap, BUILD_SHARED if shared else 0,
                                    _stream(stream) if strat else None)
     if out is None:
@@ -531,13 +557,13 @@ def taps_build_tables(graph, cluster, mesh=None, out: Optional["Tables"] = None,
         out = Tables(offs, torch.empty((max(n_str, 1), STRATEGY_BYTES), dtype=torch.uint8,
                                        device=device),
                      alloc_table(n_str, device), eoffs, alloc_table(n_edge, device))
-    s_cap = min(int(out.strategies.shape[0]), *(int(v.numel()) for v in out.node.values()))
-    e_cap = min(int(v.numel()) for v in out.edge.values())
-    _check(call(C.c_void_p(out.strategies.data_ptr()), s_cap, out.node, out.edge, e_cap),
+    s_cap = min(out.strategies.shape[0], _capacity(out.node))
+    e_cap = _capacity(out.edge)
+    _check(call(out.strategies.data_ptr(), s_cap, out.node, out.edge, e_cap),
            "taps_build_tables")
     n_str, n_edge = int(offs[-1]), int(eoffs[-1])
-    return Tables(offs, out.strategies[:n_str], {k: v[:n_str] for k, v in out.node.items()}, eoffs,
-                  {k: v[:n_edge] for k, v in out.edge.items()})
+    return Tables(offs, _first(out.strategies, n_str), _first_of(out.node, n_str), eoffs,
+                  _first_of(out.edge, n_edge))
 
 
 def taps_build_tables_noalloc(graph, cluster, out: "Tables", mesh=None, stream=None,
@@ -550,16 +576,16 @@ def taps_build_tables_noalloc(graph, cluster, out: "Tables", mesh=None, stream=N
     ms = pack_mesh(mesh) if mesh is not None else None
     offs = np.zeros(g.n_ops + 1, dtype=np.uint64)
     eoffs = np.zeros(g.n_edges + 1, dtype=np.uint64)
-    s_cap = min(int(out.strategies.shape[0]), *(int(v.numel()) for v in out.node.values()))
-    e_cap = min(int(v.numel()) for v in out.edge.values())
+    s_cap = min(out.strategies.shape[0], _capacity(out.node))
+    e_cap = _capacity(out.edge)
     _check(load().taps_build_tables_noalloc(
-        C.byref(g.struct), C.byref(cl), C.byref(ms) if ms else None, _u64_array(offs),
-        C.c_void_p(out.strategies.data_ptr()), s_cap, _table(out.node), _u64_array(eoffs),
+        C.byref(g.struct), C.byref(cl), C.byref(ms) if ms else None, _u64(offs),
+        out.strategies.data_ptr(), s_cap, _table(out.node), _u64(eoffs),
         _table(out.edge), e_cap, BUILD_SHARED if shared else 0, _stream(stream)),
         "taps_build_tables_noalloc")
     n_str, n_edge = int(offs[-1]), int(eoffs[-1])
-    return Tables(offs, out.strategies[:n_str], {k: v[:n_str] for k, v in out.node.items()},
-                  eoffs, {k: v[:n_edge] for k, v in out.edge.items()})
+    return Tables(offs, _first(out.strategies, n_str), _first_of(out.node, n_str),
+                  eoffs, _first_of(out.edge, n_edge))
 
 
 class PreparedBuild:
@@ -575,14 +601,14 @@ class PreparedBuild:
         self._offs = np.zeros(self._g.n_ops + 1, dtype=np.uint64)
         self._eoffs = np.zeros(self._g.n_edges + 1, dtype=np.uint64)
         self._out = out
-        s_cap = min(int(out.strategies.shape[0]), *(int(v.numel()) for v in out.node.values()))
-        e_cap = min(int(v.numel()) for v in out.edge.values())
+        s_cap = min(out.strategies.shape[0], _capacity(out.node))
+        e_cap = _capacity(out.edge)
         L = load()
         self._fn = L.taps_build_tables
         self._args = (C.byref(self._g.struct), C.byref(self._cl),
-                      C.byref(self._ms) if self._ms else None, _u64_array(self._offs),
-                      C.c_void_p(out.strategies.data_ptr()), s_cap, _table(out.node),
-                      _u64_array(self._eoffs), _table(out.edge), e_cap,
+                      C.byref(self._ms) if self._ms else None, _u64(self._offs),
+                      out.strategies.data_ptr(), s_cap, _table(out.node),
+                      _u64(self._eoffs), _table(out.edge), e_cap,
                       BUILD_SHARED if shared else 0, _stream(stream))
 
     def __call__(self) -> None:
