@@ -18,9 +18,14 @@
 //     bits and the number of free levels inside a node in the upper 3.  A
 //     gather of an axis adds the axis's byte of `D` (its width, and its levels
 //     inside a node << 5), a slice subtracts it.  Where the order of the gathers
-//     is known beforehand ("remove", "rearrange", the untargeted gathers of
+//     is known beforehand ("remove", "rearrange", either kind of gather of
 //     Algorithm 1) the states before all of them come from one prefix sum over
 //     bytes in producer order: a multiplication by 0x01010101 per half.
+//   * Algorithm 1's loop over gathers is in closed form too: which axes it
+//     gathers, which move after which of them, and which slices come a pass
+//     late, follow from the producer's order along the chains.  As a loop it
+//     took 74 instructions per round, 2.0 rounds for the slowest of 64 lanes;
+//     without it the 96-layer GPT's tables take 1409 us instead of 1529.
 //   * Each axis held off its target is moved exactly once by every candidate,
 //     so a candidate is described by the state each axis was moved at.  Powers
 //     of two of a byte are a table lookup by v_perm_b32, a gather's volume fits
@@ -116,6 +121,11 @@ __host__ __device__ inline taps_b8 taps_none(const taps_b8 &x) {
     return {taps_perm(0u, 0u, x.lo & 0x80808080u), taps_perm(0u, 0u, x.hi & 0x80808080u)};
 }
 
+// FF where the byte is above 0x0C, else 0; an index that names no level is.
+__host__ __device__ inline taps_b8 taps_above(const taps_b8 &x) {
+    return {taps_perm(0u, 0u, x.lo), taps_perm(0u, 0u, x.hi)};
+}
+
 // FF where bit 3 is clear, 0 where it is set (selector 8 reads a sign that is 0).
 __host__ __device__ inline taps_b8 taps_not_lowest(const taps_b8 &x) {
     return {taps_perm(0u, 0xFFu, x.lo & 0x08080808u), taps_perm(0u, 0xFFu, x.hi & 0x08080808u)};
@@ -170,15 +180,14 @@ __host__ __device__ inline taps_b8 taps_states(const taps_b8 &e, uint32_t g, uin
 // Strategy descriptors
 // ---------------------------------------------------------------------------
 
-// A strategy on binary levels, every field 8 indexed nibbles in the order that
-// two masks turn into a byte vector: index k < 4 in the low nibble of byte k,
-// k >= 4 in the high nibble of byte k - 4.
+// A strategy on binary levels.  owner and place are 8 indexed nibbles in the
+// order that two masks turn into a byte vector: index k < 4 in the low nibble
+// of byte k, k >= 4 in the high nibble of byte k - 4.
 struct taps_packed {
     uint32_t owner;   // per level: the op axis that owns it (0 above the last level)
     uint32_t place;   // per level: its distance from the top of its axis's run, + 8 when it is the
                       // run's lowest level (15 above the last level)
-    uint32_t end;     // per op axis: top level + 1 of its run (0 = not split)
-    uint32_t width;   // per op axis: the run's width
+    taps_b8 runs;     // per op axis: top level + 1 of its run, and << 4 the run's width (0: not split)
 };
 
 __host__ __device__ inline taps_b8 taps_unnibble(uint32_t x) {
@@ -237,15 +246,15 @@ __host__ __device__ inline taps_runs taps_lay_out(const taps_nibbles &S, uint32_
     const uint32_t above = n < 8u ? ~0u << (4u * n) : 0u;
     R.packed.owner = taps_deal(owner & ~above);
     R.packed.place = taps_deal(place | above);
-    R.packed.end = taps_deal(end);
-    R.packed.width = taps_deal(R.width);
+    R.packed.runs = {taps_spread(end & 0xFFFFu) | (taps_spread(R.width & 0xFFFFu) << 4),
+                     taps_spread(end >> 16) | (taps_spread(R.width >> 16) << 4)};
     return R;
 }
 
 // Levels of op axis a.
 __host__ __device__ inline uint32_t taps_axis_levels(const taps_packed &p, uint32_t a) {
-    const uint32_t s = taps_nibble_shift(a);
-    const uint32_t w = (p.width >> s) & 15u, end = (p.end >> s) & 15u;
+    const uint32_t run = (a < 4u ? p.runs.lo : p.runs.hi) >> (8u * (a & 3u));
+    const uint32_t w = (run >> 4) & 15u, end = run & 15u;
     return taps_levels(end < w ? 0u : end - w, w);
 }
 
@@ -265,6 +274,14 @@ __host__ __device__ inline taps_side taps_make_side(uint32_t axes, uint32_t rank
         s.axis_of = (s.axis_of & ~(15u << sd)) | (a << sd);
     }
     return s;
+}
+
+// FF at the op axes that an edge's tensor has on this side.
+__host__ __device__ inline taps_b8 taps_in_tensor(const taps_side &s, uint32_t rank) {
+    // dimension 7 stands for "none" below rank 8
+    const taps_b8 dim = taps_unnibble(s.dim_of);
+    const uint32_t hi = rank < TAPS_D_MAX_RANK ? 0x00FFFFFFu : 0xFFFFFFFFu;
+    return {taps_perm(hi, 0xFFFFFFFFu, dim.lo), taps_perm(hi, 0xFFFFFFFFu, dim.hi)};
 }
 
 // ---------------------------------------------------------------------------
@@ -325,7 +342,7 @@ __host__ __device__ inline taps_levels_model taps_make_levels(uint32_t n, uint32
 // AllToAll moves all but 2^-w of the shard, Eq. 10), of link 256 - 2^(8 - w + k)
 // with k that of the axis's own class (of that, all but what stays inside the
 // blocks, Eq. 14; 0 inside a node).  0 at the other levels.
-struct taps_top_row {
+struct alignas(16) taps_top_row {
     taps_b8 d, tops, a2a, link;
 };
 
@@ -389,14 +406,15 @@ __host__ __device__ inline taps_top_row taps_make_top_row(const taps_top_table &
     return row;
 }
 
-// The source side of a row: its levels' dimensions and places, the ends and
-// widths of its dimensions, its positions in order.
+// The source side of a row: its levels' positions as the target side's axes
+// meet them, and the target's axes that carry their dimensions.
 struct taps_source {
-    taps_b8 dim;      // per level: tensor dimension (7: none)
-    taps_b8 place;    // per level: position bit in the dimension (taps_packed::place without the flag)
-    taps_b8 next;     // per level: place + 1, at least 9 for a run's lowest level
-    taps_b8 top;      // per dimension: 7F + end of its run
-    taps_b8 room;     // per dimension: 80 - width
+    taps_b8 axis;     // per level: the target's axis of its tensor dimension (0x0C: none)
+    taps_b8 from;     // per level: 7F - its position bit in the dimension (taps_packed::place
+                      // without the flag)
+    taps_b8 below;    // per level: 7E - that bit, at most 76 for a run's lowest level
+    taps_b8 top;      // per target axis: 7F + end of the run on its dimension
+    taps_b8 room;     // per target axis: 80 - width of that run
     taps_b8 held;     // FF at the levels the tensor's map uses
     taps_b8 uncut;    // FF where no cut lies below the level
     taps_b8 rank;     // per level: its place among the positions in order (dimension, then bit)
@@ -406,30 +424,28 @@ struct taps_source {
     uint32_t h;       // more than two classes: the free levels below beta[2], and << 4 below beta[3]
 };
 
-// FF at the dimensions that an edge's tensor has (dimension 7 stands for
-// "none" below rank 8).
-__host__ __device__ inline taps_b8 taps_in_tensor(uint32_t rank, const taps_b8 &dim) {
-    const uint32_t hi = rank < TAPS_D_MAX_RANK ? 0x00FFFFFFu : 0xFFFFFFFFu;
-    return {taps_perm(hi, 0xFFFFFFFFu, dim.lo), taps_perm(hi, 0xFFFFFFFFu, dim.hi)};
-}
-
 template <uint32_t C>
 __host__ __device__ inline taps_source taps_make_source(const taps_packed &p, const taps_side &side,
-                                                        uint32_t rank, const taps_levels_model &m) {
+                                                        const taps_side &to, uint32_t rank,
+                                                        const taps_levels_model &m) {
     taps_source P;
-    const taps_b8 axis_of = taps_unnibble(side.axis_of);
-    P.dim = taps_map(taps_unnibble(side.dim_of), taps_unnibble(p.owner));
-    const taps_b8 place = taps_unnibble(p.place);
-    P.place = place & taps_all(0x07070707u);
-    P.next = place + taps_all(0x01010101u);
-    const taps_b8 width = taps_map(taps_unnibble(p.width), axis_of);
-    P.top = taps_map(taps_unnibble(p.end), axis_of) + taps_all(0x7F7F7F7Fu);
-    P.room = taps_all(0x80808080u) - width;
-    P.held = taps_in_tensor(rank, P.dim);
-    P.uncut = taps_not_lowest(place);
+    const taps_b8 owner = taps_unnibble(p.owner);
+    const taps_b8 dim = taps_map(taps_unnibble(side.dim_of), owner);
+    P.axis = taps_map(taps_unnibble(to.axis_of), dim);
+    const taps_b8 flagged = taps_unnibble(p.place);
+    const taps_b8 place = flagged & taps_all(0x07070707u);
+    P.from = taps_all(0x7F7F7F7Fu) - place;
+    P.below = taps_all(0x7E7E7E7Eu) - flagged;
+    const taps_b8 runs = taps_map(p.runs, taps_unnibble(side.axis_of));
+    const taps_b8 width = {(runs.lo >> 4) & 0x0F0F0F0Fu, (runs.hi >> 4) & 0x0F0F0F0Fu};
+    const taps_b8 dim_of = taps_unnibble(to.dim_of);
+    P.top = taps_map((runs & taps_all(0x0F0F0F0Fu)) + taps_all(0x7F7F7F7Fu), dim_of);
+    P.room = taps_map(taps_all(0x80808080u) - width, dim_of);
+    P.held = taps_map(taps_in_tensor(side, rank), owner);
+    P.uncut = taps_not_lowest(flagged);
     uint32_t used;
     const taps_b8 first = taps_states(width, 0u, used);   // positions before each dimension
-    P.rank = (taps_map(first, P.dim) + P.place) & taps_all(0x07070707u);
+    P.rank = (taps_map(first, dim) + place) & taps_all(0x07070707u);
     uint64_t order = 0x0C0C0C0C0C0C0C0Cull;
 #pragma unroll
     for (uint32_t l = 0; l < TAPS_D_MAX_LEVELS; ++l) {
@@ -475,35 +491,36 @@ __host__ __device__ inline taps_b8 taps_hop(const taps_b8 &x, const taps_b8 &to)
     return x & taps_map(x, to);
 }
 
-// tab, low: taps_make_top_row's by tops mask (low is read for more than two
-// classes).
+// in_tensor: taps_in_tensor of the target side; tab, low: taps_make_top_row's
+// by tops mask (low is read for more than two classes).
 template <uint32_t C>
 __host__ __device__ inline void taps_three_candidates(const taps_source &P, const taps_packed &q,
-                                                      const taps_side &side, uint32_t rank,
+                                                      const taps_b8 &in_tensor,
                                                       const taps_levels_model &m,
                                                       const taps_top_row *tab, const taps_b8 *low,
                                                       taps_three<C> &out) {
     constexpr bool kLow = C > 2;   // the free levels below further boundaries are followed too
-    // the target side's levels and dimensions, as in taps_source
-    const taps_b8 axis_of = taps_unnibble(side.axis_of);
-    const taps_b8 dim = taps_map(taps_unnibble(side.dim_of), taps_unnibble(q.owner));
-    const taps_b8 flagged = taps_unnibble(q.place);
+    const taps_b8 owner = taps_unnibble(q.owner), flagged = taps_unnibble(q.place);
     const taps_b8 place = flagged & taps_all(0x07070707u);
-    const taps_b8 top = taps_map(taps_unnibble(q.end), axis_of) + taps_all(0x7F7F7F7Fu);
-    const taps_b8 room = taps_all(0x80808080u) - taps_map(taps_unnibble(q.width), axis_of);
+    // of the target's runs on the source levels' dimensions
+    const taps_b8 runs = taps_map(q.runs, P.axis), end = runs & taps_all(0x0F0F0F0Fu);
+    const taps_b8 width_p = {(runs.lo >> 4) & 0x0F0F0F0Fu, (runs.hi >> 4) & 0x0F0F0F0Fu};
 
     // prev[c]: the source level at the position that target level c goes to;
     // next[p]: the target level that goes to source level p's position.  The
     // byte differences keep bit 7 set; place + 80 - width has it set when the
-    // position lies past the other side's run.  below_*: the same for the cuts
-    // inside what both sides split (all levels there but the lowest).
+    // position lies past the other side's run (7F - place + width, clear).
+    // below_*: the same for the cuts inside what both sides split (all levels
+    // there but the lowest).
+    constexpr uint32_t kPast = (TAPS_A & TAPS_B) | ((0xFFu ^ TAPS_A) & TAPS_C);
+    constexpr uint32_t kNotPast = (TAPS_A & (0xFFu ^ TAPS_B)) | ((0xFFu ^ TAPS_A) & TAPS_C);
     const taps_b8 high = taps_all(0x80808080u);
-    const taps_b8 past = taps_map(P.room, dim), from = taps_map(P.top, dim) - place;
-    const taps_b8 prev = taps_blend(high, place + past, from);
-    taps_b8 below_c = taps_blend(high, flagged + taps_all(0x01010101u) + past, from);
-    const taps_b8 past_p = taps_map(room, P.dim), from_p = taps_map(top, P.dim) - P.place;
-    const taps_b8 next = taps_blend(high, P.place + past_p, from_p);
-    taps_b8 below_p = taps_blend(high, P.next + past_p, from_p);
+    const taps_b8 past = taps_map(P.room, owner), from = taps_map(P.top, owner) - place;
+    const taps_b8 prev = taps_bitop3<kPast>(high, place + past, from);
+    taps_b8 below_c = taps_bitop3<kPast>(high, flagged + taps_all(0x01010101u) + past, from);
+    const taps_b8 from_p = end + P.from;
+    const taps_b8 next = taps_bitop3<kNotPast>(high, P.from + width_p, from_p);
+    taps_b8 below_p = taps_bitop3<kNotPast>(high, P.below + width_p, from_p);
 
     // unification (Table 1): the cuts of both sides, closed under both maps
     taps_b8 uncut = taps_not_lowest(flagged) & P.uncut;
@@ -514,7 +531,10 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     below_c = taps_map(below_c, below_c);
     below_p = taps_map(below_p, below_p);
     uncut = taps_bitop3<TAPS_AND3>(uncut, taps_map(uncut, below_c), taps_map(uncut, below_p));
-    const uint32_t tp = m.full & ~(taps_bits(uncut) >> 1);
+    // a level is a top if a cut lies below the next: of FF bytes at the levels with
+    // none, the sum by the weights of the levels below them is, up to bit 7, -1 less
+    const uint32_t tp = m.full & taps_dot4(uncut.hi, 0x40201008u,
+                                           taps_dot4(uncut.lo, 0x04020100u, ~0u));
     const taps_top_row row = taps_entry<5>(tab, tp);
     const taps_b8 D = row.d;
     taps_b8 D2 = {0u, 0u};
@@ -523,9 +543,10 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     // away: not at the same position on both sides
     const taps_b8 away = {taps_perm(0xFFFFFFFFu, 0xFFFFFF00u, prev.lo ^ 0x03020100u),
                           taps_perm(0xFFFFFFFFu, 0xFFFFFF00u, prev.hi ^ 0x07060504u)};
-    const taps_b8 dst = row.tops & taps_in_tensor(rank, dim);
+    const taps_b8 dst = row.tops & taps_map(in_tensor, owner);
     const taps_b8 held = taps_bitop3<TAPS_AND3>(row.tops, P.held, away);
-    const taps_b8 unwanted = taps_none(next);   // source positions no target axis goes to
+    const taps_b8 unwanted = taps_above(next);   // source positions no target axis goes to
+    const taps_b8 ns = taps_map(next, P.order);
     // the common start of Algorithm 1 and "rearrange": the first InferSlice
     const taps_b8 open = taps_map(~held, prev);   // targets no held axis blocks
     const taps_b8 todo0 = dst & away;
@@ -550,77 +571,102 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
         a2a = ~stay;
         at = taps_all(G * 0x01010101u) & a2a;
         if (kLow) at2 = taps_all(H * 0x01010101u) & a2a;
-        taps_b8 left = held & stay, wait = todo & stay;
-        // the slices those moves make possible: at once if the first InferSlice
-        // found something, else with the next pass
-        const taps_b8 ug = left & unwanted;
-        const bool now = taps_any(sliced), gathers = taps_any(ug);
-        uint32_t g = G, pending = 0u, h = H, pending2 = 0u;
-        if (taps_wave_any(now | gathers)) {
-            taps_b8 freed = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
-            freed = freed & taps_all((now | gathers) ? ~0u : 0u);
-            wait = wait & ~freed;
-            const uint32_t f = taps_sum(D & freed, 0u);
-            g -= now ? f : 0u;
-            pending = now ? 0u : f;
-            if (kLow) {
-                const uint32_t f2 = taps_sum(D2 & freed, 0u);
-                h -= now ? f2 : 0u;
-                pending2 = now ? 0u : f2;
+        const taps_b8 left = held & stay, wait = todo & stay;
+        if (taps_wave_any(taps_any(left))) {
+            // the slices those moves make possible: at once if the first InferSlice
+            // found something, else after the next gather, whose state is higher then
+            const taps_b8 ug = left & unwanted;
+            const taps_b8 freed = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
+            const bool now = taps_any(sliced), gathers = taps_any(ug);
+            uint32_t pending = taps_sum(D & freed, 0u), g = G - pending;
+            pending = now ? 0u : pending;
+            uint32_t pending2 = kLow ? taps_sum(D2 & freed, 0u) : 0u, h = H - pending2;
+            pending2 = now ? 0u : pending2;
+            // untargeted gathers in producer order
+            if (taps_wave_any(gathers)) {
+                const taps_b8 us = taps_map(ug, P.order);   // its lowest byte: the first
+                const uint32_t f_lo = us.lo & (0u - us.lo), f_hi = us.lo ? 0u : us.hi & (0u - us.hi);
+                taps_b8 s = taps_states(taps_map(D & ug, P.order), g, g);
+                s = s + taps_b8{f_lo * pending, f_hi * pending};
+                at = taps_blend(ug, taps_map(s, P.rank), at);
+                pending = gathers ? 0u : pending;
+                if (kLow) {
+                    s = taps_states(taps_map(D2 & ug, P.order), h, h);
+                    s = s + taps_b8{f_lo * pending2, f_hi * pending2};
+                    at2 = taps_blend(ug, taps_map(s, P.rank), at2);
+                    pending2 = gathers ? 0u : pending2;
+                }
             }
-        }
-        // untargeted gathers in producer order; a pending slice follows the first
-        if (taps_wave_any(gathers)) {
-            const taps_b8 us = taps_map(ug, P.order);
-            const uint32_t f_lo = us.lo & (0u - us.lo), f_hi = us.lo ? 0u : us.hi & (0u - us.hi);
-            taps_b8 e = taps_map(D & ug, P.order);
-            e.lo -= f_lo * pending;
-            e.hi -= f_hi * pending;
-            at = taps_blend(ug, taps_map(taps_states(e, g, g), P.rank), at);
-            if (kLow) {
-                taps_b8 e2 = taps_map(D2 & ug, P.order);
-                e2.lo -= f_lo * pending2;
-                e2.hi -= f_hi * pending2;
-                at2 = taps_blend(ug, taps_map(taps_states(e2, h, h), P.rank), at2);
+            // What is left blocks itself: cycles, and chains down to an axis without a
+            // target.  AllGatherFirstUndoneDim takes the first in the producer's order,
+            // which frees all that wait for it along the chain; so an axis is gathered
+            // if it comes before all that its own target waits for (of a cycle, the
+            // first), and is moved else, after the next one along the chain that is.
+            // The last that waits before a gathered axis is sliced in the same pass.
+            const taps_b8 rest = left & ~ug;
+            if (taps_wave_any(taps_any(rest))) {
+                // ranks not met along the chain, and those below the axis's own
+                taps_b8 unmet = {taps_perm(0x7FBFDFEFu, 0xF7FBFDFEu, P.rank.lo),
+                                 taps_perm(0x7FBFDFEFu, 0xF7FBFDFEu, P.rank.hi)};
+                const taps_b8 under = {taps_perm(0x7F3F1F0Fu, 0x07030100u, P.rank.lo),
+                                       taps_perm(0x7F3F1F0Fu, 0x07030100u, P.rank.hi)};
+                unmet = taps_hop(unmet, hop1);
+                unmet = taps_hop(unmet, hop2);
+                unmet = taps_hop(unmet, hop4);
+                const taps_b8 moved = rest & taps_above((under & ~unmet) + taps_all(0x0C0C0C0Cu));
+                const taps_b8 taken = rest & ~moved;
+                const taps_b8 self = {0x03020100u, 0x07060504u};
+                // the gathered axis along the chain, and the axis that waits up to it
+                taps_b8 to = taps_blend(taken, self, prev), up = taps_blend(moved, next, self);
+                to = taps_map(to, to);
+                up = taps_map(up, up);
+                to = taps_map(to, to);
+                up = taps_map(up, up);
+                to = taps_map(to, to);
+                up = taps_map(taps_map(up, up), next);
+                const taps_b8 xs = taps_map(taken, P.order), rank_to = taps_map(P.rank, to);
+                const taps_b8 plus = taps_map(D, P.order) & xs;
+                const taps_b8 minus = taps_map(taps_map(D & todo, up), P.order) & xs;
+                taps_b8 s = taps_states(plus - minus, g, g), s2 = {0u, 0u};
+                const taps_b8 after = s + plus;
+                taps_b8 after2 = {0u, 0u}, minus2 = {0u, 0u};
+                if (kLow) {
+                    const taps_b8 plus2 = taps_map(D2, P.order) & xs;
+                    minus2 = taps_map(taps_map(D2 & todo, up), P.order) & xs;
+                    s2 = taps_states(plus2 - minus2, h, h);
+                    after2 = s2 + plus2;
+                }
+                // A slice that only the AllToAlls of its pass make possible waits for the
+                // next pass, after its gather, unless InferSlice found something before
+                // them: an earlier such slice, or one into the gathered axis's position.
+                // bit k of gathers_at: a gather at place k; bit k of late: a slice of the
+                // gather at place k - 1 (0: pending) may wait so
+                const taps_b8 via = taps_bitop3<TAPS_AND3>(taps_map(moved, ns), xs,
+                                                           taps_all(0x01010101u));
+                const uint32_t gathers_at = taps_bits(xs);
+                uint32_t late = 2u * taps_dot4(via.hi, 0x80402010u, taps_dot4(via.lo, 0x08040201u, 0u)) +
+                                ((pending | pending2) ? 1u : 0u);
+                uint32_t higher = gathers_at & (late | (0u - late));   // from the first such on
+                if (taps_wave_any(higher != 0u)) {
+                    const uint64_t by = (taps_u64(minus) << 8) | (pending & 0xFFu);
+                    const uint64_t by2 = kLow ? (taps_u64(minus2) << 8) | (pending2 & 0xFFu) : 0u;
+                    for (uint32_t it = 0; it < TAPS_D_MAX_LEVELS && higher; ++it) {
+                        const uint32_t from = 8u * taps_ctz(late), to_byte = 8u * taps_ctz(higher);
+                        s = taps_from(taps_u64(s) + (((by >> from) & 0xFFu) << to_byte));
+                        if (kLow) s2 = taps_from(taps_u64(s2) + (((by2 >> from) & 0xFFu) << to_byte));
+                        // that gather's own slice does not wait
+                        late &= (late - 1u) & ~(2u * (higher & (0u - higher)));
+                        higher = gathers_at & (late | (0u - late));
+                    }
+                }
+                a2a = a2a | moved;
+                at = taps_blend(taken, taps_map(s, rank_to), at);
+                at = taps_blend(moved, taps_map(after, rank_to), at);
+                if (kLow) {
+                    at2 = taps_blend(taken, taps_map(s2, rank_to), at2);
+                    at2 = taps_blend(moved, taps_map(after2, rank_to), at2);
+                }
             }
-            left = left & ~ug;
-        }
-        // AllGatherFirstUndoneDim and a pass, until nothing is held; each round
-        // takes at least one held axis
-        uint32_t hb = taps_bits(taps_map(left, P.order));
-        for (uint32_t it = 0; it < TAPS_D_MAX_LEVELS && hb; ++it) {
-            const uint32_t level = taps_perm(P.order.hi, P.order.lo, taps_ctz(hb) * 0x01010101u);
-            const taps_b8 x = {taps_perm(0u, 0xFFu, level ^ 0x03020100u),
-                               taps_perm(0u, 0xFFu, level ^ 0x07060504u)};
-            at = taps_blend(x, taps_all(g * 0x01010101u), at);
-            g = taps_sum(D & x, g);
-            if (kLow) {
-                at2 = taps_blend(x, taps_all(h * 0x01010101u), at2);
-                h = taps_sum(D2 & x, h);
-            }
-            left = left & ~x;
-            const taps_b8 s1 = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
-            wait = wait & ~s1;
-            g -= taps_sum(D & s1, 0u);
-            if (kLow) h -= taps_sum(D2 & s1, 0u);
-            // the axes the gathered one's position holds up, directly or not
-            taps_b8 keep = ~x;
-            keep = taps_hop(keep, hop1);
-            keep = taps_hop(keep, hop2);
-            keep = taps_hop(keep, hop4);
-            const taps_b8 moved = left & ~keep;
-            at = taps_blend(moved, taps_all(g * 0x01010101u), at);
-            if (kLow) at2 = taps_blend(moved, taps_all(h * 0x01010101u), at2);
-            a2a = a2a | moved;
-            left = left & ~moved;
-            wait = wait & ~moved;
-            if (taps_any(s1)) {
-                const taps_b8 s2 = taps_bitop3<TAPS_A_NOTB_C>(wait, left, taps_map(~left, prev));
-                wait = wait & ~s2;
-                g -= taps_sum(D & s2, 0u);
-                if (kLow) h -= taps_sum(D2 & s2, 0u);
-            }
-            hb = taps_bits(taps_map(left, P.order));
         }
     }
 
@@ -628,16 +674,15 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     taps_b8 at_r, at_r2 = {0u, 0u};
     {
         // a targeted axis whose blocker comes before it
-        const taps_b8 before = taps_none((P.rank + taps_all(0x7F7F7F7Fu)) -
-                                         (taps_map(P.rank, prev) & taps_all(0x0F0F0F0Fu)));
+        const taps_b8 before = taps_above((P.rank + taps_all(0x0C0C0C0Cu)) -
+                                          (taps_map(P.rank, prev) & taps_all(0x07070707u)));
         const taps_b8 ready = open | taps_bitop3<TAPS_A_NOTB_C>(held, unwanted, before);
         // sliced straight back when its target is open by then; the others stay
         // gathered and are sliced, like the axes not held at all, when their
         // blocker is gathered
         const taps_b8 kept = taps_bitop3<TAPS_A & (0xFFu ^ (TAPS_B & TAPS_C))>(held, dst, ready);
         const taps_b8 later = todo & ~ready;
-        const taps_b8 ns = taps_map(next, P.order);
-        const taps_b8 us = taps_none(ns);
+        const taps_b8 us = taps_map(unwanted, P.order);
         const taps_b8 plus = taps_map(D & kept, P.order);
         const taps_b8 minus = taps_map(D & later, ns) & ~us;
         uint32_t g;
@@ -669,49 +714,51 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     // 2^(e + w) - 2^e (Eq. 9), an AllToAll 2^e - 2^(e - w) (Eq. 10); out of a block,
     // 2^(beta - u) groups share the link, u the free levels below beta, the
     // axis's own among them (Algorithm 3).
-    const taps_b8 width = Dh & taps_all(0x0F0F0F0Fu), below = Dh & taps_all(0xE0E0E0E0u);
-    const taps_b8 x1 = at + below, x2 = at_r + below, x3 = at_m + below;
-    const taps_b8 z1 = at2 + Dh2, z2 = at_r2 + Dh2, z3 = at_m2 + Dh2;
+    const taps_b8 width = Dh & taps_all(0x0F0F0F0Fu);
     uint32_t in1 = 0, in2 = 0, a2a_in = 0, out1 = 0, out2 = 0, out3 = 0, a2a_out = 0;
     uint32_t ct1 = 0, ct2 = 0, ct3 = 0;
     uint32_t link1[TAPS_D_MAX_CLASSES] = {0u}, link2[TAPS_D_MAX_CLASSES] = {0u};
     uint32_t link3[TAPS_D_MAX_CLASSES] = {0u}, a2a_link[TAPS_D_MAX_CLASSES] = {0u};
-    // the gathers' volumes, a byte each, of the axes in mask
-    auto volumes = [](uint32_t x, uint32_t more, uint32_t mask) {
-        const uint32_t e = x & 0x07070707u;
-        const uint32_t hi = taps_perm(0xFF7F3F1Fu, 0x0F070301u, e + more);   // 2^(k + 1) - 1
-        const uint32_t lo = taps_perm(0x7F3F1F0Fu, 0x07030100u, e);          // 2^k - 1
-        return taps_bitop3<TAPS_A & (0xFFu ^ TAPS_B) & TAPS_C>(hi, lo, mask);
-    };
     const taps_b8 more = width - (held & taps_all(0x01010101u));   // w - 1
     auto inside = [&](uint32_t l) {   // levels l .. l + 3 inside a node
         const uint32_t sel = taps_four(l, m.first[1]);
         const uint32_t hm = taps_perm(held.hi, held.lo, sel), mo = taps_perm(more.hi, more.lo, sel);
         const uint32_t am = taps_perm(a2a.hi, a2a.lo, sel);
-        const uint32_t y1 = taps_perm(x1.hi, x1.lo, sel), y2 = taps_perm(x2.hi, x2.lo, sel);
-        in1 = taps_dot4(volumes(y1, mo, hm & ~am), 0x01010101u, in1);
-        in2 = taps_dot4(volumes(y2, mo, hm), 0x01010101u, in2);
-        const uint32_t part = taps_perm(row.a2a.hi, row.a2a.lo, sel) & am;
-        a2a_in = taps_dot4(part, taps_pow2(y1 & 0x07070707u), a2a_in);
+        // 2^w - 1 of the axes held, and of those gathered
+        const uint32_t gain = taps_perm(0xFF7F3F1Fu, 0x0F070301u, mo) & hm;
+        const uint32_t e1 = taps_pow2(taps_perm(at.hi, at.lo, sel) & 0x07070707u);
+        const uint32_t e2 = taps_pow2(taps_perm(at_r.hi, at_r.lo, sel) & 0x07070707u);
+        in1 = taps_dot4(gain & ~am, e1, in1);
+        in2 = taps_dot4(gain, e2, in2);
+        a2a_in = taps_dot4(taps_perm(row.a2a.hi, row.a2a.lo, sel) & am, e1, a2a_in);
     };
     auto outside = [&](uint32_t c, uint32_t l) {   // levels l .. l + 3 of class c
         const uint32_t sel = taps_four(l, m.first[c + 1u]);
         const uint32_t hm = taps_perm(held.hi, held.lo, sel), mo = taps_perm(more.hi, more.lo, sel);
         const uint32_t am = taps_perm(a2a.hi, a2a.lo, sel), one = hm & 0x01010101u;
-        const uint32_t y1 = taps_perm(x1.hi, x1.lo, sel), y2 = taps_perm(x2.hi, x2.lo, sel);
-        const uint32_t y3 = taps_perm(x3.hi, x3.lo, sel);
-        // the free levels below this class's boundary
+        const uint32_t y1 = taps_perm(at.hi, at.lo, sel), y2 = taps_perm(at_r.hi, at_r.lo, sel);
+        const uint32_t y3 = taps_perm(at_m.hi, at_m.lo, sel);
+        // the axes' own levels below this class's boundary, and with them the free ones
+        const uint32_t own = c == 1u ? taps_perm(Dh.hi, Dh.lo, sel) & 0xE0E0E0E0u
+                                     : taps_perm(Dh2.hi, Dh2.lo, sel);
         auto u_of = [&](uint32_t y, const taps_b8 &z) {
-            const uint32_t f = c == 1u ? y : taps_perm(z.hi, z.lo, sel);
+            const uint32_t f = (c == 1u ? y : taps_perm(z.hi, z.lo, sel)) + own;
             return (c == 1u ? f >> 5 : c == 2u ? f : f >> 4) & 0x07070707u;
         };
-        const uint32_t u1 = u_of(y1, z1);
+        const uint32_t u1 = u_of(y1, at2);
         const taps_b8 share = m.share[c];
         const uint32_t s1 = taps_perm(share.hi, share.lo, u1);
-        const uint32_t s2 = taps_perm(share.hi, share.lo, u_of(y2, z2));
-        const uint32_t s3 = taps_perm(share.hi, share.lo, u_of(y3, z3));
-        const uint32_t v1 = volumes(y1, mo, hm & ~am), v2 = volumes(y2, mo, hm);
-        const uint32_t v3 = volumes(y3, mo, hm);
+        const uint32_t s2 = taps_perm(share.hi, share.lo, u_of(y2, at_r2));
+        const uint32_t s3 = taps_perm(share.hi, share.lo, u_of(y3, at_m2));
+        // the gathers' volumes, a byte each, of the axes in mask
+        auto volumes = [&](uint32_t e, uint32_t mask) {
+            const uint32_t hi = taps_perm(0xFF7F3F1Fu, 0x0F070301u, e + mo);   // 2^(k + 1) - 1
+            const uint32_t lo = taps_perm(0x7F3F1F0Fu, 0x07030100u, e);        // 2^k - 1
+            return taps_bitop3<TAPS_A & (0xFFu ^ TAPS_B) & TAPS_C>(hi, lo, mask);
+        };
+        const uint32_t e = y1 & 0x07070707u;
+        const uint32_t v1 = volumes(e, hm & ~am), v2 = volumes(y2 & 0x07070707u, hm);
+        const uint32_t v3 = volumes(y3 & 0x07070707u, hm);
         out1 = taps_dot4(v1, 0x01010101u, out1);
         out2 = taps_dot4(v2, 0x01010101u, out2);
         out3 = taps_dot4(v3, 0x01010101u, out3);
@@ -723,11 +770,8 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
         ct3 = taps_dot4(one, s3, ct3);
         // AllToAlls: the link carries 2^e times the share without the axis's own
         // levels, 2^x with x up to 14: the bytes of x < 8 and of x >= 8 apart
-        const uint32_t e = y1 & 0x07070707u;
         a2a_out = taps_dot4(taps_perm(row.a2a.hi, row.a2a.lo, sel) & am, taps_pow2(e), a2a_out);
-        const taps_b8 own = c == 1u ? below : Dh2;
-        const uint32_t o = taps_perm(own.hi, own.lo, sel);
-        const uint32_t kap = (c == 1u ? o >> 5 : c == 2u ? o : o >> 4) & 0x07070707u;
+        const uint32_t kap = (c == 1u ? own >> 5 : c == 2u ? own : own >> 4) & 0x07070707u;
         const uint32_t x = e + m.beta[c] * 0x01010101u - (u1 & hm) + kap;
         const uint32_t part = taps_perm(row.link.hi, row.link.lo, sel) & am;
         const uint32_t p = taps_pow2(x & 0x07070707u);

@@ -45,7 +45,9 @@ __device__ inline T *at_byte(T *base, uint32_t offset) {
 // than non-temporal stores, by a third on the stores alone).
 __device__ inline void store_entry(const taps_table &out, uint64_t row, uint32_t j,
                                    const taps_entry_out &o, uint32_t meta) {
-    const uint32_t o8 = j * 8u, o4 = j * 4u;
+    uint32_t o8 = j * 8u, o4 = j * 4u;
+    // made here and not kept across the loop as five 64-bit addresses
+    __asm__ volatile("" : "+v"(o8), "+v"(o4));
     *at_byte(out.t + row, o8) = o.t;
     *at_byte(out.vol + row, o8) = o.vol;
     *at_byte(out.intra + row, o8) = o.intra;
@@ -351,6 +353,13 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_front(
 // 128-byte lines, and rows shorter than a wavefront leave no lane idle.  The
 // source side of a lane's row is made again only in tiles where a lane's row
 // changes.
+//
+// Bound by the issue of vector instructions (about 4 cycles each whatever the
+// mix: half of them have a rate of 2 alone), hence by their number per tile.
+// Everything a row fixes is made with the row (positions as the target's axes
+// meet them), places in a window are 32-bit scalars, and the addresses of the
+// five stores are scalar bases and one offset: together 1409 -> 1299 us on the
+// 96-layer GPT's build.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kWindowsPerBlock = 4;
 
@@ -433,11 +442,17 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
     if (w >= win.n_windows) return;
     const uint64_t span = (uint64_t)win.tiles * kWave;
     const uint64_t begin = w * span;
-    const uint64_t end = win.total - begin < span ? win.total : begin + span;
+    // places in the window, 32 bits each (a scalar compare; 64 bits take vector ones)
+    const uint32_t size = (uint32_t)(win.total - begin < span ? win.total - begin : span);
     uint32_t e = win.window_edge[w];
     taps_edge_params E = win.params[e];
+    taps_b8 in_tensor = taps_in_tensor(E.to, E.rank);
     uint64_t e_start = uniform(win.starts[e]), e_end = uniform(win.starts[e + 1u]);
-    uint64_t to_out = uniform(E.out_offset) - e_start;
+    auto place = [&](uint64_t x) {   // of entry x, one past the window's for all behind it
+        return x - begin > size ? size + 1u : (uint32_t)(x - begin);
+    };
+    uint32_t stop = place(e_end);
+    uint64_t to_out = begin + uniform(E.out_offset) - e_start;
     uint32_t mul = row_multiplier(E.nd);
     const uint64_t local = begin - e_start;   // below ns * nd
     cell c;
@@ -448,28 +463,28 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
     uint32_t row = ~0u;              // the row P holds
     uint32_t cached = ~0u - kWave;   // the cache holds rows cached .. cached + 63 of edge e
     taps_packed q = desc[E.dst_base + (c.i < E.ns ? c.j : 0u)];
-    for (uint64_t v0 = begin; v0 < end; v0 += kWave) {
-        const uint64_t tile_end = end - v0 < kWave ? end : v0 + kWave;
+    for (uint32_t v = 0; v < size; v += kWave) {
+        const uint32_t tile_end = size - v < kWave ? size : v + kWave;
         // the next tile's target side, asked for a tile ahead (before this tile's
         // stores, which a later load would wait for)
         cell next = c;
         taps_packed next_q = q;
-        if (e_end > tile_end) {   // uniform
+        if (stop > tile_end) {   // uniform
             next.j += kWave;
             wrap(next, E.nd, mul);
             next_q = desc[E.dst_base + (next.i < E.ns ? next.j : 0u)];
         }
         uint32_t first = 0;   // lanes below this are done
         for (;;) {            // uniform: one edge per pass
-            const uint32_t last = (uint32_t)((e_end < tile_end ? e_end : tile_end) - v0);
-            const bool mine = lane >= first && lane < last;
+            const uint32_t last = (stop < tile_end ? stop : tile_end) - v;
+            const bool mine = lane - first < last - first;
             if (__any(mine && c.i != row)) {
                 if (__any(mine && c.i - cached >= kWave)) {
                     cached = __builtin_amdgcn_readlane(c.i, first);
                     const uint32_t r = cached + lane;
                     fill_rows(rows[wave],
                               taps_make_source<C>(desc[E.src_base + (r < E.ns ? r : cached)],
-                                                  E.from, E.rank, m), lane);
+                                                  E.from, E.to, E.rank, m), lane);
                 }
                 // (an entry's row is within 63 of the first's, as every row has one at least)
                 P = read_row(rows[wave], mine ? c.i - cached : 0u);
@@ -478,16 +493,18 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
             // every lane, so that the branches on the node boundary stay uniform
             // (a lane without an entry computes one that it does not store)
             taps_three<C> r;
-            taps_three_candidates<C>(P, q, E.to, E.rank, m, tops, low, r);
-            if (mine) emit(E, v0 + to_out, lane, r);
-            if (e_end >= tile_end && (e_end > tile_end || tile_end == end)) break;
+            taps_three_candidates<C>(P, q, in_tensor, m, tops, low, r);
+            if (mine) emit(E, to_out + v, lane, r);
+            if (stop >= tile_end && (stop > tile_end || tile_end == size)) break;
             // the next edge starts in this tile, or with the next one
             first = last;
             ++e;
             E = win.params[e];
+            in_tensor = taps_in_tensor(E.to, E.rank);
             e_start = e_end;
             e_end = uniform(win.starts[e + 1u]);
-            to_out = uniform(E.out_offset) - e_start;
+            stop = place(e_end);
+            to_out = begin + uniform(E.out_offset) - e_start;
             mul = row_multiplier(E.nd);
             row = ~0u;
             cached = ~0u - kWave;
@@ -497,7 +514,7 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
             next = c;
             if (lane < first) next.i = 0u;
             next.j += kWave;
-            if (first == (uint32_t)(tile_end - v0)) {
+            if (first == tile_end - v) {
                 // it starts with the next tile (first == 64): lane l there is its entry l
                 wrap(next, E.nd, mul);
                 next_q = desc[E.dst_base + (next.i < E.ns ? next.j : 0u)];

@@ -59,7 +59,7 @@ void layouts() {
                     sum += w;
                     ok = ok && (w == 0u || ((part >> a) & 1u));
                     if (w) positions |= 1u << taps_nib(S.pos, a), ++split;
-                    ok = ok && ((R.packed.width >> s) & 15u) == w;
+                    ok = ok && ((taps_u64(R.packed.runs) >> (8u * a + 4u)) & 15u) == w;
                     ok = ok && taps_axis_levels(R.packed, a) ==
                                    taps_levels(taps_nib(D.lo, a), taps_nib(D.width, a));
                 }
@@ -160,7 +160,8 @@ void entries(uint64_t budget) {
             P.a2a = rows;
             P.expand = expand;
             P.a2a_cls = cls_rows;
-            const taps_source S = taps_make_source<C>(taps_lay_out(Sp, pm, n).packed, from, rank, m);
+            const taps_source S = taps_make_source<C>(taps_lay_out(Sp, pm, n).packed, from, to,
+                                                         rank, m);
             for (uint32_t j = 0; j < 24u; ++j) {
                 const taps_nibbles Sq = taps_unrank(qm, n, rnd() % tq, kW.v);
                 taps_col Q;
@@ -175,8 +176,8 @@ void entries(uint64_t budget) {
                 want[1] = taps_rearrange_t(P, Q, L, M, st).c;
                 want[2] = taps_remove_h(P, L, M);
                 taps_three<C> got;
-                taps_three_candidates<C>(S, taps_lay_out(Sq, qm, n).packed, to, rank, m, tops, low,
-                                         got);
+                taps_three_candidates<C>(S, taps_lay_out(Sq, qm, n).packed,
+                                         taps_in_tensor(to, rank), m, tops, low, got);
                 bool ok = got.a2a_in == want[0].xa;
                 for (uint32_t k = 0; k < 3u; ++k) {
                     const uint32_t link[3] = {want[k].x1, want[k].x2, want[k].x3};
