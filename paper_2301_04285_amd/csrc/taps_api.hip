@@ -540,7 +540,8 @@ void plan_copies(const std::vector<uint64_t> &eoff, const std::vector<uint32_t> 
                 c.count = (uint32_t)(size - k < TAPS_COPY_CHUNK ? size - k : TAPS_COPY_CHUNK);
                 c.dst_begin = begin + m;
                 c.n_dst = n_dst - m < TAPS_COPY_DSTS ? n_dst - m : TAPS_COPY_DSTS;
-                c.pad = 0;
+                const uint64_t after = size - k - c.count;
+                c.extra = (uint32_t)(after < TAPS_COPY_EXTRA ? after : TAPS_COPY_EXTRA);
                 copies.push_back(c);
             }
     }

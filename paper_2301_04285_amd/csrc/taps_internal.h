@@ -35,10 +35,12 @@ struct taps_edge_params {
 // dst[k] = dst_list[dst_begin + k].
 struct taps_copy_task {
     uint64_t src, offset;
-    uint32_t count, dst_begin, n_dst, pad;
+    uint32_t count, dst_begin, n_dst;
+    uint32_t extra;   // entries of the table after these, at most TAPS_COPY_EXTRA
 };
-#define TAPS_COPY_CHUNK 2048    // entries per copy task (8 per thread of 256)
-#define TAPS_COPY_DSTS 6        // tables one copy task writes (4-6 measured best, 16 is 20 % slower)
+#define TAPS_COPY_CHUNK 2048    // entries per copy task (4 per thread of 512; 1024 and 4096 are slower)
+#define TAPS_COPY_DSTS 6        // tables one copy task writes (4, 8 and 12 measure within 1 %)
+#define TAPS_COPY_EXTRA 32u     // entries of a 128-byte line, of the narrowest array
 
 // The edge kernels run over windows: window w is the 64 T entries
 // [64 T w, 64 T (w + 1)) of the computed tables laid end to end (aligned, so

@@ -40,19 +40,19 @@ __device__ inline T *at_byte(T *base, uint32_t offset) {
 
 // Entry j of a row whose records start at `row` (uniform): 32-bit byte offsets
 // from the uniform row bases, j < 2^21 (8 axes on 8 levels give at most
-// 1,047,376 strategies per operator); five cached stores (L2 merges the
-// partial 128-byte lines where neighbouring segments meet; measured faster
-// than non-temporal stores, by a third on the stores alone).
+// 1,047,376 strategies per operator); five non-temporal stores of whole
+// 128-byte lines (nothing is left to merge but at a tile of two edges; cached
+// stores take the 24-layer GPT's build from 80.6 to 82.5 us).
 __device__ inline void store_entry(const taps_table &out, uint64_t row, uint32_t j,
                                    const taps_entry_out &o, uint32_t meta) {
     uint32_t o8 = j * 8u, o4 = j * 4u;
     // made here and not kept across the loop as five 64-bit addresses
     __asm__ volatile("" : "+v"(o8), "+v"(o4));
-    *at_byte(out.t + row, o8) = o.t;
-    *at_byte(out.vol + row, o8) = o.vol;
-    *at_byte(out.intra + row, o8) = o.intra;
-    *at_byte(out.inter + row, o8) = o.inter;
-    *at_byte(out.meta + row, o4) = meta;
+    __builtin_nontemporal_store(o.t, at_byte(out.t + row, o8));
+    __builtin_nontemporal_store(o.vol, at_byte(out.vol + row, o8));
+    __builtin_nontemporal_store(o.intra, at_byte(out.intra + row, o8));
+    __builtin_nontemporal_store(o.inter, at_byte(out.inter + row, o8));
+    __builtin_nontemporal_store(meta, at_byte(out.meta + row, o4));
 }
 
 __device__ inline uint32_t lanes_below(uint64_t mask) {
@@ -710,37 +710,43 @@ __global__ __launch_bounds__(256) void k_node_costs_h(const taps_op *__restrict_
 }
 
 // Shared tables: each task holds `count` (<= TAPS_COPY_CHUNK) consecutive
-// entries of a computed table, staged once in LDS and stored into every table
-// that shares it, at the same offset; blockIdx.y picks the array.  The tables
-// start at arbitrary entries, so each destination is written with 16-byte
-// stores aligned to its own 16-byte boundaries (LDS absorbs the difference in
-// alignment between source and destination), plus single-entry stores for the
-// head and tail.
-struct alignas(16) vec16 {
-    uint32_t w[4];
-};
+// entries of a computed table, staged once in LDS with the `extra` entries
+// after them and stored into every table that shares it; blockIdx.y picks the
+// array.  The tables start at arbitrary entries, so into each destination a
+// task stores the whole 128-byte lines that its entries end: from the first
+// line boundary at or after them to the one at or after their end (LDS absorbs
+// the difference in alignment), with single entries only at a table's ends.
+// Bound by the stores: the 96-layer GPT's 3.5 GB take 688 us when each task
+// stores just its entries, in cached stores, which leaves a part of a line at
+// either end of each to merge; 640 us so, 5.5 TB/s (a plain store of five
+// arrays side by side: 570 - 640 us).
+constexpr uint32_t kCopyThreads = 512;
 
 template <typename T>
 __device__ inline void copy_range(T *base, const taps_copy_task &c,
                                   const uint64_t *__restrict__ dst_list, T *stage) {
-    constexpr uint32_t kV = 16 / sizeof(T);   // entries per 16-byte store
+    constexpr uint32_t kV = 16 / sizeof(T);      // entries per 16-byte store
+    constexpr uint32_t kLine = 128 / sizeof(T);  // and per line
+    static_assert(kLine <= TAPS_COPY_EXTRA && TAPS_COPY_CHUNK % kLine == 0, "whole lines per task");
+    typedef uint32_t quad __attribute__((ext_vector_type(4)));
     const T *s = base + c.src;
-    for (uint32_t x = threadIdx.x; x < c.count; x += blockDim.x) stage[x] = s[x];
+    const uint32_t have = c.count + c.extra;
+    for (uint32_t x = threadIdx.x; x < have; x += blockDim.x) stage[x] = s[x];
     __syncthreads();
     for (uint32_t k = 0; k < c.n_dst; ++k) {
         T *d = base + dst_list[c.dst_begin + k] + c.offset;
-        const uint32_t mis = (uint32_t)(((uintptr_t)d & 15u) / sizeof(T));
-        const uint32_t head = mis ? (kV - mis < c.count ? kV - mis : c.count) : 0u;
-        const uint32_t n_vec = (c.count - head) / kV;
-        const uint32_t tail = head + n_vec * kV;
-        if (threadIdx.x < head) d[threadIdx.x] = stage[threadIdx.x];
-        vec16 *dv = (vec16 *)(d + head);
+        const uint32_t mis = (uint32_t)(((uintptr_t)d & 127u) / sizeof(T));
+        const uint32_t skip = mis ? kLine - mis : 0u;   // entries before the first line boundary
+        const uint32_t lo = skip < have ? skip : have;
+        const uint32_t hi = c.count + skip < have ? c.count + skip : have;
+        const uint32_t n_vec = (hi - lo) / kV, tail = lo + n_vec * kV;
+        if (c.offset == 0 && threadIdx.x < lo) d[threadIdx.x] = stage[threadIdx.x];
         for (uint32_t v = threadIdx.x; v < n_vec; v += blockDim.x) {
-            vec16 val;
-            __builtin_memcpy(&val, stage + head + v * kV, 16);
-            dv[v] = val;
+            quad val;
+            __builtin_memcpy(&val, stage + lo + v * kV, 16);
+            __builtin_nontemporal_store(val, (quad *)(d + lo) + v);
         }
-        if (tail + threadIdx.x < c.count) d[tail + threadIdx.x] = stage[tail + threadIdx.x];
+        if (tail + threadIdx.x < hi) d[tail + threadIdx.x] = stage[tail + threadIdx.x];
     }
 }
 
@@ -753,10 +759,10 @@ __global__ __launch_bounds__(256) void k_pull(const uint4 *__restrict__ src,
         dst[k] = src[k];
 }
 
-__global__ __launch_bounds__(256) void k_copy_tables(const taps_copy_task *__restrict__ tasks,
+__global__ __launch_bounds__(kCopyThreads) void k_copy_tables(const taps_copy_task *__restrict__ tasks,
                                                      const uint64_t *__restrict__ dst_list,
                                                      taps_table out) {
-    __shared__ uint64_t stage[TAPS_COPY_CHUNK];
+    __shared__ uint64_t stage[TAPS_COPY_CHUNK + TAPS_COPY_EXTRA];
     const taps_copy_task c = tasks[blockIdx.x];
     switch (blockIdx.y) {
     case 0: copy_range(out.t, c, dst_list, (double *)stage); break;
@@ -903,7 +909,7 @@ hipError_t taps_launch_pull(const void *src, void *dst, uint64_t bytes, hipStrea
 hipError_t taps_launch_copy_tables(const taps_copy_task *tasks, uint32_t n_tasks,
                                    const uint64_t *dst_list, taps_table out, hipStream_t stream) {
     if (n_tasks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_copy_tables, dim3(n_tasks, 5), dim3(256), 0, stream, tasks, dst_list,
+    hipLaunchKernelGGL(k_copy_tables, dim3(n_tasks, 5), dim3(kCopyThreads), 0, stream, tasks, dst_list,
                        out);
     return hipGetLastError();
 }

@@ -56,3 +56,39 @@ def test_windows_at_their_edges(T, devices, axes, ops, long_windows):  # noqa: F
                         name)
     finally:
         T.taps_set_long_segments_min(prev)
+
+
+@pytest.mark.parametrize("devices,axes,ops", [
+    (1, 2, 40),     # tables of one entry
+    (2, 3, 12),     # 9
+    (8, 4, 7),      # 2704: a chunk and a part of one
+    (32, 3, 9),     # 3969
+    (64, 3, 15),    # 8649, into more tables than one task writes
+])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_shared_tables_are_copied_whole(T, devices, axes, ops, shift):  # noqa: F811
+    """Copies start and end on the lines of each destination: every entry, and none behind
+    the last, into arrays that start on a line or `shift` entries after one."""
+    import torch
+    r = W.Graph()
+    prev = None
+    for k in range(ops):   # one kind of operator: all tables but one are copies
+        op = r.add(W.elementwise(f"e{k}", "e", tuple("abcd"[:axes]), (256,) * axes, 1, 2))
+        if prev is not None:
+            r.connect(prev, op, 0)
+        prev = op
+    cl = W.Cluster(1, devices, 600 * W.GB, 100 * W.GB)
+    say(f"[gpu] {ops} shared tables on {devices}, {axes} axes, shift {shift}")
+    want = T.taps_build_tables(r, cl)
+    n = int(want.edge_offsets[-1])
+    wide = {k: v.view(torch.int32 if k == "meta" else torch.int64)
+            for k, v in T.alloc_table(n + shift + 40).items()}
+    for v in wide.values():
+        v.fill_(-7)
+    edge = {k: v[shift:shift + n].view(want.edge[k].dtype) for k, v in wide.items()}
+    out = T.Tables(want.op_offsets, torch.empty_like(want.strategies),
+                   T.alloc_table(len(want.strategies)), want.edge_offsets, edge)
+    got = T.taps_build_tables(r, cl, out=out, shared=True)
+    for k, v in wide.items():
+        assert torch.equal(got.edge[k].view(v.dtype), want.edge[k].view(v.dtype)), k
+        assert bool((v[:shift] == -7).all()) and bool((v[shift + n:] == -7).all()), k
