@@ -706,14 +706,11 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
         return st;
     if ((st = sc.alloc((void **)&d_win, sizeof(uint32_t) * win.n_windows)) != TAPS_OK) return st;
     if ((st = sc.alloc((void **)&d_tops, TAPS_TOPS_BYTES)) != TAPS_OK) return st;
-    hipError_t err = taps_launch_describe(strategies, total, lp.n, d_desc, stream);
     const taps_windows tw = device_windows(win, d_params, d_win, d_tops, dev, ch[3], ch[7],
                                            hier ? hier_levels(*hier, lp.n) : taps_make_levels(lp.n, lp.lam));
-    if (err == hipSuccess) {
-        const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[4],
-                                              d_params, d_win, d_tops, reverse);
-        err = taps_launch_edge_setup(pa, lp, stream);
-    }
+    const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[4], d_params,
+                                          d_win, d_tops, reverse);
+    hipError_t err = taps_launch_edge_front(strategies, total, d_desc, pa, lp, stream);
     // the edge-table kernel launches (entries > 0): use the events, if any, once
     const hipEvent_t before = g_kernel_before, after = g_kernel_after;
     g_kernel_before = g_kernel_after = nullptr;
@@ -1311,12 +1308,9 @@ taps_status taps_node_costs(const taps_graph *graph, const taps_cluster *cluster
                           {op_offsets, sizeof(uint64_t) * (n_ops + 1), 0}};
     void *dev = nullptr;
     if ((st = upload(sc, ch, &dev)) != TAPS_OK) return st;
-    taps_packed *d_desc = nullptr;
-    if ((st = sc.alloc((void **)&d_desc, sizeof(taps_packed) * total)) != TAPS_OK) return st;
-    hipError_t err = taps_launch_describe(strategies, total, lp.n, d_desc, stream);
-    if (err == hipSuccess)
-        err = taps_launch_node_costs(at<taps_op>(dev, ch[0]), n_ops, at<uint64_t>(dev, ch[1]),
-                                     d_desc, total, lp, out, stream);
+    const hipError_t err = taps_launch_node_costs(at<taps_op>(dev, ch[0]), n_ops,
+                                                  at<uint64_t>(dev, ch[1]), strategies, total, lp,
+                                                  out, stream);
     if (err != hipSuccess) return hip_fail(err, "node costs");
     return TAPS_OK;
 }
@@ -1362,12 +1356,9 @@ taps_status taps_node_costs_topology(const taps_graph *graph, const taps_topolog
     void *dev = nullptr;
     if ((st = upload(sc, ch, &dev)) != TAPS_OK) return st;
     const uint32_t n = log2u(topology->domain[H.n_classes - 1]);
-    taps_packed *d_desc = nullptr;
-    if ((st = sc.alloc((void **)&d_desc, sizeof(taps_packed) * total)) != TAPS_OK) return st;
-    hipError_t err = taps_launch_describe(strategies, total, n, d_desc, stream);
-    if (err == hipSuccess)
-        err = taps_launch_node_costs_h(at<taps_op>(dev, ch[0]), n_ops, at<uint64_t>(dev, ch[1]),
-                                       d_desc, total, n, H, out, stream);
+    const hipError_t err = taps_launch_node_costs_h(at<taps_op>(dev, ch[0]), n_ops,
+                                                    at<uint64_t>(dev, ch[1]), strategies, total, n,
+                                                    H, out, stream);
     if (err != hipSuccess) return hip_fail(err, "node costs");
     return TAPS_OK;
 }

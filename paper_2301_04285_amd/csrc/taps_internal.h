@@ -60,11 +60,9 @@ struct taps_copy_task {
 #define TAPS_WINDOW_SWEEP 4
 #define TAPS_LONG_SEGS_MIN 32768
 
-hipError_t taps_launch_describe(const taps_strategy *s, uint64_t total, uint32_t n,
-                                taps_packed *desc, hipStream_t stream);
 hipError_t taps_launch_node_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
-                                  const taps_packed *desc, uint64_t total, const taps_launch &lp,
-                                  taps_table out, hipStream_t stream);
+                                  const taps_strategy *strategies, uint64_t total,
+                                  const taps_launch &lp, taps_table out, hipStream_t stream);
 // The edge plan of a launch (device arrays): the constants of the n_edges
 // computed edges (edge computed[k], or k without that list) into params, and
 // the edge that each window starts in.  starts: n_edges + 1 first entries of
@@ -85,8 +83,10 @@ struct taps_plan_args {
     taps_levels_model model;
 };
 #define TAPS_TOPS_BYTES ((sizeof(taps_top_row) + sizeof(taps_b8)) * 256)
-hipError_t taps_launch_edge_setup(const taps_plan_args &pa, const taps_launch &lp,
-                                  hipStream_t stream);
+// The plan and the `total` strategies' descriptors.
+hipError_t taps_launch_edge_front(const taps_strategy *strategies, uint64_t total,
+                                  taps_packed *desc, const taps_plan_args &pa,
+                                  const taps_launch &lp, hipStream_t stream);
 // What the edge kernels run over (the plan's results).
 struct taps_windows {
     const taps_edge_params *params;
@@ -130,7 +130,7 @@ hipError_t taps_launch_build_strategies(const taps_op *ops, const taps_build_chu
                                         uint32_t n_chunks, uint32_t allowed_cuts,
                                         const taps_launch &lp, taps_strategy *out,
                                         taps_packed *desc, taps_table node, hipStream_t stream);
-// taps_launch_build_strategies and taps_launch_edge_setup as one launch (the
+// taps_launch_build_strategies and the edge plan as one launch (the
 // plan needs only the host-counted strategy offsets).
 hipError_t taps_launch_build_front(const taps_build_chunk *chunks, uint32_t n_chunks,
                                    uint32_t allowed_cuts, const taps_launch &lp, taps_strategy *out,
@@ -140,7 +140,7 @@ hipError_t taps_launch_build_front(const taps_build_chunk *chunks, uint32_t n_ch
 hipError_t taps_launch_edge_costs_h(const taps_windows &win, const taps_packed *desc,
                                     const taps_hier &H, taps_table out, hipStream_t stream);
 hipError_t taps_launch_node_costs_h(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
-                                    const taps_packed *desc, uint64_t total, uint32_t n,
+                                    const taps_strategy *strategies, uint64_t total, uint32_t n,
                                     const taps_hier &H, taps_table out, hipStream_t stream);
 // Copies `bytes` (a multiple of 16, below 2^36) from src, fine-grained pinned
 // host memory mapped for the device, to device memory at dst.

@@ -72,14 +72,6 @@ __device__ inline taps_nibbles strategy_nibbles(const taps_strategy &st) {
     return S;
 }
 
-__global__ __launch_bounds__(256) void k_describe(const taps_strategy *__restrict__ s,
-                                                  uint64_t total, uint32_t n,
-                                                  taps_packed *__restrict__ desc) {
-    const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    desc[idx] = taps_lay_out(strategy_nibbles(s[idx]), 0xFFu, n).packed;
-}
-
 // largest k in [0, n) with offsets[k] <= x
 __device__ inline uint32_t find_owner(const uint64_t *offsets, uint32_t n, uint64_t x) {
     uint32_t lo = 0, hi = n;
@@ -93,39 +85,137 @@ __device__ inline uint32_t find_owner(const uint64_t *offsets, uint32_t n, uint6
     return lo;
 }
 
-__device__ inline void node_tensor(taps_acc &c, const taps_op &op, const taps_tensor &t,
-                                   const taps_packed &D, uint32_t full, uint32_t lam) {
-    uint32_t used = 0;
-    uint64_t bytes = op.dtype_bytes;
-    for (uint32_t d = 0; d < t.rank && d < TAPS_MAX_RANK; ++d) {
-        const uint32_t a = t.axis[d] & 7u;
-        used |= taps_axis_levels(D, a);
-        bytes *= (uint64_t)op.axis_len[a];
+// The owner of a wavefront's lane's x (x of lane l: first + l, or less at the
+// end), as find_owner: 64 offsets per step for the first lane's, then the
+// offsets after that one, at most one per lane as every range holds something.
+// All lanes take part.
+__device__ inline uint32_t wave_owner(const uint64_t *offsets, uint32_t n, uint64_t x) {
+    const uint32_t lane = threadIdx.x % kWave;
+    const uint64_t first = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32)) << 32) |
+                           __builtin_amdgcn_readfirstlane((uint32_t)x);
+    uint32_t lo = 0, size = n;   // largest k in [lo, lo + size) with offsets[k] <= first
+    for (;;) {
+        const uint32_t stride = (size + kWave - 1u) / kWave, k = lane * stride;
+        const uint64_t m = __ballot(k < size && offsets[lo + (k < size ? k : 0u)] <= first);
+        const uint32_t j = ((uint32_t)__builtin_popcountll(m) - 1u) * stride;
+        lo += j;
+        if (stride == 1u) break;
+        size = size - j < stride ? size - j : stride;
     }
-    taps_allreduce(c, full & ~used, bytes, lam);
+    const uint64_t next = offsets[n - lo > lane + 1u ? lo + lane + 1u : n];
+    uint32_t more = 0;
+#pragma unroll
+    for (uint32_t step = kWave / 2; step; step /= 2) {
+        const uint32_t at = more + step - 1u;
+        const uint64_t o = ((uint64_t)__shfl((uint32_t)(next >> 32), at) << 32) |
+                           __shfl((uint32_t)next, at);
+        more += o <= x ? step : 0u;
+    }
+    return lo + more;
 }
 
+// An operator's description in registers, read as words all at once: its bytes
+// one by one are a chain of some 30 dependent loads.
+struct op_words {
+    uint32_t w[sizeof(taps_op) / 4u];
+    __device__ uint32_t byte(uint32_t at) const { return (w[at / 4u] >> (8u * (at % 4u))) & 0xFFu; }
+    __device__ uint64_t length(uint32_t a) const {
+        const uint32_t at = offsetof(taps_op, axis_len) / 4u + 2u * a;
+        return ((uint64_t)w[at + 1u] << 32) | w[at];
+    }
+    // the axes of the tensor at byte `at`, which names an axis at most once
+    __device__ uint32_t axes(uint32_t at) const {
+        const uint32_t rank = byte(at);
+        uint32_t m = 0;
+#pragma unroll
+        for (uint32_t d = 0; d < TAPS_MAX_RANK; ++d)
+            if (d < rank) m |= 1u << (byte(at + 1u + d) & 7u);
+        return m;
+    }
+    // f(at) for the output, the inputs and the weights
+    template <typename F> __device__ void tensors(bool inputs, const F &f) const {
+        const uint32_t n_in = inputs ? byte(offsetof(taps_op, n_in)) : 0u;
+        const uint32_t n_w = byte(offsetof(taps_op, n_w));
+        f(offsetof(taps_op, out));
+#pragma unroll
+        for (uint32_t q = 0; q < TAPS_MAX_INPUTS; ++q)
+            if (q < n_in) f(offsetof(taps_op, in) + q * sizeof(taps_tensor));
+#pragma unroll
+        for (uint32_t q = 0; q < TAPS_MAX_WEIGHTS; ++q)
+            if (q < n_w) f(offsetof(taps_op, w) + q * sizeof(taps_tensor));
+    }
+};
+
+// A lane's own operator.
+__device__ inline op_words read_op(const taps_op *op) {
+    static_assert(sizeof(taps_op) % 16 == 0, "16-byte loads of operators");
+    op_words o;
+#pragma unroll
+    for (uint32_t x = 0; x < sizeof(taps_op) / 16u; ++x) {
+        const uint4 v = ((const uint4 *)op)[x];
+        o.w[4 * x] = v.x, o.w[4 * x + 1] = v.y, o.w[4 * x + 2] = v.z, o.w[4 * x + 3] = v.w;
+    }
+    return o;
+}
+
+// add(levels without the tensor, its bytes) for every tensor of an operator;
+// byte a of (hi, lo): the levels of axis a.
+template <typename Add>
+__device__ inline void node_tensors(const op_words &op, uint32_t lo, uint32_t hi, uint32_t full,
+                                    const Add &add) {
+    op.tensors(true, [&](uint32_t at) {
+        const uint32_t axes = op.axes(at);
+        uint64_t size = op.byte(offsetof(taps_op, dtype_bytes));
+        uint32_t used = 0;
+#pragma unroll
+        for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a)
+            if ((axes >> a) & 1u) {
+                size *= op.length(a);
+                used |= (a < 4u ? lo : hi) >> (8u * (a & 3u));
+            }
+        add(full & ~used, size);
+    });
+}
+
+// The same for strategy s of a lane's own operator.
+template <typename Add>
+__device__ inline void strategy_tensors(const taps_op *op, const taps_strategy &s, uint32_t n,
+                                        const Add &add) {
+    const op_words o = read_op(op);
+    const taps_packed D = taps_lay_out(strategy_nibbles(s), 0xFFu, n).packed;
+    uint32_t lo = 0, hi = 0;
+#pragma unroll
+    for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a)
+        (a < 4u ? lo : hi) |= (taps_axis_levels(D, a) & 0xFFu) << (8u * (a & 3u));
+    node_tensors(o, lo, hi, taps_low_mask(n), add);
+}
+
+__device__ inline void store_node(const taps_table &node, uint64_t idx, const taps_acc &c,
+                                  const taps_launch &lp) {
+    node.t[idx] = (double)c.intra * lp.inv_n_bintra + (double)c.inter * lp.inv_n_binter;
+    node.vol[idx] = c.vol;
+    node.intra[idx] = c.intra;
+    node.inter[idx] = c.inter;
+    node.meta[idx] = taps_meta(0, c);
+}
+
+// One thread per strategy, from the strategies themselves.  Bound by latency:
+// the owner's offsets, then operator and strategy together, then arithmetic
+// (6,400 strategies 4.9 us, 9.3 with descriptors from a launch of their own and
+// the operators read byte by byte; k_memory_costs 3.8, 6.4 before).
 __global__ __launch_bounds__(256) void k_node_costs(const taps_op *__restrict__ ops, uint32_t n_ops,
                                                     const uint64_t *__restrict__ offsets,
-                                                    const taps_packed *__restrict__ desc,
+                                                    const taps_strategy *__restrict__ strategies,
                                                     uint64_t total, taps_launch lp, taps_table out) {
     const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const taps_op &op = ops[find_owner(offsets, n_ops, idx)];
-    const taps_packed D = desc[idx];
-    const uint32_t full = taps_low_mask(lp.n);
+    const uint64_t x = idx < total ? idx : total - 1u;
+    const taps_op *op = ops + wave_owner(offsets, n_ops, x);
     taps_acc c;
     taps_acc_zero(c);
-    node_tensor(c, op, op.out, D, full, lp.lam);
-    for (uint32_t k = 0; k < op.n_in && k < TAPS_MAX_INPUTS; ++k)
-        node_tensor(c, op, op.in[k], D, full, lp.lam);
-    for (uint32_t k = 0; k < op.n_w && k < TAPS_MAX_WEIGHTS; ++k)
-        node_tensor(c, op, op.w[k], D, full, lp.lam);
-    out.t[idx] = (double)c.intra * lp.inv_n_bintra + (double)c.inter * lp.inv_n_binter;
-    out.vol[idx] = c.vol;
-    out.intra[idx] = c.intra;
-    out.inter[idx] = c.inter;
-    out.meta[idx] = taps_meta(0, c);
+    strategy_tensors(op, strategies[x], lp.n, [&](uint32_t missing, uint64_t bytes) {
+        taps_allreduce(c, missing, bytes, lp.lam);
+    });
+    if (idx < total) store_node(out, idx, c, lp);
 }
 
 // GenerateStrategySet, and the whole strategy side of a single-call build, in
@@ -153,20 +243,14 @@ __device__ inline void build_chunk(const taps_build_chunk &ck, const taps_op *__
     // its bytes one by one were a chain of some 30 dependent vector loads, most of
     // this kernel's time) and taken apart on the scalar unit
     const uint32_t *words = (const uint32_t *)(ops + ck.op);
-    uint32_t op[sizeof(taps_op) / 4u];
+    op_words op;
 #pragma unroll
-    for (uint32_t x = 0; x < sizeof(taps_op) / 4u; ++x) op[x] = words[x];
-    auto byte = [&](uint32_t at) { return (op[at / 4u] >> (8u * (at % 4u))) & 0xFFu; };
-    auto length = [&](uint32_t a) {
-        const uint32_t at = offsetof(taps_op, axis_len) / 4u + 2u * a;
-        return ((uint64_t)op[at + 1u] << 32) | op[at];
-    };
-    const uint32_t part = byte(offsetof(taps_op, part_mask));
-    const uint32_t n_in = byte(offsetof(taps_op, n_in)), n_w = byte(offsetof(taps_op, n_w));
+    for (uint32_t x = 0; x < sizeof(taps_op) / 4u; ++x) op.w[x] = words[x];
+    const uint32_t part = op.byte(offsetof(taps_op, part_mask));
     uint32_t most = 0;   // nibble a: the largest exponent that divides axis a's length
 #pragma unroll
     for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a) {
-        const uint64_t len = length(a) | 256u;   // exponents end at 8
+        const uint64_t len = op.length(a) | 256u;   // exponents end at 8
         most |= (uint32_t)__builtin_ctzll(len) << (4u * a);
     }
     __syncthreads();
@@ -207,34 +291,10 @@ __device__ inline void build_chunk(const taps_build_chunk &ck, const taps_op *__
     }
     taps_acc c;
     taps_acc_zero(c);
-    auto tensor = [&](uint32_t at) {   // the tensor at byte `at` of the operator
-        const uint32_t rank = byte(at);
-        uint32_t axes = 0;
-        uint64_t size = byte(offsetof(taps_op, dtype_bytes));
-#pragma unroll
-        for (uint32_t d = 0; d < TAPS_MAX_RANK; ++d)
-            if (d < rank) axes |= 1u << (byte(at + 1u + d) & 7u);
-        uint32_t used = 0;
-#pragma unroll
-        for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a)
-            if ((axes >> a) & 1u) {   // uniform; a tensor names an axis at most once
-                size *= length(a);
-                used |= (a < 4u ? lv_lo : lv_hi) >> (8u * (a & 3u));
-            }
-        taps_allreduce(c, full & ~used, size, lp.lam);
-    };
-    tensor(offsetof(taps_op, out));
-#pragma unroll
-    for (uint32_t q = 0; q < TAPS_MAX_INPUTS; ++q)
-        if (q < n_in) tensor(offsetof(taps_op, in) + q * sizeof(taps_tensor));
-#pragma unroll
-    for (uint32_t q = 0; q < TAPS_MAX_WEIGHTS; ++q)
-        if (q < n_w) tensor(offsetof(taps_op, w) + q * sizeof(taps_tensor));
-    node.t[idx] = (double)c.intra * lp.inv_n_bintra + (double)c.inter * lp.inv_n_binter;
-    node.vol[idx] = c.vol;
-    node.intra[idx] = c.intra;
-    node.inter[idx] = c.inter;
-    node.meta[idx] = taps_meta(0, c);
+    node_tensors(op, lv_lo, lv_hi, full, [&](uint32_t missing, uint64_t bytes) {
+        taps_allreduce(c, missing, bytes, lp.lam);
+    });
+    store_node(node, idx, c, lp);
 }
 
 __global__ __launch_bounds__(kBuildThreads) void k_build_strategies(
@@ -244,31 +304,27 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_strategies(
     build_chunk(chunks[blockIdx.x], ops, allowed_cuts, lp, out, desc, node);
 }
 
-// Bytes of one shard of tensor t under strategy s: each dimension's length
-// divided by its split degree, times the element size.
-__device__ inline uint64_t shard_bytes(const taps_op &op, const taps_tensor &t,
-                                       const taps_strategy &s) {
-    uint64_t b = op.dtype_bytes;
-    for (uint32_t d = 0; d < t.rank && d < TAPS_MAX_RANK; ++d) {
-        const uint32_t a = t.axis[d] & 7u;
-        const uint32_t e = s.pos[a] >= 0 ? (s.log2_deg[a] & 15u) : 0u;
-        b *= (uint64_t)op.axis_len[a] >> e;
-    }
-    return b;
-}
-
+// Bytes of one shard of the output and of every weight: each dimension's
+// length divided by its split degree, times the element size.
 __global__ __launch_bounds__(256) void k_memory_costs(const taps_op *__restrict__ ops,
                                                       uint32_t n_ops,
                                                       const uint64_t *__restrict__ offsets,
                                                       const taps_strategy *__restrict__ strategies,
                                                       uint64_t total, uint64_t *__restrict__ memory) {
     const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const taps_op &op = ops[find_owner(offsets, n_ops, idx)];
-    const taps_strategy s = strategies[idx];
-    uint64_t m = shard_bytes(op, op.out, s);
-    for (uint32_t k = 0; k < op.n_w && k < TAPS_MAX_WEIGHTS; ++k) m += shard_bytes(op, op.w[k], s);
-    memory[idx] = m;
+    const uint64_t x = idx < total ? idx : total - 1u;
+    const op_words op = read_op(ops + wave_owner(offsets, n_ops, x));
+    const taps_strategy s = strategies[x];
+    uint64_t m = 0;
+    op.tensors(false, [&](uint32_t at) {
+        const uint32_t axes = op.axes(at);
+        uint64_t b = op.byte(offsetof(taps_op, dtype_bytes));
+#pragma unroll
+        for (uint32_t a = 0; a < TAPS_MAX_AXES; ++a)
+            if ((axes >> a) & 1u) b *= op.length(a) >> (s.pos[a] >= 0 ? (s.log2_deg[a] & 15u) : 0u);
+        m += b;
+    });
+    if (idx < total) memory[idx] = m;
 }
 
 // Constants of computed edge k.
@@ -326,9 +382,19 @@ __device__ inline void edge_plan_block(uint32_t b, uint32_t setup_blocks, const 
     }
 }
 
-__global__ __launch_bounds__(256) void k_edge_plan(taps_plan_args pa, taps_launch lp,
-                                                   uint32_t setup_blocks) {
-    edge_plan_block(blockIdx.x, setup_blocks, pa, lp);
+// The front of an edge call on given strategies: their descriptors, then the
+// edge plan, in one launch (two take 3 us more on the host and on the GPU).
+__global__ __launch_bounds__(256) void k_edge_front(const taps_strategy *__restrict__ s,
+                                                    uint64_t total, uint32_t describe_blocks,
+                                                    taps_packed *__restrict__ desc,
+                                                    taps_plan_args pa, taps_launch lp,
+                                                    uint32_t setup_blocks) {
+    if (blockIdx.x >= describe_blocks) {
+        edge_plan_block(blockIdx.x - describe_blocks, setup_blocks, pa, lp);
+        return;
+    }
+    const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx < total) desc[idx] = taps_lay_out(strategy_nibbles(s[idx]), 0xFFu, lp.n).packed;
 }
 
 // The front of a single-call build: the strategy chunks, then the edge plan
@@ -679,28 +745,17 @@ __global__ __launch_bounds__(256, 4) void k_edge_costs_h(taps_windows win,
 __global__ __launch_bounds__(256) void k_node_costs_h(const taps_op *__restrict__ ops,
                                                       uint32_t n_ops,
                                                       const uint64_t *__restrict__ offsets,
-                                                      const taps_packed *__restrict__ desc,
+                                                      const taps_strategy *__restrict__ strategies,
                                                       uint64_t total, uint32_t n, taps_hier H,
                                                       taps_table out) {
     const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const taps_op &op = ops[find_owner(offsets, n_ops, idx)];
-    const taps_packed D = desc[idx];
-    const uint32_t full = taps_low_mask(n);
+    const uint64_t x = idx < total ? idx : total - 1u;
+    const taps_op *op = ops + wave_owner(offsets, n_ops, x);
     taps_acch c = {0, 0, 0, 0, 0, 0, 0, 0};
-    auto tensor = [&](const taps_tensor &t) {
-        uint32_t used = 0;
-        uint64_t bytes = op.dtype_bytes;
-        for (uint32_t d = 0; d < t.rank && d < TAPS_MAX_RANK; ++d) {
-            const uint32_t a = t.axis[d] & 7u;
-            used |= taps_axis_levels(D, a);
-            bytes *= (uint64_t)op.axis_len[a];
-        }
-        taps_allreduce_h(c, full & ~used, bytes, H);
-    };
-    tensor(op.out);
-    for (uint32_t k = 0; k < op.n_in && k < TAPS_MAX_INPUTS; ++k) tensor(op.in[k]);
-    for (uint32_t k = 0; k < op.n_w && k < TAPS_MAX_WEIGHTS; ++k) tensor(op.w[k]);
+    strategy_tensors(op, strategies[x], n, [&](uint32_t missing, uint64_t bytes) {
+        taps_allreduce_h(c, missing, bytes, H);
+    });
+    if (idx >= total) return;
     out.t[idx] = (double)c.x0 * H.inv_n_bw[0] + (double)c.x1 * H.inv_n_bw[1] +
                  (double)c.x2 * H.inv_n_bw[2] + (double)c.x3 * H.inv_n_bw[3];
     out.vol[idx] = c.vol;
@@ -793,20 +848,12 @@ inline uint32_t blocks_for(uint64_t n, uint32_t per) { return (uint32_t)((n + pe
 
 }  // namespace
 
-hipError_t taps_launch_describe(const taps_strategy *s, uint64_t total, uint32_t n,
-                                taps_packed *desc, hipStream_t stream) {
-    if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_describe, dim3(blocks_for(total, 256)), dim3(256), 0, stream, s, total, n,
-                       desc);
-    return hipGetLastError();
-}
-
 hipError_t taps_launch_node_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
-                                  const taps_packed *desc, uint64_t total, const taps_launch &lp,
-                                  taps_table out, hipStream_t stream) {
+                                  const taps_strategy *strategies, uint64_t total,
+                                  const taps_launch &lp, taps_table out, hipStream_t stream) {
     if (total == 0) return hipSuccess;
     hipLaunchKernelGGL(k_node_costs, dim3(blocks_for(total, 256)), dim3(256), 0, stream, ops,
-                       n_ops, offsets, desc, total, lp, out);
+                       n_ops, offsets, strategies, total, lp, out);
     return hipGetLastError();
 }
 
@@ -819,13 +866,15 @@ hipError_t taps_launch_memory_costs(const taps_op *ops, uint32_t n_ops, const ui
     return hipGetLastError();
 }
 
-hipError_t taps_launch_edge_setup(const taps_plan_args &pa, const taps_launch &lp,
-                                  hipStream_t stream) {
+hipError_t taps_launch_edge_front(const taps_strategy *strategies, uint64_t total,
+                                  taps_packed *desc, const taps_plan_args &pa,
+                                  const taps_launch &lp, hipStream_t stream) {
     if (pa.n_edges == 0) return hipSuccess;
+    const uint32_t describe_blocks = blocks_for(total, 256);
     const uint32_t setup_blocks = blocks_for(pa.n_edges, 256);
     const uint32_t map_blocks = blocks_for(pa.n_windows, 256);
-    hipLaunchKernelGGL(k_edge_plan, dim3(setup_blocks + map_blocks), dim3(256), 0, stream, pa, lp,
-                       setup_blocks);
+    hipLaunchKernelGGL(k_edge_front, dim3(describe_blocks + setup_blocks + map_blocks), dim3(256),
+                       0, stream, strategies, total, describe_blocks, desc, pa, lp, setup_blocks);
     return hipGetLastError();
 }
 
@@ -889,11 +938,11 @@ hipError_t taps_launch_edge_costs_h(const taps_windows &win, const taps_packed *
 }
 
 hipError_t taps_launch_node_costs_h(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
-                                    const taps_packed *desc, uint64_t total, uint32_t n,
+                                    const taps_strategy *strategies, uint64_t total, uint32_t n,
                                     const taps_hier &H, taps_table out, hipStream_t stream) {
     if (total == 0) return hipSuccess;
     hipLaunchKernelGGL(k_node_costs_h, dim3(blocks_for(total, 256)), dim3(256), 0, stream, ops,
-                       n_ops, offsets, desc, total, n, H, out);
+                       n_ops, offsets, strategies, total, n, H, out);
     return hipGetLastError();
 }
 
