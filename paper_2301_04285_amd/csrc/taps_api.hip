@@ -24,12 +24,15 @@
 #include "taps_internal.h"
 
 // The fixed workspace of taps_build_tables_noalloc: a file-scope device array
-// of TAPS_NOALLOC_SCRATCH_BYTES, one copy on every GPU the library runs on.
+// of TAPS_NOALLOC_SCRATCH_BYTES and the edge kernels' table by tops mask, one
+// copy on every GPU the library runs on.
 // In host code its name is only a stand-in for the symbol; the device address
 // comes from hipGetSymbolAddress, taken once per device with that device
 // current, and only that address is used.  Nothing in it has to start at
 // zero: every kernel of a build writes what it later reads.
-static __device__ __align__(256) char scratch[TAPS_NOALLOC_SCRATCH_BYTES];
+constexpr uint64_t kFixedBytes = TAPS_NOALLOC_SCRATCH_BYTES + TAPS_TOPS_BYTES;
+static_assert(TAPS_TOPS_BYTES % 256 == 0, "carved in steps of 256");
+static __device__ __align__(256) char scratch[kFixedBytes];
 
 namespace {
 
@@ -1064,7 +1067,7 @@ struct fixed_workspace : workspace {
     taps_status open() { return scratch_address(&base); }
     taps_status carve(void **p, size_t bytes) override {
         const size_t size = carve_size(bytes);
-        if (used + size > TAPS_NOALLOC_SCRATCH_BYTES)   // the caller checked the whole need
+        if (used + size > kFixedBytes)   // the caller checked the whole need
             return fail(TAPS_ERR_CAPACITY, "fixed workspace exhausted");
         *p = base + used;
         used += size;
@@ -1174,8 +1177,7 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
         for (const chunk &c : ch) up += align256(c.bytes);
         const size_t need = carve_size(up) + carve_size(sizeof(taps_packed) * total) +
                             carve_size(sizeof(taps_edge_params) * win.n_edges) +
-                            carve_size(sizeof(uint32_t) * win.n_windows) +
-                            carve_size(TAPS_TOPS_BYTES);
+                            carve_size(sizeof(uint32_t) * win.n_windows);
         if (need > TAPS_NOALLOC_SCRATCH_BYTES)
             return fail(TAPS_ERR_CAPACITY,
                         "this build needs %llu bytes of device workspace; the fixed workspace of "
