@@ -258,7 +258,7 @@ taps_status taps_build_tables(const taps_graph *graph, const taps_cluster *clust
  * hipMalloc.  Same arguments, outputs and errors, the same tables bit for
  * bit; the caller still provides every output array.  The call's device
  * workspace (the uploaded graph and plan, strategy descriptors, per-edge
- * constants, row segments) lives in a fixed array of
+ * constants, windows) lives in a fixed array of
  * TAPS_NOALLOC_SCRATCH_BYTES that each GPU the library runs on holds until
  * the process ends; the plan is uploaded with one hipMemcpyAsync from
  * pageable host memory.  No hipMalloc, hipFree, hipHostMalloc or other
@@ -422,14 +422,12 @@ taps_status taps_set_edge_kernel_events(void *before, void *after);
 /* Launch-shape setting, not part of the method: single-table edge launches
  * (taps_edge_costs, taps_edge_costs_shared, taps_edge_costs_backward,
  * taps_edge_costs_topology, taps_build_tables) whose tables hold at least
- * `min_segments` row segments of eight 64-entry tiles run those long segments
- * (each edge's full-length segments first, the rows' remainders last, longest
- * first); smaller launches run segments of at most two tiles in row order (the
- * bandwidth sweep runs aligned 64-entry windows of its tables instead).  Every
- * shape writes the same tables; the setting only moves the size at which a
- * single-table launch changes shape (default 32768; 0 or 1: every launch with at least one segment
- * runs long ones).  Process-wide, read when a
- * launch is planned; returns the previous value.  Never fails. */
+ * `min_segments` windows of the longest kind (sixteen aligned 64-entry tiles
+ * per wavefront; two for several bandwidth points) run those; smaller launches
+ * run shorter windows, by the square root of their tiles.  Every shape writes
+ * the same tables; the setting only moves the size from which a launch is sure
+ * to run the longest windows (default 32768; 0: every launch).  Process-wide,
+ * read when a launch is planned; returns the previous value.  Never fails. */
 uint64_t taps_set_long_segments_min(uint64_t min_segments);
 
 /* Static name of a status code. */

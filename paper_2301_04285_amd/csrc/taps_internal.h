@@ -54,10 +54,11 @@ struct taps_copy_task {
 // 1600 / 1561 / 1565, 145 k tiles 215 / 183 / 169 / 165 / 170 / 197, 64 k tiles
 // 120 / 106 / 101 / 102 / 105 / 119, 16 k tiles 99 / 95 / 94 / 96 / 105 / 131
 // (whole builds).  Several bandwidth points are bound by their stores, which
-// longer windows scatter (four points, 1.5 M tiles: 2633 / 2477 / 2641 / 2745 at
-// T = 2 / 3-4 / 8 / 16).
+// longer windows scatter (four points, 1.5 M tiles, us, T = 1 / 2 / 3 / 4 / 8:
+// cached stores 3012 / 2505 / 2653 / 2700 / 2650, non-temporal ones 2689 / 2695 /
+// 2690 at 2 / 4 / 8).
 #define TAPS_WINDOW_LONG 16
-#define TAPS_WINDOW_SWEEP 4
+#define TAPS_WINDOW_SWEEP 2
 #define TAPS_LONG_SEGS_MIN 32768
 
 hipError_t taps_launch_node_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,

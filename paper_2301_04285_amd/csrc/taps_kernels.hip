@@ -42,12 +42,22 @@ __device__ inline T *at_byte(T *base, uint32_t offset) {
 // from the uniform row bases, j < 2^21 (8 axes on 8 levels give at most
 // 1,047,376 strategies per operator); five non-temporal stores of whole
 // 128-byte lines (nothing is left to merge but at a tile of two edges; cached
-// stores take the 24-layer GPT's build from 80.6 to 82.5 us).
+// stores take the 24-layer GPT's build from 80.6 to 82.5 us).  Cached: ordinary
+// stores, the faster ones into the tables of several bandwidth points.
+template <bool Cached>
 __device__ inline void store_entry(const taps_table &out, uint64_t row, uint32_t j,
                                    const taps_entry_out &o, uint32_t meta) {
     uint32_t o8 = j * 8u, o4 = j * 4u;
     // made here and not kept across the loop as five 64-bit addresses
     __asm__ volatile("" : "+v"(o8), "+v"(o4));
+    if (Cached) {
+        *at_byte(out.t + row, o8) = o.t;
+        *at_byte(out.vol + row, o8) = o.vol;
+        *at_byte(out.intra + row, o8) = o.intra;
+        *at_byte(out.inter + row, o8) = o.inter;
+        *at_byte(out.meta + row, o4) = meta;
+        return;
+    }
     __builtin_nontemporal_store(o.t, at_byte(out.t + row, o8));
     __builtin_nontemporal_store(o.vol, at_byte(out.vol + row, o8));
     __builtin_nontemporal_store(o.intra, at_byte(out.intra + row, o8));
@@ -656,12 +666,14 @@ __global__ __launch_bounds__(256) void k_edge_costs(taps_windows win,
     run_window<2>(win, desc, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
                                  const taps_three<2> &r) {
         const taps_entry_out o = select_entry<Narrow>(r, K, E.scale);
-        store_entry(out, at, lane, o, o.meta);
+        store_entry<false>(out, at, lane, o, o.meta);
     });
 }
 
 // Several bandwidth points: the candidates of each entry are costed once and
-// selected, scaled and stored once per point.
+// selected, scaled and stored once per point.  Bound by the stores, which spread
+// over five arrays per point: short windows keep what is written at a time close
+// together (TAPS_WINDOW_SWEEP).
 template <bool Narrow>
 __global__ __launch_bounds__(256) void k_edge_costs_sweep(taps_windows win,
                                                           const taps_packed *__restrict__ desc,
@@ -675,7 +687,7 @@ __global__ __launch_bounds__(256) void k_edge_costs_sweep(taps_windows win,
                 taps_make_scaler(E.scale.tbytes, sw.inv_n_bintra[k], sw.inv_n_binter[k]);
             const taps_entry_out o = Narrow || K.narrow ? select_entry<true>(r, K, S)
                                                         : select_entry<false>(r, K, S);
-            store_entry(sw.out[k], at, lane, o, o.meta);
+            store_entry<true>(sw.out[k], at, lane, o, o.meta);
         }
     });
 }
@@ -738,7 +750,7 @@ __global__ __launch_bounds__(256, 4) void k_edge_costs_h(taps_windows win,
     run_window<C>(win, desc, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
                                  const taps_three<C> &r) {
         const taps_entry_out o = select_entry_h<C>(r, H, E.scale);
-        store_entry(out, at, lane, o, o.meta);
+        store_entry<false>(out, at, lane, o, o.meta);
     });
 }
 

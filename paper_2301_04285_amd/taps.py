@@ -460,9 +460,9 @@ def taps_edge_costs_sweep(graph, clusters, strategies, op_offsets, out=None, str
 
 
 def taps_set_long_segments_min(min_segments: int) -> int:
-    """Single-table edge launches with at least ``min_segments`` row segments
-    run long (eight-tile) segments, remainders last; returns the previous
-    threshold.  The tables are the same either way."""
+    """Edge launches of at least ``min_segments`` windows of the longest kind run
+    those (smaller ones run shorter windows); returns the previous threshold.
+    The tables are the same either way."""
     return int(load().taps_set_long_segments_min(int(min_segments)))
 
 
