@@ -184,9 +184,10 @@ __host__ __device__ inline taps_b8 taps_states(const taps_b8 &e, uint32_t g, uin
 // order that two masks turn into a byte vector: index k < 4 in the low nibble
 // of byte k, k >= 4 in the high nibble of byte k - 4.
 struct taps_packed {
-    uint32_t owner;   // per level: the op axis that owns it (0 above the last level)
+    uint32_t owner;   // per level: the op axis that owns it (0x0C: none, the degrees multiply to less
+                      // than 2^n; 0 above the last level)
     uint32_t place;   // per level: its distance from the top of its axis's run, + 8 when it is the
-                      // run's lowest level (15 above the last level)
+                      // run's lowest level (7: no owner; 15 above the last level)
     taps_b8 runs;     // per op axis: top level + 1 of its run, and << 4 the run's width (0: not split)
 };
 
@@ -244,8 +245,12 @@ __host__ __device__ inline taps_runs taps_lay_out(const taps_nibbles &S, uint32_
     }
     R.cuts &= ~1u;
     const uint32_t above = n < 8u ? ~0u << (4u * n) : 0u;
-    R.packed.owner = taps_deal(owner & ~above);
-    R.packed.place = taps_deal(place | above);
+    // levels past the last run, if the degrees multiply to less than 2^n: no axis
+    // holds them (the tensors are replicated along them), and no cut lies below
+    const uint32_t covered = (first >> 28) + (by_pos >> 28);
+    const uint32_t idle = covered < n ? ~above & (~0u << (4u * covered)) : 0u;
+    R.packed.owner = taps_deal((owner & ~above) | (0xCCCCCCCCu & idle));
+    R.packed.place = taps_deal(place | above | (0x77777777u & idle));
     R.packed.runs = {taps_spread(end & 0xFFFFu) | (taps_spread(R.width & 0xFFFFu) << 4),
                      taps_spread(end >> 16) | (taps_spread(R.width >> 16) << 4)};
     return R;
@@ -411,8 +416,8 @@ __host__ __device__ inline taps_top_row taps_make_top_row(const taps_top_table &
 struct taps_source {
     taps_b8 axis;     // per level: the target's axis of its tensor dimension (0x0C: none)
     taps_b8 from;     // per level: 7F - its position bit in the dimension (taps_packed::place
-                      // without the flag)
-    taps_b8 below;    // per level: 7E - that bit, at most 76 for a run's lowest level
+                      // without the flag), 77 without an owner
+    taps_b8 below;    // per level: 7E - that bit, at most 76 for a run's lowest level (77: no owner)
     taps_b8 top;      // per target axis: 7F + end of the run on its dimension
     taps_b8 room;     // per target axis: 80 - width of that run
     taps_b8 held;     // FF at the levels the tensor's map uses
@@ -434,7 +439,9 @@ __host__ __device__ inline taps_source taps_make_source(const taps_packed &p, co
     P.axis = taps_map(taps_unnibble(to.axis_of), dim);
     const taps_b8 flagged = taps_unnibble(p.place);
     const taps_b8 place = flagged & taps_all(0x07070707u);
-    P.from = taps_all(0x7F7F7F7Fu) - place;
+    // 77 at a level without an owner: past every run of the target's side
+    const taps_b8 idle = {(owner.lo >> 3) & 0x01010101u, (owner.hi >> 3) & 0x01010101u};
+    P.from = taps_all(0x7F7F7F7Fu) - place - idle;
     P.below = taps_all(0x7E7E7E7Eu) - flagged;
     const taps_b8 runs = taps_map(p.runs, taps_unnibble(side.axis_of));
     const taps_b8 width = {(runs.lo >> 4) & 0x0F0F0F0Fu, (runs.hi >> 4) & 0x0F0F0F0Fu};
@@ -509,7 +516,9 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     // prev[c]: the source level at the position that target level c goes to;
     // next[p]: the target level that goes to source level p's position.  The
     // byte differences keep bit 7 set; place + 80 - width has it set when the
-    // position lies past the other side's run (7F - place + width, clear).
+    // position lies past the other side's run (7F - place + width, clear).  A
+    // target level without an owner reads 0 for top and room: its difference
+    // borrows, from levels above it alone, and is 78 or 79 below bit 7, no level.
     // below_*: the same for the cuts inside what both sides split (all levels
     // there but the lowest).
     constexpr uint32_t kPast = (TAPS_A & TAPS_B) | ((0xFFu ^ TAPS_A) & TAPS_C);

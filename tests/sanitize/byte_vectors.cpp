@@ -2,8 +2,9 @@
 // the host) against the step-by-step form in csrc/taps_device.h: unification,
 // Algorithm 1, "rearrange" and "remove" of random strategy pairs of random
 // operators (1-8 axes, tensors of rank 0-8) on 1-256 devices, for 1-4 link
-// classes at random boundaries, every field of every candidate; and of every
-// candidate rank of every set of partitionable axes the level runs, cuts and
+// classes at random boundaries, every field of every candidate, also where the
+// degrees multiply to less than the devices (the tensors are replicated along
+// the levels left); and of every candidate rank of every set of partitionable axes the level runs, cuts and
 // packed descriptor against their definition.  Prints "N compared, 0
 // mismatches".
 #include <cstdio>
@@ -96,8 +97,27 @@ uint32_t pick_axes(uint32_t of, uint32_t rank) {
     return r;
 }
 
+// A random strategy over the axes of `mask` on 2^n devices, or (partial) one whose
+// degrees may multiply to less.
+taps_nibbles draw_strategy(uint32_t mask, uint32_t n, bool partial) {
+    uint32_t k = n;
+    if (partial)
+        do k = rnd() % (n + 1u);
+        while (!candidates(mask, k));
+    return taps_unrank(mask, k, rnd() % candidates(mask, k), kW.v);
+}
+
+// Whether the levels that S's runs cover end at a boundary of the unified axes.
+// (Elsewhere an axis lies partly in a run and partly above it, and the step-by-step
+// form slices into levels that are no axis's top.)
+bool ends_at_a_boundary(const taps_nibbles &S, uint32_t tops) {
+    uint32_t covered = 0;
+    for (uint32_t a = 0; a < 8u; ++a) covered += taps_nib(S.expo, a);
+    return covered == 0u || ((tops >> (covered - 1u)) & 1u);
+}
+
 template <uint32_t C>
-void entries(uint64_t budget) {
+void entries(uint64_t budget, bool partial) {
     const taps_width_table widths = taps_make_widths();
     const taps_a2a_table a2a = taps_make_a2a();
     const taps_expand_table ex = taps_make_expand();
@@ -146,12 +166,12 @@ void entries(uint64_t budget) {
         const uint32_t na = 1u + rnd() % 8u, nb = 1u + rnd() % 8u;
         const uint32_t pm = rnd() & taps_low_mask(na), qm = rnd() & taps_low_mask(nb);
         const uint32_t tp = candidates(pm, n), tq = candidates(qm, n);
-        if (!tp || !tq) continue;
+        if (!partial && (!tp || !tq)) continue;
         const uint32_t rank = rnd() % ((na < nb ? na : nb) + 1u);
         const uint32_t pax = pick_axes(na, rank), qax = pick_axes(nb, rank);
         const taps_side from = taps_make_side(pax, rank), to = taps_make_side(qax, rank);
         for (uint32_t i = 0; i < 8u; ++i) {
-            const taps_nibbles Sp = taps_unrank(pm, n, rnd() % tp, kW.v);
+            const taps_nibbles Sp = draw_strategy(pm, n, partial);
             taps_row P;
             taps_make_row(P, describe(Sp), pax, rank, n, lam);
             taps_fill_rank_table(P, rank_table, 0, 1);
@@ -163,12 +183,13 @@ void entries(uint64_t budget) {
             const taps_source S = taps_make_source<C>(taps_lay_out(Sp, pm, n).packed, from, to,
                                                          rank, m);
             for (uint32_t j = 0; j < 24u; ++j) {
-                const taps_nibbles Sq = taps_unrank(qm, n, rnd() % tq, kW.v);
+                const taps_nibbles Sq = draw_strategy(qm, n, partial);
                 taps_col Q;
                 std::memset(&Q, 0, sizeof(Q));
                 taps_make_col(Q, describe(Sq), qax, rank);
                 taps_lv L;
                 taps_unify(P, Q, L);
+                if (!ends_at_a_boundary(Sp, L.tp) || !ends_at_a_boundary(Sq, L.tp)) continue;
                 const taps_start st = taps_begin(P, L);
                 taps_fach want[3];
                 const taps_hier_model_t<C> M{&H, 0, 0, false, cls_rows, expand};
@@ -195,7 +216,7 @@ void entries(uint64_t budget) {
                         ok = ok && two[k].vol == got.c[k].vol && two[k].intra == got.c[k].in &&
                              two[k].inter == got.c[k].link[0] && two[k].ct == got.c[k].ct;
                 }
-                check(ok, "entry", n, C);
+                check(ok, partial ? "entry of partial strategies" : "entry", n, C);
             }
         }
     }
@@ -205,10 +226,12 @@ void entries(uint64_t budget) {
 
 int main() {
     layouts();
-    entries<1>(20000);
-    entries<2>(150000);
-    entries<3>(100000);
-    entries<4>(100000);
+    for (const bool partial : {false, true}) {
+        entries<1>(20000, partial);
+        entries<2>(150000, partial);
+        entries<3>(100000, partial);
+        entries<4>(100000, partial);
+    }
     printf("%llu compared, %llu mismatches\n", (unsigned long long)compared,
            (unsigned long long)bad);
     return bad != 0;

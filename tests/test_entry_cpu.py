@@ -27,7 +27,7 @@ def test_byte_vector_entries_equal_the_steps(tmp_path):
                        env=dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0"))
     assert p.returncode == 0, p.stdout + p.stderr
     assert "runtime error" not in p.stderr and "Sanitizer" not in p.stderr, p.stderr
-    assert " 0 mismatches" in p.stdout and int(p.stdout.split()[0]) > 370_000, p.stdout
+    assert " 0 mismatches" in p.stdout and int(p.stdout.split()[0]) > 740_000, p.stdout
 
 
 @pytest.mark.parametrize("nd", range(1, 64))

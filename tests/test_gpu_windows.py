@@ -92,3 +92,48 @@ def test_shared_tables_are_copied_whole(T, devices, axes, ops, shift):  # noqa: 
     for k, v in wide.items():
         assert torch.equal(got.edge[k].view(v.dtype), want.edge[k].view(v.dtype)), k
         assert bool((v[:shift] == -7).all()) and bool((v[shift + n:] == -7).all()), k
+
+
+@pytest.mark.parametrize("devices", [4, 16, 256])
+def test_strategies_that_leave_levels_unused(T, devices):  # noqa: F811
+    """Degrees that multiply to less than the devices: the tensors are replicated along the
+    levels left, as when an axis that no edge tensor has holds the outermost of them.  Every
+    entry whose runs end where the other side has a boundary (the rest has no reference)."""
+    import numpy as np
+    import torch
+    g = W.Graph()
+    a, b = g.add(W.matmul("a", 256, 256, 256, 2)), g.add(W.matmul("b", 256, 256, 256, 2))
+    g.connect(a, b, 0)
+    n, per_node = devices.bit_length() - 1, max(2, devices // 8)
+    cl = W.Cluster(devices // per_node, per_node, 600 * W.GB, 100 * W.GB)
+    say(f"[gpu] unused levels on {devices}")
+    offs, full = T.taps_enumerate_strategies(g, cl)
+    deg, pos = T.strategies_to_numpy(full)
+    ends, cuts = [], []
+    for s in range(len(full)):
+        free = 1 if s < offs[1] else 2   # a's inner axis, b's output columns
+        order = sorted((int(pos[s, x]), int(deg[s, x]), x) for x in range(3) if deg[s, x])
+        starts = [sum(w for _, w, _ in order[:k]) for k in range(1, len(order))]
+        if order and order[-1][2] == free:   # outermost: left out of the partial strategy
+            deg[s, free], pos[s, free] = 0, -1
+            starts = starts[:-1]
+        ends.append(sum(int(deg[s, x]) for x in range(3)))
+        cuts.append(set(starts) | {0, n})
+    partial = torch.from_numpy(np.concatenate([deg, pos.view(np.uint8)], 1)).to(full.device)
+    na = int(offs[1])
+    clean = np.array([[ends[i] in cuts[j] and ends[j] in cuts[i]
+                       for j in range(na, len(full))] for i in range(na)])
+    left = np.array([[min(ends[i], ends[j]) < n for j in range(na, len(full))] for i in range(na)])
+    assert int((clean & left).sum()) > 2
+    topo = W.Topology((per_node, devices // 2, devices), (600 * W.GB, 100 * W.GB, 25 * W.GB))
+    points = [cl, W.Cluster(cl.nodes, per_node, 600 * W.GB, 25 * W.GB)]
+    for what, call, keep in (
+            ("edges", lambda s: T.taps_edge_costs(g, cl, s, offs)[1], clean),
+            ("backward", lambda s: T.taps_edge_costs(g, cl, s, offs, backward=True)[1], clean.T),
+            ("sweep", lambda s: T.taps_edge_costs_sweep(g, points, s, offs)[1][1], clean),
+            ("classes", lambda s: T.taps_edge_costs_topology(g, topo, s, offs)[1], clean)):
+        want, got = call(full), call(partial)
+        mask = torch.from_numpy(keep.ravel().copy()).to(full.device)
+        for k, v in want.items():
+            signed = torch.int32 if k == "meta" else torch.int64
+            assert torch.equal(got[k].view(signed)[mask], v.view(signed)[mask]), (what, k)
