@@ -556,6 +556,7 @@ void plan_copies(const std::vector<uint64_t> &eoff, const std::vector<uint32_t> 
 struct window_plan {
     std::vector<uint32_t> edges;
     std::vector<uint64_t> starts;
+    std::vector<uint32_t> crowded;   // windows with entries of more than TAPS_CROWDED tables
     uint32_t n_edges = 0, tiles = 1;
     uint64_t total = 0, n_windows = 0;
 };
@@ -591,6 +592,16 @@ window_plan plan_windows(const std::vector<uint64_t> &eoff, const std::vector<ui
         p.tiles = (uint32_t)t;
     }
     p.n_windows = (tiles + p.tiles - 1) / p.tiles;
+    const uint64_t *starts = shared ? p.starts.data() : eoff.data();
+    const uint64_t span = (uint64_t)p.tiles * TAPS_TILE_COLS;
+    const uint32_t most_edges = TAPS_CROWDED(p.tiles);
+    for (uint32_t e = 0; p.n_edges - e > most_edges; ++e) {
+        if (starts[e + most_edges] - starts[e + 1] >= span) continue;
+        // the last window that begins in table e, if one does: only it can reach so far
+        const uint64_t w = (starts[e + 1] - 1) / span;
+        if (w * span >= starts[e] && starts[e + most_edges] < (w + 1) * span)
+            p.crowded.push_back((uint32_t)w);
+    }
     return p;
 }
 
@@ -599,10 +610,11 @@ window_plan plan_windows(const std::vector<uint64_t> &eoff, const std::vector<ui
 // the plan kernel fills.
 taps_windows device_windows(const window_plan &p, const taps_edge_params *params,
                             const uint32_t *window_edge, const taps_top_row *tops, void *dev,
-                            const chunk &offsets, const chunk &starts,
+                            const chunk &offsets, const chunk &starts, const chunk &crowded,
                             const taps_levels_model &model) {
     return {params, at<uint64_t>(dev, p.edges.empty() ? offsets : starts), window_edge, tops,
-            p.n_windows, p.total, p.tiles, 0u, model};
+            at<uint32_t>(dev, crowded), p.n_windows, p.total, p.tiles, p.n_edges,
+            (uint32_t)p.crowded.size(), 0u, model};
 }
 
 taps_plan_args device_plan(const window_plan &p, const taps_windows &w, void *dev, const chunk &ops,
@@ -612,7 +624,8 @@ taps_plan_args device_plan(const window_plan &p, const taps_windows &w, void *de
     return {at<taps_op>(dev, ops), at<taps_edge>(dev, edges), at<uint64_t>(dev, op_offsets),
             at<uint64_t>(dev, edge_offsets),
             p.edges.empty() ? nullptr : at<uint32_t>(dev, computed), w.starts, params, window_edge,
-            tops, w.n_windows, p.n_edges, p.tiles * TAPS_TILE_COLS, reverse ? 1u : 0u, 0u, w.model};
+            tops, w.n_windows, p.n_edges, p.tiles * TAPS_TILE_COLS, reverse ? 1u : 0u,
+            p.crowded.empty() ? 0u : TAPS_CROWDED(p.tiles), w.model};
 }
 
 // The levels of a hierarchy's classes.
@@ -697,7 +710,8 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
                           {win.edges.data(), sizeof(uint32_t) * win.edges.size(), 0},
                           {copies.data(), sizeof(taps_copy_task) * copies.size(), 0},
                           {dst_list.data(), sizeof(uint64_t) * dst_list.size(), 0},
-                          {win.starts.data(), sizeof(uint64_t) * win.starts.size(), 0}};
+                          {win.starts.data(), sizeof(uint64_t) * win.starts.size(), 0},
+                          {win.crowded.data(), sizeof(uint32_t) * win.crowded.size(), 0}};
     void *dev = nullptr;
     if ((st = upload(sc, ch, &dev)) != TAPS_OK) return st;
     taps_packed *d_desc = nullptr;
@@ -709,7 +723,7 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
         return st;
     if ((st = sc.alloc((void **)&d_win, sizeof(uint32_t) * win.n_windows)) != TAPS_OK) return st;
     if ((st = sc.alloc((void **)&d_tops, TAPS_TOPS_BYTES)) != TAPS_OK) return st;
-    const taps_windows tw = device_windows(win, d_params, d_win, d_tops, dev, ch[3], ch[7],
+    const taps_windows tw = device_windows(win, d_params, d_win, d_tops, dev, ch[3], ch[7], ch[8],
                                            hier ? hier_levels(*hier, lp.n) : taps_make_levels(lp.n, lp.lam));
     const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[4], d_params,
                                           d_win, d_tops, reverse);
@@ -1171,7 +1185,8 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
                           {copies.data(), sizeof(taps_copy_task) * copies.size(), 0},
                           {dst_list.data(), sizeof(uint64_t) * dst_list.size(), 0},
                           {bchunks.data(), sizeof(taps_build_chunk) * bchunks.size(), 0},
-                          {win.starts.data(), sizeof(uint64_t) * win.starts.size(), 0}};
+                          {win.starts.data(), sizeof(uint64_t) * win.starts.size(), 0},
+                          {win.crowded.data(), sizeof(uint32_t) * win.crowded.size(), 0}};
     if (fixed) {   // the whole need, checked on the host before any HIP call
         size_t up = 0;
         for (const chunk &c : ch) up += align256(c.bytes);
@@ -1208,7 +1223,7 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
     if ((st = ws->carve((void **)&d_tops, TAPS_TOPS_BYTES)) != TAPS_OK) return st;
     // the strategies, and the edge plan when there are edge entries, in one launch
     const bool edges_on = eoff[n_edges] > 0;
-    const taps_windows tw = device_windows(win, d_params, d_win, d_tops, dev, ch[3], ch[8],
+    const taps_windows tw = device_windows(win, d_params, d_win, d_tops, dev, ch[3], ch[8], ch[9],
                                            taps_make_levels(lp.n, lp.lam));
     const taps_plan_args pa = device_plan(win, tw, dev, ch[0], ch[1], ch[2], ch[3], ch[4], d_params,
                                           d_win, d_tops, false);

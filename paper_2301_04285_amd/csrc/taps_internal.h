@@ -60,13 +60,20 @@ struct taps_copy_task {
 #define TAPS_WINDOW_LONG 16
 #define TAPS_WINDOW_SWEEP 2
 #define TAPS_LONG_SEGS_MIN 32768
+// A wavefront takes the tables that meet in its window one after the other,
+// about 1.6 us each.  A window that holds entries of more than TAPS_CROWDED(T)
+// tables goes to the k_*_crowded kernels instead, a lane its own table (calls,
+// us, as windows / crowded: 255 tables of one entry 129 / 23, 1,000 tables of
+// 441 entries and of one in turns of a hundred 206 / 58, 199 of 9 entries, eight
+// to a tile and not crowded, 31).
+#define TAPS_CROWDED(tiles) (2u * (tiles) + 6u)
 
 hipError_t taps_launch_node_costs(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,
                                   const taps_strategy *strategies, uint64_t total,
                                   const taps_launch &lp, taps_table out, hipStream_t stream);
 // The edge plan of a launch (device arrays): the constants of the n_edges
 // computed edges (edge computed[k], or k without that list) into params, and
-// the edge that each window starts in.  starts: n_edges + 1 first entries of
+// the edge that each window starts in (~0: a crowded one).  starts: n_edges + 1 first entries of
 // the computed tables laid end to end; window: entries per window; reverse:
 // the backward tables (source side = the consumer's input map).
 struct taps_plan_args {
@@ -80,7 +87,8 @@ struct taps_plan_args {
     uint32_t *window_edge;
     taps_top_row *tops;          // TAPS_TOPS_BYTES: 256 rows, then their `low` bytes
     uint64_t n_windows;
-    uint32_t n_edges, window, reverse, pad;
+    uint32_t n_edges, window, reverse;
+    uint32_t crowded;            // tables from which on a window is (0: no window is)
     taps_levels_model model;
 };
 #define TAPS_TOPS_BYTES ((sizeof(taps_top_row) + sizeof(taps_b8)) * 256)
@@ -94,8 +102,10 @@ struct taps_windows {
     const uint64_t *starts;
     const uint32_t *window_edge;
     const taps_top_row *tops;
+    const uint32_t *crowded;     // the crowded windows
     uint64_t n_windows, total;   // total: computed entries
-    uint32_t tiles, pad;         // tiles per window
+    uint32_t tiles;              // tiles per window
+    uint32_t n_edges, n_crowded, pad;
     taps_levels_model model;
 };
 hipError_t taps_launch_edge_costs(const taps_windows &win, const taps_packed *desc,

@@ -16,6 +16,7 @@
 //   k_edge_costs_sweep  the same at several bandwidth points: the candidates
 //                 once per entry, one selection and store per point
 //   k_edge_costs_h  the same under a hierarchy of link classes
+//   k_*_crowded   the windows in which many small tables meet, a lane its own
 //   k_copy_tables shared tables: one workgroup per chunk of a computed
 //                 table, written to every table that shares it
 //   k_pull        a call's upload, read from pinned host memory
@@ -369,9 +370,13 @@ __device__ inline void edge_setup_one(uint32_t k, const taps_plan_args &pa, cons
     pa.params[k] = p;
 }
 
-// The computed edge that holds the first entry of window w.
+// The computed edge that holds the first entry of window w, ~0 for a crowded window.
 __device__ inline void window_one(uint64_t w, const taps_plan_args &pa) {
-    pa.window_edge[w] = find_owner(pa.starts, pa.n_edges, w * pa.window);
+    uint32_t e = find_owner(pa.starts, pa.n_edges, w * pa.window);
+    if (pa.crowded && pa.n_edges - e > pa.crowded &&   // uniform, mostly 0
+        pa.starts[e + pa.crowded] < (w + 1u) * pa.window)
+        e = ~0u;
+    pa.window_edge[w] = e;
 }
 
 // The edge plan in one launch: blocks [0, setup_blocks) set up the edges (the
@@ -498,8 +503,18 @@ __device__ inline taps_source read_row(const row_cache &cache, uint32_t r) {
     return P;
 }
 
-// Emit(E, v, r): stores the entry of an edge with constants E at entry v of
-// the computed tables, from its candidates r.
+// The table by tops mask, into LDS (a whole workgroup).
+template <uint32_t C>
+__device__ inline void load_tops(const taps_windows &win, taps_top_row *tops, taps_b8 *low) {
+    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) {
+        tops[x] = win.tops[x];
+        if (C > 2) low[x] = ((const taps_b8 *)(win.tops + 256))[x];
+    }
+    __syncthreads();
+}
+
+// Emit(E, at, lane, r): stores the entry at + lane of an edge with constants E
+// from its candidates r.
 template <uint32_t C, typename Emit>
 __device__ inline void run_window(const taps_windows &win, const taps_packed *__restrict__ desc,
                                   const Emit &emit) {
@@ -507,11 +522,7 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
     __shared__ taps_b8 low[C > 2 ? 256 : 1];
     __shared__ row_cache rows[kWindowsPerBlock];
     const taps_levels_model &m = win.model;
-    for (uint32_t x = threadIdx.x; x < 256u; x += blockDim.x) {
-        tops[x] = win.tops[x];
-        if (C > 2) low[x] = ((const taps_b8 *)(win.tops + 256))[x];
-    }
-    __syncthreads();
+    load_tops<C>(win, tops, low);
     const uint32_t lane = threadIdx.x % kWave;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint64_t w = (uint64_t)blockIdx.x * kWindowsPerBlock + wave;
@@ -521,6 +532,7 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
     // places in the window, 32 bits each (a scalar compare; 64 bits take vector ones)
     const uint32_t size = (uint32_t)(win.total - begin < span ? win.total - begin : span);
     uint32_t e = win.window_edge[w];
+    if (e == ~0u) return;   // crowded
     taps_edge_params E = win.params[e];
     taps_b8 in_tensor = taps_in_tensor(E.to, E.rank);
     uint64_t e_start = uniform(win.starts[e]), e_end = uniform(win.starts[e + 1u]);
@@ -605,6 +617,33 @@ __device__ inline void run_window(const taps_windows &win, const taps_packed *__
     }
 }
 
+// A crowded window: one wavefront per tile, a lane's edge, row and column its
+// own.  Bound by latency: the chain from the starts over the edge's constants
+// to the descriptors, and the candidates once.
+template <uint32_t C, typename Emit>
+__device__ inline void run_crowded(const taps_windows &win, const taps_packed *__restrict__ desc,
+                                   const Emit &emit) {
+    __shared__ taps_top_row tops[256];
+    __shared__ taps_b8 low[C > 2 ? 256 : 1];
+    load_tops<C>(win, tops, low);
+    const uint32_t lane = threadIdx.x % kWave;
+    const uint64_t k = (uint64_t)blockIdx.x * kWindowsPerBlock + threadIdx.x / kWave;
+    if (k >= (uint64_t)win.n_crowded * win.tiles) return;
+    const uint64_t tile = (uint64_t)win.crowded[k / win.tiles] * win.tiles + k % win.tiles;
+    if (tile * kWave >= win.total) return;   // the last window may be shorter
+    const uint64_t at = tile * kWave + lane, x = at < win.total ? at : win.total - 1u;
+    const uint32_t e = wave_owner(win.starts, win.n_edges, x);
+    const taps_edge_params E = win.params[e];
+    const uint64_t local = x - win.starts[e];   // below ns * nd
+    const uint32_t i = (uint32_t)(local / E.nd), j = (uint32_t)(local % E.nd);
+    const taps_packed q = desc[E.dst_base + j];
+    const taps_source P =
+        taps_make_source<C>(desc[E.src_base + i], E.from, E.to, E.rank, win.model);
+    taps_three<C> r;
+    taps_three_candidates<C>(P, q, taps_in_tensor(E.to, E.rank), win.model, tops, low, r);
+    if (at < win.total) emit(E, E.out_offset + local, 0u, r);
+}
+
 // Selection among the candidates under one bandwidth point's keys (ties go to
 // the earlier candidate), scaled.  Narrow: 64-bit keys.
 template <bool Narrow>
@@ -659,15 +698,30 @@ __device__ inline taps_entry_out select_entry(const taps_three<2> &r, const taps
 
 // Narrow: both reduced bandwidths are below 2^32 (64-bit keys).
 template <bool Narrow>
+struct emit_one {
+    const taps_keys &K;
+    const taps_table &out;
+    __device__ void operator()(const taps_edge_params &E, uint64_t at, uint32_t lane,
+                               const taps_three<2> &r) const {
+        const taps_entry_out o = select_entry<Narrow>(r, K, E.scale);
+        store_entry<false>(out, at, lane, o, o.meta);
+    }
+};
+
+template <bool Narrow>
 __global__ __launch_bounds__(256) void k_edge_costs(taps_windows win,
                                                     const taps_packed *__restrict__ desc,
                                                     taps_launch lp, taps_table out) {
     const taps_keys K = {lp.b_inter_red, lp.b_intra_red, Narrow};
-    run_window<2>(win, desc, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
-                                 const taps_three<2> &r) {
-        const taps_entry_out o = select_entry<Narrow>(r, K, E.scale);
-        store_entry<false>(out, at, lane, o, o.meta);
-    });
+    run_window<2>(win, desc, emit_one<Narrow>{K, out});
+}
+
+template <bool Narrow>
+__global__ __launch_bounds__(256) void k_edge_costs_crowded(taps_windows win,
+                                                            const taps_packed *__restrict__ desc,
+                                                            taps_launch lp, taps_table out) {
+    const taps_keys K = {lp.b_inter_red, lp.b_intra_red, Narrow};
+    run_crowded<2>(win, desc, emit_one<Narrow>{K, out});
 }
 
 // Several bandwidth points: the candidates of each entry are costed once and
@@ -675,11 +729,10 @@ __global__ __launch_bounds__(256) void k_edge_costs(taps_windows win,
 // over five arrays per point: short windows keep what is written at a time close
 // together (TAPS_WINDOW_SWEEP).
 template <bool Narrow>
-__global__ __launch_bounds__(256) void k_edge_costs_sweep(taps_windows win,
-                                                          const taps_packed *__restrict__ desc,
-                                                          taps_sweep sw) {
-    run_window<2>(win, desc, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
-                                 const taps_three<2> &r) {
+struct emit_sweep {
+    const taps_sweep &sw;
+    __device__ void operator()(const taps_edge_params &E, uint64_t at, uint32_t lane,
+                               const taps_three<2> &r) const {
         for (uint32_t k = 0; k < sw.count; ++k) {
             // Narrow: 64-bit keys at every point
             const taps_keys K = {sw.b_inter_red[k], sw.b_intra_red[k], Narrow || sw.narrow[k] != 0};
@@ -689,7 +742,20 @@ __global__ __launch_bounds__(256) void k_edge_costs_sweep(taps_windows win,
                                                         : select_entry<false>(r, K, S);
             store_entry<true>(sw.out[k], at, lane, o, o.meta);
         }
-    });
+    }
+};
+
+template <bool Narrow>
+__global__ __launch_bounds__(256) void k_edge_costs_sweep(taps_windows win,
+                                                          const taps_packed *__restrict__ desc,
+                                                          taps_sweep sw) {
+    run_window<2>(win, desc, emit_sweep<Narrow>{sw});
+}
+
+template <bool Narrow>
+__global__ __launch_bounds__(256) void k_edge_costs_sweep_crowded(
+    taps_windows win, const taps_packed *__restrict__ desc, taps_sweep sw) {
+    run_crowded<2>(win, desc, emit_sweep<Narrow>{sw});
 }
 
 // Link-class hierarchies: each entry selected by the exact key over the classes
@@ -741,17 +807,31 @@ __device__ inline taps_entry_out select_entry_h(const taps_three<C> &r, const ta
     return o;
 }
 
+template <uint32_t C>
+struct emit_classes {
+    const taps_hier &H;
+    const taps_table &out;
+    __device__ void operator()(const taps_edge_params &E, uint64_t at, uint32_t lane,
+                               const taps_three<C> &r) const {
+        const taps_entry_out o = select_entry_h<C>(r, H, E.scale);
+        store_entry<false>(out, at, lane, o, o.meta);
+    }
+};
+
 // At least 4 wavefronts per SIMD: three classes take 140 registers without the
 // bound (3 wavefronts: 2220 us on the 96-layer GPT's build against 2180).
 template <uint32_t C>
 __global__ __launch_bounds__(256, 4) void k_edge_costs_h(taps_windows win,
                                                       const taps_packed *__restrict__ desc,
                                                       taps_hier H, taps_table out) {
-    run_window<C>(win, desc, [&](const taps_edge_params &E, uint64_t at, uint32_t lane,
-                                 const taps_three<C> &r) {
-        const taps_entry_out o = select_entry_h<C>(r, H, E.scale);
-        store_entry<false>(out, at, lane, o, o.meta);
-    });
+    run_window<C>(win, desc, emit_classes<C>{H, out});
+}
+
+template <uint32_t C>
+__global__ __launch_bounds__(256) void k_edge_costs_h_crowded(taps_windows win,
+                                                              const taps_packed *__restrict__ desc,
+                                                              taps_hier H, taps_table out) {
+    run_crowded<C>(win, desc, emit_classes<C>{H, out});
 }
 
 __global__ __launch_bounds__(256) void k_node_costs_h(const taps_op *__restrict__ ops,
@@ -890,28 +970,42 @@ hipError_t taps_launch_edge_front(const taps_strategy *strategies, uint64_t tota
     return hipGetLastError();
 }
 
+namespace {
+
+// The window kernel over the windows, unless all are crowded, then the other one over the
+// tiles of those.
+template <typename Kernel, typename... Args>
+hipError_t launch_windows(const taps_windows &win, hipStream_t stream, Kernel windows,
+                          Kernel crowded, Args... args) {
+    const dim3 block(kWave * kWindowsPerBlock);
+    if (win.n_windows > win.n_crowded)
+        hipLaunchKernelGGL(windows, dim3(blocks_for(win.n_windows, kWindowsPerBlock)), block, 0,
+                           stream, win, args...);
+    if (win.n_crowded)
+        hipLaunchKernelGGL(crowded,
+                           dim3(blocks_for((uint64_t)win.n_crowded * win.tiles, kWindowsPerBlock)),
+                           block, 0, stream, win, args...);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t taps_launch_edge_costs(const taps_windows &win, const taps_packed *desc,
                                   const taps_launch &lp, taps_table out, hipStream_t stream) {
-    if (win.n_windows == 0) return hipSuccess;
-    const dim3 grid(blocks_for(win.n_windows, kWindowsPerBlock)), block(kWave * kWindowsPerBlock);
-    if (lp.narrow)
-        hipLaunchKernelGGL(k_edge_costs<true>, grid, block, 0, stream, win, desc, lp, out);
-    else
-        hipLaunchKernelGGL(k_edge_costs<false>, grid, block, 0, stream, win, desc, lp, out);
-    return hipGetLastError();
+    return lp.narrow ? launch_windows(win, stream, k_edge_costs<true>, k_edge_costs_crowded<true>,
+                                      desc, lp, out)
+                     : launch_windows(win, stream, k_edge_costs<false>, k_edge_costs_crowded<false>,
+                                      desc, lp, out);
 }
 
 hipError_t taps_launch_edge_costs_sweep(const taps_windows &win, const taps_packed *desc,
                                         const taps_sweep &sw, hipStream_t stream) {
-    if (win.n_windows == 0) return hipSuccess;
-    const dim3 grid(blocks_for(win.n_windows, kWindowsPerBlock)), block(kWave * kWindowsPerBlock);
     bool narrow = true;
     for (uint32_t k = 0; k < sw.count; ++k) narrow = narrow && sw.narrow[k] != 0;
-    if (narrow)
-        hipLaunchKernelGGL(k_edge_costs_sweep<true>, grid, block, 0, stream, win, desc, sw);
-    else
-        hipLaunchKernelGGL(k_edge_costs_sweep<false>, grid, block, 0, stream, win, desc, sw);
-    return hipGetLastError();
+    return narrow ? launch_windows(win, stream, k_edge_costs_sweep<true>,
+                                   k_edge_costs_sweep_crowded<true>, desc, sw)
+                  : launch_windows(win, stream, k_edge_costs_sweep<false>,
+                                   k_edge_costs_sweep_crowded<false>, desc, sw);
 }
 
 hipError_t taps_launch_build_strategies(const taps_op *ops, const taps_build_chunk *chunks,
@@ -938,15 +1032,15 @@ hipError_t taps_launch_build_front(const taps_build_chunk *chunks, uint32_t n_ch
 
 hipError_t taps_launch_edge_costs_h(const taps_windows &win, const taps_packed *desc,
                                     const taps_hier &H, taps_table out, hipStream_t stream) {
-    if (win.n_windows == 0) return hipSuccess;
-    const dim3 grid(blocks_for(win.n_windows, kWindowsPerBlock)), block(kWave * kWindowsPerBlock);
+    auto launch = [&](auto windows, auto crowded) {
+        return launch_windows(win, stream, windows, crowded, desc, H, out);
+    };
     switch (H.n_classes) {
-    case 1: hipLaunchKernelGGL(k_edge_costs_h<1>, grid, block, 0, stream, win, desc, H, out); break;
-    case 2: hipLaunchKernelGGL(k_edge_costs_h<2>, grid, block, 0, stream, win, desc, H, out); break;
-    case 3: hipLaunchKernelGGL(k_edge_costs_h<3>, grid, block, 0, stream, win, desc, H, out); break;
-    default: hipLaunchKernelGGL(k_edge_costs_h<4>, grid, block, 0, stream, win, desc, H, out); break;
+    case 1: return launch(k_edge_costs_h<1>, k_edge_costs_h_crowded<1>);
+    case 2: return launch(k_edge_costs_h<2>, k_edge_costs_h_crowded<2>);
+    case 3: return launch(k_edge_costs_h<3>, k_edge_costs_h_crowded<3>);
+    default: return launch(k_edge_costs_h<4>, k_edge_costs_h_crowded<4>);
     }
-    return hipGetLastError();
 }
 
 hipError_t taps_launch_node_costs_h(const taps_op *ops, uint32_t n_ops, const uint64_t *offsets,

@@ -8,7 +8,8 @@ import random
 import pytest
 
 from paper_2301_04285_amd import workloads as W
-from test_gpu_parity import T, _topology_check, full_check, say, sweep_check  # noqa: F401
+from test_gpu_parity import (T, _topology_check, backward_check, full_check, say,  # noqa: F401
+                             sweep_check)
 
 pytestmark = pytest.mark.gpu
 
@@ -56,6 +57,40 @@ def test_windows_at_their_edges(T, devices, axes, ops, long_windows):  # noqa: F
                         name)
     finally:
         T.taps_set_long_segments_min(prev)
+
+
+@pytest.mark.parametrize("pattern", [
+    "n" * 9, "n" * 10,                 # 8 tables of one entry in a window, and 9: the first crowded one
+    "n" * 65, "n" * 66, "n" * 131,     # a whole tile of them, one more, a whole tile after those
+    "w" + "n" * 70 + "www" + "n" * 20 + "w" + "n" * 150 + "ww",   # crowded windows between others
+    "wn" * 60,                         # tables of 21 entries: three to a tile, 48 to a long window
+])
+@pytest.mark.parametrize("long_windows", [False, True])
+def test_windows_of_many_tables(T, pattern, long_windows):  # noqa: F811
+    """Operators of one strategy (n) and of 21 (w) in a chain."""
+    g, prev = W.Graph(), None
+    for k, kind in enumerate(pattern):
+        op = g.add(W.Op(f"{kind}{k}", "e", ("a", "b", "c"), (256, 256, 256),
+                        (True,) + (kind == "w",) * 2, 2, ins=((0, 1, 2),), ws=(), out=(0, 1, 2)))
+        if prev is not None:
+            g.connect(prev, op, 0)
+        prev = op
+    cl = W.Cluster(4, 2, 600 * W.GB, 100 * W.GB)
+    name = f"chain {pattern}, long windows {long_windows}"
+    say(f"[gpu] {name}")
+    before = T.taps_set_long_segments_min(0 if long_windows else 1 << 40)
+    try:
+        full_check(T, g, cl, name)
+        backward_check(T, g, cl, name)
+        wide = W.Cluster(4, 2, 600 * W.GB + 1, 100 * W.GB + 3)
+        for points in ([cl, W.Cluster(4, 2, 600 * W.GB, 25 * W.GB)], [wide, cl]):
+            sweep_check(T, g, points, name)
+        full_check(T, g, wide, name + ", 128-bit keys")
+        for domains in ((8,), (2, 8), (2, 4, 8), (1, 2, 4, 8)):
+            _topology_check(T, g, cl, W.Topology(domains, (600 * W.GB, 100 * W.GB, 50 * W.GB,
+                                                           25 * W.GB)[:len(domains)]), name)
+    finally:
+        T.taps_set_long_segments_min(before)
 
 
 @pytest.mark.parametrize("devices,axes,ops", [
