@@ -263,6 +263,15 @@ __host__ __device__ inline uint32_t taps_axis_levels(const taps_packed &p, uint3
     return taps_levels(end < w ? 0u : end - w, w);
 }
 
+// A strategy's 16 bytes, degrees then positions, to any address: the caller's
+// array may start anywhere (still one 16-byte store, which global memory takes
+// unaligned).
+__host__ __device__ inline void taps_store_strategy(void *at, const taps_b8 &degrees,
+                                                    const taps_b8 &positions) {
+    const taps_b8 bytes[2] = {degrees, positions};
+    __builtin_memcpy(at, bytes, sizeof bytes);
+}
+
 // One side of an edge: which tensor dimension an op axis carries (7: none; a
 // tensor of rank 8 uses every axis) and which axis a dimension lies on (0x0C:
 // none), as nibbles in the order of taps_packed.

@@ -288,8 +288,8 @@ __device__ inline void build_chunk(const taps_build_chunk &ck, const taps_op *__
     auto bytes = [](uint32_t nibbles) { return taps_spread(nibbles & 0xFFFFu); };
     const uint32_t not_lo = bytes(0x11111111u & ~whole) * 0xFFu;
     const uint32_t not_hi = bytes((0x11111111u & ~whole) >> 16) * 0xFFu;
-    *(uint4 *)(out + idx) = uint4{bytes(S.expo), bytes(S.expo >> 16), bytes(S.pos) | not_lo,
-                                  bytes(S.pos >> 16) | not_hi};
+    taps_store_strategy(out + idx, {bytes(S.expo), bytes(S.expo >> 16)},
+                        {bytes(S.pos) | not_lo, bytes(S.pos >> 16) | not_hi});
     if (desc) desc[idx] = R.packed;   // uniform: descriptors and node records are optional
     if (!node.t) return;
     // levels of every axis, a byte each

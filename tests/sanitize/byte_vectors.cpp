@@ -4,9 +4,9 @@
 // operators (1-8 axes, tensors of rank 0-8) on 1-256 devices, for 1-4 link
 // classes at random boundaries, every field of every candidate, also where the
 // degrees multiply to less than the devices (the tensors are replicated along
-// the levels left); and of every candidate rank of every set of partitionable axes the level runs, cuts and
-// packed descriptor against their definition.  Prints "N compared, 0
-// mismatches".
+// the levels left); of every candidate rank of every set of partitionable axes
+// the level runs, cuts and packed descriptor against their definition; and
+// strategies stored at any address.  Prints "N compared, 0 mismatches".
 #include <cstdio>
 #include <cstdint>
 #include <cstring>
@@ -83,6 +83,18 @@ void layouts() {
                 check(ok, "layout", n, r);
             }
         }
+}
+
+// A strategy at every address, also one that no wider type starts at.
+void stores() {
+    alignas(16) uint8_t b[48];
+    for (uint32_t at = 0; at < 17u; ++at) {
+        std::memset(b, 0xEE, sizeof b);
+        taps_store_strategy(b + at, {0x03020100u, 0x07060504u}, {0x0B0A0908u, 0x0F0E0D0Cu});
+        bool ok = true;
+        for (uint32_t k = 0; k < 48u; ++k) ok = ok && b[k] == (k - at < 16u ? k - at : 0xEEu);
+        check(ok, "strategy store", at, 0);
+    }
 }
 
 uint32_t pick_axes(uint32_t of, uint32_t rank) {
@@ -226,6 +238,7 @@ void entries(uint64_t budget, bool partial) {
 
 int main() {
     layouts();
+    stores();
     for (const bool partial : {false, true}) {
         entries<1>(20000, partial);
         entries<2>(150000, partial);

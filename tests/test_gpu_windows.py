@@ -172,3 +172,25 @@ def test_strategies_that_leave_levels_unused(T, devices):  # noqa: F811
         for k, v in want.items():
             signed = torch.int32 if k == "meta" else torch.int64
             assert torch.equal(got[k].view(signed)[mask], v.view(signed)[mask]), (what, k)
+
+
+@pytest.mark.parametrize("shift", [1, 6])
+def test_strategies_at_any_address(T, shift):  # noqa: F811
+    """A strategy is 16 bytes and its array may start on any of them."""
+    import torch
+    g, cl = W.mlp2(), W.Cluster(2, 2, 600 * W.GB, 100 * W.GB)
+    say(f"[gpu] strategies {shift} bytes after an aligned address")
+    want = T.taps_build_tables(g, cl)
+    n = len(want.strategies)
+    wide = torch.full((16 * n + 16,), 0xEE, dtype=torch.uint8, device="cuda")
+    out = T.Tables(want.op_offsets, wide[shift:shift + 16 * n].view(n, 16),
+                   T.alloc_table(n), want.edge_offsets, T.alloc_table(int(want.edge_offsets[-1])))
+    got = T.taps_build_tables(g, cl, out=out)
+    assert torch.equal(got.strategies, want.strategies)
+    assert bool((wide[:shift] == 0xEE).all()) and bool((wide[shift + 16 * n:] == 0xEE).all())
+    _, again = T.taps_edge_costs(g, cl, got.strategies, want.op_offsets)
+    node = T.taps_node_costs(g, cl, got.strategies, want.op_offsets)
+    for k in want.edge:
+        signed = torch.int32 if k == "meta" else torch.int64
+        for a, b in ((got.edge[k], want.edge[k]), (again[k], want.edge[k]), (node[k], want.node[k])):
+            assert torch.equal(a.view(signed), b.view(signed)), k
