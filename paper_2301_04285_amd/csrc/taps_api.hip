@@ -162,6 +162,24 @@ taps_status check_offsets(const taps_graph *g, const uint64_t *op_offsets) {
     return TAPS_OK;
 }
 
+// The first entries of the edges' tables laid end to end, and their end (held
+// at 2^64 - 1).  op_offsets: below 2^32.
+std::vector<uint64_t> table_offsets(const taps_graph *g, const uint64_t *op_offsets) {
+    std::vector<uint64_t> eoff(g->n_edges + 1, 0);
+    for (uint32_t e = 0; e < g->n_edges; ++e) {
+        const taps_edge &E = g->edges[e];
+        const uint64_t np = op_offsets[E.src_op + 1] - op_offsets[E.src_op];
+        const uint64_t nc = op_offsets[E.dst_op + 1] - op_offsets[E.dst_op];
+        if (__builtin_add_overflow(eoff[e], np * nc, &eoff[e + 1])) eoff[e + 1] = UINT64_MAX;
+    }
+    return eoff;
+}
+
+taps_status check_entries(uint64_t entries) {
+    if (entries <= TAPS_MAX_ENTRIES) return TAPS_OK;
+    return fail(TAPS_ERR_ARG, "more than %llu edge entries", (unsigned long long)TAPS_MAX_ENTRIES);
+}
+
 // Pinned staging for host-to-device uploads: a small pool of fine-grained
 // host buffers, each with the event recorded after the kernel that reads it
 // (k_pull: no copy engine, so the build's kernels follow on the same queue
@@ -663,16 +681,7 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
     if (st != TAPS_OK) return st;
     if (!edge_offsets) return fail(TAPS_ERR_ARG, "edge_offsets is NULL");
     const uint32_t n_ops = graph->n_ops, n_edges = graph->n_edges;
-    std::vector<uint64_t> eoff(n_edges + 1, 0);
-    uint64_t all_segs = 0;   // row segments without sharing (an upper bound)
-    for (uint32_t e = 0; e < n_edges; ++e) {
-        const taps_edge &E = graph->edges[e];
-        const uint64_t np = op_offsets[E.src_op + 1] - op_offsets[E.src_op];
-        const uint64_t nc = op_offsets[E.dst_op + 1] - op_offsets[E.dst_op];
-        const uint64_t ns = reverse ? nc : np, nd = reverse ? np : nc;   // rows, columns
-        eoff[e + 1] = eoff[e] + ns * nd;
-        all_segs += ns * ((nd + TAPS_TILE_COLS - 1) / TAPS_TILE_COLS);
-    }
+    const std::vector<uint64_t> eoff = table_offsets(graph, op_offsets);
     bool none = true, all = outs != nullptr;
     for (uint32_t k = 0; outs && k < n_points; ++k) {
         const taps_table &o = outs[k];
@@ -685,7 +694,7 @@ taps_status edge_costs(const taps_graph *graph, const taps_cluster *clusters, ui
         return fail(TAPS_ERR_CAPACITY, "%llu entries, capacity %llu",
                     (unsigned long long)eoff[n_edges], (unsigned long long)capacity);
     if (all && eoff[n_edges] > 0 && !strategies) return fail(TAPS_ERR_ARG, "strategies is NULL");
-    if (all_segs >= 0x7FFFFFFFull) return fail(TAPS_ERR_ARG, "more than 2^31 row segments");
+    if ((st = check_entries(eoff[n_edges])) != TAPS_OK) return st;
     std::memcpy(edge_offsets, eoff.data(), sizeof(uint64_t) * (n_edges + 1));
     if (none || eoff[n_edges] == 0) return TAPS_OK;
     hipStream_t stream = (hipStream_t)stream_;
@@ -1135,16 +1144,8 @@ taps_status build_tables(const taps_graph *graph, const taps_cluster *cluster, c
     if (flags & TAPS_BUILD_SHARED) {
         rep = group_edges(graph);
     }
-    std::vector<uint64_t> eoff(n_edges + 1, 0);
-    uint64_t all_segs = 0;
-    for (uint32_t e = 0; e < n_edges; ++e) {
-        const taps_edge &E = graph->edges[e];
-        const uint64_t ns = offs[E.src_op + 1] - offs[E.src_op];
-        const uint64_t nd = offs[E.dst_op + 1] - offs[E.dst_op];
-        eoff[e + 1] = eoff[e] + ns * nd;
-        all_segs += ns * ((nd + TAPS_TILE_COLS - 1) / TAPS_TILE_COLS);
-    }
-    if (all_segs >= 0x7FFFFFFFull) return fail(TAPS_ERR_ARG, "more than 2^31 row segments");
+    const std::vector<uint64_t> eoff = table_offsets(graph, offs.data());
+    if ((st = check_entries(eoff[n_edges])) != TAPS_OK) return st;
     std::vector<uint64_t> dst_list;
     std::vector<taps_copy_task> copies;
     plan_copies(eoff, rep, copies, dst_list);

@@ -46,6 +46,8 @@ struct taps_copy_task {
 // [64 T w, 64 T (w + 1)) of the computed tables laid end to end (aligned, so
 // that every store covers whole lines), taken by one wavefront 64 at a time.
 #define TAPS_TILE_COLS 64
+// Entries of one call: its tiles, and so its windows and blocks, stay below 2^31.
+#define TAPS_MAX_ENTRIES (0x7FFFFFFFull * TAPS_TILE_COLS)
 // T: a window's set-up (its place, the row cache, the LDS table) is paid once
 // per T tiles, and the launch's end leaves wavefronts idle for up to a window,
 // so T grows with the square root of the tiles, up to TAPS_WINDOW_LONG, which

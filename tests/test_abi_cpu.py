@@ -234,6 +234,25 @@ def test_edge_size_query_offsets(lib):
     assert len(g.edges) == 18 * 2 - 2
 
 
+@pytest.mark.parametrize("rows,columns,status", [
+    (2 ** 31, 1, T.OK),                    # as many rows as there may be tiles, of one entry
+    (2 ** 31 - 1, 64, T.OK),               # as many entries as there may be
+    (2 ** 31, 64, T.ERR_ARG),
+    (2 ** 31, 2 ** 31 - 2, T.ERR_ARG),     # two such tables pass 2^63, five 2^64
+])
+def test_most_entries_of_a_call(lib, rows, columns, status):
+    g = W.mlp2()
+    for edges in ([W.Edge(0, 1, 0)], [W.Edge(0, 1, 0)] * 5):
+        one = len(edges) == 1
+        st, eo = _size_query(lib, W.Graph(list(g.ops), edges),
+                             [0, rows, rows + columns, rows + columns + 1])
+        assert st == (status if one or rows * columns * 5 <= 64 * (2 ** 31 - 1) else T.ERR_ARG)
+        if st == T.OK:
+            assert int(eo[-1]) == rows * columns * len(edges)
+        else:
+            assert "entries" in T.last_error() and np.all(eo == 0)
+
+
 def test_offsets_must_increase(lib):
     st, _ = _size_query(lib, W.mlp2(), [0, 9, 9, 18])
     assert st == T.ERR_ARG
