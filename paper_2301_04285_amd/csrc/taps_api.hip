@@ -602,7 +602,7 @@ window_plan plan_windows(const std::vector<uint64_t> &eoff, const std::vector<ui
     }
     const uint64_t tiles = (p.total + TAPS_TILE_COLS - 1) / TAPS_TILE_COLS;
     const uint64_t most = n_points == 1 ? TAPS_WINDOW_LONG : TAPS_WINDOW_SWEEP;
-    if (tiles / most >= g_long_segs_min.load(std::memory_order_relaxed)) {
+    if ((tiles + most - 1) / most >= g_long_segs_min.load(std::memory_order_relaxed)) {
         p.tiles = (uint32_t)most;
     } else {
         uint64_t t = 1;   // sqrt(tiles / 2048)

@@ -304,6 +304,49 @@ def test_noalloc_rejects_a_build_beyond_its_workspace(lib):
         assert np.all(offs3 == 0) and np.all(eo3 == 0)   # nothing written on error
 
 
+def _noalloc_need(lib, graph, cl):
+    """The device workspace of a build above the fixed array's size, by its refusal."""
+    g, none = T.pack_graph(graph), T.Table(None, None, None, None, None)
+    offs, eo = np.zeros(g.n_ops + 1, np.uint64), np.zeros(g.n_edges + 1, np.uint64)
+    head = (C.byref(g.struct), C.byref(T.pack_cluster(cl)), None, T._u64_array(offs))
+    assert lib.taps_build_tables_noalloc(*head, None, 0, none, T._u64_array(eo), none, 0, 0,
+                                         None) == T.OK
+    fake = T.Table(256, 256, 256, 256, 256)
+    st = lib.taps_build_tables_noalloc(*head, C.c_void_p(256), int(offs[-1]), fake,
+                                       T._u64_array(eo), fake, int(eo[-1]), 0, None)
+    assert st == T.ERR_CAPACITY
+    return int(T.last_error().split(" needs ")[1].split()[0])
+
+
+def _many_strategies(ops, more):
+    """Operators of 1432 strategies on 256 devices, and `more` of one."""
+    g = W.Graph()
+    for k in range(ops):
+        g.add(W.elementwise(f"w{k}", "e", tuple("abcd"), (256,) * 4, 1, 2))
+    for k in range(more):
+        g.add(W.elementwise(f"n{k}", "e", ("a",), (256,), 1, 2))
+    return g
+
+
+def test_longest_windows_from_a_number_on(lib):
+    """156 tiles are ten windows of the longest kind: with that or a lower threshold the
+    windows' list takes 512 bytes less than one entry per tile."""
+    g, cl, prev = _many_strategies(1500, 0), W.Cluster(32, 8, 10, 1), None
+    for k in range(40):   # 39 tables of 256 entries
+        op = g.add(W.elementwise(f"e{k}", "e", ("a", "b"), (256, 256), 1, 2))
+        if prev is not None:
+            g.connect(prev, op, 0)
+        prev = op
+    before = T.taps_set_long_segments_min(11)
+    try:
+        short = _noalloc_need(lib, g, cl)
+        for threshold in (0, 1, 10):
+            T.taps_set_long_segments_min(threshold)
+            assert _noalloc_need(lib, g, cl) == short - 512
+    finally:
+        T.taps_set_long_segments_min(before)
+
+
 def test_shared_size_query_matches(lib):
     g = T.pack_graph(W.gpt(2, 64, 4, 32, 4, 2))
     cl = T.pack_cluster(W.Cluster(2, 2, 10, 1))
