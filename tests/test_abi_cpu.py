@@ -6,6 +6,7 @@ import subprocess
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2301_04285_amd import taps as T
 from paper_2301_04285_amd import workloads as W
@@ -305,7 +306,8 @@ def test_noalloc_rejects_a_build_beyond_its_workspace(lib):
 
 
 def _noalloc_need(lib, graph, cl):
-    """The device workspace of a build above the fixed array's size, by its refusal."""
+    """The device workspace a build asks for, by the refusal of one above the fixed array's
+    size (None: it fits; the arrays of this call are not memory, so only without a GPU)."""
     g, none = T.pack_graph(graph), T.Table(None, None, None, None, None)
     offs, eo = np.zeros(g.n_ops + 1, np.uint64), np.zeros(g.n_edges + 1, np.uint64)
     head = (C.byref(g.struct), C.byref(T.pack_cluster(cl)), None, T._u64_array(offs))
@@ -314,7 +316,9 @@ def _noalloc_need(lib, graph, cl):
     fake = T.Table(256, 256, 256, 256, 256)
     st = lib.taps_build_tables_noalloc(*head, C.c_void_p(256), int(offs[-1]), fake,
                                        T._u64_array(eo), fake, int(eo[-1]), 0, None)
-    assert st == T.ERR_CAPACITY
+    if st != T.ERR_CAPACITY:
+        assert st == T.ERR_DEVICE
+        return None
     return int(T.last_error().split(" needs ")[1].split()[0])
 
 
@@ -326,6 +330,27 @@ def _many_strategies(ops, more):
     for k in range(more):
         g.add(W.elementwise(f"n{k}", "e", ("a",), (256,), 1, 2))
     return g
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the accepted build would run on the GPU")
+def test_noalloc_takes_a_build_up_to_its_limit(lib):
+    """Everything but the table by tops mask, which has a place of its own, counts against
+    the 32 MiB: the largest build that fits, and one operator more."""
+    cl, limit = W.Cluster(32, 8, 10, 1), 32 << 20
+
+    def need(ops, more):
+        def up(*arrays):
+            return sum(max(256, -(-x // 256) * 256) for x in arrays)
+        strategies, n = 1432 * ops + more, ops + more
+        chunks = -(-1432 // 256) * ops + more
+        sent = [C.sizeof(T.Op) * n, 8 * (n + 1), 8, 24 * chunks]   # operators, offsets, plan
+        return sum(-(-x // 256) * 256 for x in sent) + up(16 * strategies, 0, 0)
+
+    ops = max(k for k in range(1, 2000) if need(k, 0) <= limit)
+    more = max(k for k in range(0, 500) if need(ops, k) <= limit)
+    assert limit - need(ops, more) < 10240   # the table would not fit below the limit as well
+    assert _noalloc_need(lib, _many_strategies(ops, more), cl) is None
+    assert _noalloc_need(lib, _many_strategies(ops, more + 1), cl) == need(ops, more + 1)
 
 
 def test_longest_windows_from_a_number_on(lib):
