@@ -121,20 +121,25 @@ def test_full_tables_config3_both_views(T):
 
 
 def test_long_segments_on_small_configs(T):
-    """The long-segment launch shape (eight-tile row segments, each edge's
-    full-length ones first, the rows' remainders last, longest first), which
-    only launches of at least 32,768 segments take by default, forced on
-    configurations 1-4 and random graphs and compared with the oracle in full."""
-    prev = T.taps_set_long_segments_min(1)
+    """The longest windows (sixteen tiles per wavefront, here with several edges,
+    short rows and a part of a tile in one), which only launches of half a
+    million tiles take by default, forced on configurations 1-4 and random
+    graphs, those of a few entries and of some thousands, and compared with the
+    oracle in full."""
+    prev = T.taps_set_long_segments_min(0)
     try:
         for cfg in (1, 2, 3, 4):
             w = W.config(cfg)
             for name, cl in w.clusters:
-                full_check(T, w.graph, cl, f"long segments {w.name}/{name}")
+                full_check(T, w.graph, cl, f"longest windows {w.name}/{name}")
         from paper_2301_04285_amd.taps import TapsError
-        for k, (g, cl) in enumerate(_random_cases(7, 12)):
+        some = [(g, cl) for g, cl in _random_cases(8, 400, 30_000)
+                if _entries(g, cl.devices) > 1000 and len(g.edges) > 1
+                and all(len(O.enumerate_strategies(op, cl.devices)) for op in g.ops)][:12]
+        assert len(some) == 12
+        for k, (g, cl) in enumerate([*_random_cases(7, 12), *some]):
             try:
-                full_check(T, g, cl, f"long segments random {k}")
+                full_check(T, g, cl, f"longest windows random {k}")
             except TapsError as ex:
                 assert ex.status == T.ERR_NO_STRATEGY
     finally:
@@ -195,8 +200,8 @@ def test_largest_config_sampled(T):
 
 def test_largest_config_full_oracle(T):
     """Every one of the 96-layer GPT's 98,668,128 edge entries against the
-    oracle, built by the benchmark's call (taps_build_tables: long row segments,
-    the rows' remainders launched last).  The oracle's edge tables are computed
+    oracle, built by the benchmark's call (taps_build_tables: the longest
+    windows).  The oracle's edge tables are computed
     by a pool of host threads (its calls release the interpreter lock) and each
     is compared with the GPU's slice as it arrives."""
     import os
@@ -944,7 +949,7 @@ def test_sweep_tables(T):
     sweep_check(T, w.graph, [cl for _, cl in w.clusters], w.name)
     w = W.config(2)
     sweep_check(T, w.graph, [W.Cluster(2, 8, 400 * W.GB, b * W.GB) for b in (50, 6, 400)], w.name)
-    # one point: the single-table launch (row segments, not windows)
+    # one point: the single-table launch (its own kernel and window length)
     sweep_check(T, w.graph, [W.Cluster(2, 8, 400 * W.GB, 50 * W.GB)], w.name + " one point")
     rng = random.Random(5151)
     n = 0
