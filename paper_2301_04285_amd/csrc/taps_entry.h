@@ -1,9 +1,19 @@
 // taps_entry.h -- the candidates of one edge entry on byte vectors.
 //
-// The same method as taps_device.h (binary levels; a unified axis is named by
-// its top level; positions, closures and costs as described there), laid out
-// for one entry per lane with no loop over dimensions and no table per row, so
-// that the lanes of a wavefront may hold different rows.
+// The edge tensor T leaves its source under strategy P and enters its target
+// under strategy Q.  Both device matrices and the tensor's shape are unified
+// (Table 1) by closing the strategies' cuts, boundaries between adjacent levels,
+// under the maps between their sides: a cut inside one side's run of a dimension
+// forces the cut at the same bit of that dimension on the other side.  An axis of
+// the unified matrix is named by its top level.  Position t of dimension d, the
+// part that starts at its bit t, is held on either side by the axis whose top is
+// the dimension's run's end less 1 + t; so every relation between the two tensor
+// maps that Algorithm 1 needs is a map between levels.  With e = n - (levels the
+// map uses) a device's shard is tbytes * 2^e nb, and the volumes of Eq. 9, 10
+// and 14 follow from the state each axis is moved at (in factor units: taps_fac).
+//
+// Laid out for one entry per lane with no loop over dimensions and no table per
+// row, so that the lanes of a wavefront may hold different rows:
 //
 //   * A set of levels is a vector of 8 bytes (two registers), byte l = FF when
 //     level l is in it.  A map between levels is a vector of 8 indices, and
@@ -573,8 +583,18 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
     const uint32_t G = P.g - taps_sum(D & sliced, 0u);
     const uint32_t H = kLow ? P.h - taps_sum(D2 & sliced, 0u) : 0u;
 
-    // ---- Algorithm 1: the state every axis is moved at, and the axes that
-    // AllToAlls move (taps_alg1_t has the schedule)
+    // ---- Algorithm 1 ("replace" in Table 2): the state every axis is moved at, and
+    // the axes that AllToAlls move.  The printed loop comes to this:
+    //   * one pass of the inner loop is InferSlice, then InferAll2All until nothing
+    //     moves; a slice frees no position, so a second pass can only slice (targets
+    //     that the AllToAlls freed) and a third finds nothing;
+    //   * an AllGather of an axis whose position no target axis goes to frees nothing
+    //     that anyone waits for, and the axis cannot be sliced back (with a free
+    //     target it would have moved): such gathers run back to back, in producer
+    //     order, but the first alone before the slices still pending;
+    //   * the axes left sit at targeted positions, and AllGatherFirstUndoneDim takes
+    //     the first in producer order, a pass after each;
+    //   * with nothing held at a source position only slices remain, which are free.
     taps_b8 at, at2 = {0u, 0u}, a2a;   // at2: the free levels of H
     {
         // the first closure: movable axes, then those whose targets they free
@@ -688,7 +708,9 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
         }
     }
 
-    // ---- "rearrange": untargeted axes in producer order, then targeted ones
+    // ---- "rearrange" (Algorithm 1 without AllToAll): untargeted axes in producer
+    // order, then targeted ones; each is sliced back at once if its target is open,
+    // and what waits for its position is sliced into that
     taps_b8 at_r, at_r2 = {0u, 0u};
     {
         // a targeted axis whose blocker comes before it
@@ -717,7 +739,9 @@ __host__ __device__ inline void taps_three_candidates(const taps_source &P, cons
         }
     }
 
-    // ---- "remove": every axis gathered in producer order
+    // ---- "remove": every axis gathered in producer order.  ("Naive", the fourth of
+    // Table 2, gathers a superset of these in the same order: never cheaper, and it
+    // wins no tie.)
     const taps_b8 Dh = D & held;
     uint32_t g_end;
     const taps_b8 at_m = taps_map(taps_states(taps_map(Dh, P.order), P.g, g_end), P.rank);

@@ -692,7 +692,6 @@ __device__ inline taps_entry_out select_entry(const taps_three<2> &r, const taps
     }
     o.t = (double)intra * S.a_intra + (double)inter * S.a_inter;
     o.meta = cand | r.coll | (ct << 12);
-    o.ok = true;
     return o;
 }
 
@@ -803,7 +802,6 @@ __device__ inline taps_entry_out select_entry_h(const taps_three<C> &r, const ta
         o.inter = taps_scale(S, links);
     }
     o.meta = cand | r.coll | (best.ct << 12);
-    o.ok = true;
     return o;
 }
 

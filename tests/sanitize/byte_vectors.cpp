@@ -1,5 +1,5 @@
 // Host check of the edge kernels' entry code (csrc/taps_entry.h, compiled for
-// the host) against the step-by-step form in csrc/taps_device.h: unification,
+// the host) against the step-by-step form in steps.h: unification,
 // Algorithm 1, "rearrange" and "remove" of random strategy pairs of random
 // operators (1-8 axes, tensors of rank 0-8) on 1-256 devices, for 1-4 link
 // classes at random boundaries, every field of every candidate, also where the
@@ -11,6 +11,7 @@
 #include <cstdint>
 #include <cstring>
 
+#include "steps.h"
 #include "taps_entry.h"
 
 namespace {
@@ -56,7 +57,7 @@ void layouts() {
                 uint32_t sum = 0, positions = 0, split = 0;
                 bool ok = R.cuts == D.cuts && R.width == D.width;
                 for (uint32_t a = 0; a < 8u; ++a) {
-                    const uint32_t w = taps_nib(S.expo, a), s = taps_nibble_shift(a);
+                    const uint32_t w = taps_nib(S.expo, a);
                     sum += w;
                     ok = ok && (w == 0u || ((part >> a) & 1u));
                     if (w) positions |= 1u << taps_nib(S.pos, a), ++split;
@@ -146,7 +147,7 @@ void entries(uint64_t budget, bool partial) {
         for (uint32_t c = 0; c + 1u < C; ++c) b[c] = rnd() % (n + 1u);
         for (uint32_t c = 1; c + 1u < C; ++c)
             if (b[c] < b[c - 1u]) b[c] = b[c - 1u];
-        taps_hier H;
+        taps_hier_steps H;
         std::memset(&H, 0, sizeof(H));
         H.n_classes = C;
         H.a2a_own = 1;   // AllToAlls of class 0 apart
@@ -204,9 +205,9 @@ void entries(uint64_t budget, bool partial) {
                 if (!ends_at_a_boundary(Sp, L.tp) || !ends_at_a_boundary(Sq, L.tp)) continue;
                 const taps_start st = taps_begin(P, L);
                 taps_fach want[3];
-                const taps_hier_model_t<C> M{&H, 0, 0, false, cls_rows, expand};
-                want[0] = taps_alg1_t(P, Q, L, M, st).c;
-                want[1] = taps_rearrange_t(P, Q, L, M, st).c;
+                const taps_hier_model_t<C> M{&H, cls_rows, expand};
+                want[0] = taps_alg1_t(P, L, M, st);
+                want[1] = taps_rearrange_t(P, L, M, st);
                 want[2] = taps_remove_h(P, L, M);
                 taps_three<C> got;
                 taps_three_candidates<C>(S, taps_lay_out(Sq, qm, n).packed,
@@ -221,8 +222,8 @@ void entries(uint64_t budget, bool partial) {
                 const uint32_t coll = taps_collectives_h(L, H);
                 ok = ok && got.coll == (((coll & 0xFFu) << 2) | ((coll >> 8) << 7));
                 if (C == 2) {   // the two-class closed forms
-                    const taps_fac two[3] = {taps_alg1(P, Q, L, st).c,
-                                             taps_rearrange(P, Q, L, taps_limit{}, taps_keys{}, st).c,
+                    const taps_fac two[3] = {taps_alg1(P, L, st),
+                                             taps_rearrange(P, L, st),
                                              taps_remove(P, L)};
                     for (uint32_t k = 0; k < 3u; ++k)
                         ok = ok && two[k].vol == got.c[k].vol && two[k].intra == got.c[k].in &&

@@ -1,18 +1,18 @@
-// Host check of the edge kernels' batched AllToAll costing (csrc/taps_device.h,
-// compiled for the host): every closure of every tops mask on n <= 8 binary
-// levels, at every shard shift and node boundary, costed by the closed forms
-// (byte dot products against the shard-fraction tables) and axis by axis from
-// the definitions (Eq. 10 and Eq. 14: an axis of width w moves all but 2^-w of
-// the shard, across the inter-node link when its groups cross a node, with the
-// group count of Algorithm 3; the axis straddling the node boundary sends only
-// its members outside the node), for the two-class model and for hierarchies
-// of link classes.  Prints "N closures, 0 mismatches".
+// Host check of the batched AllToAll costing of the step-by-step form (steps.h),
+// which byte_vectors.cpp holds the edge kernels' against: every closure of every
+// tops mask on n <= 8 binary levels, at every shard shift and node boundary,
+// costed by the closed forms (byte dot products against the shard-fraction
+// tables) and axis by axis from the definitions (Eq. 10 and Eq. 14: an axis of
+// width w moves all but 2^-w of the shard, across the inter-node link when its
+// groups cross a node, with the group count of Algorithm 3; the axis straddling
+// the node boundary sends only its members outside the node), for the two-class
+// model and for hierarchies of link classes.  Prints "N closures, 0 mismatches".
 #include <cstdio>
 #include <cstdlib>
 #include <cstdint>
 #include <cstring>
 
-#include "taps_device.h"
+#include "steps.h"
 
 namespace {
 
@@ -122,7 +122,7 @@ int main() {
     for (uint32_t trial = 0; trial < 400u; ++trial) {
         const uint32_t n = 1u + rnd() % 8u;
         const uint32_t C = 1u + rnd() % 4u;
-        taps_hier H;
+        taps_hier_steps H;
         std::memset(&H, 0, sizeof(H));
         H.n_classes = C;
         uint32_t b[TAPS_D_MAX_CLASSES] = {0, 0, 0, 0};   // boundaries, non-decreasing
@@ -149,7 +149,7 @@ int main() {
                 cls_rows[m * TAPS_D_MAX_CLASSES + c] =
                     taps_pair{a2a.lo[m] & (ex.lo[lv] * 0xFFu), a2a.hi[m] & (ex.hi[lv] * 0xFFu)};
             }
-        const taps_hier_model_t<TAPS_D_MAX_CLASSES> M{&H, 0, 0, false, cls_rows, expand};
+        const taps_hier_model_t<TAPS_D_MAX_CLASSES> M{&H, cls_rows, expand};
         const uint32_t full = (1u << n) - 1u;
         for (uint32_t k = 0; k < 64u; ++k) {
             const uint32_t tp = ((rnd() & full) | (1u << (n - 1u))) & full;

@@ -1,5 +1,5 @@
 """The edge kernels' entry code on byte vectors against the step-by-step form of
-the same method, compiled for the host under AddressSanitizer and
+the same method (sanitize/steps.h), compiled for the host under AddressSanitizer and
 UndefinedBehaviorSanitizer."""
 import os
 import shutil

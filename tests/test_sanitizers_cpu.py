@@ -53,11 +53,11 @@ def test_library_host_code_under_sanitizers(tmp_path):
 
 
 def test_batched_alltoall_closed_forms(tmp_path):
-    """The edge kernels' closed-form AllToAll costing (byte dot products over
-    shard-fraction tables) against axis-by-axis costing from the definitions,
-    on every closure of every tops mask (two classes) and on random
-    hierarchies of link classes; host build of the device header, under the
-    sanitizers."""
+    """The batched AllToAll costing of the step-by-step form that the edge
+    kernels' entry code is held against (test_entry_cpu.py): byte dot products
+    over shard-fraction tables against axis-by-axis costing from the
+    definitions, on every closure of every tops mask (two classes) and on
+    random hierarchies of link classes, under the sanitizers."""
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
