@@ -2,17 +2,16 @@
 // support for the benchmark's roofline, not part of the cost-table path).
 //
 // Each kernel runs 8 independent dependency chains of one 32-bit integer
-// VALU instruction per thread, 8 wavefronts per SIMD (the most a SIMD holds;
-// the edge kernel runs 7, as many as its scalar registers allow, and held to
-// 8 it ran no faster), so the issue rate, not the latency, bounds it.  The instruction
-// count per launch is exact (inline assembly, 16 instructions per block); the
-// caller divides it by the measured time.
+// VALU instruction per thread, 8 wavefronts per SIMD (the most a SIMD holds), so
+// the issue rate, not the latency, bounds it.  The edge kernel runs 4, as many as
+// its vector registers allow.  The instruction count per launch is exact (inline
+// assembly, 16 instructions per block); the caller divides it by the measured
+// time.
 //   kind 0: v_add_u32 / v_xor_b32 with vector operands -- on gfx950 the class
 //           of simple 32-bit operations issued at the highest rate
 //   kind 1: v_bfe_u32 / v_lshl_or_b32 -- the class of 3-operand and bit-field
 //           operations, issued at a lower rate
-//   kinds 2-12: one instruction each (the classes the edge kernels' choice of
-//           instructions rests on), 8 per block: see kKindNames
+//   kinds 2-12: one instruction each, 8 per block: see kKindNames
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
