@@ -423,9 +423,9 @@ taps_status taps_set_edge_kernel_events(void *before, void *after);
  * (taps_edge_costs, taps_edge_costs_shared, taps_edge_costs_backward,
  * taps_edge_costs_topology, taps_build_tables) whose tables hold at least
  * `min_segments` windows of the longest kind (sixteen aligned 64-entry tiles
- * per wavefront; two for several bandwidth points) run those; smaller launches
- * run shorter windows, by the square root of their tiles.  Every shape writes
- * the same tables; the setting only moves the size from which a launch is sure
+ * per wavefront; eight for two bandwidth points, four for three, two for more)
+ * run those; smaller launches run shorter windows, by the square root of their
+ * tiles.  Every shape writes the same tables; the setting only moves the size from which a launch is sure
  * to run the longest windows (default 32768; 0 or 1: every launch).  Process-wide,
  * read when a launch is planned; returns the previous value.  Never fails. */
 uint64_t taps_set_long_segments_min(uint64_t min_segments);

@@ -601,7 +601,7 @@ window_plan plan_windows(const std::vector<uint64_t> &eoff, const std::vector<ui
         p.n_edges = (uint32_t)p.edges.size();
     }
     const uint64_t tiles = (p.total + TAPS_TILE_COLS - 1) / TAPS_TILE_COLS;
-    const uint64_t most = n_points == 1 ? TAPS_WINDOW_LONG : TAPS_WINDOW_SWEEP;
+    const uint64_t most = n_points == 1 ? TAPS_WINDOW_LONG : TAPS_WINDOW_SWEEP(n_points);
     if ((tiles + most - 1) / most >= g_long_segs_min.load(std::memory_order_relaxed)) {
         p.tiles = (uint32_t)most;
     } else {

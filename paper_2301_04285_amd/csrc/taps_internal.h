@@ -55,12 +55,17 @@ struct taps_copy_task {
 // Measured (us, T = 1 / 2 / 4 / 8 / 16 / 32): 1.5 M tiles 2233 / 1858 / 1680 /
 // 1600 / 1561 / 1565, 145 k tiles 215 / 183 / 169 / 165 / 170 / 197, 64 k tiles
 // 120 / 106 / 101 / 102 / 105 / 119, 16 k tiles 99 / 95 / 94 / 96 / 105 / 131
-// (whole builds).  Several bandwidth points are bound by their stores, which
-// longer windows scatter (four points, 1.5 M tiles, us, T = 1 / 2 / 3 / 4 / 8:
-// cached stores 3012 / 2505 / 2653 / 2700 / 2650, non-temporal ones 2689 / 2695 /
-// 2690 at 2 / 4 / 8).
+// (whole builds).  Several bandwidth points are bound by their stores, into five
+// arrays per point.  The fewer the points, the longer the windows may be (1.5 M
+// tiles, us, T = 1 / 2 / 3 / 4 / 8, cached stores; non-temporal ones are 4-8 %
+// faster up to T = 4 at two and three points, slower elsewhere):
+//   2 points  2393 / 1984 / 1806 / 1710 / 1567    3 points  2718 / 2208 / 1954 / 1877 / 1922
+//   4 points  2991 / 2403 / 2643 / 2664 / 2651    5 points  3308 / 3260 / 3295 / 3291 / 3275
+//   8 points  5482 / 5356 / 5380 / 5343 / 5368
+// and alike on 215 k tiles (2 points 405 / 345 / 320 / 309 / 298, 4 points 471 /
+// 405 / 451 / 453 / 465).  Why four points have their best at two tiles is not known.
 #define TAPS_WINDOW_LONG 16
-#define TAPS_WINDOW_SWEEP 2
+#define TAPS_WINDOW_SWEEP(points) ((points) == 2 ? 8 : (points) == 3 ? 4 : 2)
 #define TAPS_LONG_SEGS_MIN 32768
 // A wavefront takes the tables that meet in its window one after the other,
 // about 1.6 us each.  A window that holds entries of more than TAPS_CROWDED(T)

@@ -725,8 +725,7 @@ __global__ __launch_bounds__(256) void k_edge_costs_crowded(taps_windows win,
 
 // Several bandwidth points: the candidates of each entry are costed once and
 // selected, scaled and stored once per point.  Bound by the stores, which spread
-// over five arrays per point: short windows keep what is written at a time close
-// together (TAPS_WINDOW_SWEEP).
+// over five arrays per point (window lengths by points: TAPS_WINDOW_SWEEP).
 template <bool Narrow>
 struct emit_sweep {
     const taps_sweep &sw;
