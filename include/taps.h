@@ -258,13 +258,13 @@ taps_status taps_build_tables(const taps_graph *graph, const taps_cluster *clust
  * hipMalloc.  Same arguments, outputs and errors, the same tables bit for
  * bit; the caller still provides every output array.  The call's device
  * workspace (the uploaded graph and plan, strategy descriptors, per-edge
- * constants, windows) lives in a fixed array of
- * TAPS_NOALLOC_SCRATCH_BYTES that each GPU the library runs on holds until
- * the process ends; the plan is uploaded with one hipMemcpyAsync from
- * pageable host memory.  No hipMalloc, hipFree, hipHostMalloc or other
- * allocating routine is called.
+ * constants, windows) lives in a fixed array of TAPS_NOALLOC_SCRATCH_BYTES,
+ * and 10 KB for a table that does not count against them, which each GPU the
+ * library runs on holds until the process ends; the plan is uploaded with one
+ * hipMemcpyAsync from pageable host memory.  No hipMalloc, hipFree,
+ * hipHostMalloc or other allocating routine is called.
  * TAPS_ERR_CAPACITY, before any GPU work, if a build needs more workspace
- * than that (the 96-layer GPT on 128 devices needs about 21 MB).
+ * than that (the 96-layer GPT on 128 devices needs about 10 MB).
  * Every call on one GPU uses that GPU's single array: calls that overlap on
  * one GPU (other streams, other threads) race and must be serialised by the
  * caller; consecutive calls on one stream are ordered and safe. */

@@ -154,7 +154,7 @@ __host__ __device__ inline uint32_t taps_pow2(uint32_t x) {
 // Selector of levels l .. l + 3, 0 from `end` on.
 __host__ __device__ inline uint32_t taps_four(uint32_t l, uint32_t end) {
     const uint32_t idx = 0x03020100u + l * 0x01010101u;
-    const uint32_t k = end - l;   // at least 1
+    const uint32_t k = end - l;   // 0 where a launch has no such levels
     const uint32_t keep = k >= 4u ? ~0u : (1u << (8u * k)) - 1u;
     return (idx & keep) | (0x0C0C0C0Cu & ~keep);
 }

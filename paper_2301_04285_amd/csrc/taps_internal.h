@@ -44,7 +44,8 @@ struct taps_copy_task {
 
 // The edge kernels run over windows: window w is the 64 T entries
 // [64 T w, 64 T (w + 1)) of the computed tables laid end to end (aligned, so
-// that every store covers whole lines), taken by one wavefront 64 at a time.
+// that tiles are whole lines of the output, unless tables are shared or the
+// arrays start between lines), taken by one wavefront 64 at a time.
 #define TAPS_TILE_COLS 64
 // Entries of one call: its tiles, and so its windows and blocks, stay below 2^31.
 #define TAPS_MAX_ENTRIES (0x7FFFFFFFull * TAPS_TILE_COLS)

@@ -4,12 +4,12 @@
 //                 operator: GenerateStrategySet in canonical order at
 //                 host-counted offsets (ballot, LDS scan), optionally each
 //                 strategy's descriptor and node record
-//   k_describe    one thread per strategy: level runs, owners and cuts
 //   k_node_costs  one thread per strategy: the intra-op AllReduces
 //   k_memory_costs one thread per strategy: weight and output shard bytes
-//   k_edge_plan   one thread per computed edge (its constants), then one
-//                 thread per window (the edge it starts in)
-//   k_build_front k_build_strategies and k_edge_plan in one launch
+//   k_edge_front  the descriptors of given strategies, one thread each, and the
+//                 edge plan: one thread per computed edge (its constants), one
+//                 per window (the edge it starts in)
+//   k_build_front k_build_strategies and the edge plan in one launch
 //   k_edge_costs  one wavefront per window of aligned 64-entry tiles of the
 //                 concatenated tables, one entry per lane whatever its row
 //                 (taps_entry.h); whole-line stores
@@ -39,12 +39,13 @@ __device__ inline T *at_byte(T *base, uint32_t offset) {
     return (T *)((char *)base + offset);
 }
 
-// Entry j of a row whose records start at `row` (uniform): 32-bit byte offsets
-// from the uniform row bases, j < 2^21 (8 axes on 8 levels give at most
-// 1,047,376 strategies per operator); five non-temporal stores of whole
-// 128-byte lines (nothing is left to merge but at a tile of two edges; cached
-// stores take the 24-layer GPT's build from 80.6 to 82.5 us).  Cached: ordinary
-// stores, the faster ones into the tables of several bandwidth points.
+// Entry row + j (of a window: row uniform, j the lane; 32-bit byte offsets from
+// the five scalar bases).  Non-temporal stores: a tile of one edge is whole
+// 128-byte lines where the tables lie end to end from a line on, as in a build
+// without sharing, and nothing is left to merge (cached stores take the 24-layer
+// GPT's build from 80.6 to 82.5 us; arrays that start between lines, the
+// 96-layer GPT's edges from 1284 to 1326).  Cached: ordinary stores, the faster
+// ones into the tables of four bandwidth points and more.
 template <bool Cached>
 __device__ inline void store_entry(const taps_table &out, uint64_t row, uint32_t j,
                                    const taps_entry_out &o, uint32_t meta) {
@@ -430,13 +431,18 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_front(
 //
 // Wavefront w takes window w, one 64-entry tile at a time, lane l entry l of
 // the tile: its edge is uniform (a tile that runs into the next edge is taken
-// in two passes), its row and column are its own.  Every store covers whole
-// 128-byte lines, and rows shorter than a wavefront leave no lane idle.  The
+// in two passes), its row and column are its own.  Rows shorter than a wavefront
+// leave no lane idle, and a tile of one edge is stored in whole 128-byte lines
+// (but for shared tables, whose places in the output are not their windows', and
+// arrays that start between lines).  The
 // source side of a lane's row is made again only in tiles where a lane's row
 // changes.
 //
-// Bound by the issue of vector instructions (about 4 cycles each whatever the
-// mix: half of them have a rate of 2 alone), hence by their number per tile.
+// Bound by the issue of vector instructions, hence by their number per tile: 531
+// at 3.9 cycles of a SIMD each.  The ones used most (v_perm_b32, v_dot4_u32_u8,
+// v_mul_lo_u32, v_mad_u64_u32) take 4.1-4.2 alone, v_and_b32 and v_bitop3_b32
+// 2.3, but in turns with v_perm_b32 3.9: a mixture gains little from its fast
+// half (4.0 at the 4 wavefronts per SIMD that run here).
 // Everything a row fixes is made with the row (positions as the target's axes
 // meet them), places in a window are 32-bit scalars, and the addresses of the
 // five stores are scalar bases and one offset: together 1409 -> 1299 us on the
