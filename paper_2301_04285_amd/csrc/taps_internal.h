@@ -58,11 +58,12 @@ struct taps_copy_task {
 // 120 / 106 / 101 / 102 / 105 / 119, 16 k tiles 99 / 95 / 94 / 96 / 105 / 131
 // (whole builds).  Several bandwidth points are bound by their stores, into five
 // arrays per point.  The fewer the points, the longer the windows may be (1.5 M
-// tiles, us, T = 1 / 2 / 3 / 4 / 8, cached stores; non-temporal ones are 4-8 %
-// faster up to T = 4 at two and three points, slower elsewhere):
-//   2 points  2393 / 1984 / 1806 / 1710 / 1567    3 points  2718 / 2208 / 1954 / 1877 / 1922
-//   4 points  2991 / 2403 / 2643 / 2664 / 2651    5 points  3308 / 3260 / 3295 / 3291 / 3275
-//   8 points  5482 / 5356 / 5380 / 5343 / 5368
+// tiles, us, T = 1 / 2 / 3 / 4 / 8, cached stores, then non-temporal ones):
+//   2 points  2393 / 1984 / 1806 / 1710 / 1567,  2069 / 1759 / 1612 / 1576 / 1508
+//   3 points  2718 / 2208 / 1954 / 1877 / 1922,  2200 / 1915 / 1946 / 1989 / 2002
+//   4 points  2991 / 2403 / 2643 / 2664 / 2651,  2564 / 2630 / 2700 / 2693 / 2673
+//   5 points  3308 / 3260 / 3295 / 3291 / 3275,  3447 / 3265 / 3313 / 3334 / 3327
+//   8 points  5482 / 5356 / 5380 / 5343 / 5368,  5518 / 5434 / 5434 / 5461 / 5486
 // and alike on 215 k tiles (2 points 405 / 345 / 320 / 309 / 298, 4 points 471 /
 // 405 / 451 / 453 / 465).  Why four points have their best at two tiles is not known.
 #define TAPS_WINDOW_LONG 16
@@ -72,7 +73,7 @@ struct taps_copy_task {
 // about 1.6 us each.  A window that holds entries of more than TAPS_CROWDED(T)
 // tables goes to the k_*_crowded kernels instead, a lane its own table (calls,
 // us, as windows / crowded: 255 tables of one entry 129 / 23, 1,000 tables of
-// 441 entries and of one in turns of a hundred 206 / 58, 199 of 9 entries, eight
+// 3,969 entries and of one in turns of a hundred 206 / 58, 199 of 9 entries, eight
 // to a tile and not crowded, 31).
 #define TAPS_CROWDED(tiles) (2u * (tiles) + 6u)
 
@@ -81,9 +82,9 @@ hipError_t taps_launch_node_costs(const taps_op *ops, uint32_t n_ops, const uint
                                   const taps_launch &lp, taps_table out, hipStream_t stream);
 // The edge plan of a launch (device arrays): the constants of the n_edges
 // computed edges (edge computed[k], or k without that list) into params, and
-// the edge that each window starts in (~0: a crowded one).  starts: n_edges + 1 first entries of
-// the computed tables laid end to end; window: entries per window; reverse:
-// the backward tables (source side = the consumer's input map).
+// the edge that each window starts in (~0: a crowded one).  starts: n_edges + 1
+// first entries of the computed tables laid end to end; window: entries per
+// window; reverse: the backward tables (source side = the consumer's input map).
 struct taps_plan_args {
     const taps_op *ops;
     const taps_edge *edges;

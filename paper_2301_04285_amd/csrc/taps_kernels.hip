@@ -44,8 +44,8 @@ __device__ inline T *at_byte(T *base, uint32_t offset) {
 // 128-byte lines where the tables lie end to end from a line on, as in a build
 // without sharing, and nothing is left to merge (cached stores take the 24-layer
 // GPT's build from 80.6 to 82.5 us; arrays that start between lines, the
-// 96-layer GPT's edges from 1284 to 1326).  Cached: ordinary stores, the faster
-// ones into the tables of four bandwidth points and more.
+// 96-layer GPT's edges from 1284 to 1326).  Cached: ordinary stores, into the
+// tables of several bandwidth points (TAPS_WINDOW_SWEEP has both).
 template <bool Cached>
 __device__ inline void store_entry(const taps_table &out, uint64_t row, uint32_t j,
                                    const taps_entry_out &o, uint32_t meta) {
